@@ -112,8 +112,10 @@ size_t asl_workspace_bytes(int32_t max_seq_len, int32_t max_kv_heads, int32_t ma
  * Logits are scaled q.k with the causal mask on the last W x W block; softmax over all N keys;
  * column sums over the W rows and the G heads of a group, past columns only; AvgPool1D(S,
  * stride 1, zero pad floor(S/2), divisor S).  bf16 inputs with d in {64, 128} and G*W <= 512 use
- * bf16 MFMA with fp32 accumulation; other shapes take plain fp32-FMA kernels, which are meant for
- * small problems (ASL_EUNSUPPORTED when Hq*W*N*d exceeds 6e11).  Softmax and sums are fp32 and
+ * bf16 MFMA with fp32 accumulation at any size.  Other shapes are taken up to Hq*W*N*d = 6e11
+ * (ASL_EUNSUPPORTED beyond): by MFMA kernels as well (fp32 MFMA for fp32 inputs) when d <= 256 and rows,
+ * pointers and strides are multiples of 16 bytes, else by plain fp32-FMA kernels, which are meant for
+ * small problems.  Softmax and sums are fp32 and
  * deterministic (fixed reduction order, no float atomics). */
 asl_status asl_score_layer(asl_ctx* ctx, const asl_params* params, const void* q_obs,
                            const void* k, const float* lse, float* p_head, float* s_all,

@@ -286,12 +286,13 @@ static asl_status check_score_operands(asl_ctx* ctx, const asl_params* p, const 
        (p->k_stride_head * eb) % 16 != 0))
     return fail(ctx, ASL_EUNSUPPORTED, "q_obs/k must be 16-byte aligned with 16-byte-multiple strides");
   // the plain-FMA kernels walk every key with one thread per query row or per key: refuse the sizes
-  // at which that would take seconds rather than hand back a call that looks hung
+  // at which that would take seconds rather than hand back a call that looks hung (one limit for all
+  // shapes beside the main ones, whichever kernels their alignment gets them)
   if (!asl::score_mfma_supported(*p) || (p->flags & ASL_FLAG_GENERIC_SCORE)) {
     const double work = (double)p->n_q_heads * p->window * (double)p->seq_len * p->head_dim;
     if (work > 6.0e11)
       return fail(ctx, ASL_EUNSUPPORTED,
-                  "this shape (dtype/head_dim/G*W) has no MFMA scoring kernel and is too large for the plain one");
+                  "this shape (dtype/head_dim/G*W) is not one of the main scoring shapes and too large for the others");
   }
   return ASL_OK;
 }

@@ -19,15 +19,17 @@
 namespace asl {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-#ifndef ASL_SCORE_KT
-#define ASL_SCORE_KT 64
-#endif
 #ifndef ASL_SCORE_STAGES
 #define ASL_SCORE_STAGES 3
 #endif
-constexpr int KT = ASL_SCORE_KT;              // keys per LDS tile (a multiple of 32)
+// A key row is handled as 16-byte pieces, P of them per (padded) row: 8 bf16 or 4 fp32 elements each.
+typedef uint32_t Piece __attribute__((ext_vector_type(4)));
+// Keys per LDS tile (a multiple of 32): tiles of at most 16 KB up to 512-byte rows, so that three
+// workgroups' rings fit a compute unit.
+template <int P> constexpr int key_tile() { return P <= 16 ? 64 : 32; }
 #ifndef ASL_SCORE_STAGES_RB2
 #define ASL_SCORE_STAGES_RB2 4
 #endif
@@ -46,48 +48,53 @@ __device__ __forceinline__ int acc_row(int r, int half) { return 8 * (r >> 2) + 
 
 // K tile staging: global memory -> LDS directly (global_load_lds_dwordx4: each lane names its own
 // 16-byte global source, the hardware writes lane i's data to  wave base + 16*i  in LDS), a ring of
-// LDS buffers, one workgroup barrier per tile.  The tile is stored unpadded; bank conflicts on the
-// fragment reads are avoided by an XOR swizzle applied on the global side: LDS slot (row r,
-// piece c') holds the row's 16-byte piece  c = c' ^ (r mod CPR).
-// Rows past N are clamped to the last key (they are masked or discarded later).
+// LDS buffers, one workgroup barrier per tile.  Bank conflicts on the fragment reads are avoided by an
+// XOR swizzle applied on the global side: LDS slot (row r, piece c') holds the row's 16-byte piece
+// c = c' ^ (r mod 16)  (mod 8 where P is no multiple of 16).
+// Rows past N are clamped to the last key (they are masked or discarded later).  With PAD the row has
+// only np <= P pieces: the slots behind them repeat the row's last piece, and the query fragments hold
+// zeros there, so that they add nothing.
 // Per-thread constants of the tile loader: for each of its NLOAD pieces the byte offset of the
 // (swizzled) source piece from the tile's first key.
 // The first NT threads of the workgroup do the loading, NT = the largest power of two that is at most
 // the workgroup size and the number of pieces (see loader_threads): every loading wavefront then
 // issues the same number of loads per tile, which the counted waits below rely on; the other
 // wavefronts issue none and are held by the workgroup barrier alone.
-template <int D, int NT>
+template <int P, int NT>
 struct TilePieces {
-  static constexpr int CPR = D / 8;                   // 16-byte pieces per key row
-  static constexpr int SLOTS = KT * CPR;
+  static constexpr int KT = key_tile<P>();
+  static constexpr int SWZ = (P % 16 == 0) ? 15 : 7;
+  static_assert(P % 8 == 0, "the swizzle permutes the pieces of a row in aligned groups of 8 or 16");
+  static constexpr int SLOTS = KT * P;
   static_assert(SLOTS % NT == 0, "loader threads must divide the pieces of a tile");
   static constexpr int NLOAD = SLOTS / NT;
   uint32_t src_off[NLOAD];
-  // tile row and first element of the (swizzled) source piece of this thread's i-th load
-  static __device__ __forceinline__ int row(int i, int tid) { return (i * NT + tid) / CPR; }
-  static __device__ __forceinline__ int col8(int i, int tid) {
+  // tile row and (swizzled) source piece of this thread's i-th load; `last` = the row's last piece
+  static __device__ __forceinline__ int row(int i, int tid) { return (i * NT + tid) / P; }
+  static __device__ __forceinline__ int piece(int i, int tid, int last) {
     const int q = i * NT + tid;
-    return ((q % CPR) ^ ((q / CPR) & (CPR - 1))) * 8;
+    return min((q % P) ^ ((q / P) & SWZ), last);
   }
-  __device__ __forceinline__ void init(int64_t kst, int tid) {
+  __device__ __forceinline__ void init(int64_t row_stride_bytes, int tid, int last) {
 #pragma unroll
-    for (int i = 0; i < NLOAD; ++i) src_off[i] = (uint32_t)(((int64_t)row(i, tid) * kst + col8(i, tid)) * 2);
+    for (int i = 0; i < NLOAD; ++i) src_off[i] = (uint32_t)((int64_t)row(i, tid) * row_stride_bytes + piece(i, tid, last) * 16);
   }
 };
 
-template <int D, int NT, bool FULL>
-__device__ __forceinline__ void issue_tile_loads_impl(const TilePieces<D, NT>& tp,
-                                                      const __bf16* __restrict__ kg, int64_t kst, int key0,
-                                                      int N, __bf16* __restrict__ lds_buf, int tid) {
-  constexpr int NLOAD = TilePieces<D, NT>::NLOAD;
+// kg, rsb: first key of the KV head and the key stride in bytes.
+template <int P, int NT, bool FULL>
+__device__ __forceinline__ void issue_tile_loads_impl(const TilePieces<P, NT>& tp, const char* __restrict__ kg,
+                                                      int64_t rsb, int key0, int N, int last_piece,
+                                                      Piece* __restrict__ lds_buf, int tid) {
+  constexpr int NLOAD = TilePieces<P, NT>::NLOAD;
   const int wave_slot0 = __builtin_amdgcn_readfirstlane(tid) & ~63;
   if (wave_slot0 >= NT) return;                         // not a loading wavefront (wave-uniform)
-  const char* tile_base = reinterpret_cast<const char*>(kg + (int64_t)key0 * kst);   // uniform
+  const char* tile_base = kg + (int64_t)key0 * rsb;     // uniform
   if (FULL) {
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
       const char* src = tile_base + tp.src_off[i];
-      __bf16* dst = lds_buf + (int64_t)(i * NT + wave_slot0) * 8;     // wave-uniform base
+      Piece* dst = lds_buf + (i * NT + wave_slot0);     // wave-uniform base
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                        (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
     }
@@ -97,9 +104,9 @@ __device__ __forceinline__ void issue_tile_loads_impl(const TilePieces<D, NT>& t
     const int last = N - 1 - key0;                        // last valid row of the tile
 #pragma unroll 1
     for (int i = 0; i < NLOAD; ++i) {
-      const int r = min(TilePieces<D, NT>::row(i, tid), last);
-      const char* src = tile_base + ((int64_t)r * kst + TilePieces<D, NT>::col8(i, tid)) * 2;
-      __bf16* dst = lds_buf + (int64_t)(i * NT + wave_slot0) * 8;
+      const int r = min(TilePieces<P, NT>::row(i, tid), last);
+      const char* src = tile_base + (int64_t)r * rsb + TilePieces<P, NT>::piece(i, tid, last_piece) * 16;
+      Piece* dst = lds_buf + (i * NT + wave_slot0);
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                        (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
     }
@@ -107,14 +114,13 @@ __device__ __forceinline__ void issue_tile_loads_impl(const TilePieces<D, NT>& t
 }
 
 // Full tiles take the precomputed offsets; only a tile that reaches past N pays for clamping.
-template <int D, int NT>
-__device__ __forceinline__ void issue_tile_loads(const TilePieces<D, NT>& tp, const __bf16* __restrict__ kg,
-                                                 int64_t kst, int key0, int N, __bf16* __restrict__ lds_buf,
-                                                 int tid) {
-  if (key0 + KT <= N)
-    issue_tile_loads_impl<D, NT, true>(tp, kg, kst, key0, N, lds_buf, tid);
+template <int P, int NT>
+__device__ __forceinline__ void issue_tile_loads(const TilePieces<P, NT>& tp, const char* __restrict__ kg, int64_t rsb,
+                                                 int key0, int N, int last_piece, Piece* __restrict__ lds_buf, int tid) {
+  if (key0 + key_tile<P>() <= N)
+    issue_tile_loads_impl<P, NT, true>(tp, kg, rsb, key0, N, last_piece, lds_buf, tid);
   else
-    issue_tile_loads_impl<D, NT, false>(tp, kg, kst, key0, N, lds_buf, tid);
+    issue_tile_loads_impl<P, NT, false>(tp, kg, rsb, key0, N, last_piece, lds_buf, tid);
 }
 
 // Wait until at most CNT of this wave's vector-memory operations (incl. its LDS-direct loads) are
@@ -131,16 +137,12 @@ __device__ __forceinline__ void wait_vmem() {
 }
 
 // Threads of an NW-wavefront workgroup that load the K tiles.
-template <int D, int NW>
+template <int P, int NW>
 constexpr int loader_threads() {
   int n = 64;
-  while (n * 2 <= NW * 64 && n * 2 <= KT * (D / 8)) n *= 2;
+  while (n * 2 <= NW * 64 && n * 2 <= key_tile<P>() * P) n *= 2;
   return n;
 }
-
-// Loads each loading wave issues per tile.
-template <int D, int NT>
-constexpr int tile_loads_per_wave() { return (KT * (D / 8)) / NT; }
 
 // Top-of-iteration wait: the current tile must have landed.  `younger` = tiles issued after it that
 // are still in flight (at most STAGES-2).  With a uniform per-wave load count those may stay
@@ -154,9 +156,9 @@ __device__ __forceinline__ void wait_younger(int younger) {
     else wait_younger<L, Y - 1>(younger);
   }
 }
-template <int D, int NT, int STAGES>
+template <int P, int NT, int STAGES>
 __device__ __forceinline__ void wait_tile(int younger) {
-  constexpr int L = tile_loads_per_wave<D, NT>();
+  constexpr int L = TilePieces<P, NT>::NLOAD;           // loads each loading wave issues per tile
   static_assert(STAGES >= 2, "ring depth");
   if constexpr (L > 0 && L * (STAGES - 2) < 64)
     wait_younger<L, STAGES - 2>(younger);
@@ -164,47 +166,60 @@ __device__ __forceinline__ void wait_tile(int younger) {
     wait_vmem<0>();
 }
 
-// K fragment of kstep ks for the 32-key sub-tile `sub`: lane (ln, half) holds key ln,
-// d = 16*ks + 8*half .. +8  (logical piece 2*ks + half, un-swizzled here).
-template <int D>
-__device__ __forceinline__ bf16x8 load_k_frag(const __bf16* buf, int sub, int ln, int half, int ks) {
-  constexpr int CPR = D / 8;
+// K fragment of step ks for the 32-key sub-tile `sub`: lane (ln, half) holds piece 2*ks + half of key
+// ln (un-swizzled here).  The query fragments hold the same pieces of their rows, so whatever elements
+// a step covers, both operands of its MFMAs cover the same ones.
+template <int P>
+__device__ __forceinline__ Piece load_k_frag(const Piece* buf, int sub, int ln, int half, int ks) {
   const int r = sub * 32 + ln;
-  const int cp = (2 * ks + half) ^ (r & (CPR - 1));
-  return *reinterpret_cast<const bf16x8*>(buf + (r * CPR + cp) * 8);
+  return buf[r * P + ((2 * ks + half) ^ (r & TilePieces<P, 64>::SWZ))];
 }
 
-// QK^T of one 32-key sub-tile against this wave's RB blocks of 32 query rows (d/16 chained MFMAs
+// One fragment step: a 32x32x16 bf16 MFMA, or the four 32x32x2 fp32 MFMAs whose two elements per row
+// are element i of the two lane halves' pieces.
+template <typename TE>
+__device__ __forceinline__ f32x16 mma_step(const Piece& a, const Piece& b, f32x16 acc) {
+  if constexpr (sizeof(TE) == 2) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+  } else {
+    const f32x4 av = __builtin_bit_cast(f32x4, a), bv = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv[i], acc, 0, 0, 0);
+    return acc;
+  }
+}
+
+// QK^T of one 32-key sub-tile against this wave's RB blocks of 32 query rows (P/2 chained steps
 // per block; every K fragment is read from LDS once and used for all RB blocks).
 // KEYS_ON_REGS: accumulator register axis = keys (pass 1), else = query rows (pass 2).
-template <int D, bool KEYS_ON_REGS, int RB>
-__device__ __forceinline__ void mma_subtile(const __bf16* __restrict__ buf, int sub, int ln, int half,
-                                            const bf16x8 (&qf)[RB][D / 16], f32x16 (&acc)[RB]) {
+template <typename TE, int P, bool KEYS_ON_REGS, int RB>
+__device__ __forceinline__ void mma_subtile(const Piece* __restrict__ buf, int sub, int ln, int half,
+                                            const Piece (&qf)[RB][P / 2], f32x16 (&acc)[RB]) {
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[rb][r] = 0.f;
 #pragma unroll
-  for (int ks = 0; ks < D / 16; ++ks) {
-    const bf16x8 kf = load_k_frag<D>(buf, sub, ln, half, ks);
+  for (int ks = 0; ks < P / 2; ++ks) {
+    const Piece kf = load_k_frag<P>(buf, sub, ln, half, ks);
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
-      acc[rb] = KEYS_ON_REGS ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[rb][ks], acc[rb], 0, 0, 0)
-                             : __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[rb][ks], kf, acc[rb], 0, 0, 0);
+      acc[rb] = KEYS_ON_REGS ? mma_step<TE>(kf, qf[rb][ks], acc[rb]) : mma_step<TE>(qf[rb][ks], kf, acc[rb]);
   }
 }
 
 // Query fragments of this wave's RB 32-row blocks (block rb = rows row0 + 32*rb ..): lane (ln, half)
-// holds row ln of each block, d = 16*ks + 8*half .. +8.
+// holds pieces 2*ks + half of row ln of each block; rows from m1 on and pieces from np on are zeros.
 #define ASL_LOAD_Q_FRAGS()                                                                        \
-  bf16x8 qf[RB][KS];                                                                              \
+  Piece qf[RB][KS];                                                                               \
   _Pragma("unroll") for (int rb = 0; rb < RB; ++rb) {                                             \
     const int qr_ = row0 + rb * 32 + ln;                                                          \
-    const __bf16* qg_ = q_obs + (int64_t)g * M * D + (int64_t)min(qr_, M - 1) * D + half * 8;     \
+    const Piece* qg_ = reinterpret_cast<const Piece*>(q_obs) + ((int64_t)g * M + min(qr_, m1 - 1)) * (PAD ? np : P); \
     _Pragma("unroll") for (int ks = 0; ks < KS; ++ks) {                                           \
-      uint4 raw_ = *reinterpret_cast<const uint4*>(qg_ + ks * 16);                                \
-      if (qr_ >= M) raw_ = make_uint4(0u, 0u, 0u, 0u);      /* padded rows: zero queries */       \
-      qf[rb][ks] = __builtin_bit_cast(bf16x8, raw_);                                              \
+      const int c_ = 2 * ks + half;                                                               \
+      Piece raw_ = qg_[PAD ? min(c_, np - 1) : c_];                                               \
+      if (qr_ >= m1 || (PAD && c_ >= np)) raw_ = Piece{0u, 0u, 0u, 0u};                           \
+      qf[rb][ks] = raw_;                                                                          \
     }                                                                                             \
   }
 
@@ -291,24 +306,25 @@ __device__ __forceinline__ void rowstats_fold(const f32x16 (&acc)[RB], bool need
 // One tile of pass 1: start the next tile's LDS-direct loads into `nxt`, then fold the tile in
 // `cur` into the running (max, sum).  The two LDS buffers are distinct restrict pointers so that
 // the compiler knows the fragment reads of `cur` need not wait for the loads into `nxt`.
-template <int D, int NT, int RB>
-__device__ __forceinline__ void rowstats_tile(const __bf16* __restrict__ cur, __bf16* __restrict__ nxt,
-                                              bool prefetch, const TilePieces<D, NT>& tp, const __bf16* __restrict__ kg, int64_t kst,
-                                              int prefetch_key0, int tile, int N, int T, const int (&wi)[RB], int tid, int ln,
-                                              int half, const bf16x8 (&qf)[RB][D / 16], float c1, float (&m_run)[RB],
-                                              float (&z_run)[RB]) {
-  if (prefetch) issue_tile_loads<D, NT>(tp, kg, kst, prefetch_key0, N, nxt, tid);
+template <typename TE, int P, int NT, int RB>
+__device__ __forceinline__ void rowstats_tile(const Piece* __restrict__ cur, Piece* __restrict__ nxt,
+                                              bool prefetch, const TilePieces<P, NT>& tp, const char* __restrict__ kg, int64_t rsb,
+                                              int prefetch_key0, int last_piece, int tile, int N, int T, const int (&wi)[RB],
+                                              int tid, int ln, int half, const Piece (&qf)[RB][P / 2], float c1,
+                                              float (&m_run)[RB], float (&z_run)[RB]) {
+  constexpr int KT = key_tile<P>();
+  if (prefetch) issue_tile_loads<P, NT>(tp, kg, rsb, prefetch_key0, N, last_piece, nxt, tid);
   const int kbase = tile * KT;
   const bool need_mask = (kbase + KT > T);      // touches the window block or the tail past N
   // Software pipeline over the 32-key sub-tiles: the MFMAs of sub-tile s+1 are issued before
   // the softmax arithmetic of sub-tile s, so the matrix pipe and the vector ALU run side by side.
   f32x16 acc[RB];
-  mma_subtile<D, true, RB>(cur, 0, ln, half, qf, acc);
+  mma_subtile<TE, P, true, RB>(cur, 0, ln, half, qf, acc);
 #pragma unroll
   for (int sub = 0; sub < KT / 32; ++sub) {
     f32x16 nxt_acc[RB];
     if (sub + 1 < KT / 32) {
-      mma_subtile<D, true, RB>(cur, sub + 1, ln, half, qf, nxt_acc);
+      mma_subtile<TE, P, true, RB>(cur, sub + 1, ln, half, qf, nxt_acc);
     } else {
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) nxt_acc[rb] = acc[rb];
@@ -320,37 +336,40 @@ __device__ __forceinline__ void rowstats_tile(const __bf16* __restrict__ cur, __
 }
 
 // ---------------------------------------------------------------------------------------------
-// Pass 1: per-row running (max, sum) over this workgroup's key chunk, in the log2 domain.
+// Pass 1: per-row running (max, sum) over this workgroup's key chunk, in the log2 domain, for query
+// rows [m0, m1) of every KV head (m1 - m0 <= NW * 32 * RB).  ksh, kst: head and key strides in bytes.
 // row_part[((g*n_chunks + chunk)*M + row)*2 + {0,1}] = (m, z) with  sum_j 2^(c1*l_j) = z * 2^m.
-template <int D, int NW, int RB>
+template <typename TE, int P, int NW, int RB, bool PAD>
 __global__ void __launch_bounds__(NW * 64)
-score_rowstats_kernel(const __bf16* __restrict__ q_obs, const __bf16* __restrict__ k, int64_t ksh,
-                      int64_t kst, int Hk, int M, int W, int N, int n_cu, int n_chunks,
+score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, int64_t ksh,
+                      int64_t kst, int np, int Hk, int M, int m0, int m1, int W, int N, int n_cu, int n_chunks,
                       float c1, float* __restrict__ row_part) {
-  constexpr int NT = loader_threads<D, NW>();      // threads that load the K tiles
-  constexpr int KS = D / 16;
-  constexpr int TILE_ELEMS = KT * D;
+  constexpr int NT = loader_threads<P, NW>();      // threads that load the K tiles
+  constexpr int KS = P / 2, KT = key_tile<P>();
+  constexpr int TILE_ELEMS = KT * P;
   constexpr int STAGES = ring_stages<RB>();
-  __shared__ __attribute__((aligned(16))) __bf16 lds_k[STAGES * TILE_ELEMS];
+  __shared__ Piece lds_k[STAGES * TILE_ELEMS];
 
   const int g = blockIdx.x % Hk, chunk = blockIdx.x / Hk;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, ln = lane & 31, half = lane >> 5;
   const int T = N - W;
-  const int row0 = wave * 32 * RB;              // first query row of this wave
+  const int row0 = m0 + wave * 32 * RB;         // first query row of this wave
+  const int last_piece = PAD ? np - 1 : P - 1;
   int wi[RB];                                   // window row of this lane's query row, per block
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) wi[rb] = (row0 + rb * 32 + ln) % W;
-  const __bf16* kg = k + (int64_t)g * ksh;
+  const char* kg = k + (int64_t)g * ksh;
   const ChunkRange cr = chunk_range(chunk, g, Hk, n_chunks, (N + KT - 1) / KT, n_cu);
   const int tile0 = cr.tile0, tile_end = cr.tile_end;
 
   ASL_LOAD_Q_FRAGS();
-  TilePieces<D, NT> tp;
-  tp.init(kst, tid);
+  TilePieces<P, NT> tp;
+  tp.init(kst, tid, last_piece);
   // prologue: STAGES-1 tiles in flight (after the Q loads, so the in-order wait counts line up)
 #pragma unroll
   for (int j = 0; j < STAGES - 1; ++j)
-    if (tile0 + j < tile_end) issue_tile_loads<D, NT>(tp, kg, kst, (tile0 + j) * KT, N, lds_k + j * TILE_ELEMS, tid);
+    if (tile0 + j < tile_end)
+      issue_tile_loads<P, NT>(tp, kg, kst, (tile0 + j) * KT, N, last_piece, lds_k + j * TILE_ELEMS, tid);
 
   float m_run[RB], z_run[RB];
 #pragma unroll
@@ -360,12 +379,12 @@ score_rowstats_kernel(const __bf16* __restrict__ q_obs, const __bf16* __restrict
   }
   int stage = 0;                                  // buffer that holds tile `tile`
   for (int tile = tile0; tile < tile_end; ++tile) {
-    wait_tile<D, NT, STAGES>(min(STAGES - 2, tile_end - 1 - tile));
+    wait_tile<P, NT, STAGES>(min(STAGES - 2, tile_end - 1 - tile));
     __syncthreads();      // tile `tile` has landed for every wave; the buffer of tile-1 is free again
     const int free_stage = (stage == 0) ? STAGES - 1 : stage - 1;
-    rowstats_tile<D, NT, RB>(lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS,
-                             tile + STAGES - 1 < tile_end, tp, kg, kst, (tile + STAGES - 1) * KT, tile, N, T, wi, tid,
-                             ln, half, qf, c1, m_run, z_run);
+    rowstats_tile<TE, P, NT, RB>(lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS,
+                                 tile + STAGES - 1 < tile_end, tp, kg, kst, (tile + STAGES - 1) * KT, last_piece, tile, N,
+                                 T, wi, tid, ln, half, qf, c1, m_run, z_run);
     stage = (stage + 1 == STAGES) ? 0 : stage + 1;
   }
 #pragma unroll
@@ -376,7 +395,7 @@ score_rowstats_kernel(const __bf16* __restrict__ q_obs, const __bf16* __restrict
     const float za = z_run[rb] * fast_exp2(m_run[rb] - m), zb = z_o * fast_exp2(m_o - m);
     const float z = (half == 0) ? (za + zb) : (zb + za);
     const int qrow = row0 + rb * 32 + ln;
-    if (half == 0 && qrow < M) {
+    if (half == 0 && qrow < m1) {
       float* dst = row_part + ((int64_t)(g * n_chunks + chunk) * M + qrow) * 2;
       dst[0] = m;
       dst[1] = z;
@@ -458,37 +477,42 @@ score_combine_kernel(const float* __restrict__ row_part, int Hk, int M, int n_ch
 
 // This lane's share of the column sums of one 32-key sub-tile (query rows on the accumulator's
 // register axis): the normalised probabilities of its 16 rows per block, added in a fixed order.
-template <int RB>
+// DENORM: probabilities below 2^-126 keep their (denormal) value instead of becoming zero.
+template <int RB, bool DENORM>
 __device__ __forceinline__ float colsum_fold(const f32x16 (&acc)[RB], const float (&rc)[RB][16], float c1) {
   float cs = 0.f;
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) cs += fast_exp2(fmaf(acc[rb][r], c1, -rc[rb][r]));
+    for (int r = 0; r < 16; ++r) {
+      const float x = fmaf(acc[rb][r], c1, -rc[rb][r]);
+      cs += DENORM ? exp2f(x) : fast_exp2(x);
+    }
   return cs;
 }
 
 // One tile of pass 2: start the next tile's loads into `nxt`, then the column partial sums of
 // this wave's 32*RB rows for the KT keys in `cur` (written to red_w[0..KT-1]).
-template <int D, int NT, int RB>
-__device__ __forceinline__ void colsum_tile(const __bf16* __restrict__ cur, __bf16* __restrict__ nxt,
-                                            bool prefetch, const TilePieces<D, NT>& tp, const __bf16* __restrict__ kg, int64_t kst,
-                                            int prefetch_key0, int N, int tid, int ln, int half,
-                                            const bf16x8 (&qf)[RB][D / 16], const float (&rc)[RB][16], float c1,
+template <typename TE, int P, int NT, int RB, bool DENORM>
+__device__ __forceinline__ void colsum_tile(const Piece* __restrict__ cur, Piece* __restrict__ nxt,
+                                            bool prefetch, const TilePieces<P, NT>& tp, const char* __restrict__ kg, int64_t rsb,
+                                            int prefetch_key0, int last_piece, int N, int tid, int ln, int half,
+                                            const Piece (&qf)[RB][P / 2], const float (&rc)[RB][16], float c1,
                                             float* __restrict__ red_w) {
-  if (prefetch) issue_tile_loads<D, NT>(tp, kg, kst, prefetch_key0, N, nxt, tid);
+  constexpr int KT = key_tile<P>();
+  if (prefetch) issue_tile_loads<P, NT>(tp, kg, rsb, prefetch_key0, N, last_piece, nxt, tid);
   f32x16 acc[RB];
-  mma_subtile<D, false, RB>(cur, 0, ln, half, qf, acc);
+  mma_subtile<TE, P, false, RB>(cur, 0, ln, half, qf, acc);
 #pragma unroll
   for (int sub = 0; sub < KT / 32; ++sub) {
     f32x16 nxt_acc[RB];
     if (sub + 1 < KT / 32) {
-      mma_subtile<D, false, RB>(cur, sub + 1, ln, half, qf, nxt_acc);   // overlaps the exps below
+      mma_subtile<TE, P, false, RB>(cur, sub + 1, ln, half, qf, nxt_acc);   // overlaps the exps below
     } else {
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) nxt_acc[rb] = acc[rb];
     }
-    const float cs = colsum_fold<RB>(acc, rc, c1);
+    const float cs = colsum_fold<RB, DENORM>(acc, rc, c1);
     const float other = __shfl_xor(cs, 32);
     if (half == 0) red_w[sub * 32 + ln] = cs + other;
 #pragma unroll
@@ -497,32 +521,34 @@ __device__ __forceinline__ void colsum_tile(const __bf16* __restrict__ cur, __bf
 }
 
 // ---------------------------------------------------------------------------------------------
-// Pass 2: u_group[g][j] = sum over the M rows of 2^(c1*l_rj - rc_r),  j < T,
+// Pass 2: u_group[g][j] = sum over query rows [m0, m1) of 2^(c1*l_rj - rc_r),  j < T,
 // rc_r = rc_mul * row_const[g*M + r]  (log2-domain offset that already contains log2 Z_r).
-template <int D, int NW, int RB>
+// From the second row group on (m0 > 0) the sum is added to what the launch before left there.
+template <typename TE, int P, int NW, int RB, bool PAD>
 __global__ void __launch_bounds__(NW * 64)
-score_colsum_kernel(const __bf16* __restrict__ q_obs, const __bf16* __restrict__ k, int64_t ksh,
-                    int64_t kst, int Hk, int M, int N, int T, int n_cu, float c1,
+score_colsum_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, int64_t ksh,
+                    int64_t kst, int np, int Hk, int M, int m0, int m1, int N, int T, int n_cu, float c1,
                     const float* __restrict__ row_const, float rc_mul, const float* __restrict__ row_part,
                     int n_parts, float* __restrict__ u_group) {
-  constexpr int NT = loader_threads<D, NW>();      // threads that load the K tiles
+  constexpr int NT = loader_threads<P, NW>();      // threads that load the K tiles
   constexpr int NTHREADS = NW * 64;
-  constexpr int KS = D / 16;
-  constexpr int TILE_ELEMS = KT * D;
+  constexpr int KS = P / 2, KT = key_tile<P>();
+  constexpr int TILE_ELEMS = KT * P;
   constexpr int STAGES = ring_stages<RB>();
-  __shared__ __attribute__((aligned(16))) __bf16 lds_k[STAGES * TILE_ELEMS];
+  __shared__ Piece lds_k[STAGES * TILE_ELEMS];
   __shared__ float red[2][NW][KT];              // per-wave column partials, double-buffered
 
   const int g = blockIdx.x % Hk, chunk = blockIdx.x / Hk;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, ln = lane & 31, half = lane >> 5;
-  const int row0 = wave * 32 * RB;              // first query row of this wave
-  const __bf16* kg = k + (int64_t)g * ksh;
+  const int row0 = m0 + wave * 32 * RB;         // first query row of this wave
+  const int last_piece = PAD ? np - 1 : P - 1;
+  const char* kg = k + (int64_t)g * ksh;
   const ChunkRange cr = chunk_range(chunk, g, Hk, (int)(gridDim.x / Hk), (T + KT - 1) / KT, n_cu);
   const int tile0 = cr.tile0, tile_end = cr.tile_end;
 
   ASL_LOAD_Q_FRAGS();
-  TilePieces<D, NT> tp;
-  tp.init(kst, tid);
+  TilePieces<P, NT> tp;
+  tp.init(kst, tid, last_piece);
   // The chunk is walked from its last tile to its first: pass 1 walked it first to last, so the
   // tiles read most recently (still in the last-level cache) are the ones this pass reads first.
   const int n_my = max(tile_end - tile0, 0);
@@ -530,7 +556,8 @@ score_colsum_kernel(const __bf16* __restrict__ q_obs, const __bf16* __restrict__
   // hides behind the first tiles' (later loads complete later: the counted waits below stay valid)
 #pragma unroll
   for (int j = 0; j < STAGES - 1; ++j)
-    if (j < n_my) issue_tile_loads<D, NT>(tp, kg, kst, (tile_end - 1 - j) * KT, N, lds_k + j * TILE_ELEMS, tid);
+    if (j < n_my)
+      issue_tile_loads<P, NT>(tp, kg, kst, (tile_end - 1 - j) * KT, N, last_piece, lds_k + j * TILE_ELEMS, tid);
 
   // Log2-domain softmax offsets of this lane's accumulator rows: from the caller's log-sum-exp
   // (row_const, scaled by rc_mul), or folded here from pass 1's per-chunk partials (row_part).
@@ -542,7 +569,7 @@ score_colsum_kernel(const __bf16* __restrict__ q_obs, const __bf16* __restrict__
     const float2* ps[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
-      ps[rb] = reinterpret_cast<const float2*>(row_part) + (int64_t)g * n_parts * M + min(row0 + rb * 32 + ln, M - 1);
+      ps[rb] = reinterpret_cast<const float2*>(row_part) + (int64_t)g * n_parts * M + min(row0 + rb * 32 + ln, m1 - 1);
     combine_rows<RB, (RB == 1 ? 48 : 32)>(reinterpret_cast<const float2* const (&)[RB]>(ps), M, n_parts, half, mine);
   }
 #pragma unroll
@@ -554,8 +581,8 @@ score_colsum_kernel(const __bf16* __restrict__ q_obs, const __bf16* __restrict__
       if (row_part != nullptr)
         v = __shfl(mine[rb], acc_row(r, half));         // lanes 0..31 hold rows 0..31 of the block
       else
-        v = row_const[(int64_t)g * M + min(row, M - 1)] * rc_mul;
-      rc[rb][r] = (row < M) ? v : INFINITY;              // padded rows add 2^-inf = 0
+        v = row_const[(int64_t)g * M + min(row, m1 - 1)] * rc_mul;
+      rc[rb][r] = (row < m1) ? v : INFINITY;             // padded rows add 2^-inf = 0
     }
   }
   // sum the waves' partials of one finished tile in a fixed order and store the past columns
@@ -564,20 +591,23 @@ score_colsum_kernel(const __bf16* __restrict__ q_obs, const __bf16* __restrict__
       float s = red[buf_idx][0][j];
 #pragma unroll
       for (int w = 1; w < NW; ++w) s += red[buf_idx][w][j];
-      if (kbase + j < T) u_group[(int64_t)g * T + kbase + j] = s;
+      if (kbase + j < T) {
+        float* dst = u_group + (int64_t)g * T + kbase + j;
+        *dst = (m0 > 0) ? *dst + s : s;
+      }
     }
   };
 
   int stage = 0;                                  // buffer that holds the current tile
   for (int it = 0; it < n_my; ++it) {
     const int tile = tile_end - 1 - it;
-    wait_tile<D, NT, STAGES>(min(STAGES - 2, n_my - 1 - it));
+    wait_tile<P, NT, STAGES>(min(STAGES - 2, n_my - 1 - it));
     __syncthreads();      // the tile has landed; previous tile's fragment reads and partials are done
     if (it > 0) reduce_store((it - 1) & 1, (tile + 1) * KT);
     const int free_stage = (stage == 0) ? STAGES - 1 : stage - 1;
-    colsum_tile<D, NT, RB>(lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS, it + STAGES - 1 < n_my,
-                           tp, kg, kst, (tile - (STAGES - 1)) * KT, N, tid, ln, half, qf, rc, c1,
-                           &red[it & 1][wave][0]);
+    colsum_tile<TE, P, NT, RB, PAD>(lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS, it + STAGES - 1 < n_my,
+                                    tp, kg, kst, (tile - (STAGES - 1)) * KT, last_piece, N, tid, ln, half, qf, rc, c1,
+                                    &red[it & 1][wave][0]);
     stage = (stage + 1 == STAGES) ? 0 : stage + 1;
   }
   if (n_my > 0) {
@@ -587,8 +617,8 @@ score_colsum_kernel(const __bf16* __restrict__ q_obs, const __bf16* __restrict__
 }
 
 // ---------------------------------------------------------------------------------------------
-// Generic path (any d, any M, fp32 or bf16 storage, plain fp32 FMA): small shapes and the on-GPU
-// cross-check of the MFMA path.
+// Generic path (any d, any M, fp32 or bf16 storage, plain fp32 FMA): rows that are no whole 16-byte pieces
+// or longer than 256 elements, and the on-GPU cross-check of the MFMA path.
 template <typename TIn> __device__ __forceinline__ float ldf(const TIn* p);
 template <> __device__ __forceinline__ float ldf<float>(const float* p) { return *p; }
 template <> __device__ __forceinline__ float ldf<__bf16>(const __bf16* p) { return (float)*p; }
@@ -659,8 +689,8 @@ score_colsum_generic(const TIn* __restrict__ q_obs, const TIn* __restrict__ k, i
 }
 
 // ---------------------------------------------------------------------------------------------
-// Largest number of query rows per KV head (G*W) the MFMA kernels take: eight wavefronts of two
-// 32-row blocks.
+// Largest number of query rows per KV head (G*W) one launch of the MFMA kernels takes: eight
+// wavefronts of two 32-row blocks.
 constexpr int kMaxMfmaRows = 512;
 
 bool score_mfma_supported(const asl_params& p) {
@@ -682,9 +712,9 @@ static int device_cu_count() {
 
 // Key chunks per KV head for a pass whose kernel fits `resident` workgroups per compute unit: one
 // resident round of workgroups, so that no second, partly filled round trails behind.
-static int score_chunks(const asl_params& p, int resident) {
+static int score_chunks(const asl_params& p, int kt, int resident) {
   const int target = device_cu_count() * resident;
-  const int n_tiles = (p.seq_len + KT - 1) / KT;
+  const int n_tiles = (p.seq_len + kt - 1) / kt;
   int want = target / p.n_kv_heads;
   if (want > kMaxChunks) want = kMaxChunks;
   if (want > n_tiles) want = n_tiles;
@@ -704,23 +734,27 @@ static int resident_per_cu(K kernel, int threads, size_t dynamic_lds = 0) {
   return n;
 }
 
-template <int D, int NW, int RB>
-static hipError_t launch_score_mfma(const asl_params& p, const Workspace& ws, const __bf16* q,
-                                    const __bf16* k, const float* lse, float* lse_out, float c1,
-                                    hipStream_t st) {
+template <typename TE, int P, int NW, int RB, bool PAD>
+static hipError_t launch_score_mfma(const asl_params& p, const Workspace& ws, const void* q_obs, const void* k_ptr,
+                                    const float* lse, float* lse_out, float c1, hipStream_t st) {
+  constexpr int KT = key_tile<P>(), kRows = NW * 32 * RB;
   const int Hk = p.n_kv_heads, M = (p.n_q_heads / Hk) * p.window, N = p.seq_len, T = N - p.window;
+  const char *q = static_cast<const char*>(q_obs), *k = static_cast<const char*>(k_ptr);
+  const int64_t ksh = p.k_stride_head * (int64_t)sizeof(TE), kst = p.k_stride_tok * (int64_t)sizeof(TE);
+  const int np = p.head_dim * (int)sizeof(TE) / 16;
   // both passes use the same LDS ring and nearly the same registers; take the smaller residency
   static const int resident = [] {
-    const int a = resident_per_cu(score_rowstats_kernel<D, NW, RB>, NW * 64);
-    const int b = resident_per_cu(score_colsum_kernel<D, NW, RB>, NW * 64);
+    const int a = resident_per_cu(score_rowstats_kernel<TE, P, NW, RB, PAD>, NW * 64);
+    const int b = resident_per_cu(score_colsum_kernel<TE, P, NW, RB, PAD>, NW * 64);
     return a < b ? a : b;
   }();
-  const int n_chunks = score_chunks(p, resident);
+  const int n_chunks = score_chunks(p, KT, resident);
   const int n_cu = device_cu_count();
   if (!lse) {
-    ASL_LAUNCH(ws.prof, kKernRowstats, st, (score_rowstats_kernel<D, NW, RB>), dim3(Hk * n_chunks), dim3(NW * 64), 0, st, q, k,
-                       p.k_stride_head, p.k_stride_tok, Hk, M, p.window, N, n_cu, n_chunks, c1,
-                       ws.row_part);
+    for (int m0 = 0; m0 < M; m0 += kRows)
+      ASL_LAUNCH(ws.prof, kKernRowstats, st, (score_rowstats_kernel<TE, P, NW, RB, PAD>), dim3(Hk * n_chunks), dim3(NW * 64), 0,
+                 st, q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, p.window, N, n_cu, n_chunks, c1,
+                 ws.row_part);
     if (lse_out) {                                 // only the row normalisers were asked for
       const int rows = Hk * M;
       ASL_LAUNCH(ws.prof, kKernCombine, st, score_combine_kernel, dim3((rows + 127) / 128), dim3(256), 0, st, ws.row_part,
@@ -731,33 +765,72 @@ static hipError_t launch_score_mfma(const asl_params& p, const Workspace& ws, co
   const int n_tiles2 = (T + KT - 1) / KT;
   const int n_chunks2 = n_chunks < n_tiles2 ? n_chunks : n_tiles2;
   // without the caller's log-sum-exp every pass-2 workgroup folds pass 1's partials of its own rows
-  ASL_LAUNCH(ws.prof, kKernColsum, st, (score_colsum_kernel<D, NW, RB>), dim3(Hk * n_chunks2), dim3(NW * 64), 0, st, q, k,
-                     p.k_stride_head, p.k_stride_tok, Hk, M, N, T, n_cu, c1,
-                     lse, kLog2e, lse ? nullptr : ws.row_part, n_chunks, ws.u_group);
+  for (int m0 = 0; m0 < M; m0 += kRows)
+    ASL_LAUNCH(ws.prof, kKernColsum, st, (score_colsum_kernel<TE, P, NW, RB, PAD>), dim3(Hk * n_chunks2), dim3(NW * 64), 0, st,
+               q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, N, T, n_cu, c1, lse, kLog2e,
+               lse ? nullptr : ws.row_part, n_chunks, ws.u_group);
   return hipGetLastError();
 }
 
-// Wavefronts and 32-row blocks per wavefront for M query rows per KV head: one block per wavefront
-// up to 128 rows; two above, with ceil(M / 64) wavefronts (up to eight, M <= 512).
-template <int D>
-static hipError_t dispatch_nw(int M, const asl_params& p, const Workspace& ws, const __bf16* q,
-                              const __bf16* k, const float* lse, float* lse_out, float c1, hipStream_t st) {
+// Wavefronts and 32-row blocks per wavefront for M query rows per KV head (bf16, d = 8 P): one block per
+// wavefront up to 128 rows; two above, with ceil(M / 64) wavefronts (up to eight: more than 512 rows
+// take several launches of 512).
+template <int P>
+static hipError_t dispatch_nw(int M, const asl_params& p, const Workspace& ws, const void* q,
+                              const void* k, const float* lse, float* lse_out, float c1, hipStream_t st) {
   if (M <= 128) {
     switch ((M + 31) / 32) {
-      case 1: return launch_score_mfma<D, 1, 1>(p, ws, q, k, lse, lse_out, c1, st);
-      case 2: return launch_score_mfma<D, 2, 1>(p, ws, q, k, lse, lse_out, c1, st);
-      case 3: return launch_score_mfma<D, 3, 1>(p, ws, q, k, lse, lse_out, c1, st);
-      default: return launch_score_mfma<D, 4, 1>(p, ws, q, k, lse, lse_out, c1, st);
+      case 1: return launch_score_mfma<__bf16, P, 1, 1, false>(p, ws, q, k, lse, lse_out, c1, st);
+      case 2: return launch_score_mfma<__bf16, P, 2, 1, false>(p, ws, q, k, lse, lse_out, c1, st);
+      case 3: return launch_score_mfma<__bf16, P, 3, 1, false>(p, ws, q, k, lse, lse_out, c1, st);
+      default: return launch_score_mfma<__bf16, P, 4, 1, false>(p, ws, q, k, lse, lse_out, c1, st);
     }
   }
   switch ((M + 63) / 64) {
-    case 3: return launch_score_mfma<D, 3, 2>(p, ws, q, k, lse, lse_out, c1, st);
-    case 4: return launch_score_mfma<D, 4, 2>(p, ws, q, k, lse, lse_out, c1, st);
-    case 5: return launch_score_mfma<D, 5, 2>(p, ws, q, k, lse, lse_out, c1, st);
-    case 6: return launch_score_mfma<D, 6, 2>(p, ws, q, k, lse, lse_out, c1, st);
-    case 7: return launch_score_mfma<D, 7, 2>(p, ws, q, k, lse, lse_out, c1, st);
-    default: return launch_score_mfma<D, 8, 2>(p, ws, q, k, lse, lse_out, c1, st);
+    case 3: return launch_score_mfma<__bf16, P, 3, 2, false>(p, ws, q, k, lse, lse_out, c1, st);
+    case 4: return launch_score_mfma<__bf16, P, 4, 2, false>(p, ws, q, k, lse, lse_out, c1, st);
+    case 5: return launch_score_mfma<__bf16, P, 5, 2, false>(p, ws, q, k, lse, lse_out, c1, st);
+    case 6: return launch_score_mfma<__bf16, P, 6, 2, false>(p, ws, q, k, lse, lse_out, c1, st);
+    case 7: return launch_score_mfma<__bf16, P, 7, 2, false>(p, ws, q, k, lse, lse_out, c1, st);
+    case 8: return launch_score_mfma<__bf16, P, 8, 2, false>(p, ws, q, k, lse, lse_out, c1, st);
+    default: return launch_score_mfma<__bf16, P, 8, 2, true>(p, ws, q, k, lse, lse_out, c1, st);
   }
+}
+
+// The other row lengths and fp32.  Latency-bound at ordinary sizes; the plain kernels, which this replaced
+// for whole-piece rows, walk M rows x d elements one after the other per key: fp32 Hq4/Hk2/d64, N = 512,
+// W = 16: 247 + 6.5 us, here 4.5 + 4.5; bf16 Hq8/Hk4/d256, N = 8192, W = 32: 2104 + 177 us, here ~10 + ~10
+// (the whole call 2274 -> 25.5 us).  fp32 MFMA multiplies and adds in full fp32.
+// np pieces of a row in the next longer of the built row lengths P; one
+// 32-row block per wavefront, up to 128 query rows per launch.
+template <typename TE, int P>
+static hipError_t dispatch_padded_nw(int M, const asl_params& p, const Workspace& ws, const void* q,
+                                     const void* k, const float* lse, float* lse_out, float c1, hipStream_t st) {
+  if (M <= 32) return launch_score_mfma<TE, P, 1, 1, true>(p, ws, q, k, lse, lse_out, c1, st);
+  if (M <= 64) return launch_score_mfma<TE, P, 2, 1, true>(p, ws, q, k, lse, lse_out, c1, st);
+  return launch_score_mfma<TE, P, 4, 1, true>(p, ws, q, k, lse, lse_out, c1, st);
+}
+template <typename TE>
+static hipError_t dispatch_padded(int M, const asl_params& p, const Workspace& ws, const void* q,
+                                  const void* k, const float* lse, float* lse_out, float c1, hipStream_t st) {
+  const int np = p.head_dim * (int)sizeof(TE) / 16;
+  if (np <= 8) return dispatch_padded_nw<TE, 8>(M, p, ws, q, k, lse, lse_out, c1, st);
+  if (np <= 16) return dispatch_padded_nw<TE, 16>(M, p, ws, q, k, lse, lse_out, c1, st);
+  if (np <= 24) return dispatch_padded_nw<TE, 24>(M, p, ws, q, k, lse, lse_out, c1, st);
+  if constexpr (sizeof(TE) == 4) {
+    if (np > 48) return dispatch_padded_nw<TE, 64>(M, p, ws, q, k, lse, lse_out, c1, st);
+    if (np > 32) return dispatch_padded_nw<TE, 48>(M, p, ws, q, k, lse, lse_out, c1, st);
+  }
+  return dispatch_padded_nw<TE, 32>(M, p, ws, q, k, lse, lse_out, c1, st);
+}
+
+// Whether the MFMA kernels can read these operands: whole 16-byte pieces on 16-byte boundaries, rows
+// of at most 256 elements, and a tile's rows within the loader's 32-bit byte offsets.
+static bool mfma_takes(const asl_params& p, const void* q_obs, const void* k) {
+  const int64_t eb = p.dtype == ASL_BF16 ? 2 : 4;
+  const int64_t low = reinterpret_cast<intptr_t>(q_obs) | reinterpret_cast<intptr_t>(k) | (p.head_dim * eb) |
+                      (p.k_stride_tok * eb) | (p.k_stride_head * eb);
+  return (low & 15) == 0 && p.head_dim <= 256 && p.k_stride_tok * eb * 64 < (int64_t(1) << 32);
 }
 
 template <typename TIn>
@@ -785,11 +858,14 @@ hipError_t launch_score(const asl_params& p, const Workspace& ws, const void* q_
   const float scale = p.scale > 0.f ? p.scale : 1.0f / sqrtf((float)p.head_dim);
   const float c1 = scale * kLog2e;
   const int M = (p.n_q_heads / p.n_kv_heads) * p.window;
-  if (score_mfma_supported(p) && !(p.flags & ASL_FLAG_GENERIC_SCORE)) {
-    const __bf16* q = static_cast<const __bf16*>(q_obs);
-    const __bf16* kk = static_cast<const __bf16*>(k);
-    return p.head_dim == 128 ? dispatch_nw<128>(M, p, ws, q, kk, lse, lse_out, c1, st)
-                             : dispatch_nw<64>(M, p, ws, q, kk, lse, lse_out, c1, st);
+  if (!(p.flags & ASL_FLAG_GENERIC_SCORE)) {
+    const bool takes = mfma_takes(p, q_obs, k);
+    if (score_mfma_supported(p) || (takes && p.dtype == ASL_BF16 && (p.head_dim == 64 || p.head_dim == 128)))
+      return p.head_dim == 128 ? dispatch_nw<16>(M, p, ws, q_obs, k, lse, lse_out, c1, st)
+                               : dispatch_nw<8>(M, p, ws, q_obs, k, lse, lse_out, c1, st);
+    if (takes)
+      return p.dtype == ASL_BF16 ? dispatch_padded<__bf16>(M, p, ws, q_obs, k, lse, lse_out, c1, st)
+                                 : dispatch_padded<float>(M, p, ws, q_obs, k, lse, lse_out, c1, st);
   }
   if (p.dtype == ASL_BF16)
     return launch_score_generic<__bf16>(p, ws, static_cast<const __bf16*>(q_obs),

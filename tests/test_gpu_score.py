@@ -75,6 +75,58 @@ def test_other_head_dims_take_the_plain_kernels(gpu_device, d, dtype):
     _compare(gpu_device, _small(4, 2, d, 700, 8, dtype=dtype, seed=d))
 
 
+def _close_to_64_bits(P, s, L):
+    """Tighter than the score tolerance: a logit's error is a few 2^-24 of the sum of its |products| (below
+    20 in base 2 for these inputs), so a probability is within 2e-5 of itself however the sums are ordered."""
+    P_ref, s_ref = orc.score_layer(L.q_obs, L.k, L.shape.W, L.shape.S)
+    np.testing.assert_allclose(P, P_ref, rtol=2e-5, atol=1e-12)
+    np.testing.assert_allclose(s, s_ref, rtol=2e-5, atol=1e-12)
+
+
+# Row lengths around the built ones (128, 256, 384, 512, 768 and 1024 bytes): shorter by one 16-byte
+# piece, full, longer by one; row lengths with no whole pieces (bf16 d = 20, fp32 d = 30) and beyond 256
+# elements stay with the plain kernels.  Key counts at and around the 32- and 64-key tiles.
+@pytest.mark.parametrize("dtype,d", [("bf16", d) for d in (8, 56, 72, 80, 96, 120, 136, 192, 200, 248, 256, 264, 20)] +
+                         [("f32", d) for d in (4, 28, 32, 36, 64, 68, 96, 100, 128, 132, 192, 196, 256, 260, 30)])
+def test_row_lengths(gpu_device, dtype, d):
+    for i, (Hq, Hk, W, N) in enumerate([(4, 2, 16, 512), (3, 1, 13, 97 + d), (5, 1, 64, 32 * 9 + 64), (2, 2, 1, 2)]):
+        L = _small(Hq, Hk, d, N, W, dtype=dtype, seed=d + i)
+        print(f"{dtype} d={d} {L.name}", flush=True)
+        P, s = _run_score(gpu_device, L)
+        _close_to_64_bits(P, s, L)
+        _compare(gpu_device, L, use_lse=True)
+
+
+@pytest.mark.parametrize("Hq,Hk,d,W,dtype", [(16, 1, 128, 48, "bf16"), (33, 1, 64, 16, "bf16"), (9, 1, 256, 64, "bf16"),
+                                             (10, 2, 128, 64, "f32")])
+def test_row_groups(gpu_device, Hq, Hk, d, W, dtype):
+    """More query rows per KV head than one launch takes (512 for bf16 with d in {64, 128}, else 128): 768,
+    528, 576 and 320 rows, the last group partly filled."""
+    L = _small(Hq, Hk, d, 1500 + Hq, W, dtype=dtype, seed=Hq)
+    P, s = _run_score(gpu_device, L)
+    _close_to_64_bits(P, s, L)
+    _compare(gpu_device, L, use_lse=True)
+
+
+def test_misaligned_rows_stay_with_the_plain_kernels(gpu_device):
+    """fp32 K one element off a 16-byte boundary, and with a token stride of d + 1."""
+    import torch
+    L = _small(4, 2, 64, 300, 16, dtype="f32", seed=9)
+    sh = L.shape
+    ctx = gu.ctx_for(sh)
+    P = torch.empty((sh.Hk, sh.T), dtype=torch.float32, device=gpu_device)
+    s = torch.empty((sh.T,), dtype=torch.float32, device=gpu_device)
+    q, k = gu.to_dev(L.q_obs, "f32", gpu_device), gu.to_dev(L.k, "f32", gpu_device)
+    for off, st in ((1, sh.d), (0, sh.d + 1), (3, sh.d + 4)):
+        buf = torch.zeros(off + sh.Hk * sh.N * st, device=gpu_device)
+        kv = buf[off:].view(sh.Hk, sh.N, st)[:, :, :sh.d]
+        kv.copy_(k)
+        p = asl.make_params(sh.Hq, sh.Hk, sh.d, sh.N, sh.W, sh.S, sh.budget, dtype=asl.ASL_F32, k_strides=(sh.N * st, st))
+        ctx.asl_score_layer(p, q, kv, P, s)
+        _close_to_64_bits(P.cpu().numpy(), s.cpu().numpy(), L)
+    ctx.close()
+
+
 def test_random_shapes(gpu_device):
     """Sixteen seeded random shapes: group sizes 1-8, windows 1-64 (M = G*W up to 256, so both the
     one-block and the two-block wavefront layouts and every wavefront count occur), d in {64, 128},
