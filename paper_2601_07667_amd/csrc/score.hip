@@ -9,11 +9,13 @@
 //
 // Work split: a workgroup owns one KV head and a contiguous chunk of keys; wave w owns RB blocks of
 // 32 query rows (RB = 1 up to M = 128 rows, 2 above) and keeps their bf16 fragments in registers for
-// the whole kernel; K tiles of 64 keys stream global -> LDS directly (ring of 3-4 buffers,
+// the whole kernel; K tiles of 64 keys stream global -> LDS directly (ring of 3 buffers,
 // XOR-swizzled) and every wave reads all of them as the other MFMA operand
 // (v_mfma_f32_32x32x16_bf16), each fragment once for all its row blocks.  Pass 1 puts keys on the
 // accumulator's register axis (row statistics reduce in-lane), pass 2 puts query rows there
 // (column sums reduce in-lane).  All reductions have a fixed order: results are deterministic.
+#include <type_traits>
+
 #include "asl_internal.h"
 
 namespace asl {
@@ -30,13 +32,10 @@ typedef uint32_t Piece __attribute__((ext_vector_type(4)));
 // Keys per LDS tile (a multiple of 32): tiles of at most 16 KB up to 512-byte rows, so that three
 // workgroups' rings fit a compute unit.
 template <int P> constexpr int key_tile() { return P <= 16 ? 64 : 32; }
-#ifndef ASL_SCORE_STAGES_RB2
-#define ASL_SCORE_STAGES_RB2 4
-#endif
-// LDS tile buffers of the K ring: STAGES-1 tiles in flight while one is consumed.  RB = 32-row query
-// blocks per wavefront: 1 for M <= 128 query rows (three workgroups per compute unit), 2 above
-// (two larger workgroups per compute unit, hence a deeper ring each).
-template <int RB> constexpr int ring_stages() { return RB > 1 ? ASL_SCORE_STAGES_RB2 : ASL_SCORE_STAGES; }
+// LDS tile buffers of the K ring: STAGES-1 tiles in flight while one is consumed (four or more: the same
+// or slower, the longer prologue costs what the depth gains).  RB = 32-row query blocks per wavefront: 1
+// for M <= 128 query rows, 2 above.
+constexpr int kStages = ASL_SCORE_STAGES;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kNegBig = -1.0e30f;           // finite stand-in for "no maximum yet"
@@ -225,41 +224,28 @@ __device__ __forceinline__ void mma_subtile(const Piece* __restrict__ buf, int s
 
 
 // Share of the key tiles a workgroup takes.  All workgroups of a pass are resident at once (one
-// round), block b being the (b / n_cu)-th workgroup placed on its compute unit; on this part the
-// first-placed workgroup of a compute unit progresses fastest and the last-placed slowest
-// (measured finish times 0.70 : 0.85 : 0.98 of the kernel with three per unit, 0.76 : 0.98 with two).
-// With three per unit (M <= 128) the kernels are bound by the unit's share of the HBM stream and
-// weighting the shares does not shorten them, so the weights are equal; with two per unit (M > 128)
-// the arithmetic is not hidden any more, the second workgroup ends up alone on its unit for the last
-// quarter of the kernel, and giving the first one a larger share is worth 4-5 %.  Weights in 1/1024,
-// tunable at build time.
-#ifndef ASL_SCORE_W3
-#define ASL_SCORE_W3 1024, 1024, 1024
-#endif
-#ifndef ASL_SCORE_W2
-#define ASL_SCORE_W2 1250, 798
-#endif
+// round), block b being the (b / n_cu)-th workgroup placed on its compute unit.  A unit's older wavefronts
+// go first, so with two workgroups per unit the second ends up alone on it for the last part of the
+// kernel: the first gets a larger share, the more so the more the arithmetic bounds the kernel (pass 1 +
+// pass 2 at 256K, W = 64, RB = 2: equal shares 152 + 158 us, 1250 : 798 147 + 153, 1350 : 698 145 + 150;
+// 128K, RB = 1: 58 + 51, 55 + 50, 54 + 52).  Weights in 1/1024.
 struct ChunkRange {
   int tile0, tile_end;
 };
-__device__ __forceinline__ int pick3(int i, int a, int b, int c) { return i == 0 ? a : (i == 1 ? b : c); }
-__device__ __forceinline__ int pick2(int i, int a, int b) { return i == 0 ? a : b; }
 // Tiles [tile0, tile_end) of chunk `chunk` (0 .. n_chunks-1) of KV head g; the chunks of a head tile
-// [0, n_tiles) exactly, in order.  (Selects instead of indexed tables: no private memory.)
+// [0, n_tiles) exactly, in order.
+template <int RB>
 __device__ __forceinline__ ChunkRange chunk_range(int chunk, int g, int Hk, int n_chunks, int n_tiles, int n_cu) {
+  constexpr int kFirst = RB > 1 ? 1350 : 1250, kSecond = 2048 - kFirst;
   const int grid = n_chunks * Hk;
-  const int n_slots = (grid + n_cu - 1) / n_cu;
+  const bool two = grid > n_cu && grid <= 2 * n_cu;
   // cumulative weight of this head's chunks 0 .. c-1: chunk c' is block c'*Hk + g, placed as number
-  // (c'*Hk + g) / n_cu on its compute unit
+  // (c'*Hk + g) / n_cu on its compute unit; the first on it iff c' < ceil((n_cu - g) / Hk)
+  const int n_first = max((n_cu - g + Hk - 1) / Hk, 0);
   auto cum = [&](int c) -> int {
-    if (n_slots != 2 && n_slots != 3) return 1024 * c;
-    // chunks with (c'*Hk + g) < n_cu*(s+1)  <=>  c' < ceil((n_cu*(s+1) - g) / Hk)
-    const int u0 = min(max((n_cu - g + Hk - 1) / Hk, 0), c);
-    const int u1 = (n_slots == 2) ? c : min(max((2 * n_cu - g + Hk - 1) / Hk, u0), c);
-    const int w0 = (n_slots == 3) ? pick3(0, ASL_SCORE_W3) : pick2(0, ASL_SCORE_W2);
-    const int w1 = (n_slots == 3) ? pick3(1, ASL_SCORE_W3) : pick2(1, ASL_SCORE_W2);
-    const int w2 = pick3(2, ASL_SCORE_W3);
-    return w0 * u0 + w1 * (u1 - u0) + w2 * (c - u1);      // < 2^21 for n_chunks <= 256
+    if (!two) return 1024 * c;
+    const int u0 = min(n_first, c);
+    return kFirst * u0 + kSecond * (c - u0);              // < 2^21 for n_chunks <= 256
   };
   // Boundaries in fp32 (a 64-bit integer division would cost microseconds at the start of every
   // workgroup): neighbours evaluate the same expression on the same inputs, so their shared
@@ -277,15 +263,15 @@ __device__ __forceinline__ float max2(float a, float b) { return __builtin_fmaxf
 
 // Fold the logits of one 32-key sub-tile (keys on the accumulator's register axis; `key_lo` = key of
 // this lane's register 0) into the running (max, sum) of the lane's query row, per row block.
-template <int RB>
-__device__ __forceinline__ void rowstats_fold(const f32x16 (&acc)[RB], bool need_mask, int key_lo, int N, int T,
+template <int RB, bool MASK>
+__device__ __forceinline__ void rowstats_fold(const f32x16 (&acc)[RB], int key_lo, int N, int T,
                                               const int (&wi)[RB], float c1, float (&m_run)[RB], float (&z_run)[RB]) {
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     float x[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) x[r] = acc[rb][r];
-    if (need_mask) {
+    if (MASK) {
       // visible iff key < N and (key < T or key - T <= wi)  <=>  key < min(N, T + wi + 1)
       const int lim = min(N, T + wi[rb] + 1) - key_lo;
 #pragma unroll
@@ -303,33 +289,27 @@ __device__ __forceinline__ void rowstats_fold(const f32x16 (&acc)[RB], bool need
   }
 }
 
-// One tile of pass 1: start the next tile's LDS-direct loads into `nxt`, then fold the tile in
-// `cur` into the running (max, sum).  The two LDS buffers are distinct restrict pointers so that
-// the compiler knows the fragment reads of `cur` need not wait for the loads into `nxt`.
-template <typename TE, int P, int NT, int RB>
+// One tile of pass 1: start the next tile's LDS-direct loads into `nxt`, then work on the tile in
+// `cur`.  The two LDS buffers are distinct restrict pointers so that the compiler knows the fragment
+// reads of `cur` need not wait for the loads into `nxt`.
+// Software pipeline over the 32-key sub-tiles, across tile boundaries: the MFMAs of a sub-tile stand
+// in one block of straight-line code with the softmax arithmetic of the sub-tile before it (`acc`, the
+// last sub-tile of the tile before on entry), so that a wavefront's own vector instructions fill the
+// time its MFMAs take.  MASK: tiles that touch the window block or the tail past N (they come last).
+template <typename TE, int P, int NT, int RB, bool MASK>
 __device__ __forceinline__ void rowstats_tile(const Piece* __restrict__ cur, Piece* __restrict__ nxt,
                                               bool prefetch, const TilePieces<P, NT>& tp, const char* __restrict__ kg, int64_t rsb,
                                               int prefetch_key0, int last_piece, int tile, int N, int T, const int (&wi)[RB],
                                               int tid, int ln, int half, const Piece (&qf)[RB][P / 2], float c1,
-                                              float (&m_run)[RB], float (&z_run)[RB]) {
+                                              f32x16 (&acc)[RB], float (&m_run)[RB], float (&z_run)[RB]) {
   constexpr int KT = key_tile<P>();
   if (prefetch) issue_tile_loads<P, NT>(tp, kg, rsb, prefetch_key0, N, last_piece, nxt, tid);
-  const int kbase = tile * KT;
-  const bool need_mask = (kbase + KT > T);      // touches the window block or the tail past N
-  // Software pipeline over the 32-key sub-tiles: the MFMAs of sub-tile s+1 are issued before
-  // the softmax arithmetic of sub-tile s, so the matrix pipe and the vector ALU run side by side.
-  f32x16 acc[RB];
-  mma_subtile<TE, P, true, RB>(cur, 0, ln, half, qf, acc);
 #pragma unroll
   for (int sub = 0; sub < KT / 32; ++sub) {
     f32x16 nxt_acc[RB];
-    if (sub + 1 < KT / 32) {
-      mma_subtile<TE, P, true, RB>(cur, sub + 1, ln, half, qf, nxt_acc);
-    } else {
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) nxt_acc[rb] = acc[rb];
-    }
-    rowstats_fold<RB>(acc, need_mask, kbase + sub * 32 + 4 * half, N, T, wi, c1, m_run, z_run);
+    mma_subtile<TE, P, true, RB>(cur, sub, ln, half, qf, nxt_acc);
+    // the sub-tile before this one: keys (tile * KT + (sub - 1) * 32) + 4 * half ..
+    rowstats_fold<RB, MASK>(acc, tile * KT + (sub - 1) * 32 + 4 * half, N, T, wi, c1, m_run, z_run);
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) acc[rb] = nxt_acc[rb];
   }
@@ -347,7 +327,7 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
   constexpr int NT = loader_threads<P, NW>();      // threads that load the K tiles
   constexpr int KS = P / 2, KT = key_tile<P>();
   constexpr int TILE_ELEMS = KT * P;
-  constexpr int STAGES = ring_stages<RB>();
+  constexpr int STAGES = kStages;
   __shared__ Piece lds_k[STAGES * TILE_ELEMS];
 
   const int g = blockIdx.x % Hk, chunk = blockIdx.x / Hk;
@@ -359,7 +339,7 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) wi[rb] = (row0 + rb * 32 + ln) % W;
   const char* kg = k + (int64_t)g * ksh;
-  const ChunkRange cr = chunk_range(chunk, g, Hk, n_chunks, (N + KT - 1) / KT, n_cu);
+  const ChunkRange cr = chunk_range<RB>(chunk, g, Hk, n_chunks, (N + KT - 1) / KT, n_cu);
   const int tile0 = cr.tile0, tile_end = cr.tile_end;
 
   ASL_LOAD_Q_FRAGS();
@@ -377,16 +357,29 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
     m_run[rb] = kNegBig;
     z_run[rb] = 0.f;
   }
+  f32x16 acc[RB];                                 // "no sub-tile before the first": adds nothing
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[rb][r] = -INFINITY;
   int stage = 0;                                  // buffer that holds tile `tile`
-  for (int tile = tile0; tile < tile_end; ++tile) {
+  auto step = [&](int tile, auto mask) {
     wait_tile<P, NT, STAGES>(min(STAGES - 2, tile_end - 1 - tile));
     __syncthreads();      // tile `tile` has landed for every wave; the buffer of tile-1 is free again
     const int free_stage = (stage == 0) ? STAGES - 1 : stage - 1;
-    rowstats_tile<TE, P, NT, RB>(lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS,
-                                 tile + STAGES - 1 < tile_end, tp, kg, kst, (tile + STAGES - 1) * KT, last_piece, tile, N,
-                                 T, wi, tid, ln, half, qf, c1, m_run, z_run);
+    rowstats_tile<TE, P, NT, RB, decltype(mask)::value>(
+        lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS, tile + STAGES - 1 < tile_end, tp, kg, kst,
+        (tile + STAGES - 1) * KT, last_piece, tile, N, T, wi, tid, ln, half, qf, c1, acc, m_run, z_run);
     stage = (stage + 1 == STAGES) ? 0 : stage + 1;
-  }
+  };
+  // tiles of visible keys only, then those that touch the window block or the end (at most
+  // (W + KT - 1) / KT + 1 of a head's last tiles)
+  const int tile_mid = min(max(T / KT, tile0), tile_end);
+  int tile = tile0;
+  for (; tile < tile_mid; ++tile) step(tile, std::false_type());
+  for (; tile < tile_end; ++tile) step(tile, std::true_type());
+  if (tile_end > tile0)                           // the last sub-tile is still to be folded
+    rowstats_fold<RB, true>(acc, tile_end * KT - 32 + 4 * half, N, T, wi, c1, m_run, z_run);
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     // the two lane halves hold disjoint keys of the same query row
@@ -409,8 +402,10 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
 // so every caller gets the same bits for the same partials.
 // p points at the row's partial of chunk 0; consecutive chunks are M float2 apart.
 // Batches of kB chunks per lane: all loads of a batch are issued before the first is used.
+// (fold_batch: as many as the registers hold beside the query fragments.)
 // NR rows at once (pointers p[0..NR-1]): the loads of a batch go out for all of them before the first
 // is used, so NR rows cost as many memory round trips as one.
+template <int RB> constexpr int fold_batch() { return RB == 1 ? 48 : 32; }
 template <int NR, int kB>
 __device__ __forceinline__ void combine_rows(const float2* const (&p)[NR], int M, int n_chunks, int half,
                                              float (&out)[NR]) {
@@ -454,7 +449,7 @@ __device__ __forceinline__ void combine_rows(const float2* const (&p)[NR], int M
 __device__ __forceinline__ float combine_row(const float2* __restrict__ p, int M, int n_chunks, int half) {
   const float2* const ps[1] = {p};
   float out[1];
-  combine_rows<1, 48>(ps, M, n_chunks, half, out);
+  combine_rows<1, fold_batch<1>()>(ps, M, n_chunks, half, out);
   return out[0];
 }
 
@@ -491,30 +486,34 @@ __device__ __forceinline__ float colsum_fold(const f32x16 (&acc)[RB], const floa
   return cs;
 }
 
-// One tile of pass 2: start the next tile's loads into `nxt`, then the column partial sums of
-// this wave's 32*RB rows for the KT keys in `cur` (written to red_w[0..KT-1]).
+// This wave's column partials of one 32-key sub-tile, lane halves added (all lanes get the sum; the
+// halves swap through the vector ALU, not through LDS).
+template <int RB, bool DENORM>
+__device__ __forceinline__ float colsum_subtile(const f32x16 (&acc)[RB], const float (&rc)[RB][16], float c1) {
+  const uint32_t cs = __float_as_uint(colsum_fold<RB, DENORM>(acc, rc, c1));
+  const auto sw = __builtin_amdgcn_permlane32_swap(cs, cs, false, false);    // {low half, high half} in every lane
+  return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+}
+
+// One tile of pass 2: start the next tile's loads into `nxt`, then the MFMAs of the tile in `cur`
+// beside the column partial sums of the sub-tile before each (`acc`; the last sub-tile of the tile
+// before on entry): the same pipeline as pass 1's.  red_prev, red_cur: this wave's partial sums of the
+// KT keys of the tile before and of this one.
 template <typename TE, int P, int NT, int RB, bool DENORM>
 __device__ __forceinline__ void colsum_tile(const Piece* __restrict__ cur, Piece* __restrict__ nxt,
                                             bool prefetch, const TilePieces<P, NT>& tp, const char* __restrict__ kg, int64_t rsb,
                                             int prefetch_key0, int last_piece, int N, int tid, int ln, int half,
                                             const Piece (&qf)[RB][P / 2], const float (&rc)[RB][16], float c1,
-                                            float* __restrict__ red_w) {
+                                            f32x16 (&acc)[RB], float* __restrict__ red_prev, float* __restrict__ red_cur) {
   constexpr int KT = key_tile<P>();
   if (prefetch) issue_tile_loads<P, NT>(tp, kg, rsb, prefetch_key0, N, last_piece, nxt, tid);
-  f32x16 acc[RB];
-  mma_subtile<TE, P, false, RB>(cur, 0, ln, half, qf, acc);
 #pragma unroll
   for (int sub = 0; sub < KT / 32; ++sub) {
     f32x16 nxt_acc[RB];
-    if (sub + 1 < KT / 32) {
-      mma_subtile<TE, P, false, RB>(cur, sub + 1, ln, half, qf, nxt_acc);   // overlaps the exps below
-    } else {
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) nxt_acc[rb] = acc[rb];
-    }
-    const float cs = colsum_fold<RB, DENORM>(acc, rc, c1);
-    const float other = __shfl_xor(cs, 32);
-    if (half == 0) red_w[sub * 32 + ln] = cs + other;
+    mma_subtile<TE, P, false, RB>(cur, sub, ln, half, qf, nxt_acc);
+    const float cs = colsum_subtile<RB, DENORM>(acc, rc, c1);
+    float* red = (sub == 0) ? red_prev + KT - 32 : red_cur + (sub - 1) * 32;
+    if (half == 0) red[ln] = cs;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) acc[rb] = nxt_acc[rb];
   }
@@ -534,16 +533,16 @@ score_colsum_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, 
   constexpr int NTHREADS = NW * 64;
   constexpr int KS = P / 2, KT = key_tile<P>();
   constexpr int TILE_ELEMS = KT * P;
-  constexpr int STAGES = ring_stages<RB>();
+  constexpr int STAGES = kStages;
   __shared__ Piece lds_k[STAGES * TILE_ELEMS];
-  __shared__ float red[2][NW][KT];              // per-wave column partials, double-buffered
+  __shared__ float red[3][NW][KT];              // per-wave column partials of three tiles in turn
 
   const int g = blockIdx.x % Hk, chunk = blockIdx.x / Hk;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, ln = lane & 31, half = lane >> 5;
   const int row0 = m0 + wave * 32 * RB;         // first query row of this wave
   const int last_piece = PAD ? np - 1 : P - 1;
   const char* kg = k + (int64_t)g * ksh;
-  const ChunkRange cr = chunk_range(chunk, g, Hk, (int)(gridDim.x / Hk), (T + KT - 1) / KT, n_cu);
+  const ChunkRange cr = chunk_range<RB>(chunk, g, Hk, (int)(gridDim.x / Hk), (T + KT - 1) / KT, n_cu);
   const int tile0 = cr.tile0, tile_end = cr.tile_end;
 
   ASL_LOAD_Q_FRAGS();
@@ -570,7 +569,7 @@ score_colsum_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, 
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
       ps[rb] = reinterpret_cast<const float2*>(row_part) + (int64_t)g * n_parts * M + min(row0 + rb * 32 + ln, m1 - 1);
-    combine_rows<RB, (RB == 1 ? 48 : 32)>(reinterpret_cast<const float2* const (&)[RB]>(ps), M, n_parts, half, mine);
+    combine_rows<RB, fold_batch<RB>()>(reinterpret_cast<const float2* const (&)[RB]>(ps), M, n_parts, half, mine);
   }
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
@@ -598,21 +597,32 @@ score_colsum_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, 
     }
   };
 
+  f32x16 acc[RB];                                 // "no sub-tile before the first"
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[rb][r] = -INFINITY;
   int stage = 0;                                  // buffer that holds the current tile
+  int cur_red = 0, prev_red = 2;                  // red buffers of this tile and of the one before
   for (int it = 0; it < n_my; ++it) {
     const int tile = tile_end - 1 - it;
     wait_tile<P, NT, STAGES>(min(STAGES - 2, n_my - 1 - it));
-    __syncthreads();      // the tile has landed; previous tile's fragment reads and partials are done
-    if (it > 0) reduce_store((it - 1) & 1, (tile + 1) * KT);
+    __syncthreads();      // the tile has landed; tile it-1's fragment reads and tile it-2's partials are done
+    if (it > 1) reduce_store(3 - cur_red - prev_red, (tile + 2) * KT);
     const int free_stage = (stage == 0) ? STAGES - 1 : stage - 1;
     colsum_tile<TE, P, NT, RB, PAD>(lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS, it + STAGES - 1 < n_my,
-                                    tp, kg, kst, (tile - (STAGES - 1)) * KT, last_piece, N, tid, ln, half, qf, rc, c1,
-                                    &red[it & 1][wave][0]);
+                                    tp, kg, kst, (tile - (STAGES - 1)) * KT, last_piece, N, tid, ln, half, qf, rc, c1, acc,
+                                    &red[prev_red][wave][0], &red[cur_red][wave][0]);
     stage = (stage + 1 == STAGES) ? 0 : stage + 1;
+    prev_red = cur_red;
+    cur_red = (cur_red == 2) ? 0 : cur_red + 1;
   }
   if (n_my > 0) {
+    const float cs = colsum_subtile<RB, PAD>(acc, rc, c1);
+    if (half == 0) red[prev_red][wave][KT - 32 + ln] = cs;
     __syncthreads();
-    reduce_store((n_my - 1) & 1, tile0 * KT);
+    if (n_my > 1) reduce_store(3 - cur_red - prev_red, (tile0 + 1) * KT);
+    reduce_store(prev_red, tile0 * KT);
   }
 }
 
@@ -710,17 +720,27 @@ static int device_cu_count() {
   return n;
 }
 
+// Workgroups per compute unit: with the matrix and vector work of a wavefront interleaved, two
+// workgroups (8 wavefronts) keep a unit's pipes and its share of the HBM stream as busy as three do,
+// start sooner and leave fewer partials to fold.  N = 32K / 128K, 8B shape, pass 1 + pass 2: three per unit
+// 17.4 + 21.7 / 54.6 + 51.5 us, two 16.1 + 20.3 / 54.5 + 49.2 us; one 16.2 + 22.0 / 50.5 + 62.4 us.
+constexpr int kScorePerCu = 2;
+
 // Key chunks per KV head for a pass whose kernel fits `resident` workgroups per compute unit: one
-// resident round of workgroups, so that no second, partly filled round trails behind.
-static int score_chunks(const asl_params& p, int kt, int resident) {
-  const int target = device_cu_count() * resident;
+// resident round of workgroups, so that no second, partly filled round trails behind.  `batch` = chunks
+// that pass 2's prologue folds in one memory round trip: more chunks than that are only worth their
+// second round trip (4-7 us) where fewer would leave compute units idle or cost long chunks
+// (28 heads / 4 KV heads, pass 1 + pass 2: N = 8K 10.4 + 20.1 with 128 chunks, 8.6 + 12.2 us with 64;
+// 32K 17.5 + 25.3, 15.8 + 18.5; 128K 41.2 + 45.9, 42.5 + 43.0).
+static int score_chunks(const asl_params& p, int kt, int resident, int batch) {
+  const int n_cu = device_cu_count();
+  const int target = n_cu * (resident < kScorePerCu ? resident : kScorePerCu);
   const int n_tiles = (p.seq_len + kt - 1) / kt;
   int want = target / p.n_kv_heads;
   if (want > kMaxChunks) want = kMaxChunks;
   if (want > n_tiles) want = n_tiles;
-  if (want < 1) want = 1;
-  const int tpc = (n_tiles + want - 1) / want;
-  return (n_tiles + tpc - 1) / tpc;
+  if (want > batch && ((int64_t)batch * p.n_kv_heads >= n_cu ? n_tiles <= 16 * batch : n_tiles <= 2 * batch)) want = batch;
+  return want < 1 ? 1 : want;
 }
 
 // Workgroups of `kernel` that fit on one compute unit at once (registers, LDS, wave slots).
@@ -748,7 +768,7 @@ static hipError_t launch_score_mfma(const asl_params& p, const Workspace& ws, co
     const int b = resident_per_cu(score_colsum_kernel<TE, P, NW, RB, PAD>, NW * 64);
     return a < b ? a : b;
   }();
-  const int n_chunks = score_chunks(p, KT, resident);
+  const int n_chunks = score_chunks(p, KT, resident, 2 * fold_batch<RB>());
   const int n_cu = device_cu_count();
   if (!lse) {
     for (int m0 = 0; m0 < M; m0 += kRows)
