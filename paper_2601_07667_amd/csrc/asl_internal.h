@@ -110,7 +110,6 @@ __host__ __device__ inline int sel_sample_stride(int T) { return T / sel_sample_
 constexpr int kFlagCountBits = 14;
 constexpr int kFlagTagShift = 2 * kFlagCountBits;
 constexpr unsigned long long kFlagTagMask = (1ull << (64 - kFlagTagShift)) - 1ull;
-constexpr int kFlagBatch = 16;             // words a thread polls at once
 constexpr int kFlagSpinLimit = 1 << 17;    // polls before a waiter gives up (each takes ~1 us or more)
 
 
@@ -207,22 +206,22 @@ __device__ __forceinline__ uint32_t flag_count0(unsigned long long v) {
 __device__ __forceinline__ uint32_t flag_count1(unsigned long long v) {
   return (uint32_t)(v >> kFlagCountBits) & ((1u << kFlagCountBits) - 1u);
 }
-// Reads the words  col[(t0 + u * STEP) * stride]  for u < kFlagBatch (those with t < n) until every
+// Reads the words  col[(t0 + u * STEP) * stride]  for u < BATCH (those with t < n) until every
 // one carries `tag`.  Returns false if that has not happened after kFlagSpinLimit polls.
-template <int STEP>
+template <int STEP, int BATCH>
 __device__ __forceinline__ bool flag_poll_batch(const unsigned long long* col, int stride, int t0, int n,
-                                                unsigned long long tag, unsigned long long (&v)[kFlagBatch]) {
+                                                unsigned long long tag, unsigned long long (&v)[BATCH]) {
   const unsigned long long want = tag & kFlagTagMask;
   for (int spins = 0;; ++spins) {
     bool ok = true;
 #pragma unroll
-    for (int u = 0; u < kFlagBatch; ++u) {
+    for (int u = 0; u < BATCH; ++u) {
       const int t = t0 + u * STEP;
       v[u] = (t < n) ? __hip_atomic_load(col + (int64_t)t * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
                      : (want << kFlagTagShift);
     }
 #pragma unroll
-    for (int u = 0; u < kFlagBatch; ++u) ok = ok && ((v[u] >> kFlagTagShift) == want);
+    for (int u = 0; u < BATCH; ++u) ok = ok && ((v[u] >> kFlagTagShift) == want);
     if (ok) return true;
     if (spins >= kFlagSpinLimit) return false;
     __builtin_amdgcn_s_sleep(1);

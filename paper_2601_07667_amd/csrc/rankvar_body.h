@@ -138,8 +138,8 @@ __device__ __forceinline__ void rankvar_body(RankvarShared& sh, const RankvarArg
   unsigned long long total = 0;
   uint32_t m = 0;
   for (int b = tid; b < n_blocks; b += kVarThreads) {
-    unsigned long long v[kFlagBatch];
-    if (!flag_poll_batch<1>(a.table + (int64_t)b * 4, 1, 0, 4, tag, v)) sh.gave_up = 1;
+    unsigned long long v[4];
+    if (!flag_poll_batch<1, 4>(a.table + (int64_t)b * 4, 1, 0, 4, tag, v)) sh.gave_up = 1;
     const unsigned long long piece0 = (unsigned long long)flag_count0(v[0]) | ((unsigned long long)flag_count1(v[0]) << 14);
     const unsigned long long piece1 = (unsigned long long)flag_count0(v[1]) | ((unsigned long long)flag_count1(v[1]) << 14);
     total += piece0 | (piece1 << 28) | ((unsigned long long)flag_count0(v[2]) << 56);

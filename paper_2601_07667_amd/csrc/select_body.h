@@ -58,11 +58,13 @@ __device__ __forceinline__ void block_scan2(uint32_t a, uint32_t b, uint32_t* sm
 // threads take part.  The keys' common leading bits are skipped: digits are taken from
 // key - min over the bits in which min and max differ, so the first digit already spreads the keys
 // over the bins (scores of one row share their sign and most of their exponent).
+// With `slack` > 0 the search may stop early: thr_out is then a key that at least k and at most k + slack
+// of the keys do not exceed (k_rem_out is meaningless).
 // h: kHistWords-word LDS histogram (bank-staggered copies), sm: >= 2 * kFinWaves + 2 words.
 constexpr int kSelBatch = 4;                           // keys a thread reads together in the selection loops
 template <typename KeyAt>
 __device__ __forceinline__ void radix_select_block(int n, uint32_t k, KeyAt key_at, uint32_t* h, uint32_t* sm,
-                                                   uint32_t& thr_out, uint32_t& k_rem_out) {
+                                                   uint32_t& thr_out, uint32_t& k_rem_out, uint32_t slack = 0) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   // The loops over the keys take kSelBatch of a thread's keys at a time (positions past the end
   // re-read the thread's first key of the batch), so that their reads are in flight together.
@@ -119,6 +121,7 @@ __device__ __forceinline__ void radix_select_block(int n, uint32_t k, KeyAt key_
     if (tid == 0) {
       sm[4] = 0;                                       // defined even if no digit qualifies
       sm[5] = 1;                                       // (cannot happen while 1 <= k <= n)
+      sm[6] = 0xffffffffu;
     }
     __syncthreads();
     if (tid < 256) {
@@ -127,11 +130,17 @@ __device__ __forceinline__ void radix_select_block(int n, uint32_t k, KeyAt key_
       if (excl < k_rem && excl + cnt >= k_rem) {       // exactly one digit satisfies this
         sm[4] = (uint32_t)tid;
         sm[5] = k_rem - excl;
+        sm[6] = cnt;
       }
     }
     __syncthreads();
     prefix = (prefix << 8) | sm[4];
     k_rem = sm[5];
+    if (slack > 0 && sm[6] - k_rem <= slack) {          // uniform: the whole bin may pass
+      const uint32_t top = (prefix << shift) | ((1u << shift) - 1u);
+      prefix = top < span ? top : span;
+      break;
+    }
   }
   thr_out = lo + prefix;
   k_rem_out = k_rem;
@@ -155,7 +164,8 @@ struct GuessShared {
   uint32_t sm[2 * kFinWaves + 2];
 };
 
-// Step 1: bound[row] = the m-th smallest key of the row's strided sample (0xffffffff: admit all).
+// Step 1: bound[row] = the m-th smallest key of the row's strided sample, or a key that up to an eighth more of
+// the sample's keys do not exceed (which saves one or two of the four digit passes); 0xffffffff: admit all.
 __device__ __forceinline__ void select_guess_body(GuessShared& sh, const SelectArgs& a, int row) {
   const int tid = threadIdx.x, T = a.T;
   const int stride = sel_sample_stride(T);
@@ -191,7 +201,7 @@ __device__ __forceinline__ void select_guess_body(GuessShared& sh, const SelectA
   for (int u = 0; u < kSampPer; ++u)
     if (tid + u * kFinThreads < n_s) sh.samp[tid + u * kFinThreads] = v[u];
   uint32_t thr, k_rem;
-  radix_select_block(n_s, (uint32_t)m, [&](int i) { return sh.samp[i]; }, sh.h, sh.sm, thr, k_rem);
+  radix_select_block(n_s, (uint32_t)m, [&](int i) { return sh.samp[i]; }, sh.h, sh.sm, thr, k_rem, (uint32_t)m / 8u);
   if (tid == 0) a.bound[row] = thr;
 }
 
