@@ -585,9 +585,10 @@ asl_status asl_layer_step(asl_ctx* ctx, const asl_params* p, const void* q_obs, 
   hipStream_t hs = static_cast<hipStream_t>(stream);
   DeviceGuard guard(ctx->device);
   if (guard.err != hipSuccess) return hip_fail(ctx, guard.err, "set device");
-  // when the four-launch tail will follow, the pooling kernel leaves the top-k's sample behind
+  // when the shared launches of the tail will follow, the pooling kernel leaves the top-k's sample behind
   const bool fused = !(p->flags & ASL_FLAG_DEFER_JOIN) && asl::tail_takes(ctx->ws, Hk + 1, T);
-  st = score_layer_impl(ctx, p, q_obs, k, lse, p_head, s_all, stream, true, fused);
+  const bool want_sample = fused && T > asl::kShortT;   // short rows need no bound
+  st = score_layer_impl(ctx, p, q_obs, k, lse, p_head, s_all, stream, true, want_sample);
   if (st != ASL_OK) return st;
   if (fused) {
     // one stream: launch i carries pass i of the ranking sort and stage i of top-k + compaction
@@ -601,20 +602,13 @@ asl_status asl_layer_step(asl_ctx* ctx, const asl_params* p, const void* q_obs, 
     }
     bool taken = false;
     int32_t* row = rank_ring + (int64_t)(layer_idx % l_obs) * T;
-    // below L_min nothing is evaluated: the statistic's place in the last launch stays empty and the
-    // state is advanced by the one-thread kernel instead
-    const asl::RankvarArgs ra = asl::rankvar_args(ctx->ws, rank_ring, l_obs, T, layer_idx, k_sel, tau, 1, state, out);
+    // below L_min nothing is evaluated: the statistic's place in the last launch only advances the state
+    asl::RankvarArgs ra = asl::rankvar_args(ctx->ws, rank_ring, l_obs, T, layer_idx, k_sel, tau, 1, state, out);
+    ra.skip = layer_idx < l_min ? 1 : 0;
     hipError_t et = asl::launch_tail(ctx->ws, scores, Hk + 1, T, k_sel, p->window, row, idx_out,
-                                     k_out != nullptr ? &ga : nullptr, Hk, true, layer_idx < l_min ? nullptr : &ra, hs,
-                                     &taken);
+                                     k_out != nullptr ? &ga : nullptr, Hk, want_sample, ra, hs, &taken);
     if (et != hipSuccess) return hip_fail(ctx, et, "tail launch");
-    if (taken) {
-      if (layer_idx < l_min) {
-        et = asl::launch_stat_skip(ctx->ws.prof, out, state, layer_idx, l_obs, 1, hs);
-        if (et != hipSuccess) return hip_fail(ctx, et, "rankvar launch");
-      }
-      return ASL_OK;
-    }
+    if (taken) return ASL_OK;
     // sizes these launches do not take: the two-stream sequence of single calls below
   }
   // fork: top-k + KV compaction on the side stream, ranking + statistic on the caller's stream

@@ -84,6 +84,8 @@ struct Workspace {
 #endif
 constexpr int kSortTile = ASL_SORT_TILE;   // elements per radix-sort workgroup tile (a multiple of 256)
 constexpr int kSelTile = ASL_SEL_TILE;     // elements per select workgroup tile (a multiple of 256)
+constexpr int kShortT = 12288;           // longest score vector that one workgroup holds in LDS (below 64 KB with the
+                                         // selection's counters): ranked and selected from in one launch
 constexpr int kMaxChunks = 256;        // key chunks per KV head in scoring pass 1
 constexpr int kVarMaxBlocks = 256;     // workgroups of the rank-variance kernel
 constexpr int kSortMaxTiles = 512;     // workgroups of one sort launch (they wait for each other)
@@ -257,6 +259,7 @@ int64_t rank_max_tokens(); // largest T one ranking call takes on this device
 // that does not follow state->last_layer restarts the ring)
 hipError_t launch_rankvar(const Workspace& ws, const int32_t* ring, int l_obs, int T, int layer_idx,
                           int k, double tau, int push, asl_state* state, asl_stat* out, hipStream_t st);
+// push as above; the statistic itself is not evaluated (a layer below L_min)
 hipError_t launch_stat_skip(Prof* prof, asl_stat* out, asl_state* state, int layer_idx, int l_obs,
                             int push, hipStream_t st);
 hipError_t launch_select(const Workspace& ws, const float* scores, int rows, int T, int k, int W,
@@ -286,7 +289,7 @@ bool gather_prepare(GatherArgs& a);   // sets cpr_shift; returns whether cpr is 
 // compaction in five launches on one stream (tail.hip); *taken = false when the sizes do not fit and nothing was launched.
 struct RankvarArgs;
 hipError_t launch_tail(const Workspace& ws, const float* scores, int rows, int T, int k, int W, int32_t* rank_row,
-                       int32_t* idx_out, const GatherArgs* gather, int Hk, bool have_sample, const RankvarArgs* stat,
+                       int32_t* idx_out, const GatherArgs* gather, int Hk, bool have_sample, const RankvarArgs& stat,
                        hipStream_t st, bool* taken);
 // Whether launch_tail would take these sizes (so that the pooling kernel can prepare the sample).
 bool tail_takes(const Workspace& ws, int rows, int T);

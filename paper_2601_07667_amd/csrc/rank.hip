@@ -5,6 +5,8 @@
 // 32-bit transform of the fp32 score, 8 bits per pass, ONE kernel per pass; the last pass scatters
 // positions to rank[index] instead of writing the sorted pairs.
 //
+// Short vectors (kShortT) are ranked by counting instead, in one launch (rank_count_body).
+//
 // In a pass every workgroup owns one tile of consecutive elements.  It counts its tile's digits in
 // LDS, publishes the 256 counts, reads every tile's counts (total per digit and the part that
 // belongs to earlier tiles), and then ranks its elements inside the tile with wavefront ballots
@@ -28,6 +30,11 @@ template <int R, bool FIRST, bool LAST>
 __global__ void __launch_bounds__(kSortThreads) sort_pass_kernel(SortArgs a) {
   __shared__ SortShared sh;
   sort_pass_body<R, FIRST, LAST>(sh, a, (int)blockIdx.x);
+}
+
+__global__ void __launch_bounds__(kSortThreads) rank_count_kernel(const float* __restrict__ s, int T, int32_t* __restrict__ rank_out) {
+  __shared__ CountShared sh;
+  rank_count_body(sh, s, T, rank_out, (int)blockIdx.x);
 }
 
 int rank_max_tiles() {
@@ -95,6 +102,10 @@ static hipError_t launch_rank_r(const Workspace& ws, const float* s, int T, int 
 }
 
 hipError_t launch_rank(const Workspace& ws, const float* s, int T, int32_t* rank_out, hipStream_t st) {
+  if (T <= kShortT) {
+    ASL_LAUNCH(ws.prof, kKernSortScatter, st, rank_count_kernel, dim3(rank_count_blocks(T)), dim3(kSortThreads), 0, st, s, T, rank_out);
+    return hipGetLastError();
+  }
   const SortPlan plan = sort_plan(T, rank_max_tiles());
   if (plan.n_tiles == 0) return hipErrorInvalidConfiguration;
   return plan.big ? launch_rank_r<kSortRoundsBig>(ws, s, T, plan.n_tiles, rank_out, st)

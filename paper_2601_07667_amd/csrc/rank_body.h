@@ -41,6 +41,46 @@ struct SortArgs {
   int32_t* rank_out;             // last pass only
 };
 
+// Ranks of kCountTokens tokens of a short vector (T <= kShortT) by counting: a workgroup reads all keys into LDS,
+// 32 lanes share a token and compare its key with every other one: rank = keys before it in the order
+// (key ascending, index ascending).  T * T comparisons, two vector instructions each, spread over T / 32
+// workgroups: 5 us at 8000 tokens, one launch and one barrier, against 25 us for four sort passes, which
+// are latency from end to end at these sizes.  At 12288 tokens both jobs of a layer step's launch take ~11 us;
+// beyond, the comparisons grow past what the sort takes (16384: ~14 us, 32768: ~55 us).
+constexpr int kCountTokens = kSortThreads / 32;
+struct CountShared {
+  uint32_t keys[kShortT];
+};
+__device__ __forceinline__ void rank_count_body(CountShared& sh, const float* __restrict__ s, int T, int32_t* __restrict__ rank_out,
+                                                int block) {
+  const int tid = threadIdx.x, lane = tid & 31;
+  constexpr int kPer = kShortT / kSortThreads;
+  static_assert(kShortT % kSortThreads == 0 && kCountTokens == 32, "the keys of a workgroup's tokens are one group of 32");
+  float v[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) v[u] = s[min(tid + u * kSortThreads, T - 1)];        // one round trip
+  // positions past the end hold the largest key, which precedes nothing
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) sh.keys[tid + u * kSortThreads] = tid + u * kSortThreads < T ? order_key(v[u]) : 0xffffffffu;
+  __syncthreads();
+  const int i0 = block * kCountTokens, i = i0 + (tid >> 5);
+  const uint32_t ki = sh.keys[i];                       // i < kShortT: see the grid
+  const int n_groups = (T + 31) / 32;                   // groups of 32 keys, one per lane
+  uint32_t before = 0;
+#pragma unroll 8
+  for (int g = 0; g < block; ++g) before += (sh.keys[g * 32 + lane] <= ki) ? 1u : 0u;              // lower indices: ties precede
+#pragma unroll 8
+  for (int g = block + 1; g < n_groups; ++g) before += (sh.keys[g * 32 + lane] < ki) ? 1u : 0u;    // higher indices: ties follow
+  {
+    const uint32_t kj = sh.keys[i0 + lane];
+    before += (kj < ki || (kj == ki && i0 + lane < i)) ? 1u : 0u;
+  }
+#pragma unroll
+  for (int d = 16; d > 0; d >>= 1) before += (uint32_t)__shfl_xor((int)before, d);
+  if (lane == 0 && i < T) rank_out[i] = (int32_t)before;
+}
+inline int rank_count_blocks(int T) { return (T + kCountTokens - 1) / kCountTokens; }
+
 // Tiles of a sort of T scores: kSortTile elements each, or four times that when T would otherwise
 // need more workgroups than `limit`; n_tiles = 0 if even those are too many.
 struct SortPlan {

@@ -13,19 +13,7 @@ namespace asl {
 
 __global__ void stat_skip_kernel(asl_stat* out, asl_state* state, int layer_idx, int l_obs, int push) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  if (push) {
-    int n = state->n_valid_rows;
-    if (n > 0 && !continues_ring(state, layer_idx, l_obs)) n = 0;
-    state->n_valid_rows = n + 1 < l_obs ? n + 1 : l_obs;
-    state->last_layer = layer_idx;
-  }
-  out->var_top = __builtin_nan("");
-  out->rel_var = __builtin_nan("");
-  out->numerator = 0;
-  out->union_size = 0;
-  out->n_rows = 0;
-  out->evaluated = 0;
-  out->selected = 0;
+  stat_skip_body(out, state, layer_idx, l_obs, push);
 }
 
 __global__ void __launch_bounds__(kVarThreads) rankvar_kernel(RankvarArgs a) {

@@ -39,12 +39,30 @@ struct RankvarArgs {
   int l_obs, T, layer_idx, k;
   double tau;
   int push;
+  int skip;                      // 1: a layer below L_min, only the state is advanced and `out` says "not evaluated"
   asl_state* state;
   asl_stat* out;
   unsigned long long* table;     // [kVarMaxBlocks][4] tagged partial sums
   unsigned long long* epoch;
   uint32_t* fault;
 };
+
+// What a layer below L_min leaves behind (one thread).
+__device__ __forceinline__ void stat_skip_body(asl_stat* out, asl_state* state, int layer_idx, int l_obs, int push) {
+  if (push) {
+    int n = state->n_valid_rows;
+    if (n > 0 && !continues_ring(state, layer_idx, l_obs)) n = 0;
+    state->n_valid_rows = n + 1 < l_obs ? n + 1 : l_obs;
+    state->last_layer = layer_idx;
+  }
+  out->var_top = __builtin_nan("");
+  out->rel_var = __builtin_nan("");
+  out->numerator = 0;
+  out->union_size = 0;
+  out->n_rows = 0;
+  out->evaluated = 0;
+  out->selected = 0;
+}
 
 // Per-workgroup partial sums over the union (integers, so the order of the later addition does not
 // matter), handed to workgroup 0 through tagged words (see asl_internal.h: four words per

@@ -17,6 +17,7 @@
 // The bound is only a guess: if fewer than k keys passed it, or a tile's or the row's candidates
 // do not fit their buffers, step 3 runs the same selection over the whole row straight from the
 // scores instead (slower, same result).  The result therefore never depends on the sample.
+// Rows of at most kShortT scores need no bound: one launch, one workgroup per row, all tokens in LDS.
 // Integer work throughout: nothing depends on scheduling.
 #include "select_body.h"
 
@@ -41,6 +42,11 @@ __global__ void __launch_bounds__(kFinThreads) select_finish_kernel(SelectArgs a
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_dyn[];
   FinishShared& sh = *reinterpret_cast<FinishShared*>(lds_dyn);
   select_finish_body(sh, reinterpret_cast<uint32_t*>(lds_dyn + sizeof(FinishShared)), a, (int)blockIdx.x);
+}
+
+__global__ void __launch_bounds__(kFinThreads) select_short_kernel(SelectArgs a) {
+  __shared__ ShortSelectShared sh;
+  select_short_body(sh, a, (int)blockIdx.x);
 }
 
 SelectArgs select_args(const Workspace& ws, const float* scores, int T, int k, int W, int32_t* idx_out,
@@ -71,6 +77,10 @@ hipError_t launch_select(const Workspace& ws, const float* scores, int rows, int
   for (int row0 = 0; row0 < rows; row0 += rows_per_round) {
     const int nr = rows - row0 < rows_per_round ? rows - row0 : rows_per_round;
     const SelectArgs a = select_args(ws, scores + (int64_t)row0 * T, T, k, W, idx_out + (int64_t)row0 * (k + W), false);
+    if (T <= kShortT) {
+      ASL_LAUNCH(ws.prof, kKernSelWrite, st, select_short_kernel, dim3(nr), dim3(kFinThreads), 0, st, a);
+      continue;
+    }
     ASL_LAUNCH(ws.prof, kKernSelHist, st, select_guess_kernel, dim3(nr), dim3(kFinThreads), 0, st, a);
     // rows that start on 16-byte boundaries are read four scores at a time
     const bool vec = (T % 4 == 0) && (reinterpret_cast<uintptr_t>(a.scores) % 16 == 0);

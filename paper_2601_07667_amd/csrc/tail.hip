@@ -1,4 +1,4 @@
-// The part of a layer step that follows the scoring, in five launches on one stream.
+// The part of a layer step that follows the scoring, in five launches on one stream (two for short contexts).
 //
 // After the scores are pooled two independent chains remain: the ranking sort (four dependent
 // passes, Alg. 1 step 11) and the top-k + KV compaction (bound, filter, finish, gather: Alg. 1
@@ -28,6 +28,21 @@ union SortFilterShared {
   FilterShared filter;
 };
 constexpr size_t kSortFinishLdsBytes = sizeof(SortShared) > kFinishLdsBytes ? sizeof(SortShared) : kFinishLdsBytes;
+
+// Short contexts (T <= kShortT): ranking by counting and the top-k of every row in one launch instead of the
+// four below, for N = 4096 15 instead of 36 us.  The selecting workgroups, the longer ones, come first.
+union ShortShared {
+  ShortSelectShared select;
+  CountShared count;
+};
+__global__ void __launch_bounds__(kTailThreads) tail_short_kernel(const float* s_all, int32_t* rank_row, SelectArgs se, int rows) {
+  __shared__ ShortShared sh;
+  const int b = (int)blockIdx.x;
+  if (b < rows)
+    select_short_body(sh.select, se, b);
+  else
+    rank_count_body(sh.count, s_all, se.T, rank_row, b - rows);
+}
 
 // launch 0: sort pass 0 | top-k bound (one workgroup per score row)
 template <int R>
@@ -89,7 +104,11 @@ __global__ void __launch_bounds__(kVarThreads) tail4_kernel(RankvarArgs ra, int 
   __shared__ RankvarShared sh;
   const int b = (int)blockIdx.x;
   if (b < n_stat) {
-    rankvar_body(sh, ra, b, n_stat);
+    if (ra.skip != 0) {
+      if (threadIdx.x == 0) stat_skip_body(ra.out, ra.state, ra.layer_idx, ra.l_obs, ra.push);   // n_stat = 1
+    } else {
+      rankvar_body(sh, ra, b, n_stat);
+    }
   } else {
     const int j = b - n_stat;
     const int bx = j % gx, hw = j / gx;
@@ -117,11 +136,10 @@ static int tail_max_tiles() {
 }
 
 template <int R>
-static hipError_t launch_tail_r(const Workspace& ws, const float* scores, int rows, int T, int n_tiles, int k, int W,
-                                int32_t* rank_row, int32_t* idx_out, const GatherArgs* gather, int Hk, bool have_sample,
-                                const RankvarArgs* stat, hipStream_t st) {
-  const float* s_all = scores + (int64_t)(rows - 1) * T;       // the all-head row is the last one
-  const SelectArgs se = select_args(ws, scores, T, k, W, idx_out, have_sample);
+static void launch_sort_select(const Workspace& ws, const SelectArgs& se, const float* s_all, int rows, int n_tiles,
+                               int32_t* rank_row, hipStream_t st) {
+  const float* scores = se.scores;
+  const int T = se.T;
   const dim3 block(kTailThreads);
   ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<R>), dim3(n_tiles + rows), block, 0, st,
              sort_pass_args(ws, s_all, T, n_tiles, rank_row, 0), se);
@@ -135,34 +153,34 @@ static hipError_t launch_tail_r(const Workspace& ws, const float* scores, int ro
              sort_pass_args(ws, s_all, T, n_tiles, rank_row, 2), se);
   ASL_LAUNCH(ws.prof, kKernTail, st, (tail3_kernel<R>), dim3(n_tiles + rows), block, kSortFinishLdsBytes, st,
              sort_pass_args(ws, s_all, T, n_tiles, rank_row, 3), se);
-  // statistic beside the compaction; either may be absent (a layer below L_min, no output tensors)
-  if (stat != nullptr && gather != nullptr) {
+}
+
+// The last launch: statistic (or the note that it is not evaluated yet) beside the compaction, which may be
+// absent (no output tensors).
+static hipError_t launch_stat_gather(const Workspace& ws, const GatherArgs* gather, int Hk, const RankvarArgs& stat, hipStream_t st) {
+  if (gather != nullptr) {
     GatherArgs ga = *gather;
     const bool pow2 = gather_prepare(ga);
     const int64_t total = (int64_t)ga.n_idx * ga.cpr;
     const int per_block = kVarThreads * kGatherUnroll;
     const int gx = (int)((total + per_block - 1) / per_block);
-    const int n_stat = rankvar_blocks(T);
+    const int n_stat = stat.skip != 0 ? 1 : rankvar_blocks(stat.T);
     const dim3 grid4(n_stat + gx * Hk * ga.n_tensors);
     if (gx == 0)
-      ASL_LAUNCH(ws.prof, kKernRankvar, st, (tail4_kernel<true>), dim3(n_stat), dim3(kVarThreads), 0, st, *stat, n_stat, ga, 1, Hk);
+      ASL_LAUNCH(ws.prof, kKernRankvar, st, (tail4_kernel<true>), dim3(n_stat), dim3(kVarThreads), 0, st, stat, n_stat, ga, 1, Hk);
     else if (pow2)
-      ASL_LAUNCH(ws.prof, kKernTail, st, (tail4_kernel<true>), grid4, dim3(kVarThreads), 0, st, *stat, n_stat, ga, gx, Hk);
+      ASL_LAUNCH(ws.prof, kKernTail, st, (tail4_kernel<true>), grid4, dim3(kVarThreads), 0, st, stat, n_stat, ga, gx, Hk);
     else
-      ASL_LAUNCH(ws.prof, kKernTail, st, (tail4_kernel<false>), grid4, dim3(kVarThreads), 0, st, *stat, n_stat, ga, gx, Hk);
-  } else if (stat != nullptr) {
-    const hipError_t e = launch_rankvar(ws, stat->ring, stat->l_obs, stat->T, stat->layer_idx, stat->k, stat->tau,
-                                        stat->push, stat->state, stat->out, st);
-    if (e != hipSuccess) return e;
-  } else if (gather != nullptr) {
-    const hipError_t e = launch_gather(ws.prof, *gather, Hk, 1, st);
-    if (e != hipSuccess) return e;
+      ASL_LAUNCH(ws.prof, kKernTail, st, (tail4_kernel<false>), grid4, dim3(kVarThreads), 0, st, stat, n_stat, ga, gx, Hk);
+    return hipGetLastError();
   }
-  return hipGetLastError();
+  if (stat.skip != 0) return launch_stat_skip(ws.prof, stat.out, stat.state, stat.layer_idx, stat.l_obs, stat.push, st);
+  return launch_rankvar(ws, stat.ring, stat.l_obs, stat.T, stat.layer_idx, stat.k, stat.tau, stat.push, stat.state, stat.out, st);
 }
 
 bool tail_takes(const Workspace& ws, int rows, int T) {
   if (rows > ws.sel_rows) return false;
+  if (T <= kShortT) return true;
   const SortPlan small = sort_plan(T, tail_max_tiles<kSortRounds>());
   if (small.n_tiles > 0 && !small.big) return true;
   const int big_tile = kSortThreads * kSortRoundsBig;
@@ -170,23 +188,28 @@ bool tail_takes(const Workspace& ws, int rows, int T) {
 }
 
 hipError_t launch_tail(const Workspace& ws, const float* scores, int rows, int T, int k, int W, int32_t* rank_row,
-                       int32_t* idx_out, const GatherArgs* gather, int Hk, bool have_sample, const RankvarArgs* stat,
+                       int32_t* idx_out, const GatherArgs* gather, int Hk, bool have_sample, const RankvarArgs& stat,
                        hipStream_t st, bool* taken) {
   *taken = false;
-  if (rows > ws.sel_rows) return hipSuccess;
+  if (!tail_takes(ws, rows, T)) return hipSuccess;
   if (gather != nullptr && ((int64_t)gather->n_idx * gather->cpr >= (int64_t(1) << 31))) return hipSuccess;
-  const SortPlan small = sort_plan(T, tail_max_tiles<kSortRounds>());
-  if (small.n_tiles > 0 && !small.big) {
-    *taken = true;
-    return launch_tail_r<kSortRounds>(ws, scores, rows, T, small.n_tiles, k, W, rank_row, idx_out, gather, Hk, have_sample, stat, st);
+  *taken = true;
+  const float* s_all = scores + (int64_t)(rows - 1) * T;       // the all-head row is the last one
+  const SelectArgs se = select_args(ws, scores, T, k, W, idx_out, have_sample);
+  if (T <= kShortT) {
+    ASL_LAUNCH(ws.prof, kKernTail, st, tail_short_kernel, dim3(rows + rank_count_blocks(T)), dim3(kTailThreads), 0, st, s_all,
+               rank_row, se, rows);
+  } else {
+    const SortPlan small = sort_plan(T, tail_max_tiles<kSortRounds>());
+    if (small.n_tiles > 0 && !small.big) {
+      launch_sort_select<kSortRounds>(ws, se, s_all, rows, small.n_tiles, rank_row, st);
+    } else {
+      const int big_tile = kSortThreads * kSortRoundsBig;
+      launch_sort_select<kSortRoundsBig>(ws, se, s_all, rows, (T + big_tile - 1) / big_tile, rank_row, st);
+    }
   }
-  const int big_tile = kSortThreads * kSortRoundsBig;
-  const int n_big = (T + big_tile - 1) / big_tile;
-  if (n_big <= tail_max_tiles<kSortRoundsBig>()) {
-    *taken = true;
-    return launch_tail_r<kSortRoundsBig>(ws, scores, rows, T, n_big, k, W, rank_row, idx_out, gather, Hk, have_sample, stat, st);
-  }
-  return hipSuccess;
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : launch_stat_gather(ws, gather, Hk, stat, st);
 }
 
 }  // namespace asl

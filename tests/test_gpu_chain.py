@@ -384,6 +384,19 @@ def test_layer_step_ragged_shapes(gpu_device, Hq, Hk, d, N, W, S, budget):
     _check_layer(L, _layer_step_case(gpu_device, L))
 
 
+@pytest.mark.parametrize("N,layer_idx,L_min", [(12288 + 16, 0, 0), (12288 + 17, 0, 0), (12288 + 16, 0, 5), (12288 + 17, 3, 5),
+                                               (49, 0, 2)])
+def test_layer_step_around_the_short_limit(gpu_device, N, layer_idx, L_min):
+    """12288 past tokens (ranked and selected from in one launch) and 12289 (five launches), evaluated and
+    below L_min (the state only advances)."""
+    sh = synth.Shape(Hq=4, Hk=2, d=64, N=N, W=16, S=7, budget=300, L_min=L_min)
+    L = synth.iid_layer(sh, 2000 + N, name=f"short-limit-{N}-{layer_idx}")
+    got = _layer_step_case(gpu_device, L, layer_idx=layer_idx)
+    assert got["stat"].evaluated == 0 and got["stat"].n_rows == (0 if layer_idx < L_min else 1)
+    if layer_idx == 0 and L_min == 0:
+        _check_layer(L, got)
+
+
 def test_layer_step_at_bench_size_and_beyond(gpu_device):
     """asl_layer_step at the size the benchmark times (C3: 64 sort tiles beside the top-k stages) and at
     2^20 tokens (the ranking sort switches to its large tiles): bit-identical to the single calls, and

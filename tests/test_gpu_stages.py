@@ -110,6 +110,24 @@ def test_rank_and_select_at_tile_boundaries(ctx, gpu_device, T):
         _select_case(ctx, gpu_device, np.stack([s, -s]), budget, 8)
 
 
+# Up to 12288 scores are ranked by counting (32 tokens per workgroup) and selected from by one workgroup per
+# row; above, the sort (tiles of 2048) and the bound / filter / finish launches (tiles of 4096) take over.
+@pytest.mark.parametrize("T", [31, 32, 33, 95, 1023, 1025, 8192, 12256, 12257, 12287, 12288, 12289, 14335, 14336, 14337,
+                               16383, 16384, 16385])
+def test_short_vectors_and_their_limit(ctx, gpu_device, T):
+    rng = np.random.default_rng(T)
+    s = np.round(rng.standard_normal(T), 2).astype(np.float32)            # heavy ties
+    wild = rng.standard_normal(T).astype(np.float32) * np.float32(1e-39)  # denormals, both zeros, infinities
+    wild[rng.integers(0, T, T // 3 + 1)] = 0.0
+    wild[rng.integers(0, T, T // 4 + 1)] = -0.0
+    wild[rng.integers(0, T, 2)] = np.inf
+    wild[rng.integers(0, T, 2)] = -np.inf
+    for v in (s, wild, np.ones(T, dtype=np.float32), np.arange(T, dtype=np.float32)):
+        _rank_case(ctx, gpu_device, v)
+    for budget in (9, T // 3 + 8, T + 8):                                   # k = 1, ~T/3, T
+        _select_case(ctx, gpu_device, np.stack([s, -s, wild]), budget, 8)
+
+
 # ----------------------------------------------------------------------------- statistic
 def _stat_case(ctx, dev, R: np.ndarray, l_obs: int, k: int, tau: float, layer_idx: int,
                init_var=None):
