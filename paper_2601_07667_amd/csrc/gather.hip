@@ -9,12 +9,18 @@ namespace asl {
 
 // grid: x = blocks of kGatherThreads * kGatherUnroll pieces of one (head, tensor, layer) slab,
 //       y = KV head, z = layer * n_tensors + tensor (0 = K, 1 = V).
-template <bool POW2>
+template <bool POW2, bool STREAM>
 __global__ void __launch_bounds__(kGatherThreads)
 gather_kernel(GatherArgs a) {
-  gather_body<POW2, kGatherThreads>(a, (int)blockIdx.x, (int)blockIdx.y, (int)(blockIdx.z % (unsigned)a.n_tensors),
-                                    (int)(blockIdx.z / (unsigned)a.n_tensors));
+  gather_body<POW2, kGatherThreads, STREAM>(a, (int)blockIdx.x, (int)blockIdx.y, (int)(blockIdx.z % (unsigned)a.n_tensors),
+                                            (int)(blockIdx.z / (unsigned)a.n_tensors));
 }
+
+// Bytes read + written from which a launch's loads and stores are non-temporal: it sweeps more than the caches keep
+// for anyone, and leaving them out of it saves the evictions (HBM-bound; K and V of 8 heads, 2048 tokens:
+// 32 layers 109.0 -> 96.0 us = 5.6 TB/s, 16 layers 58.0 -> 50.6, 8 layers 31.2 -> 27.6, 6 layers (96 MiB) 22.2 either
+// way, 4 layers 14.4 with caching, 15.8 without).
+constexpr int64_t kGatherStreamBytes = int64_t(100) << 20;
 
 // Sets cpr_shift; returns whether the pieces per row are a power of two.
 bool gather_prepare(GatherArgs& a) {
@@ -34,10 +40,15 @@ hipError_t launch_gather(Prof* prof, const GatherArgs& args, int Hk, int n_layer
   const int per_block = kGatherThreads * kGatherUnroll;
   const dim3 grid((unsigned)((total + per_block - 1) / per_block), (unsigned)Hk, (unsigned)(n_layers * a.n_tensors));
   const bool pow2 = gather_prepare(a);
-  if (pow2)
-    ASL_LAUNCH(prof, kKernGather, st, gather_kernel<true>, grid, dim3(kGatherThreads), 0, st, a);
+  const bool stream = 2 * total * 16 * (int64_t)Hk * n_layers * a.n_tensors >= kGatherStreamBytes;
+  if (pow2 && stream)
+    ASL_LAUNCH(prof, kKernGather, st, (gather_kernel<true, true>), grid, dim3(kGatherThreads), 0, st, a);
+  else if (pow2)
+    ASL_LAUNCH(prof, kKernGather, st, (gather_kernel<true, false>), grid, dim3(kGatherThreads), 0, st, a);
+  else if (stream)
+    ASL_LAUNCH(prof, kKernGather, st, (gather_kernel<false, true>), grid, dim3(kGatherThreads), 0, st, a);
   else
-    ASL_LAUNCH(prof, kKernGather, st, gather_kernel<false>, grid, dim3(kGatherThreads), 0, st, a);
+    ASL_LAUNCH(prof, kKernGather, st, (gather_kernel<false, false>), grid, dim3(kGatherThreads), 0, st, a);
   return hipGetLastError();
 }
 

@@ -11,7 +11,8 @@ constexpr int kGatherUnroll = 4;      // pieces per thread (the body is written 
 // Workgroup (bx, h, which, layer) of NT threads: bx = block of NT * kGatherUnroll pieces of the slab
 // of KV head h, tensor `which` (0 = K, 1 = V), layer `layer`.  Pieces of a slab are numbered
 // q = row * cpr + c (row = output row, c = 16-byte piece of the row).
-template <bool POW2, int NT>
+// STREAM: rows and outputs pass the caches by (transfers that do not fit them anyway).
+template <bool POW2, int NT, bool STREAM = false>
 __device__ __forceinline__ void gather_body(const GatherArgs& a, int bx, int h, int which, int layer) {
   const char* src_base;
   char* dst_base;
@@ -38,6 +39,13 @@ __device__ __forceinline__ void gather_body(const GatherArgs& a, int bx, int h, 
   const GSrc src = (GSrc)src_base;
   const GDst dst = (GDst)dst_base;
   const GIdx gi = (GIdx)idx;
+  auto load = [](GSrc16 p) -> Piece { return STREAM ? __builtin_nontemporal_load(p) : *p; };
+  auto store = [](Piece v, GDst16 p) {
+    if (STREAM)
+      __builtin_nontemporal_store(v, p);
+    else
+      *p = v;
+  };
   // Loads are unconditional (piece numbers past the end are clamped to the last piece) so that all
   // four index loads, then all four row loads, are in flight together; only the stores are
   // predicated.  Written out rather than looped: the values must stay in registers.
@@ -48,14 +56,14 @@ __device__ __forceinline__ void gather_body(const GatherArgs& a, int bx, int h, 
   const uint32_t ra = POW2 ? (ca >> a.cpr_shift) : (ca / cpr), rb = POW2 ? (cb >> a.cpr_shift) : (cb / cpr);
   const uint32_t rc = POW2 ? (cc >> a.cpr_shift) : (cc / cpr), rd = POW2 ? (cd >> a.cpr_shift) : (cd / cpr);
   const int ta = gi[ra], tb = gi[rb], tc = gi[rc], td = gi[rd];
-  const Piece va = *(GSrc16)(src + (int64_t)ta * stt + (int64_t)(ca - ra * cpr) * 16);
-  const Piece vb = *(GSrc16)(src + (int64_t)tb * stt + (int64_t)(cb - rb * cpr) * 16);
-  const Piece vc = *(GSrc16)(src + (int64_t)tc * stt + (int64_t)(cc - rc * cpr) * 16);
-  const Piece vd = *(GSrc16)(src + (int64_t)td * stt + (int64_t)(cd - rd * cpr) * 16);
-  if (qa < total) *(GDst16)(dst + (int64_t)qa * 16) = va;
-  if (qb < total) *(GDst16)(dst + (int64_t)qb * 16) = vb;
-  if (qc < total) *(GDst16)(dst + (int64_t)qc * 16) = vc;
-  if (qd < total) *(GDst16)(dst + (int64_t)qd * 16) = vd;
+  const Piece va = load((GSrc16)(src + (int64_t)ta * stt + (int64_t)(ca - ra * cpr) * 16));
+  const Piece vb = load((GSrc16)(src + (int64_t)tb * stt + (int64_t)(cb - rb * cpr) * 16));
+  const Piece vc = load((GSrc16)(src + (int64_t)tc * stt + (int64_t)(cc - rc * cpr) * 16));
+  const Piece vd = load((GSrc16)(src + (int64_t)td * stt + (int64_t)(cd - rd * cpr) * 16));
+  if (qa < total) store(va, (GDst16)(dst + (int64_t)qa * 16));
+  if (qb < total) store(vb, (GDst16)(dst + (int64_t)qb * 16));
+  if (qc < total) store(vc, (GDst16)(dst + (int64_t)qc * 16));
+  if (qd < total) store(vd, (GDst16)(dst + (int64_t)qd * 16));
 }
 
 }  // namespace asl

@@ -404,6 +404,21 @@ def test_gather_empty_and_f32(ctx, gpu_device):
 
 
 # ----------------------------------------------------------------------------- errors
+@pytest.mark.parametrize("row_bytes,n_idx", [(8192, 6400), (8192, 6399), (192, 273067), (16, 3276801)])
+def test_gather_of_more_than_the_caches_hold(gpu_device, row_bytes, n_idx):
+    """100 MiB read and written is where the copies become non-temporal: at it, one row below, and past it with
+    rows that are no power of two of pieces and of a single piece."""
+    torch = _torch()
+    c = asl.Asl(64, 1, 1)
+    n_src = 5000
+    src = torch.randint(-2**31, 2**31 - 1, (n_src, row_bytes // 4), dtype=torch.int32, device=gpu_device)
+    idx = torch.randint(0, n_src, (n_idx,), dtype=torch.int32, device=gpu_device)
+    out = torch.zeros((n_idx, row_bytes // 4), dtype=torch.int32, device=gpu_device)
+    c.asl_gather_rows(src, row_bytes, row_bytes, idx, n_idx, out)
+    assert torch.equal(out, src[idx.long()])
+    c.close()
+
+
 def test_argument_errors(ctx, gpu_device):
     torch = _torch()
     sh = synth.shape_of(1)
