@@ -569,7 +569,17 @@ score_colsum_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, 
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
       ps[rb] = reinterpret_cast<const float2*>(row_part) + (int64_t)g * n_parts * M + min(row0 + rb * 32 + ln, m1 - 1);
-    combine_rows<RB, fold_batch<RB>()>(reinterpret_cast<const float2* const (&)[RB]>(ps), M, n_parts, half, mine);
+    // the smallest batch that takes all partials in one round: a batch is worked through whole, whatever it
+    // holds (always 48, pass 2 took 12.1 us at N = 512, 16.4 at 16K, 21.9 at 32K; so 8.7, 14.3, 19.8)
+    const auto& rows = reinterpret_cast<const float2* const (&)[RB]>(ps);
+    if (n_parts <= 2 * 8)
+      combine_rows<RB, 8>(rows, M, n_parts, half, mine);
+    else if (n_parts <= 2 * 16)
+      combine_rows<RB, 16>(rows, M, n_parts, half, mine);
+    else if (n_parts <= 2 * 32 && fold_batch<RB>() > 32)
+      combine_rows<RB, 32>(rows, M, n_parts, half, mine);
+    else
+      combine_rows<RB, fold_batch<RB>()>(rows, M, n_parts, half, mine);
   }
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
