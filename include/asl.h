@@ -219,7 +219,9 @@ asl_status asl_gather_rows(asl_ctx* ctx, const void* src, int64_t src_row_stride
  * (Hk per-head rows + the all-head row) and asl_gather_kv (per-head rows), with the same results as
  * the single calls.  After the scoring, ranking and top-k + compaction are independent; the call
  * runs them side by side in four launches on `stream`, launch i carrying pass i of the ranking sort
- * in some workgroups and stage i of the top-k / compaction in the others, followed by the statistic.
+ * in some workgroups and stage i of the top-k in the others, followed by one launch with the statistic
+ * (below l_min the note that it was not evaluated) beside the compaction.  Contexts of up to 12288 past
+ * tokens take one launch for the ranking and the top-k instead of four.
  *   scores  [Hk+1, T] f32 out: rows 0..Hk-1 = P (per KV head), row Hk = s (all heads).
  *   idx_out [Hk+1, k+W] int32 out: rows 0..Hk-1 = Alg. 1's per-head I, row Hk = Alg. 2's select_idx
  *           (to be used only when out->selected is set).
@@ -258,9 +260,9 @@ asl_status asl_device_fault(asl_ctx* ctx, int32_t* fault_out);
  * calls above).  Kernel ids: 0 score row statistics (pass 1), 1 its combine, 2 score column sums
  * (pass 2), 3 pool, 4 sort histogram, 5 sort scatter, 6 rank-variance finalisation (or the
  * below-L_min skip), 7 rank-variance partial sums, 8 select histogram, 9 select write, 10 gather,
- * 11 plain-FMA score kernels, 12 the four launches of asl_layer_step that carry sort passes and
+ * 11 plain-FMA score kernels, 12 the launches of asl_layer_step that carry sort passes and
  * top-k / compaction stages together.  (Each sort pass is one kernel, recorded under 5, id 4 is unused;
- * 8 covers the top-k's bound and filter kernels, 9 its finishing kernel; the statistic is one
+ * 8 covers the top-k's bound and filter kernels, 9 its finishing kernel (and the one of short rows); the statistic is one
  * kernel, 7; 6 is the below-L_min skip.)
  * asl_profile_enable: launches whose id bit is set in kernel_mask carry a HIP event pair that the
  *   runtime stamps with the kernel's start and end on the device (the call's stream; not under

@@ -67,7 +67,7 @@ struct Workspace {
   uint32_t* sel_seg_count; // [sel_rows][n_tiles] entries used in each segment
   int sel_rows;            // rows the candidate buffers hold at once
   // rank variance
-  unsigned long long* var_table;    // [kVarMaxBlocks][2] tagged per-workgroup partial sums
+  unsigned long long* var_table;    // [kVarMaxBlocks][4] tagged per-workgroup partial sums
   unsigned long long* var_epoch;    // [1]
   uint32_t* fault;         // [1] raised by a workgroup whose bounded wait for its peers ran out
   Prof* prof;              // null unless profiling is enabled
@@ -286,7 +286,7 @@ struct GatherArgs {
 hipError_t launch_gather(Prof* prof, const GatherArgs& args, int Hk, int n_layers, hipStream_t st);
 bool gather_prepare(GatherArgs& a);   // sets cpr_shift; returns whether cpr is a power of two
 // Ranking sort of the last of `rows` score rows + top-k of all rows + optional statistic and KV
-// compaction in five launches on one stream (tail.hip); *taken = false when the sizes do not fit and nothing was launched.
+// compaction in five launches (two for short contexts) on one stream (tail.hip); *taken = false when the sizes do not fit and nothing was launched.
 struct RankvarArgs;
 hipError_t launch_tail(const Workspace& ws, const float* scores, int rows, int T, int k, int W, int32_t* rank_row,
                        int32_t* idx_out, const GatherArgs* gather, int Hk, bool have_sample, const RankvarArgs& stat,

@@ -228,7 +228,10 @@ __device__ __forceinline__ void mma_subtile(const Piece* __restrict__ buf, int s
 // go first, so with two workgroups per unit the second ends up alone on it for the last part of the
 // kernel: the first gets a larger share, the more so the more the arithmetic bounds the kernel (pass 1 +
 // pass 2 at 256K, W = 64, RB = 2: equal shares 152 + 158 us, 1250 : 798 147 + 153, 1350 : 698 145 + 150;
-// 128K, RB = 1: 58 + 51, 55 + 50, 54 + 52).  Weights in 1/1024.
+// 128K, RB = 1: 58 + 51, 55 + 50, 54 + 52).  Up to four tiles per chunk that come out even to 1/16 stay equal:
+// weighted, rounding makes some chunks a tile longer (8 KV heads, whole call, weighted and equal: one tile, W = 64
+// 27.3 and 25.1 us; two tiles, W = 32 20.4 and 19.9; 2.9 22.8 and 22.2; but 2.45, W = 64 31.1 and 31.7, 2.7 of
+// d = 256 21.8 and 22.8, 5.9 28.5 and 28.9).  Weights in 1/1024.
 struct ChunkRange {
   int tile0, tile_end;
 };
@@ -238,7 +241,9 @@ template <int RB>
 __device__ __forceinline__ ChunkRange chunk_range(int chunk, int g, int Hk, int n_chunks, int n_tiles, int n_cu) {
   constexpr int kFirst = RB > 1 ? 1350 : 1250, kSecond = 2048 - kFirst;
   const int grid = n_chunks * Hk;
-  const bool two = grid > n_cu && grid <= 2 * n_cu;
+  const int slots = n_chunks * (1 + (n_tiles > n_chunks) + (n_tiles > 2 * n_chunks) + (n_tiles > 3 * n_chunks));
+  const bool even = n_tiles <= slots && 16 * (slots - n_tiles) <= slots;
+  const bool two = grid > n_cu && grid <= 2 * n_cu && !even;
   // cumulative weight of this head's chunks 0 .. c-1: chunk c' is block c'*Hk + g, placed as number
   // (c'*Hk + g) / n_cu on its compute unit; the first on it iff c' < ceil((n_cu - g) / Hk)
   const int n_first = max((n_cu - g + Hk - 1) / Hk, 0);

@@ -109,10 +109,12 @@ def test_row_groups(gpu_device, Hq, Hk, d, W, dtype):
 
 
 @pytest.mark.parametrize("Hq,Hk,W,N", [(2, 1, 32, 64 * 96), (2, 1, 32, 64 * 96 + 1), (2, 1, 32, 64 * 192 + 1), (3, 1, 64, 64 * 128 + 1),
-                                       (3, 1, 64, 64 * 64), (8, 8, 16, 64 * 65 + 3), (4, 4, 40, 64 * 257)])
+                                       (3, 1, 64, 64 * 64), (8, 8, 16, 64 * 65 + 3), (4, 4, 40, 64 * 257),
+                                       (8, 8, 16, 64 * 256 + 1), (24, 8, 64, 64 * 119 + 1)])
 def test_chunk_counts(gpu_device, Hq, Hk, W, N):
     """Key chunks of one tile and more, partials folded in one round of loads (96 chunks, 64 above 128 query
-    rows) and in several, one and two workgroups per compute unit."""
+    rows) and in several, one and two workgroups per compute unit, with weighted and (257 and 256, 119 and 120
+    tiles over 64 chunks) equal shares."""
     L = _small(Hq, Hk, 64, N, W, S=1, seed=N)
     P, s = _run_score(gpu_device, L)
     _close_to_64_bits(P, s, L)
