@@ -116,7 +116,8 @@ size_t asl_workspace_bytes(int32_t max_seq_len, int32_t max_kv_heads, int32_t ma
  * (ASL_EUNSUPPORTED beyond): by MFMA kernels as well (fp32 MFMA for fp32 inputs) when d <= 256 and rows,
  * pointers and strides are multiples of 16 bytes, else by plain fp32-FMA kernels, which are meant for
  * small problems.  Softmax and sums are fp32 and
- * deterministic (fixed reduction order, no float atomics). */
+ * deterministic (fixed reduction order, no float atomics).  A key whose logits are -Inf has probability 0;
+ * NaN logits (Inf - Inf, 0 * Inf between finite queries and infinite keys) give NaN scores. */
 asl_status asl_score_layer(asl_ctx* ctx, const asl_params* params, const void* q_obs,
                            const void* k, const float* lse, float* p_head, float* s_all,
                            void* stream);

@@ -51,8 +51,8 @@ __device__ __forceinline__ int acc_row(int r, int half) { return 8 * (r >> 2) + 
 // XOR swizzle applied on the global side: LDS slot (row r, piece c') holds the row's 16-byte piece
 // c = c' ^ (r mod 16)  (mod 8 where P is no multiple of 16).
 // Rows past N are clamped to the last key (they are masked or discarded later).  With PAD the row has
-// only np <= P pieces: the slots behind them repeat the row's last piece, and the query fragments hold
-// zeros there, so that they add nothing.
+// only np <= P pieces: the slots behind them repeat the row's last piece; the fragments of both operands
+// hold zeros there (zeros in one are not enough: 0 * Inf is NaN).
 // Per-thread constants of the tile loader: for each of its NLOAD pieces the byte offset of the
 // (swizzled) source piece from the tile's first key.
 // The first NT threads of the workgroup do the loading, NT = the largest power of two that is at most
@@ -188,11 +188,15 @@ __device__ __forceinline__ f32x16 mma_step(const Piece& a, const Piece& b, f32x1
   }
 }
 
+// Shortest row, in pieces, that a padded row length P is used for (see dispatch_padded).
+template <int P> constexpr int least_pieces() { return P <= 32 ? P - 7 : P - 15; }
+
 // QK^T of one 32-key sub-tile against this wave's RB blocks of 32 query rows (P/2 chained steps
 // per block; every K fragment is read from LDS once and used for all RB blocks).
 // KEYS_ON_REGS: accumulator register axis = keys (pass 1), else = query rows (pass 2).
-template <typename TE, int P, bool KEYS_ON_REGS, int RB>
-__device__ __forceinline__ void mma_subtile(const Piece* __restrict__ buf, int sub, int ln, int half,
+// PAD: pieces from np on are zeros; only the steps that a padded row can end in pay for the test.
+template <typename TE, int P, bool KEYS_ON_REGS, int RB, bool PAD>
+__device__ __forceinline__ void mma_subtile(const Piece* __restrict__ buf, int sub, int ln, int half, int np,
                                             const Piece (&qf)[RB][P / 2], f32x16 (&acc)[RB]) {
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
@@ -200,7 +204,8 @@ __device__ __forceinline__ void mma_subtile(const Piece* __restrict__ buf, int s
     for (int r = 0; r < 16; ++r) acc[rb][r] = 0.f;
 #pragma unroll
   for (int ks = 0; ks < P / 2; ++ks) {
-    const Piece kf = load_k_frag<P>(buf, sub, ln, half, ks);
+    Piece kf = load_k_frag<P>(buf, sub, ln, half, ks);
+    if (PAD && 2 * ks + 1 >= least_pieces<P>() && 2 * ks + half >= np) kf = Piece{0u, 0u, 0u, 0u};
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
       acc[rb] = KEYS_ON_REGS ? mma_step<TE>(kf, qf[rb][ks], acc[rb]) : mma_step<TE>(qf[rb][ks], kf, acc[rb]);
@@ -208,7 +213,9 @@ __device__ __forceinline__ void mma_subtile(const Piece* __restrict__ buf, int s
 }
 
 // Query fragments of this wave's RB 32-row blocks (block rb = rows row0 + 32*rb ..): lane (ln, half)
-// holds pieces 2*ks + half of row ln of each block; rows from m1 on and pieces from np on are zeros.
+// holds pieces 2*ks + half of row ln of each block; pieces from np on are zeros.  Rows from m1 on, whose
+// results are dropped, repeat row m1 - 1: their logits are then whatever a real row's are (a row of zeros
+// would make NaN of an infinite key and of pass 2's column sum over it).
 #define ASL_LOAD_Q_FRAGS()                                                                        \
   Piece qf[RB][KS];                                                                               \
   _Pragma("unroll") for (int rb = 0; rb < RB; ++rb) {                                             \
@@ -217,7 +224,7 @@ __device__ __forceinline__ void mma_subtile(const Piece* __restrict__ buf, int s
     _Pragma("unroll") for (int ks = 0; ks < KS; ++ks) {                                           \
       const int c_ = 2 * ks + half;                                                               \
       Piece raw_ = qg_[PAD ? min(c_, np - 1) : c_];                                               \
-      if (qr_ >= m1 || (PAD && c_ >= np)) raw_ = Piece{0u, 0u, 0u, 0u};                           \
+      if (PAD && c_ >= np) raw_ = Piece{0u, 0u, 0u, 0u};                                          \
       qf[rb][ks] = raw_;                                                                          \
     }                                                                                             \
   }
@@ -301,10 +308,10 @@ __device__ __forceinline__ void rowstats_fold(const f32x16 (&acc)[RB], int key_l
 // in one block of straight-line code with the softmax arithmetic of the sub-tile before it (`acc`, the
 // last sub-tile of the tile before on entry), so that a wavefront's own vector instructions fill the
 // time its MFMAs take.  MASK: tiles that touch the window block or the tail past N (they come last).
-template <typename TE, int P, int NT, int RB, bool MASK>
+template <typename TE, int P, int NT, int RB, bool PAD, bool MASK>
 __device__ __forceinline__ void rowstats_tile(const Piece* __restrict__ cur, Piece* __restrict__ nxt,
                                               bool prefetch, const TilePieces<P, NT>& tp, const char* __restrict__ kg, int64_t rsb,
-                                              int prefetch_key0, int last_piece, int tile, int N, int T, const int (&wi)[RB],
+                                              int prefetch_key0, int np, int last_piece, int tile, int N, int T, const int (&wi)[RB],
                                               int tid, int ln, int half, const Piece (&qf)[RB][P / 2], float c1,
                                               f32x16 (&acc)[RB], float (&m_run)[RB], float (&z_run)[RB]) {
   constexpr int KT = key_tile<P>();
@@ -312,7 +319,7 @@ __device__ __forceinline__ void rowstats_tile(const Piece* __restrict__ cur, Pie
 #pragma unroll
   for (int sub = 0; sub < KT / 32; ++sub) {
     f32x16 nxt_acc[RB];
-    mma_subtile<TE, P, true, RB>(cur, sub, ln, half, qf, nxt_acc);
+    mma_subtile<TE, P, true, RB, PAD>(cur, sub, ln, half, np, qf, nxt_acc);
     // the sub-tile before this one: keys (tile * KT + (sub - 1) * 32) + 4 * half ..
     rowstats_fold<RB, MASK>(acc, tile * KT + (sub - 1) * 32 + 4 * half, N, T, wi, c1, m_run, z_run);
 #pragma unroll
@@ -372,9 +379,9 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
     wait_tile<P, NT, STAGES>(min(STAGES - 2, tile_end - 1 - tile));
     __syncthreads();      // tile `tile` has landed for every wave; the buffer of tile-1 is free again
     const int free_stage = (stage == 0) ? STAGES - 1 : stage - 1;
-    rowstats_tile<TE, P, NT, RB, decltype(mask)::value>(
+    rowstats_tile<TE, P, NT, RB, PAD, decltype(mask)::value>(
         lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS, tile + STAGES - 1 < tile_end, tp, kg, kst,
-        (tile + STAGES - 1) * KT, last_piece, tile, N, T, wi, tid, ln, half, qf, c1, acc, m_run, z_run);
+        (tile + STAGES - 1) * KT, np, last_piece, tile, N, T, wi, tid, ln, half, qf, c1, acc, m_run, z_run);
     stage = (stage + 1 == STAGES) ? 0 : stage + 1;
   };
   // tiles of visible keys only, then those that touch the window block or the end (at most
@@ -504,10 +511,10 @@ __device__ __forceinline__ float colsum_subtile(const f32x16 (&acc)[RB], const f
 // beside the column partial sums of the sub-tile before each (`acc`; the last sub-tile of the tile
 // before on entry): the same pipeline as pass 1's.  red_prev, red_cur: this wave's partial sums of the
 // KT keys of the tile before and of this one.
-template <typename TE, int P, int NT, int RB, bool DENORM>
+template <typename TE, int P, int NT, int RB, bool PAD, bool DENORM>
 __device__ __forceinline__ void colsum_tile(const Piece* __restrict__ cur, Piece* __restrict__ nxt,
                                             bool prefetch, const TilePieces<P, NT>& tp, const char* __restrict__ kg, int64_t rsb,
-                                            int prefetch_key0, int last_piece, int N, int tid, int ln, int half,
+                                            int prefetch_key0, int np, int last_piece, int N, int tid, int ln, int half,
                                             const Piece (&qf)[RB][P / 2], const float (&rc)[RB][16], float c1,
                                             f32x16 (&acc)[RB], float* __restrict__ red_prev, float* __restrict__ red_cur) {
   constexpr int KT = key_tile<P>();
@@ -515,7 +522,7 @@ __device__ __forceinline__ void colsum_tile(const Piece* __restrict__ cur, Piece
 #pragma unroll
   for (int sub = 0; sub < KT / 32; ++sub) {
     f32x16 nxt_acc[RB];
-    mma_subtile<TE, P, false, RB>(cur, sub, ln, half, qf, nxt_acc);
+    mma_subtile<TE, P, false, RB, PAD>(cur, sub, ln, half, np, qf, nxt_acc);
     const float cs = colsum_subtile<RB, DENORM>(acc, rc, c1);
     float* red = (sub == 0) ? red_prev + KT - 32 : red_cur + (sub - 1) * 32;
     if (half == 0) red[ln] = cs;
@@ -528,7 +535,7 @@ __device__ __forceinline__ void colsum_tile(const Piece* __restrict__ cur, Piece
 // Pass 2: u_group[g][j] = sum over query rows [m0, m1) of 2^(c1*l_rj - rc_r),  j < T,
 // rc_r = rc_mul * row_const[g*M + r]  (log2-domain offset that already contains log2 Z_r).
 // From the second row group on (m0 > 0) the sum is added to what the launch before left there.
-template <typename TE, int P, int NW, int RB, bool PAD>
+template <typename TE, int P, int NW, int RB, bool PAD, bool DENORM>
 __global__ void __launch_bounds__(NW * 64)
 score_colsum_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, int64_t ksh,
                     int64_t kst, int np, int Hk, int M, int m0, int m1, int N, int T, int n_cu, float c1,
@@ -625,15 +632,15 @@ score_colsum_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, 
     __syncthreads();      // the tile has landed; tile it-1's fragment reads and tile it-2's partials are done
     if (it > 1) reduce_store(3 - cur_red - prev_red, (tile + 2) * KT);
     const int free_stage = (stage == 0) ? STAGES - 1 : stage - 1;
-    colsum_tile<TE, P, NT, RB, PAD>(lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS, it + STAGES - 1 < n_my,
-                                    tp, kg, kst, (tile - (STAGES - 1)) * KT, last_piece, N, tid, ln, half, qf, rc, c1, acc,
-                                    &red[prev_red][wave][0], &red[cur_red][wave][0]);
+    colsum_tile<TE, P, NT, RB, PAD, DENORM>(
+        lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS, it + STAGES - 1 < n_my, tp, kg, kst,
+        (tile - (STAGES - 1)) * KT, np, last_piece, N, tid, ln, half, qf, rc, c1, acc, &red[prev_red][wave][0], &red[cur_red][wave][0]);
     stage = (stage + 1 == STAGES) ? 0 : stage + 1;
     prev_red = cur_red;
     cur_red = (cur_red == 2) ? 0 : cur_red + 1;
   }
   if (n_my > 0) {
-    const float cs = colsum_subtile<RB, PAD>(acc, rc, c1);
+    const float cs = colsum_subtile<RB, DENORM>(acc, rc, c1);
     if (half == 0) red[prev_red][wave][KT - 32 + ln] = cs;
     __syncthreads();
     if (n_my > 1) reduce_store(3 - cur_red - prev_red, (tile0 + 1) * KT);
@@ -769,7 +776,8 @@ static int resident_per_cu(K kernel, int threads, size_t dynamic_lds = 0) {
   return n;
 }
 
-template <typename TE, int P, int NW, int RB, bool PAD>
+// PAD: rows of fewer than P pieces.  DENORM: see colsum_fold.
+template <typename TE, int P, int NW, int RB, bool PAD, bool DENORM>
 static hipError_t launch_score_mfma(const asl_params& p, const Workspace& ws, const void* q_obs, const void* k_ptr,
                                     const float* lse, float* lse_out, float c1, hipStream_t st) {
   constexpr int KT = key_tile<P>(), kRows = NW * 32 * RB;
@@ -780,7 +788,7 @@ static hipError_t launch_score_mfma(const asl_params& p, const Workspace& ws, co
   // both passes use the same LDS ring and nearly the same registers; take the smaller residency
   static const int resident = [] {
     const int a = resident_per_cu(score_rowstats_kernel<TE, P, NW, RB, PAD>, NW * 64);
-    const int b = resident_per_cu(score_colsum_kernel<TE, P, NW, RB, PAD>, NW * 64);
+    const int b = resident_per_cu(score_colsum_kernel<TE, P, NW, RB, PAD, DENORM>, NW * 64);
     return a < b ? a : b;
   }();
   const int n_chunks = score_chunks(p, KT, resident, 2 * fold_batch<RB>());
@@ -801,7 +809,7 @@ static hipError_t launch_score_mfma(const asl_params& p, const Workspace& ws, co
   const int n_chunks2 = n_chunks < n_tiles2 ? n_chunks : n_tiles2;
   // without the caller's log-sum-exp every pass-2 workgroup folds pass 1's partials of its own rows
   for (int m0 = 0; m0 < M; m0 += kRows)
-    ASL_LAUNCH(ws.prof, kKernColsum, st, (score_colsum_kernel<TE, P, NW, RB, PAD>), dim3(Hk * n_chunks2), dim3(NW * 64), 0, st,
+    ASL_LAUNCH(ws.prof, kKernColsum, st, (score_colsum_kernel<TE, P, NW, RB, PAD, DENORM>), dim3(Hk * n_chunks2), dim3(NW * 64), 0, st,
                q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, N, T, n_cu, c1, lse, kLog2e,
                lse ? nullptr : ws.row_part, n_chunks, ws.u_group);
   return hipGetLastError();
@@ -815,20 +823,20 @@ static hipError_t dispatch_nw(int M, const asl_params& p, const Workspace& ws, c
                               const void* k, const float* lse, float* lse_out, float c1, hipStream_t st) {
   if (M <= 128) {
     switch ((M + 31) / 32) {
-      case 1: return launch_score_mfma<__bf16, P, 1, 1, false>(p, ws, q, k, lse, lse_out, c1, st);
-      case 2: return launch_score_mfma<__bf16, P, 2, 1, false>(p, ws, q, k, lse, lse_out, c1, st);
-      case 3: return launch_score_mfma<__bf16, P, 3, 1, false>(p, ws, q, k, lse, lse_out, c1, st);
-      default: return launch_score_mfma<__bf16, P, 4, 1, false>(p, ws, q, k, lse, lse_out, c1, st);
+      case 1: return launch_score_mfma<__bf16, P, 1, 1, false, false>(p, ws, q, k, lse, lse_out, c1, st);
+      case 2: return launch_score_mfma<__bf16, P, 2, 1, false, false>(p, ws, q, k, lse, lse_out, c1, st);
+      case 3: return launch_score_mfma<__bf16, P, 3, 1, false, false>(p, ws, q, k, lse, lse_out, c1, st);
+      default: return launch_score_mfma<__bf16, P, 4, 1, false, false>(p, ws, q, k, lse, lse_out, c1, st);
     }
   }
   switch ((M + 63) / 64) {
-    case 3: return launch_score_mfma<__bf16, P, 3, 2, false>(p, ws, q, k, lse, lse_out, c1, st);
-    case 4: return launch_score_mfma<__bf16, P, 4, 2, false>(p, ws, q, k, lse, lse_out, c1, st);
-    case 5: return launch_score_mfma<__bf16, P, 5, 2, false>(p, ws, q, k, lse, lse_out, c1, st);
-    case 6: return launch_score_mfma<__bf16, P, 6, 2, false>(p, ws, q, k, lse, lse_out, c1, st);
-    case 7: return launch_score_mfma<__bf16, P, 7, 2, false>(p, ws, q, k, lse, lse_out, c1, st);
-    case 8: return launch_score_mfma<__bf16, P, 8, 2, false>(p, ws, q, k, lse, lse_out, c1, st);
-    default: return launch_score_mfma<__bf16, P, 8, 2, true>(p, ws, q, k, lse, lse_out, c1, st);
+    case 3: return launch_score_mfma<__bf16, P, 3, 2, false, false>(p, ws, q, k, lse, lse_out, c1, st);
+    case 4: return launch_score_mfma<__bf16, P, 4, 2, false, false>(p, ws, q, k, lse, lse_out, c1, st);
+    case 5: return launch_score_mfma<__bf16, P, 5, 2, false, false>(p, ws, q, k, lse, lse_out, c1, st);
+    case 6: return launch_score_mfma<__bf16, P, 6, 2, false, false>(p, ws, q, k, lse, lse_out, c1, st);
+    case 7: return launch_score_mfma<__bf16, P, 7, 2, false, false>(p, ws, q, k, lse, lse_out, c1, st);
+    case 8: return launch_score_mfma<__bf16, P, 8, 2, false, false>(p, ws, q, k, lse, lse_out, c1, st);
+    default: return launch_score_mfma<__bf16, P, 8, 2, false, true>(p, ws, q, k, lse, lse_out, c1, st);
   }
 }
 
@@ -837,26 +845,35 @@ static hipError_t dispatch_nw(int M, const asl_params& p, const Workspace& ws, c
 // W = 16: 247 + 6.5 us, here 4.5 + 4.5; bf16 Hq8/Hk4/d256, N = 8192, W = 32: 2104 + 177 us, here ~10 + ~10
 // (the whole call 2274 -> 25.5 us).  fp32 MFMA multiplies and adds in full fp32.
 // np pieces of a row in the next longer of the built row lengths P; one
-// 32-row block per wavefront, up to 128 query rows per launch.
-template <typename TE, int P>
+// 32-row block per wavefront, up to 128 query rows per launch.  Rows that fill P (the powers of two, mostly) have
+// kernels of their own, without the test for pieces behind a row: d = 256, N = 8192, `lse` supplied, 12.6 -> 12.0 us.
+template <typename TE, int P, bool PAD>
 static hipError_t dispatch_padded_nw(int M, const asl_params& p, const Workspace& ws, const void* q,
                                      const void* k, const float* lse, float* lse_out, float c1, hipStream_t st) {
-  if (M <= 32) return launch_score_mfma<TE, P, 1, 1, true>(p, ws, q, k, lse, lse_out, c1, st);
-  if (M <= 64) return launch_score_mfma<TE, P, 2, 1, true>(p, ws, q, k, lse, lse_out, c1, st);
-  return launch_score_mfma<TE, P, 4, 1, true>(p, ws, q, k, lse, lse_out, c1, st);
+  if (M <= 32) return launch_score_mfma<TE, P, 1, 1, PAD, true>(p, ws, q, k, lse, lse_out, c1, st);
+  if (M <= 64) return launch_score_mfma<TE, P, 2, 1, PAD, true>(p, ws, q, k, lse, lse_out, c1, st);
+  return launch_score_mfma<TE, P, 4, 1, PAD, true>(p, ws, q, k, lse, lse_out, c1, st);
+}
+template <typename TE, int P>
+static hipError_t dispatch_row_length(int np, int M, const asl_params& p, const Workspace& ws, const void* q,
+                                      const void* k, const float* lse, float* lse_out, float c1, hipStream_t st) {
+  if constexpr (sizeof(TE) == 4 || P > 16) {          // full bf16 rows of 8 and 16 pieces are dispatch_nw's
+    if (np == P) return dispatch_padded_nw<TE, P, false>(M, p, ws, q, k, lse, lse_out, c1, st);
+  }
+  return dispatch_padded_nw<TE, P, true>(M, p, ws, q, k, lse, lse_out, c1, st);
 }
 template <typename TE>
 static hipError_t dispatch_padded(int M, const asl_params& p, const Workspace& ws, const void* q,
                                   const void* k, const float* lse, float* lse_out, float c1, hipStream_t st) {
   const int np = p.head_dim * (int)sizeof(TE) / 16;
-  if (np <= 8) return dispatch_padded_nw<TE, 8>(M, p, ws, q, k, lse, lse_out, c1, st);
-  if (np <= 16) return dispatch_padded_nw<TE, 16>(M, p, ws, q, k, lse, lse_out, c1, st);
-  if (np <= 24) return dispatch_padded_nw<TE, 24>(M, p, ws, q, k, lse, lse_out, c1, st);
+  if (np <= 8) return dispatch_row_length<TE, 8>(np, M, p, ws, q, k, lse, lse_out, c1, st);
+  if (np <= 16) return dispatch_row_length<TE, 16>(np, M, p, ws, q, k, lse, lse_out, c1, st);
+  if (np <= 24) return dispatch_row_length<TE, 24>(np, M, p, ws, q, k, lse, lse_out, c1, st);
   if constexpr (sizeof(TE) == 4) {
-    if (np > 48) return dispatch_padded_nw<TE, 64>(M, p, ws, q, k, lse, lse_out, c1, st);
-    if (np > 32) return dispatch_padded_nw<TE, 48>(M, p, ws, q, k, lse, lse_out, c1, st);
+    if (np > 48) return dispatch_row_length<TE, 64>(np, M, p, ws, q, k, lse, lse_out, c1, st);
+    if (np > 32) return dispatch_row_length<TE, 48>(np, M, p, ws, q, k, lse, lse_out, c1, st);
   }
-  return dispatch_padded_nw<TE, 32>(M, p, ws, q, k, lse, lse_out, c1, st);
+  return dispatch_row_length<TE, 32>(np, M, p, ws, q, k, lse, lse_out, c1, st);
 }
 
 // Whether the MFMA kernels can read these operands: whole 16-byte pieces on 16-byte boundaries, rows

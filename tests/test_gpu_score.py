@@ -108,6 +108,28 @@ def test_row_groups(gpu_device, Hq, Hk, d, W, dtype):
     _compare(gpu_device, L, use_lse=True)
 
 
+# Rows that end inside the built row lengths and rows that fill them; 16 and 224 query rows, so that blocks of 32
+# are partly and wholly filled up; a row group that is (528 rows: 512 + 16).
+@pytest.mark.parametrize("Hq,Hk,d,W,dtype", [(4, 2, 80, 8, "f32"), (4, 2, 4, 8, "f32"), (4, 2, 64, 8, "f32"), (4, 2, 132, 8, "f32"),
+                                             (4, 2, 96, 8, "bf16"), (4, 2, 248, 8, "bf16"), (4, 2, 256, 8, "bf16"),
+                                             (4, 2, 128, 8, "bf16"), (7, 1, 64, 32, "bf16"), (33, 1, 64, 16, "bf16")])
+def test_infinite_keys(gpu_device, Hq, Hk, d, W, dtype):
+    """A key whose logits are all -Inf has probability 0 and leaves the other keys' scores alone (keys of the first
+    and of later tiles, the last past one, and a window key; the infinite element is the row's last)."""
+    L = _small(Hq, Hk, d, 700, W, dtype=dtype, seed=d)
+    past = [5, 333, 700 - W - 1]
+    L.q_obs[:, :, -1] = 1.5
+    L.k[:, past + [699], -1] = -np.inf
+    L.shape.S = 1
+    for use_lse in (False, True):
+        P, s = _compare(gpu_device, L, use_lse=use_lse)
+        assert np.isfinite(P).all() and np.isfinite(s).all()
+        assert (P[:, past] == 0).all() and (s[past] == 0).all()
+        Pg, _ = _compare(gpu_device, L, flags=asl.ASL_FLAG_GENERIC_SCORE, use_lse=use_lse)
+        # both kernels within 2e-5 of the 64-bit value (see _close_to_64_bits)
+        np.testing.assert_allclose(P, Pg, rtol=4e-5, atol=1e-12)
+
+
 @pytest.mark.parametrize("Hq,Hk,W,N", [(2, 1, 32, 64 * 96), (2, 1, 32, 64 * 96 + 1), (2, 1, 32, 64 * 192 + 1), (3, 1, 64, 64 * 128 + 1),
                                        (3, 1, 64, 64 * 64), (8, 8, 16, 64 * 65 + 3), (4, 4, 40, 64 * 257),
                                        (8, 8, 16, 64 * 256 + 1), (24, 8, 64, 64 * 119 + 1)])
