@@ -139,7 +139,7 @@ asl_status asl_pool(asl_ctx* ctx, const float* u, int32_t rows, int32_t T, int32
                     float* p_out, float* s_out, void* stream);
 
 /* Alg. 1 step 11, RankDesc: rank_out[t] = #{t': s[t'] > s[t]} + #{t' < t: s[t'] == s[t]}.
- *   s [T] f32 in; rank_out [T] int32 out (a permutation of 0..T-1). */
+ *   s [T] f32 in; rank_out [T] int32 out (a permutation of 0..T-1); the two may be the same memory. */
 asl_status asl_rank(asl_ctx* ctx, const float* s, int32_t T, int32_t* rank_out, void* stream);
 
 /* asl_rank for callers that cannot allocate device memory: code under HIP graph capture, tight

@@ -5,7 +5,8 @@
 // 32-bit transform of the fp32 score, 8 bits per pass, ONE kernel per pass; the last pass scatters
 // positions to rank[index] instead of writing the sorted pairs.
 //
-// Short vectors (kShortT) are ranked by counting instead, in one launch (rank_count_body).
+// Short vectors (kShortT) are ranked by counting instead, in one launch (rank_count_body), unless the ranks
+// overwrite the scores.
 //
 // In a pass every workgroup owns one tile of consecutive elements.  It counts its tile's digits in
 // LDS, publishes the 256 counts, reads every tile's counts (total per digit and the part that
@@ -102,7 +103,11 @@ static hipError_t launch_rank_r(const Workspace& ws, const float* s, int T, int 
 }
 
 hipError_t launch_rank(const Workspace& ws, const float* s, int T, int32_t* rank_out, hipStream_t st) {
-  if (T <= kShortT) {
+  // Counting workgroups read all scores while others already write ranks; the sort reads them in its first pass
+  // and writes ranks in its last, so it takes the calls that rank a vector in place.
+  const uintptr_t s0 = reinterpret_cast<uintptr_t>(s), r0 = reinterpret_cast<uintptr_t>(rank_out), bytes = (uintptr_t)T * 4;
+  const bool in_place = s0 < r0 + bytes && r0 < s0 + bytes;
+  if (T <= kShortT && !in_place) {
     ASL_LAUNCH(ws.prof, kKernSortScatter, st, rank_count_kernel, dim3(rank_count_blocks(T)), dim3(kSortThreads), 0, st, s, T, rank_out);
     return hipGetLastError();
   }

@@ -63,6 +63,21 @@ def test_rank_random_with_ties(ctx, gpu_device, T):
     _rank_case(ctx, gpu_device, s)
 
 
+@pytest.mark.parametrize("T", [1, 33, 500, 12288, 12289])
+def test_rank_over_its_own_scores(ctx, gpu_device, T):
+    """Ranks written over the scores they are made from, over part of them, and right behind them."""
+    torch = _torch()
+    s = np.round(np.random.default_rng(T).standard_normal(T), 2).astype(np.float32)
+    ref = orc.rank_desc(s.astype(np.float64))
+    for shift in (0, T // 2, T):
+        for rank in (ctx.asl_rank, asl.asl_rank_static):
+            buf = torch.zeros(2 * T, dtype=torch.float32, device=gpu_device)
+            buf[:T] = torch.from_numpy(s).to(gpu_device)
+            out = buf.view(torch.int32)[shift:shift + T]
+            rank(buf[:T], T, out)
+            np.testing.assert_array_equal(out.cpu().numpy().astype(np.int64), ref)
+
+
 @pytest.mark.parametrize("T", [524288, 524289, 700001])
 def test_rank_beyond_the_small_tile_limit(gpu_device, T):
     """Above 256 tiles of 2048 the sort switches to tiles of 8192 elements: the last size that still uses
