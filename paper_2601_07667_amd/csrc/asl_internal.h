@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <stddef.h>
 #include "asl.h"
+#include "select_bound.h"
 
 namespace asl {
 
@@ -76,34 +77,17 @@ struct Workspace {
 #ifndef ASL_SORT_TILE
 #define ASL_SORT_TILE 2048
 #endif
-#ifndef ASL_SEL_TILE
-#define ASL_SEL_TILE 4096
-#endif
 #ifndef ASL_SORT_THREADS
 #define ASL_SORT_THREADS 1024
 #endif
 constexpr int kSortTile = ASL_SORT_TILE;   // elements per radix-sort workgroup tile (a multiple of 256)
-constexpr int kSelTile = ASL_SEL_TILE;     // elements per select workgroup tile (a multiple of 256)
 constexpr int kShortT = 12288;           // longest score vector that one workgroup holds in LDS (below 64 KB with the
                                          // selection's counters): ranked and selected from in one launch
 constexpr int kMaxChunks = 256;        // key chunks per KV head in scoring pass 1
 constexpr int kVarMaxBlocks = 256;     // workgroups of the rank-variance kernel
 constexpr int kSortMaxTiles = 512;     // workgroups of one sort launch (they wait for each other)
-constexpr int kSelSegment = kSelTile / 2;   // candidate slots per select tile
-constexpr int kSelCandCap = 16384;     // candidates of one row the finishing workgroup holds in LDS
 constexpr int kSelMaxRowTiles = 1024;  // tiles per row the candidate path handles
 constexpr int kSelMaxRowsAtOnce = 256; // rows per round of select launches (bounds the candidate buffers)
-
-// ---- the strided sample the top-k takes its bound from -------------------------------------------
-// n_s = sel_sample_size(T) keys of a row at positions j * sel_sample_stride(T), j < n_s.
-constexpr int kSelMaxSample = 8192;    // sampled keys per row
-__host__ __device__ inline int sel_sample_size(int T) {
-  int n = T / 32;
-  n = n < 1024 ? 1024 : n;
-  n = n > kSelMaxSample ? kSelMaxSample : n;
-  return n < T ? n : T;
-}
-__host__ __device__ inline int sel_sample_stride(int T) { return T / sel_sample_size(T); }   // >= 1 for T >= 1
 
 // ---- counts handed between workgroups of one launch -------------------------------------------
 // A 64-bit word = (tag << 28) | (count1 << 14) | count0, written and read whole with relaxed

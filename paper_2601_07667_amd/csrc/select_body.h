@@ -13,19 +13,6 @@ constexpr int kFilterSmallFrom = 2048;                 // ... (rows x tiles per 
 constexpr uint32_t kSegOverflow = 0xffffffffu;         // a tile's count when its segment was too small
 static_assert(kSelTile % kFinThreads == 0 && kSelTile % kFilterThreads == 0, "filter tile geometry");
 
-// Rank m of the sample key taken as the bound: f = n_s / T of the row is sampled, the top-k members
-// among the sample are ~Binomial(n_s, k / T) with mean k f; m = k f + 5 sqrt(c k f) + 4 leaves the
-// bound too low with probability < 1e-6.  c = 1 for single sampled keys; c = `run` when the sample
-// consists of runs of `run` neighbouring keys, which may be as correlated as identical (pooled
-// scores are): the count's variance is then at most `run` times the binomial one.
-__host__ __device__ inline int sel_sample_rank(int T, int k, int n_s, int run) {
-  const float kf = (float)k * (float)n_s / (float)T;
-  const int m = (int)(kf + 5.0f * sqrtf((float)run * kf) + 4.0f);
-  return m;                                            // >= n_s means: no usable bound, admit everything
-}
-// Without a prepared sample the bound kernel reads runs of kSelSampleRun neighbouring keys, one run
-// per kSelSampleRun sample strides: the same number of keys from a quarter of the cache lines.
-constexpr int kSelSampleRun = 4;
 static_assert(kSelMaxSample % kFinThreads == 0, "the bound kernel's threads share the sample evenly");
 
 // Exclusive prefix over the workgroup's threads of two counters (kFinThreads threads), plus totals.
@@ -150,6 +137,8 @@ struct SelectArgs {
   const float* scores;           // [rows][T]
   const uint32_t* sample;        // [rows][kSelMaxSample] keys at the sample positions, or null
   int T, n_tiles, k, W;
+  int n_s, stride, runs;         // the sample: keys, stride between their positions, whether they come in runs
+  int m, slack;                  // rank of the bound in the sample, sample keys it may let pass beyond (see select_bound.h)
   uint32_t* bound;               // [rows]
   uint32_t* thr;                 // [rows][2] (threshold key, kept ties) when step 3 spans two launches
   uint32_t* cand_key;            // [rows][n_tiles][kSelSegment]
@@ -164,14 +153,10 @@ struct GuessShared {
   uint32_t sm[2 * kFinWaves + 2];
 };
 
-// Step 1: bound[row] = the m-th smallest key of the row's strided sample, or a key that up to an eighth more of
-// the sample's keys do not exceed (which saves one or two of the four digit passes); 0xffffffff: admit all.
+// Step 1: bound[row] = the m-th smallest key of the row's strided sample, or a key that up to sel_bound_slack more
+// of the sample's keys do not exceed (which saves one or two of the four digit passes); 0xffffffff: admit all.
 __device__ __forceinline__ void select_guess_body(GuessShared& sh, const SelectArgs& a, int row) {
-  const int tid = threadIdx.x, T = a.T;
-  const int stride = sel_sample_stride(T);
-  const bool runs = a.sample == nullptr && stride >= 2;           // stride 1: the sample is the row itself
-  const int n_s = runs ? (sel_sample_size(T) / kSelSampleRun) * kSelSampleRun : sel_sample_size(T);
-  const int m = sel_sample_rank(T, a.k, n_s, runs ? kSelSampleRun : 1);
+  const int tid = threadIdx.x, n_s = a.n_s, stride = a.stride, m = a.m;
   if (m >= n_s) {                                      // uniform
     if (tid == 0) a.bound[row] = 0xffffffffu;
     return;
@@ -185,8 +170,8 @@ __device__ __forceinline__ void select_guess_body(GuessShared& sh, const SelectA
 #pragma unroll
     for (int u = 0; u < kSampPer; ++u) v[u] = sp[min(tid + u * kFinThreads, n_s - 1)];
   } else {
-    const float* sr = a.scores + (int64_t)row * T;
-    if (runs) {                                        // key j = member j % run of run j / run
+    const float* sr = a.scores + (int64_t)row * a.T;
+    if (a.runs) {                                      // key j = member j % run of run j / run
 #pragma unroll
       for (int u = 0; u < kSampPer; ++u) {
         const int j = min(tid + u * kFinThreads, n_s - 1);
@@ -201,7 +186,7 @@ __device__ __forceinline__ void select_guess_body(GuessShared& sh, const SelectA
   for (int u = 0; u < kSampPer; ++u)
     if (tid + u * kFinThreads < n_s) sh.samp[tid + u * kFinThreads] = v[u];
   uint32_t thr, k_rem;
-  radix_select_block(n_s, (uint32_t)m, [&](int i) { return sh.samp[i]; }, sh.h, sh.sm, thr, k_rem, (uint32_t)m / 8u);
+  radix_select_block(n_s, (uint32_t)m, [&](int i) { return sh.samp[i]; }, sh.h, sh.sm, thr, k_rem, (uint32_t)a.slack);
   if (tid == 0) a.bound[row] = thr;
 }
 

@@ -1,0 +1,57 @@
+// The arithmetic behind the top-k's bound (see select.hip): the strided sample it is taken from, its rank in the
+// sample, and the candidate buffers it has to respect.  Host code: the kernels get the numbers as arguments (worked
+// out by every workgroup of the bound kernel they cost it 0.5 us).
+#pragma once
+#include <math.h>
+
+#ifndef ASL_SEL_TILE
+#define ASL_SEL_TILE 4096
+#endif
+
+namespace asl {
+
+constexpr int kSelTile = ASL_SEL_TILE;     // elements per select workgroup tile (a multiple of 256)
+constexpr int kSelSegment = kSelTile / 2;   // candidate slots per select tile
+constexpr int kSelCandCap = 16384;     // candidates of one row the finishing workgroup holds in LDS
+
+// n_s = sel_sample_size(T) keys of a row at positions j * sel_sample_stride(T), j < n_s.
+constexpr int kSelMaxSample = 8192;    // sampled keys per row
+inline int sel_sample_size(int T) {
+  int n = T / 32;
+  n = n < 1024 ? 1024 : n;
+  n = n > kSelMaxSample ? kSelMaxSample : n;
+  return n < T ? n : T;
+}
+inline int sel_sample_stride(int T) { return T / sel_sample_size(T); }   // >= 1 for T >= 1
+// Rank m of the sample key taken as the bound: f = n_s / T of the row is sampled, the top-k members
+// among the sample are ~Binomial(n_s, k / T) with mean k f; m = k f + 5 sqrt(c k f) + 4 leaves the
+// bound too low with probability < 1e-6.  c = 1 for single sampled keys; c = `run` when the sample
+// consists of runs of `run` neighbouring keys, which may be as correlated as identical (pooled
+// scores are): the count's variance is then at most `run` times the binomial one.
+inline int sel_sample_rank(int T, int k, int n_s, int run) {
+  const float kf = (float)k * (float)n_s / (float)T;
+  const int m = (int)(kf + 5.0f * sqrtf((float)run * kf) + 4.0f);
+  return m;                                            // >= n_s means: no usable bound, admit everything
+}
+// How many sample keys beyond the m-th the bound may let pass: m / 8, and no more than the candidate buffers
+// hold.  The m-th sample key admits m T / n_s tokens with standard deviation T / n_s sqrt(c m), c as above; a row's
+// buffer must keep 3 of those free.  A tile's segment holds kSelTile / n_s keys per sample key, with the bound's
+// deviation and that of the tile itself (kSelTile / 4 tokens in independent groups of 8, wider than pooling
+// couples them); it must keep 4 free, since any of a row's tiles may overflow.  A row whose buffers overflow is
+// selected from global memory (128K, one layer step: 190 us at k = 11 800 so, 235 with m / 8 throughout); where the
+// m-th key alone overflows them by a deviation, nothing is left to lose.
+inline int sel_bound_slack(int T, int m, int n_s, int run) {
+  const float per_key = (float)T / (float)n_s, per_key_tile = (float)kSelTile / (float)n_s, var = (float)run * (float)m;
+  const float row_room = (float)kSelCandCap - (float)m * per_key, row_dev = per_key * sqrtf(var);
+  const float tile_room = (float)kSelSegment - (float)m * per_key_tile, tile_dev = sqrtf(per_key_tile * per_key_tile * var + 2.0f * (float)kSelTile);
+  const int s = m / 8;
+  if (row_room < -row_dev || tile_room < -tile_dev) return s;
+  const float row = (row_room - 3.0f * row_dev) / per_key, tile = (tile_room - 4.0f * tile_dev) / per_key_tile;
+  const float cap = row < tile ? row : tile;
+  return cap <= 0.f ? 0 : ((float)s < cap ? s : (int)cap);
+}
+// Without a prepared sample the bound kernel reads runs of kSelSampleRun neighbouring keys, one run
+// per kSelSampleRun sample strides: the same number of keys from a quarter of the cache lines.
+constexpr int kSelSampleRun = 4;
+
+}  // namespace asl

@@ -1,0 +1,50 @@
+"""The top-k's bound leaves the candidate buffers room (host arithmetic of the library's header; no GPU needed)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def bound(tmp_path_factory):
+    gxx = shutil.which("g++")
+    assert gxx, "g++ is part of the toolchain this repository builds with"
+    exe = str(tmp_path_factory.mktemp("bound") / "bound_client")
+    subprocess.run([gxx, "-std=c++17", "-Wall", "-Wextra", "-Werror", "-I", os.path.join(ROOT, "paper_2601_07667_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "bound_client.cpp"), "-o", exe], check=True)
+
+    def ask(queries):
+        out = subprocess.run([exe], input="".join("%d %d %d\n" % q for q in queries), check=True, capture_output=True, text=True).stdout
+        return [tuple(int(x) for x in ln.split()) for ln in out.splitlines()]
+    return ask
+
+
+def test_slack_stays_within_the_candidate_buffers(bound):
+    """Wherever the bound may pass more than the m-th sample key, the tokens that m + slack sample keys stand for fit a
+    row's buffer with 3 standard deviations of the m-th key's count to spare, and a tile's segment with 4; or the m-th
+    key alone overflows one of them by a deviation."""
+    queries = [(T, k, runs) for T in (12289, 16352, 20001, 24544, 32736, 65504, 131040, 262080, 1048544)
+               for k in (1, 64, 500, 2016, 3000, 4000, 4540, 5250, 5730, 6540, 6990, 8160, 9000, 9090, 10000, 11440, 11800, 12600, 14000)
+               for runs in (0, 1) if k <= T]
+    used = full = 0
+    for (T, k, runs), (n_s, run, m, slack, cap, tile, seg) in zip(queries, bound(queries)):
+        assert 0 <= slack <= m // 8, (T, k, runs)
+        if slack == 0:
+            continue
+        row_dev, tile_dev = T / n_s * (run * m) ** 0.5, ((tile / n_s) ** 2 * run * m + 2 * tile) ** 0.5
+        if m * T / n_s > cap + row_dev * (1 - 1e-5) or m * tile / n_s > seg + tile_dev * (1 - 1e-5):
+            continue
+        used += 1
+        full += slack == m // 8
+        assert (m + slack) * T / n_s + 3 * row_dev <= cap * (1 + 1e-6), (T, k, runs)
+        assert (m + slack) * tile / n_s + 4 * tile_dev <= seg * (1 + 1e-6), (T, k, runs)
+    assert used > 100 and full > 80                    # the early stop is still there for ordinary budgets
+
+
+def test_ordinary_budgets_keep_the_whole_slack(bound):
+    queries = [(T, 2016, runs) for T in (32736, 131040, 262080) for runs in (0, 1)]
+    for q, (n_s, run, m, slack, *_) in zip(queries, bound(queries)):
+        assert slack == m // 8 > 0, q
