@@ -81,8 +81,6 @@ struct Workspace {
 #define ASL_SORT_THREADS 1024
 #endif
 constexpr int kSortTile = ASL_SORT_TILE;   // elements per radix-sort workgroup tile (a multiple of 256)
-constexpr int kShortT = 12288;           // longest score vector that one workgroup holds in LDS (below 64 KB with the
-                                         // selection's counters): ranked and selected from in one launch
 constexpr int kMaxChunks = 256;        // key chunks per KV head in scoring pass 1
 constexpr int kVarMaxBlocks = 256;     // workgroups of the rank-variance kernel
 constexpr int kSortMaxTiles = 512;     // workgroups of one sort launch (they wait for each other)

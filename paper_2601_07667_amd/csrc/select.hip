@@ -58,9 +58,8 @@ SelectArgs select_args(const Workspace& ws, const float* scores, int T, int k, i
   a.n_tiles = (T + kSelTile - 1) / kSelTile;
   a.k = k;
   a.W = W;
+  const int run = have_sample ? 1 : kSelSampleRun;
   a.stride = sel_sample_stride(T);
-  a.runs = !have_sample && a.stride >= 2 ? 1 : 0;                 // stride 1: the sample is the row itself
-  const int run = a.runs != 0 ? kSelSampleRun : 1;
   a.n_s = sel_sample_size(T) / run * run;
   a.m = sel_sample_rank(T, k, a.n_s, run);
   a.slack = sel_bound_slack(T, a.m, a.n_s, run);

@@ -137,7 +137,7 @@ struct SelectArgs {
   const float* scores;           // [rows][T]
   const uint32_t* sample;        // [rows][kSelMaxSample] keys at the sample positions, or null
   int T, n_tiles, k, W;
-  int n_s, stride, runs;         // the sample: keys, stride between their positions, whether they come in runs
+  int n_s, stride;               // the sample: keys and the stride between their positions
   int m, slack;                  // rank of the bound in the sample, sample keys it may let pass beyond (see select_bound.h)
   uint32_t* bound;               // [rows]
   uint32_t* thr;                 // [rows][2] (threshold key, kept ties) when step 3 spans two launches
@@ -171,15 +171,10 @@ __device__ __forceinline__ void select_guess_body(GuessShared& sh, const SelectA
     for (int u = 0; u < kSampPer; ++u) v[u] = sp[min(tid + u * kFinThreads, n_s - 1)];
   } else {
     const float* sr = a.scores + (int64_t)row * a.T;
-    if (a.runs) {                                      // key j = member j % run of run j / run
 #pragma unroll
-      for (int u = 0; u < kSampPer; ++u) {
-        const int j = min(tid + u * kFinThreads, n_s - 1);
-        v[u] = order_key(sr[(j / kSelSampleRun) * (kSelSampleRun * stride) + (j % kSelSampleRun)]);
-      }
-    } else {
-#pragma unroll
-      for (int u = 0; u < kSampPer; ++u) v[u] = order_key(sr[min(tid + u * kFinThreads, n_s - 1) * stride]);
+    for (int u = 0; u < kSampPer; ++u) {               // key j = member j % run of run j / run
+      const int j = min(tid + u * kFinThreads, n_s - 1);
+      v[u] = order_key(sr[(j / kSelSampleRun) * (kSelSampleRun * stride) + (j % kSelSampleRun)]);
     }
   }
 #pragma unroll

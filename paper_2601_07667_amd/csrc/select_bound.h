@@ -14,15 +14,16 @@ constexpr int kSelTile = ASL_SEL_TILE;     // elements per select workgroup tile
 constexpr int kSelSegment = kSelTile / 2;   // candidate slots per select tile
 constexpr int kSelCandCap = 16384;     // candidates of one row the finishing workgroup holds in LDS
 
-// n_s = sel_sample_size(T) keys of a row at positions j * sel_sample_stride(T), j < n_s.
+constexpr int kShortT = 12288;           // longest score vector that one workgroup holds in LDS (below 64 KB with the
+                                         // selection's counters): ranked and selected from in one launch
+// n_s = sel_sample_size(T) keys of a row at positions j * sel_sample_stride(T), j < n_s, for T > kShortT.
 constexpr int kSelMaxSample = 8192;    // sampled keys per row
 inline int sel_sample_size(int T) {
   int n = T / 32;
   n = n < 1024 ? 1024 : n;
-  n = n > kSelMaxSample ? kSelMaxSample : n;
-  return n < T ? n : T;
+  return n > kSelMaxSample ? kSelMaxSample : n;
 }
-inline int sel_sample_stride(int T) { return T / sel_sample_size(T); }   // >= 1 for T >= 1
+inline int sel_sample_stride(int T) { return T / sel_sample_size(T); }
 // Rank m of the sample key taken as the bound: f = n_s / T of the row is sampled, the top-k members
 // among the sample are ~Binomial(n_s, k / T) with mean k f; m = k f + 5 sqrt(c k f) + 4 leaves the
 // bound too low with probability < 1e-6.  c = 1 for single sampled keys; c = `run` when the sample
@@ -53,5 +54,6 @@ inline int sel_bound_slack(int T, int m, int n_s, int run) {
 // Without a prepared sample the bound kernel reads runs of kSelSampleRun neighbouring keys, one run
 // per kSelSampleRun sample strides: the same number of keys from a quarter of the cache lines.
 constexpr int kSelSampleRun = 4;
+static_assert(kShortT / 1024 >= kSelSampleRun && 32 >= kSelSampleRun, "a run fits the stride of any row that is sampled");
 
 }  // namespace asl

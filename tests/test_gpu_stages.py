@@ -418,7 +418,6 @@ def test_gather_empty_and_f32(ctx, gpu_device):
     assert np.array_equal(vo.cpu().numpy(), L.v[:, [3, 0, 511, 3], :])
 
 
-# ----------------------------------------------------------------------------- errors
 @pytest.mark.parametrize("row_bytes,n_idx", [(8192, 6400), (8192, 6399), (192, 273067), (16, 3276801)])
 def test_gather_of_more_than_the_caches_hold(gpu_device, row_bytes, n_idx):
     """100 MiB read and written is where the copies become non-temporal: at it, one row below, and past it with
@@ -434,6 +433,7 @@ def test_gather_of_more_than_the_caches_hold(gpu_device, row_bytes, n_idx):
     c.close()
 
 
+# ----------------------------------------------------------------------------- errors
 def test_argument_errors(ctx, gpu_device):
     torch = _torch()
     sh = synth.shape_of(1)
