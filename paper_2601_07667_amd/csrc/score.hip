@@ -751,27 +751,63 @@ static int device_cu_count() {
   return n;
 }
 
-// Workgroups per compute unit: with the matrix and vector work of a wavefront interleaved, two
-// workgroups (8 wavefronts) keep a unit's pipes and its share of the HBM stream as busy as three do,
-// start sooner and leave fewer partials to fold.  N = 32K / 128K, 8B shape, pass 1 + pass 2: three per unit
-// 17.4 + 21.7 / 54.6 + 51.5 us, two 16.1 + 20.3 / 54.5 + 49.2 us; one 16.2 + 22.0 / 50.5 + 62.4 us.
-constexpr int kScorePerCu = 2;
-
-// Key chunks per KV head for a pass whose kernel fits `resident` workgroups per compute unit: one
-// resident round of workgroups, so that no second, partly filled round trails behind.  `batch` = chunks
-// that pass 2's prologue folds in one memory round trip: more chunks than that are only worth their
-// second round trip (4-7 us) where fewer would leave compute units idle or cost long chunks
-// (28 heads / 4 KV heads, pass 1 + pass 2: N = 8K 10.4 + 20.1 with 128 chunks, 8.6 + 12.2 us with 64;
-// 32K 17.5 + 25.3, 15.8 + 18.5; 128K 41.2 + 45.9, 42.5 + 43.0).
-static int score_chunks(const asl_params& p, int kt, int resident, int batch) {
-  const int n_cu = device_cu_count();
-  const int target = n_cu * (resident < kScorePerCu ? resident : kScorePerCu);
-  const int n_tiles = (p.seq_len + kt - 1) / kt;
-  int want = target / p.n_kv_heads;
-  if (want > kMaxChunks) want = kMaxChunks;
-  if (want > n_tiles) want = n_tiles;
-  if (want > batch && ((int64_t)batch * p.n_kv_heads >= n_cu ? n_tiles <= 16 * batch : n_tiles <= 2 * batch)) want = batch;
-  return want < 1 ? 1 : want;
+// Key chunks per KV head of a launch, one workgroup each, of which a compute unit holds `resident` at once: at
+// most one resident round of workgroups, so that no second, partly filled round trails behind.
+//
+// fold = false (the caller's log-sum-exp): only the key stream counts, and it lives on workgroups in flight: three per
+// unit, four where a tile is 8 KB (8 heads, d = 64, 32 rows, 64K: 18.4 us with four, 22.3 with two), one fewer where
+// that leaves each more than one tile but less than four.  From 65 rows of 16 pieces, or 129 of 8, a unit's pipes are as busy as its
+// share of the stream: a third workgroup from 16 tiles each (8B shape, 64K: 37.2 us with two, 38.6 with three; 256K
+// 121.8 and 119.7), a second from five (28 heads, 8K: 13.5 us with two, 12.6 with one).
+//
+// fold = true: every workgroup of pass 2 first folds one partial per chunk, in rounds of `2 * fold_batch` partials
+// (one round, in smaller batches, up to 64), so that chunks cost pass 2 what they save both passes in tiles.  The
+// chunk count with the least estimated time is taken, from those that fill rounds and the largest one.  Estimated, in
+// us, fitted to graph-replayed calls (1 to 8 KV heads, 16 to 256 rows, d = 64 and 128 in bf16 and some other shapes,
+// 2K to 256K keys, nine chunk counts each: the choice is 0.5 % off the best of the nine on average, at worst 15 %):
+//  - a round beyond the first 64 partials: 4 for the batch of 48, 14 where one wavefront folds rows of 16 pieces or
+//    more, 4.3 for every further one; 1.7 each above 128 rows;
+//  - a tile, both passes: 1.4, or 4.4 in fp32 (four MFMAs per fragment step);
+//  - a unit takes `alone` workgroups before they slow each other down: its share of the stream feeds one with tiles
+//    of 16 KB (1.3 that do little with them), and 5.2 wavefronts with tiles of 8 KB; in fp32 the four matrix pipes
+//    are shared;
+//  - 0.6 for every further workgroup of a unit (start-up).
+// Examples, now and with two workgroups per unit throughout: 4 heads, 32 rows, d = 64, 128K 35.5 and 42.5 us; one
+// head, 32 rows, d = 64, 24K 16.3 and 21.5; two heads, 32 rows, d = 128, 24K 18.7 and 46.5; 8B shape unchanged.
+template <typename TE, int P, int NW, int RB>
+static int score_chunks(int Hk, int n_tiles, int n_cu, int resident, bool fold) {
+  auto fit = [&](int per_cu) {
+    const int c = n_cu * (resident < per_cu ? resident : per_cu) / Hk, most = n_tiles < kMaxChunks ? n_tiles : kMaxChunks;
+    return c < 1 ? 1 : (c < most ? c : most);
+  };
+  const bool f32 = sizeof(TE) == 4, narrow = P <= 8 && RB == 1 && !f32;
+  if (!fold) {
+    if (narrow || f32 || NW <= 2) {
+      const int want = P <= 8 ? 4 : 3, per_cu = resident < want ? resident : want, c = fit(per_cu);
+      return c < n_tiles && n_tiles < 4 * c ? fit(per_cu - 1) : c;
+    }
+    return n_tiles >= 16 * fit(3) ? fit(3) : n_tiles >= 5 * fit(2) ? fit(2) : fit(1);
+  }
+  const float alone = narrow ? 5.2f / NW : f32 ? (NW == 1 ? 3.5f : 1.0f) : NW == 1 || (NW == 2 && P > 16) ? 1.3f : 1.06f;
+  const int most = fit(3), counts[] = {32, 64, RB > 1 ? 64 : 96, 128, RB > 1 ? 128 : 192, 256, most};
+  int best = most;
+  float best_us = INFINITY;
+  for (const int c : counts) {
+    if (c > most) continue;
+    const float per_unit = (float)c * (float)Hk / (float)n_cu;
+    const float tiles = n_tiles <= 2 * c ? (float)((n_tiles + c - 1) / c) : (float)n_tiles / (float)c;
+    const int rounds = (c + 2 * fold_batch<RB>() - 1) / (2 * fold_batch<RB>());
+    float us = tiles * (f32 ? 4.4f : 1.4f) * fmaxf(1.0f, per_unit / alone) + 0.6f * fmaxf(0.0f, per_unit - 1.0f);
+    if (RB > 1)
+      us += 1.7f * (float)(rounds - 1);
+    else if (c > 64)
+      us += (NW == 1 && P >= 16 ? 14.0f : 4.0f) + 4.3f * (float)(rounds - 1);
+    if (us < best_us) {
+      best_us = us;
+      best = c;
+    }
+  }
+  return best;
 }
 
 // Workgroups of `kernel` that fit on one compute unit at once (registers, LDS, wave slots).
@@ -800,8 +836,8 @@ static hipError_t launch_score_mfma(const asl_params& p, const Workspace& ws, co
     const int b = resident_per_cu(score_colsum_kernel<TE, P, NW, RB, PAD, DENORM>, NW * 64);
     return a < b ? a : b;
   }();
-  const int n_chunks = score_chunks(p, KT, resident, 2 * fold_batch<RB>());
   const int n_cu = device_cu_count();
+  const int n_chunks = score_chunks<TE, P, NW, RB>(Hk, (N + KT - 1) / KT, n_cu, resident, lse == nullptr);
   if (!lse) {
     for (int m0 = 0; m0 < M; m0 += kRows)
       ASL_LAUNCH(ws.prof, kKernRowstats, st, (score_rowstats_kernel<TE, P, NW, RB, PAD>), dim3(Hk * n_chunks), dim3(NW * 64), 0,

@@ -134,11 +134,37 @@ def test_infinite_keys(gpu_device, Hq, Hk, d, W, dtype):
                                        (3, 1, 64, 64 * 64), (8, 8, 16, 64 * 65 + 3), (4, 4, 40, 64 * 257),
                                        (8, 8, 16, 64 * 256 + 1), (24, 8, 64, 64 * 119 + 1)])
 def test_chunk_counts(gpu_device, Hq, Hk, W, N):
-    """Key chunks of one tile and more, partials folded in one round of loads (96 chunks, 64 above 128 query
-    rows) and in several, one and two workgroups per compute unit, with weighted and (257 and 256, 119 and 120
-    tiles over 64 chunks) equal shares."""
+    """Key chunks of one tile and more, several tile counts around multiples of the chunk counts, one and more
+    workgroups per compute unit, with weighted and equal shares."""
     L = _small(Hq, Hk, 64, N, W, S=1, seed=N)
     P, s = _run_score(gpu_device, L)
+    _close_to_64_bits(P, s, L)
+
+
+# (tiles, chunks per head) on 256 compute units: partials folded in one round of loads of each batch size and in two,
+# three and four, tile counts that leave ragged shares, and the last tile ragged too
+@pytest.mark.parametrize("Hq,Hk,d,W,N", [
+    (1, 1, 64, 16, 64 * 14), (1, 1, 64, 16, 64 * 48), (6, 2, 64, 32, 64 * 95 + 1),       # 14, 48; 96 tiles in 64
+    (8, 8, 64, 32, 64 * 2000 + 1),                                                        # 2001 in 96
+    (1, 1, 64, 32, 64 * 600 + 5), (4, 4, 64, 64, 64 * 1100 + 3), (1, 1, 64, 32, 64 * 4096),   # 601 and 1101 in 192; 4096 in 256
+    (6, 1, 64, 32, 64 * 300), (6, 1, 64, 32, 64 * 2048 + 1), (48, 8, 64, 32, 64 * 65 + 9)])   # 192 rows: 300 in 128; 2049 in 256; 66 in 32
+def test_chunk_counts_of_two_passes(gpu_device, Hq, Hk, d, W, N):
+    L = _small(Hq, Hk, d, N, W, S=1, seed=N)
+    P, s = _run_score(gpu_device, L)
+    _close_to_64_bits(P, s, L)
+
+
+# the same with the log-sum-exp supplied: one to four workgroups per compute unit, a single tile each and more
+@pytest.mark.parametrize("Hq,Hk,d,W,N", [
+    (8, 8, 64, 32, 64 * 128), (8, 8, 64, 32, 64 * 512 + 3), (8, 8, 64, 16, 64 * 300), (32, 8, 64, 32, 64 * 128 + 1),
+    (8, 8, 128, 16, 64 * 65), (8, 8, 128, 16, 64 * 400 + 1), (32, 8, 128, 32, 64 * 97), (32, 8, 128, 32, 64 * 400),
+    (32, 8, 128, 32, 64 * 1540 + 7), (48, 8, 64, 32, 64 * 70), (48, 8, 64, 32, 64 * 333)])
+def test_chunk_counts_of_one_pass(gpu_device, Hq, Hk, d, W, N):
+    """A supplied log-sum-exp is rounded to fp32: half an ulp of a number below 16 moves a probability by 1e-6."""
+    L = _small(Hq, Hk, d, N, W, S=1, seed=N)
+    lse = orc.row_lse(L.q_obs, L.k, W)
+    assert np.abs(lse).max() < 16
+    P, s = _run_score(gpu_device, L, lse=lse)
     _close_to_64_bits(P, s, L)
 
 
