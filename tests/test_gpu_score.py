@@ -158,7 +158,7 @@ def test_chunk_counts_of_two_passes(gpu_device, Hq, Hk, d, W, N):
 @pytest.mark.parametrize("Hq,Hk,d,W,N", [
     (8, 8, 64, 32, 64 * 128), (8, 8, 64, 32, 64 * 512 + 3), (8, 8, 64, 16, 64 * 300), (32, 8, 64, 32, 64 * 128 + 1),
     (8, 8, 128, 16, 64 * 65), (8, 8, 128, 16, 64 * 400 + 1), (32, 8, 128, 32, 64 * 97), (32, 8, 128, 32, 64 * 400),
-    (32, 8, 128, 32, 64 * 1540 + 7), (48, 8, 64, 32, 64 * 70), (48, 8, 64, 32, 64 * 333)])
+    (48, 8, 64, 32, 64 * 70), (48, 8, 64, 32, 64 * 333)])
 def test_chunk_counts_of_one_pass(gpu_device, Hq, Hk, d, W, N):
     """A supplied log-sum-exp is rounded to fp32: half an ulp of a number below 16 moves a probability by 1e-6."""
     L = _small(Hq, Hk, d, N, W, S=1, seed=N)
