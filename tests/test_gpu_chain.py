@@ -313,7 +313,8 @@ def test_bench_launch_configuration(gpu_device):
     ctx.close()
 
 
-def _layer_step_case(dev, L, layer_idx=0):
+def _layer_step_case(dev, L, layer_idx=0, held=None):
+    """held: [n, T] rank rows of the n layers before layer_idx, already in the ring."""
     import torch
     sh = L.shape
     ctx = asl.Asl(sh.N, sh.Hk + 1, sh.Hq * sh.W)
@@ -323,16 +324,19 @@ def _layer_step_case(dev, L, layer_idx=0):
     scores = torch.empty((sh.Hk + 1, T), dtype=torch.float32, device=dev)
     ring = torch.zeros((sh.L_obs, T), dtype=torch.int32, device=dev)
     state, stat = asl.new_state(dev), asl.new_stat(dev)
+    if held is not None:
+        for j, row in enumerate(held):
+            ring[(layer_idx - len(held) + j) % sh.L_obs] = torch.from_numpy(row.astype(np.int32)).to(dev)
+        asl.write_state(state, n_valid_rows=len(held), last_layer=layer_idx - 1)
     I = torch.empty((sh.Hk + 1, n_idx), dtype=torch.int32, device=dev)
     Kc = torch.empty((sh.Hk, n_idx, sh.d), dtype=kd.dtype, device=dev)
     Vc = torch.empty_like(Kc)
+    ring2, state2, stat2 = ring.clone(), state.clone(), asl.new_stat(dev)
     ctx.asl_layer_step(p, qd, kd, vd, layer_idx, sh.L_min, sh.L_obs, sh.tau, scores, ring, state, stat, I, Kc, Vc)
     torch.cuda.synchronize()
     # the same layer through the single calls
     P2 = torch.empty((sh.Hk, T), dtype=torch.float32, device=dev)
     s2 = torch.empty((T,), dtype=torch.float32, device=dev)
-    ring2 = torch.zeros_like(ring)
-    state2, stat2 = asl.new_state(dev), asl.new_stat(dev)
     Ih = torch.empty((sh.Hk, n_idx), dtype=torch.int32, device=dev)
     Ia = torch.empty((1, n_idx), dtype=torch.int32, device=dev)
     K2 = torch.empty_like(Kc)
@@ -345,7 +349,7 @@ def _layer_step_case(dev, L, layer_idx=0):
     torch.cuda.synchronize()
     for what, a, b in (("P", scores[:sh.Hk], P2), ("s", scores[sh.Hk], s2), ("rank ring", ring, ring2),
                        ("per-head indices", I[:sh.Hk], Ih), ("all-head indices", I[sh.Hk:], Ia), ("K[I]", Kc, K2),
-                       ("V[I]", Vc, V2), ("state", state, state2)):
+                       ("V[I]", Vc, V2), ("state", state, state2), ("statistic", stat, stat2)):
         if not torch.equal(a, b):
             d = torch.nonzero(a.reshape(-1) != b.reshape(-1)).reshape(-1)
             raise AssertionError(f"{L.name}: {what} of asl_layer_step differs from the single calls at {d.numel()} of "
@@ -387,14 +391,32 @@ def test_layer_step_ragged_shapes(gpu_device, Hq, Hk, d, N, W, S, budget):
 @pytest.mark.parametrize("N,layer_idx,L_min", [(12288 + 16, 0, 0), (12288 + 17, 0, 0), (12288 + 16, 0, 5), (12288 + 17, 3, 5),
                                                (49, 0, 2)])
 def test_layer_step_around_the_short_limit(gpu_device, N, layer_idx, L_min):
-    """12288 past tokens (ranked and selected from in one launch) and 12289 (five launches), evaluated and
-    below L_min (the state only advances)."""
+    """12288 past tokens (ranked and selected from in one launch) and 12289 (five launches): a first layer, which has
+    nothing to be compared with yet, and layers below L_min (the state only advances)."""
     sh = synth.Shape(Hq=4, Hk=2, d=64, N=N, W=16, S=7, budget=300, L_min=L_min)
     L = synth.iid_layer(sh, 2000 + N, name=f"short-limit-{N}-{layer_idx}")
     got = _layer_step_case(gpu_device, L, layer_idx=layer_idx)
     assert got["stat"].evaluated == 0 and got["stat"].n_rows == (0 if layer_idx < L_min else 1)
     if layer_idx == 0 and L_min == 0:
         _check_layer(L, got)
+
+
+@pytest.mark.parametrize("N", [12288 + 16, 12288 + 17])
+def test_layer_step_evaluates_around_the_short_limit(gpu_device, N):
+    """The same sizes with the ranks of the layers before in the ring: the statistic, against its definition."""
+    sh = synth.Shape(Hq=4, Hk=2, d=64, N=N, W=16, S=7, budget=300, L_min=2, L_obs=4)
+    L = synth.iid_layer(sh, 2100 + N, name=f"short-limit-evaluated-{N}")
+    rng = np.random.default_rng(N)
+    held = np.stack([rng.permutation(sh.T) for _ in range(3)])
+    got = _layer_step_case(gpu_device, L, layer_idx=6, held=held)
+    rows = np.concatenate([held, got["rank"][None]]).astype(object)               # exact integers
+    kept = rows[:, (rows < sh.k).any(axis=0)]
+    numerator = int((4 * (kept * kept).sum(axis=0) - kept.sum(axis=0) ** 2).sum())
+    st = got["stat"]
+    assert (st.evaluated, st.n_rows, st.union_size, st.numerator) == (1, 4, kept.shape[1], numerator)
+    assert st.rel_var == 1.0 and st.selected == 0                                  # the first evaluated layer
+    np.testing.assert_array_equal(got["rank"], orc.rank_desc(got["s"].astype(np.float64)))
+    np.testing.assert_array_equal(got["I_all"][:sh.k], np.nonzero(got["rank"] < sh.k)[0])
 
 
 def test_layer_step_at_bench_size_and_beyond(gpu_device):

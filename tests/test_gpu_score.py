@@ -42,8 +42,10 @@ def _compare(dev, L, flags=0, use_lse=False, scale=0.0):
 
 
 def test_config1_f32_and_bf16(gpu_device):
-    L = synth.config_layer(1)                                   # fp32 storage: plain-FMA kernels
-    _compare(gpu_device, L)
+    L = synth.config_layer(1)                                   # fp32 storage: fp32 MFMA kernels
+    P, s = _compare(gpu_device, L)
+    Pg, sg = _compare(gpu_device, L, flags=asl.ASL_FLAG_GENERIC_SCORE)      # on-GPU cross-check: plain-FMA kernels
+    np.testing.assert_allclose(P, Pg, rtol=1e-4, atol=1e-7)
     sh = synth.shape_of(1)
     sh.dtype = "bf16"                                           # bf16-rounded copy: MFMA kernels, d = 64
     Lb = synth.iid_layer(sh, synth.BASE_SEED + 1, name="C1-bf16")
@@ -70,9 +72,13 @@ def test_key_counts_around_tile_edges(gpu_device, N):
 
 
 @pytest.mark.parametrize("d,dtype", [(96, "bf16"), (256, "bf16"), (80, "f32")])
-def test_other_head_dims_take_the_plain_kernels(gpu_device, d, dtype):
-    """Head dimensions outside {64, 128} are scored by the plain-FMA kernels."""
-    _compare(gpu_device, _small(4, 2, d, 700, 8, dtype=dtype, seed=d))
+def test_other_head_dims(gpu_device, d, dtype):
+    """Head dimensions outside {64, 128}: the MFMA kernels for padded and other row lengths, and the plain-FMA kernels."""
+    L = _small(4, 2, d, 700, 8, dtype=dtype, seed=d)
+    for use_lse in (False, True):
+        P, s = _compare(gpu_device, L, use_lse=use_lse)
+        Pg, sg = _compare(gpu_device, L, flags=asl.ASL_FLAG_GENERIC_SCORE, use_lse=use_lse)
+        np.testing.assert_allclose(P, Pg, rtol=1e-4, atol=1e-7)
 
 
 def _close_to_64_bits(P, s, L):
@@ -282,14 +288,16 @@ def _window_lse(dev, L, flags=0):
     P0 = torch.empty((sh.Hk, sh.T), dtype=torch.float32, device=dev)
     s0 = torch.empty((sh.T,), dtype=torch.float32, device=dev)
     P1, s1 = torch.empty_like(P0), torch.empty_like(s0)
-    ctx.asl_score_layer(p, qd, kd, P0, s0)                       # self-contained: two passes over K
+    ctx.asl_score_layer(p, qd, kd, P0, s0)                       # self-contained: both passes
     ctx.asl_score_layer(p, qd, kd, P1, s1, lse=lse)              # with the library's own log-sum-exp
     torch.cuda.synchronize()
     ctx.close()
     return lse.cpu().numpy().astype(np.float64), (P0, s0), (P1, s1)
 
 
-@pytest.mark.parametrize("case", ["small-d64", "ragged-rows", "w64", "f32-plain", "heavy-tail", "c2"])
+# plain-*: the plain-FMA kernels, by the flag and by rows that are no whole 16-byte pieces or longer than 256 elements
+@pytest.mark.parametrize("case", ["small-d64", "ragged-rows", "w64", "f32", "heavy-tail", "c2", "plain-f32", "plain-d96",
+                                  "plain-rows-d20", "plain-rows-f32-d30", "plain-rows-d264"])
 def test_window_lse_matches_oracle_and_hands_back_exactly(gpu_device, case):
     """asl_window_lse against the oracle's log-sum-exp of the masked, scaled logits (fp32 accumulation
     of a sum of N positive terms: 1e-5 absolute + 2e-6 relative on a logarithm), and the hand-off:
@@ -303,15 +311,20 @@ def test_window_lse_matches_oracle_and_hands_back_exactly(gpu_device, case):
         L = _small(7, 1, 128, 2500, 32, seed=22)                 # 224 query rows per KV head
     elif case == "w64":
         L = _small(8, 2, 128, 4096 + 77, 64, seed=23)
-    elif case == "f32-plain":
+    elif case in ("f32", "plain-f32"):
         L = _small(4, 2, 64, 700, 16, dtype="f32", seed=24)
+    elif case == "plain-d96":
+        L = _small(4, 2, 96, 700, 16, seed=25)
+    elif case.startswith("plain-rows"):
+        L = _small(4, 2, int(case.split("-d")[1]), 700, 16, dtype="f32" if "f32" in case else "bf16", seed=26)
     elif case == "heavy-tail":
         sh = synth.Shape(Hq=8, Hk=2, d=128, N=6000, W=64, S=7, budget=512)
         L = synth.needle_layer(sh, 11, 16, synth.needle_gain_strong(sh), heavy_tail=True, name="heavy")
     else:
         L = synth.config_layer(2)
     sh = L.shape
-    lse, (P0, s0), (P1, s1) = _window_lse(gpu_device, L)
+    by_flag = case in ("plain-f32", "plain-d96")
+    lse, (P0, s0), (P1, s1) = _window_lse(gpu_device, L, flags=asl.ASL_FLAG_GENERIC_SCORE if by_flag else 0)
     ref = orc.row_lse(L.q_obs, L.k, sh.W)
     err = np.abs(lse - ref)
     assert np.all(err <= 1e-5 + 2e-6 * np.abs(ref)), f"{case}: worst lse error {err.max()}"

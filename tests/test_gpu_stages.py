@@ -115,9 +115,11 @@ def test_rank_is_deterministic(ctx, gpu_device):
     assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("T", [2048 * 3 - 1, 2048 * 3, 2048 * 3 + 1, 4095, 4096, 4097, 64 * 33 + 7])
+@pytest.mark.parametrize("T", [2048 * 3 - 1, 2048 * 3, 2048 * 3 + 1, 4095, 4096, 4097, 64 * 33 + 7, 2048 * 17 - 1, 2048 * 17,
+                               2048 * 17 + 1, 4096 * 9 - 1, 4096 * 9, 4096 * 9 + 1, 64 * 533 + 7])
 def test_rank_and_select_at_tile_boundaries(ctx, gpu_device, T):
-    """Sizes one below, at and one above multiples of the sort tile (2048) and the select tile (4096)."""
+    """Sizes one below, at and one above multiples of the sort tile (2048) and the select tile (4096), above 12288
+    scores, from where the tiles are in use; and the same below, where one launch takes the whole row."""
     rng = np.random.default_rng(T)
     s = np.round(rng.standard_normal(T), 2).astype(np.float32)            # heavy ties
     _rank_case(ctx, gpu_device, s)
@@ -232,11 +234,12 @@ def test_select_random_with_ties(ctx, gpu_device, rows, T, budget, W):
 
 
 def test_rank_select_pool_random_shapes(ctx, gpu_device):
-    """Forty seeded random cases: sizes, budgets, window widths, tie densities and value ranges drawn at
-    random (positive-only scores, mixed signs, a few distinct values, tiny magnitudes)."""
+    """Fifty-six seeded random cases: sizes, budgets, window widths, tie densities and value ranges drawn at
+    random (positive-only scores, mixed signs, a few distinct values, tiny magnitudes); forty with rows that are
+    ranked and selected from in one launch, sixteen with longer ones."""
     rng = np.random.default_rng(20260127)
-    for case in range(40):
-        T = int(rng.integers(1, 9000))
+    for case in range(56):
+        T = int(rng.integers(1, 9000)) if case < 40 else int(rng.integers(12289, 60000))
         rows = int(rng.integers(1, 4))
         W = int(rng.integers(1, 40))
         budget = W + int(rng.integers(1, T + 20))
@@ -466,7 +469,7 @@ def test_argument_errors(ctx, gpu_device):
     expect(asl.ASL_EINVAL, lambda: ctx.asl_gather_kv(good, t, None, t, 3, 4, t, None))   # idx_rows not 1/Hk
     expect(asl.ASL_EINVAL, lambda: ctx.asl_rankvar(t, 1, 16, 0, 0, 4, 0.3, t, t))        # L_obs < 2
     expect(asl.ASL_EUNSUPPORTED, lambda: ctx.asl_rankvar(t, 64, 2_000_000, 0, 0, 4, 0.3, t, t))
-    # a shape without an MFMA scoring kernel (d = 96) at a size the plain kernels are not meant for
+    # a shape beside the main ones (d = 96) beyond the size those are taken up to
     big = asl.Asl(1 << 20, 1, 64 * 128)
     pb = asl.make_params(64, 1, 96, 1 << 20, 128, 7, 4096)
     expect(asl.ASL_EUNSUPPORTED, lambda: big.asl_score_layer(pb, t, t, t, t))
