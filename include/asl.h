@@ -264,7 +264,7 @@ asl_status asl_device_fault(asl_ctx* ctx, int32_t* fault_out);
  * 11 plain-FMA score kernels, 12 the launches of asl_layer_step that carry sort passes and
  * top-k / compaction stages together.  (Each sort pass is one kernel, recorded under 5, id 4 is unused;
  * 8 covers the top-k's bound and filter kernels, 9 its finishing kernel (and the one of short rows); the statistic is one
- * kernel, 7; 6 is the below-L_min skip.)
+ * kernel, 7; 6 is the below-L_min skip of asl_rank_stat, asl_rankvar and steps without compaction: with it, it is part of 12.)
  * asl_profile_enable: launches whose id bit is set in kernel_mask carry a HIP event pair that the
  *   runtime stamps with the kernel's start and end on the device (the call's stream; not under
  *   stream capture), up to max_records launches (further ones run unrecorded); mask 0 turns

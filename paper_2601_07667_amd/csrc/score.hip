@@ -8,12 +8,13 @@
 // hands over the rows' log-sum-exp, pass 1 is skipped.
 //
 // Work split: a workgroup owns one KV head and a contiguous chunk of keys; wave w owns RB blocks of
-// 32 query rows (RB = 1 up to M = 128 rows, 2 above) and keeps their bf16 fragments in registers for
-// the whole kernel; K tiles of 64 keys stream global -> LDS directly (ring of 3 buffers,
-// XOR-swizzled) and every wave reads all of them as the other MFMA operand
-// (v_mfma_f32_32x32x16_bf16), each fragment once for all its row blocks.  Pass 1 puts keys on the
-// accumulator's register axis (row statistics reduce in-lane), pass 2 puts query rows there
-// (column sums reduce in-lane).  All reductions have a fixed order: results are deterministic.
+// 32 query rows (RB = 1 up to M = 128 rows, 2 above for the main bf16 shapes) and keeps their
+// fragments in registers for the whole kernel; K tiles of 64 or 32 keys stream global -> LDS directly
+// (ring of 3 buffers, XOR-swizzled) and every wave reads all of them as the other MFMA operand
+// (v_mfma_f32_32x32x16_bf16, or v_mfma_f32_32x32x2_f32 for fp32), each fragment once for all its row
+// blocks.  Pass 1 puts keys on the accumulator's register axis (row statistics reduce in-lane), pass 2
+// puts query rows there (column sums reduce in-lane).  More rows per KV head than a workgroup holds
+// take further launches.  All reductions have a fixed order: results are deterministic.
 #include <type_traits>
 
 #include "asl_internal.h"
@@ -29,8 +30,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 #endif
 // A key row is handled as 16-byte pieces, P of them per (padded) row: 8 bf16 or 4 fp32 elements each.
 typedef uint32_t Piece __attribute__((ext_vector_type(4)));
-// Keys per LDS tile (a multiple of 32): tiles of at most 16 KB up to 512-byte rows, so that three
-// workgroups' rings fit a compute unit.
+// Keys per LDS tile (a multiple of 32): tiles of at most 16 KB up to 512-byte rows, so that the rings of
+// the two or three workgroups a compute unit works best with fit it (six with 8 KB tiles; see score_chunks).
 template <int P> constexpr int key_tile() { return P <= 16 ? 64 : 32; }
 // LDS tile buffers of the K ring: STAGES-1 tiles in flight while one is consumed (four or more: the same
 // or slower, the longer prologue costs what the depth gains).  RB = 32-row query blocks per wavefront: 1
@@ -896,8 +897,8 @@ static hipError_t dispatch_nw(int M, const asl_params& p, const Workspace& ws, c
 
 // The other row lengths and fp32.  Latency-bound at ordinary sizes; the plain kernels, which this replaced
 // for whole-piece rows, walk M rows x d elements one after the other per key: fp32 Hq4/Hk2/d64, N = 512,
-// W = 16: 247 + 6.5 us, here 4.5 + 4.5; bf16 Hq8/Hk4/d256, N = 8192, W = 32: 2104 + 177 us, here ~10 + ~10
-// (the whole call 2274 -> 25.5 us).  fp32 MFMA multiplies and adds in full fp32.
+// W = 16: 247 + 6.5 us, here 4.5 + 4.5; bf16 Hq8/Hk4/d256, N = 8192, W = 32: the whole call 2274 us, here
+// 17.1.  fp32 MFMA multiplies and adds in full fp32.
 // np pieces of a row in the next longer of the built row lengths P; one
 // 32-row block per wavefront, up to 128 query rows per launch.  Rows that fill P (the powers of two, mostly) have
 // kernels of their own, without the test for pieces behind a row: d = 256, N = 8192, `lse` supplied, 12.6 -> 12.0 us.
