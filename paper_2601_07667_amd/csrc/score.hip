@@ -766,9 +766,10 @@ static int device_cu_count() {
 //
 // fold = false (the caller's log-sum-exp): only the key stream counts, and it lives on workgroups in flight: three per
 // unit, four where a tile is 8 KB (8 heads, d = 64, 32 rows, 64K: 18.4 us with four, 22.3 with two), one fewer where
-// that leaves each more than one tile but less than four.  From 65 rows of 16 pieces, or 129 of 8, a unit's pipes are
+// that leaves each more than one tile but less than four.  From 65 rows of 16 pieces, or 97 of 8, a unit's pipes are
 // as busy as its share of the stream: two, from five tiles each, else one (28 heads, 8K: 13.5 us with two, 12.6 with
-// one; 8B shape, 128K layer step: 111.8 us with two, 115.0 with three).
+// one; 8B shape, 128K layer step: 111.8 us with two, 115.0 with three); of 8 pieces from two tiles each (8 heads, 128
+// rows, 16K: 12.4 us with two, 13.5 with one; 50K: 19.1 with two, 20.5 with three).
 //
 // fold = true: every workgroup of pass 2 first folds one partial per chunk, in rounds of `2 * fold_batch` partials
 // (one round, in smaller batches, up to 64), so that chunks cost pass 2 what they save both passes in tiles.  The
@@ -792,11 +793,12 @@ static int score_chunks(int Hk, int n_tiles, int n_cu, int resident, bool fold) 
   };
   const bool f32 = sizeof(TE) == 4, narrow = P <= 8 && RB == 1 && !f32;
   if (!fold) {
-    if (narrow || f32 || NW <= 2) {
+    const bool busy = !f32 && (NW > 3 || RB > 1 || (NW == 3 && P > 8));
+    if (!busy) {
       const int want = P <= 8 ? 4 : 3, per_cu = resident < want ? resident : want, c = fit(per_cu);
       return c < n_tiles && n_tiles < 4 * c ? fit(per_cu - 1) : c;
     }
-    return n_tiles >= 5 * fit(2) ? fit(2) : fit(1);
+    return n_tiles >= (P > 8 ? 5 : 2) * fit(2) ? fit(2) : fit(1);
   }
   const float alone = narrow ? 5.2f / NW : f32 ? (NW == 1 ? 3.5f : 1.0f) : NW == 1 || (NW == 2 && P > 16) ? 1.3f : 1.06f;
   const int most = fit(3), counts[] = {32, 64, RB > 1 ? 64 : 96, 128, RB > 1 ? 128 : 192, 256, most};
