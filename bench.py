@@ -291,8 +291,8 @@ def main() -> int:
         "score_colsum": sh.Hk * T * sh.d * eb + q_bytes + sh.Hk * T * 4,
         # Hk rows read, Hk pooled rows + the all-head row written
         "pool": sh.Hk * T * 4 + (sh.Hk + 1) * T * 4,
-        # one radix pass: (key, index) pairs read and written (first pass reads scores, last writes ranks)
-        "sort_scatter": T * (4 + 8 + 8 + 8 + 8 + 8 + 8 + 4) // 4,
+        # a ranking: scores read, (key, token) pairs written and read, ranks written
+        "sort_scatter": T * (4 + 8 + 8 + 4),
         # the L_obs rank rows
         "rankvar": sh.L_obs * T * 4,
         # top-k as a family (bound + filter + finish): every score once, the indices written
@@ -300,8 +300,8 @@ def main() -> int:
         # K and V rows read and written, indices read
         "gather": 2 * 2 * sh.Hk * n_idx * sh.d * eb + sh.Hk * n_idx * 4,
     }
-    # asl_layer_step's four launches that each carry one sort pass and one top-k / compaction stage
-    alg["tail_fused"] = 4 * alg["sort_scatter"] + alg["select"] + alg["gather"]
+    # asl_layer_step's launches that share the stages of the ranking, the top-k and the compaction
+    alg["tail_fused"] = alg["sort_scatter"] + alg["select"] + alg["gather"]
     useful_flops = 2.0 * sh.Hq * sh.W * sh.N * sh.d          # one QK^T over the window rows
     fam_ms = {}                                              # family -> (ms per step, launches per step)
     for name, (ms, n) in prof.items():
@@ -314,13 +314,13 @@ def main() -> int:
             by_kernel[fam] = {"us_per_step": round(ms_step * 1e3, 2), "launches_per_step": round(n_step, 2)}
             continue
         # per launch for single-kernel families; for the families made of several kernels per step
-        # (sort: 4 equal passes; select: 3 different kernels) bytes and time are both per step
+        # (ranking and select: different kernels) bytes and time are both per step
         per_launch = fam in ("score_rowstats", "score_colsum", "pool", "rankvar", "gather")
-        n_div = n_step if (per_launch or fam == "sort_scatter") else 1.0
+        n_div = n_step if per_launch else 1.0
         avg_ms = ms_step / max(n_div, 1e-9)
         gbs = alg[fam] / (avg_ms * 1e-3) / 1e9
         ent = {"bound": "hbm", "algorithmic_bytes": alg[fam], "avg_ms": round(avg_ms, 5),
-               "per": "launch" if (per_launch or fam == "sort_scatter") else f"step ({n_step:.0f} launches)",
+               "per": "launch" if per_launch else f"step ({n_step:.0f} launches)",
                "launches_per_step": round(n_step, 2), "us_per_step": round(ms_step * 1e3, 2),
                "achieved_GBps": round(gbs, 1), "frac_of_hbm_peak": round(gbs / HBM_PEAK_GBS, 4)}
         if fam in ("score_rowstats", "score_colsum"):

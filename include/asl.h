@@ -143,8 +143,8 @@ asl_status asl_pool(asl_ctx* ctx, const float* u, int32_t rows, int32_t T, int32
 asl_status asl_rank(asl_ctx* ctx, const float* s, int32_t T, int32_t* rank_out, void* stream);
 
 /* asl_rank for callers that cannot allocate device memory: code under HIP graph capture, tight
- * serving loops, harnesses that forbid hipMalloc.  It needs no context: the sort's scratch buffers
- * live in a static device array inside the library (about 4.1 MiB on every GPU the library runs
+ * serving loops, harnesses that forbid hipMalloc.  It needs no context: the ranking's scratch buffers
+ * live in a static device array inside the library (about 3 MiB on every GPU the library runs
  * on, held until the process ends), so the call allocates nothing, on the device or through any
  * library.  Same result as asl_rank, bit for bit.
  *   s [T] f32 in, rank_out [T] int32 out: device pointers on the CURRENT device; T <=
@@ -219,17 +219,16 @@ asl_status asl_gather_rows(asl_ctx* ctx, const void* src, int64_t src_row_stride
 /* One layer of Alg. 1 + Alg. 2 in a single call: asl_score_layer, asl_rank_stat, asl_select_topk
  * (Hk per-head rows + the all-head row) and asl_gather_kv (per-head rows), with the same results as
  * the single calls.  After the scoring, ranking and top-k + compaction are independent; the call
- * runs them side by side in four launches on `stream`, launch i carrying pass i of the ranking sort
- * in some workgroups and stage i of the top-k in the others, followed by one launch with the statistic
- * (below l_min the note that it was not evaluated) beside the compaction.  Contexts of up to 12288 past
- * tokens take one launch for the ranking and the top-k instead of four.
+ * runs them side by side on `stream`: the two stages of the ranking share launches with the first stages of the
+ * top-k, a last launch has the statistic (below l_min the note that it was not evaluated) beside the
+ * compaction.  Contexts of up to 12288 past tokens take one launch for the ranking and the top-k.
  *   scores  [Hk+1, T] f32 out: rows 0..Hk-1 = P (per KV head), row Hk = s (all heads).
  *   idx_out [Hk+1, k+W] int32 out: rows 0..Hk-1 = Alg. 1's per-head I, row Hk = Alg. 2's select_idx
  *           (to be used only when out->selected is set).
  *   k_out, v_out [Hk, k+W, d] out: K[I], V[I] per head; pass k_out = NULL to skip the compaction.
  * The ctx must have been created with max_kv_heads >= Hk + 1.  Other arguments as in the single
  * calls.  Not to be overlapped with any other call on the same ctx.
- * With ASL_FLAG_DEFER_JOIN in params->flags (and for sizes the four launches do not take) ranking +
+ * With ASL_FLAG_DEFER_JOIN in params->flags (and for sizes the shared launches do not take) ranking +
  * statistic run on `stream` and top-k + compaction on a second stream owned by the ctx.  With the
  * flag the call returns as soon as ranking + statistic are queued; idx_out, k_out and v_out are then
  * complete only after asl_join.  The next asl_layer_step on the ctx joins by itself before it
@@ -249,22 +248,21 @@ asl_status asl_layer_step(asl_ctx* ctx, const asl_params* params, const void* q_
  * before the next layer starts; the compacted KV of a layer is needed at decoding time. */
 asl_status asl_join(asl_ctx* ctx, void* stream);
 
-/* Health check (not a step of the paper's method).  The workgroups of a ranking or statistic
- * launch hand counts to each other inside the launch and wait for them with a bounded number
- * of polls; a workgroup whose wait runs out raises a fault word in the workspace and writes no
- * results (every wave still exits).  This call waits for the device to go idle, returns the word
- * in *fault_out (0 = no wait ever ran out) and clears it.  Results of calls issued since the last
- * check are valid iff it reads 0.  Synchronises: not for the hot loop. */
+/* Health check (not a step of the paper's method).  The workgroups of a statistic launch hand partial sums to
+ * its first one inside the launch, which waits for them with a bounded number of polls; if its wait runs
+ * out it raises a fault word in the workspace and writes no result (every wave still exits).  This call
+ * waits for the device to go idle, returns the word in *fault_out (0 = no wait ever ran out) and clears it.
+ * Results of calls issued since the last check are valid iff it reads 0.  Synchronises: not for the hot loop. */
 asl_status asl_device_fault(asl_ctx* ctx, int32_t* fault_out);
 
 /* Measurement aid (not a step of the paper's method; for callers that time the kernels of the
  * calls above).  Kernel ids: 0 score row statistics (pass 1), 1 its combine, 2 score column sums
- * (pass 2), 3 pool, 4 sort histogram, 5 sort scatter, 6 rank-variance finalisation (or the
- * below-L_min skip), 7 rank-variance partial sums, 8 select histogram, 9 select write, 10 gather,
- * 11 plain-FMA score kernels, 12 the launches of asl_layer_step that carry sort passes and
- * top-k / compaction stages together.  (Each sort pass is one kernel, recorded under 5, id 4 is unused;
- * 8 covers the top-k's bound and filter kernels, 9 its finishing kernel (and the one of short rows); the statistic is one
- * kernel, 7; 6 is the below-L_min skip of asl_rank_stat, asl_rankvar and steps without compaction: with it, it is part of 12.)
+ * (pass 2), 3 pool, 4 ranking sample, 5 ranking (partition, buckets, or counting), 6 rank-variance
+ * finalisation (or the below-L_min skip), 7 rank-variance partial sums, 8 select histogram, 9 select write,
+ * 10 gather, 11 plain-FMA score kernels, 12 the launches of asl_layer_step that carry stages of the ranking, the
+ * top-k and the compaction together.  (8 covers the top-k's bound and filter kernels, 9 its finishing kernel
+ * (and the one of short rows); the statistic is one kernel, 7; 6 is the below-L_min skip of asl_rank_stat,
+ * asl_rankvar and steps without compaction: with it, it is part of 12.)
  * asl_profile_enable: launches whose id bit is set in kernel_mask carry a HIP event pair that the
  *   runtime stamps with the kernel's start and end on the device (the call's stream; not under
  *   stream capture), up to max_records launches (further ones run unrecorded); mask 0 turns

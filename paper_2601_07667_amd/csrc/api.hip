@@ -39,22 +39,18 @@ size_t carve(char* base, int32_t max_seq_len, int32_t max_kv_heads, int32_t max_
   };
   const size_t N = (size_t)max_seq_len;
   const size_t rows = (size_t)(max_kv_heads > 1 ? max_kv_heads : 1);
-  const size_t sort_tiles = (N + asl::kSortTile - 1) / asl::kSortTile;
   asl::Workspace w;
   w.row_part = (float*)take((size_t)asl::kMaxChunks * max_q_rows * 2 * sizeof(float));
   w.row_const = (float*)take((size_t)max_q_rows * sizeof(float));
   w.u_group = (float*)take(rows * N * sizeof(float));
-  for (int i = 0; i < 2; ++i) {
-    w.sort_key[i] = (uint32_t*)take(N * sizeof(uint32_t));
-    w.sort_idx[i] = (uint32_t*)take(N * sizeof(uint32_t));
-  }
-  w.sort_table = (unsigned long long*)take(128 * sort_tiles * sizeof(unsigned long long));
-  w.sort_epoch = (unsigned long long*)take(sizeof(unsigned long long));
+  w.rank_pairs = (uint2*)take(N * sizeof(uint2));
+  w.rank_count = (uint32_t*)take(N * sizeof(uint32_t));         // tiles x buckets <= T for every T (see rank_plan)
+  w.rank_edge = (uint32_t*)take((size_t)(asl::kRankMaxBuckets + 1) * sizeof(uint32_t));
+  w.rank_sample = (uint32_t*)take((size_t)asl::kSelMaxSample * sizeof(uint32_t));
   const size_t sel_tiles = (N + asl::kSelTile - 1) / asl::kSelTile;
   w.sel_rows = (int)(rows < (size_t)asl::kSelMaxRowsAtOnce ? rows : (size_t)asl::kSelMaxRowsAtOnce);
   w.sel_sample = (uint32_t*)take((size_t)w.sel_rows * asl::kSelMaxSample * sizeof(uint32_t));
   w.sel_bound = (uint32_t*)take((size_t)w.sel_rows * sizeof(uint32_t));
-  w.sel_thr = (uint32_t*)take((size_t)w.sel_rows * 2 * sizeof(uint32_t));
   w.sel_cand_key = (uint32_t*)take((size_t)w.sel_rows * sel_tiles * asl::kSelSegment * sizeof(uint32_t));
   w.sel_cand_idx = (uint32_t*)take((size_t)w.sel_rows * sel_tiles * asl::kSelSegment * sizeof(uint32_t));
   w.sel_seg_count = (uint32_t*)take((size_t)w.sel_rows * sel_tiles * sizeof(uint32_t));
@@ -357,12 +353,9 @@ asl_status asl_pool(asl_ctx* ctx, const float* u, int32_t rows, int32_t T, int32
   return ASL_OK;
 }
 
-// The workgroups of a sort launch (one per kSortTile elements) wait for each other, so they must
-// fit on the device at once.
-static asl_status check_sort_size(asl_ctx* ctx, int32_t T) {
-  if (T > asl::rank_max_tokens())
-    return fail(ctx, ASL_EUNSUPPORTED, "T=%d is more than one ranking launch can hold on this device (%lld tokens)", T,
-                (long long)asl::rank_max_tokens());
+static asl_status check_rank_size(asl_ctx* ctx, int32_t T) {
+  if (T > asl::kRankMaxT)
+    return fail(ctx, ASL_EUNSUPPORTED, "T=%d is more than one ranking call takes (%d tokens)", T, asl::kRankMaxT);
   return ASL_OK;
 }
 
@@ -373,7 +366,7 @@ asl_status asl_rank(asl_ctx* ctx, const float* s, int32_t T, int32_t* rank_out, 
   if (T > ctx->max_seq_len) return fail(ctx, ASL_ENOMEM, "T=%d exceeds the context limit %d", T, ctx->max_seq_len);
   DeviceGuard guard(ctx->device);
   if (guard.err != hipSuccess) return hip_fail(ctx, guard.err, "set device");
-  asl_status st = check_sort_size(ctx, T);
+  asl_status st = check_rank_size(ctx, T);
   if (st != ASL_OK) return st;
   hipError_t e = asl::launch_rank(ctx->ws, s, T, rank_out, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(ctx, e, "rank launch");
@@ -420,7 +413,7 @@ asl_status asl_rank_stat(asl_ctx* ctx, const asl_params* p, const float* s_all, 
   DeviceGuard guard(ctx->device);
   if (guard.err != hipSuccess) return hip_fail(ctx, guard.err, "set device");
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  st = check_sort_size(ctx, T);
+  st = check_rank_size(ctx, T);
   if (st != ASL_OK) return st;
   int32_t* row = rank_ring + (int64_t)(layer_idx % l_obs) * T;
   hipError_t e = asl::launch_rank(ctx->ws, s_all, T, row, hs);

@@ -54,15 +54,14 @@ struct Workspace {
   float* row_part;      // [Hk][n_chunks][M][2]  pass-1 partial (max, sum) per row and key chunk
   float* row_const;     // [Hq*W]                log2-domain softmax offsets  m + log2(Z)
   float* u_group;       // [Hk][T]               group-summed past-only column sums (pre-pool)
-  // radix sort (rank)
-  uint32_t* sort_key[2];   // [T] ping-pong
-  uint32_t* sort_idx[2];   // [T]
-  unsigned long long* sort_table;   // [n_tiles][128] tagged per-tile digit counts of the current pass
-  unsigned long long* sort_epoch;   // [1] tag of the last sort launch
+  // ranking
+  uint2* rank_pairs;       // [T] (key, token) pairs, grouped by bucket inside each tile
+  uint32_t* rank_count;    // [n_tiles][n_buckets] where each tile's pairs of a bucket begin, and how many they are
+  uint32_t* rank_edge;     // [kRankMaxBuckets + 1] first key of each bucket
+  uint32_t* rank_sample;   // [kSelMaxSample] sampled keys of a vector that nobody left a sample of
   // select
   uint32_t* sel_sample;    // [sel_rows][kSelMaxSample] sampled keys of freshly pooled score rows
   uint32_t* sel_bound;     // [sel_rows] key bound guessed from the row's sample
-  uint32_t* sel_thr;       // [sel_rows][2] threshold key and kept ties of each row
   uint32_t* sel_cand_key;  // [sel_rows][n_tiles][kSelSegment] keys that passed the bound, in token order
   uint32_t* sel_cand_idx;  // same shape: their token indices
   uint32_t* sel_seg_count; // [sel_rows][n_tiles] entries used in each segment
@@ -74,16 +73,11 @@ struct Workspace {
   Prof* prof;              // null unless profiling is enabled
 };
 
-#ifndef ASL_SORT_TILE
-#define ASL_SORT_TILE 2048
-#endif
-#ifndef ASL_SORT_THREADS
-#define ASL_SORT_THREADS 1024
-#endif
-constexpr int kSortTile = ASL_SORT_TILE;   // elements per radix-sort workgroup tile (a multiple of 256)
+constexpr int kRankMaxTiles = 256;     // tiles and buckets of one ranking
+constexpr int kRankMaxBuckets = 1024;
+constexpr int kRankMaxT = kRankMaxTiles * 8192;   // longest vector one ranking call takes
 constexpr int kMaxChunks = 256;        // key chunks per KV head in scoring pass 1
 constexpr int kVarMaxBlocks = 256;     // workgroups of the rank-variance kernel
-constexpr int kSortMaxTiles = 512;     // workgroups of one sort launch (they wait for each other)
 constexpr int kSelMaxRowTiles = 1024;  // tiles per row the candidate path handles
 constexpr int kSelMaxRowsAtOnce = 256; // rows per round of select launches (bounds the candidate buffers)
 
@@ -165,6 +159,11 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long x) {
   return l0 + (l1 << 22) + (l2 << 44);
 }
 
+// Set bits of a wavefront ballot that belong to lanes below the calling one.
+__device__ __forceinline__ uint32_t lanes_below(uint64_t ballot) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(ballot >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ballot, 0u));
+}
+
 __device__ __forceinline__ void hist_clear(uint32_t* h, int tid, int n_threads) {
   for (int i = tid; i < kHistWords; i += n_threads) h[i] = 0;
 }
@@ -213,21 +212,6 @@ __device__ __forceinline__ bool flag_poll_batch(const unsigned long long* col, i
 }
 #endif
 
-// Workgroups of `kernel` that can wait for each other inside one launch: half of what the device
-// holds at once (other kernels may be running beside it), never more than `cap`.
-template <typename K>
-static inline int coresident_limit(K kernel, int threads, int cap = 1024, size_t dynamic_lds = 0) {
-  int dev = 0, cus = 0, per_cu = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, dynamic_lds) != hipSuccess) {
-    (void)hipGetLastError();
-    return 1;
-  }
-  const long n = (long)cus * per_cu / 2;
-  return (int)(n < 1 ? 1 : (n > cap ? cap : n));
-}
-
 hipError_t launch_score(const asl_params& p, const Workspace& ws, const void* q_obs, const void* k,
                         const float* lse, float* lse_out, hipStream_t st);
 // sample (optional): [rows + 1][kSelMaxSample], receives the top-k's strided sample of the pooled
@@ -235,8 +219,6 @@ hipError_t launch_score(const asl_params& p, const Workspace& ws, const void* q_
 hipError_t launch_pool(Prof* prof, const float* u, int rows, int T, int S, float* p_out, float* s_out,
                        uint32_t* sample, hipStream_t st);
 hipError_t launch_rank(const Workspace& ws, const float* s, int T, int32_t* rank_out, hipStream_t st);
-int rank_max_tiles();      // tiles (workgroups) one sort launch may have on this device
-int64_t rank_max_tokens(); // largest T one ranking call takes on this device
 // push != 0: first account for this layer's freshly written ring row in the state (a layer index
 // that does not follow state->last_layer restarts the ring)
 hipError_t launch_rankvar(const Workspace& ws, const int32_t* ring, int l_obs, int T, int layer_idx,
@@ -268,7 +250,7 @@ struct GatherArgs {
 hipError_t launch_gather(Prof* prof, const GatherArgs& args, int Hk, int n_layers, hipStream_t st);
 bool gather_prepare(GatherArgs& a);   // sets cpr_shift; returns whether cpr is a power of two
 // Ranking sort of the last of `rows` score rows + top-k of all rows + optional statistic and KV
-// compaction in five launches (two for short contexts) on one stream (tail.hip); *taken = false when the sizes do not fit and nothing was launched.
+// compaction in four launches (two for short contexts) on one stream (tail.hip); *taken = false when the sizes do not fit and nothing was launched.
 struct RankvarArgs;
 hipError_t launch_tail(const Workspace& ws, const float* scores, int rows, int T, int k, int W, int32_t* rank_row,
                        int32_t* idx_out, const GatherArgs* gather, int Hk, bool have_sample, const RankvarArgs& stat,

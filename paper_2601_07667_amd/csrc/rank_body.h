@@ -1,52 +1,17 @@
-// Device code of asl_rank's sort pass (see rank.hip for the method), written as a function over an
-// explicit shared-state struct so that another kernel can host it beside a second body.
+// Device code of asl_rank's kernels (see rank.hip for the method), written as functions over explicit
+// shared-state structs so that another kernel can host them beside a second body.
 #pragma once
-#include "asl_internal.h"
+#include "sample_body.h"
 
 namespace asl {
 
-constexpr int kSortThreads = ASL_SORT_THREADS;
+constexpr int kSortThreads = kRowThreads;
 constexpr int kSortWaves = kSortThreads / 64;
-constexpr int kSortGroups = kSortThreads / 128;              // thread groups that share the polling
-constexpr int kSortPoll = 4;                                 // words a thread polls at once (16 held 60 more registers:
-                                                             // one workgroup per compute unit instead of two)
-// Elements per thread: kSortRounds normally (tiles of kSortTile elements); kSortRoundsBig for inputs
-// whose kSortTile-element tiles would be more workgroups than one launch may have.
-constexpr int kSortRounds = kSortTile / kSortThreads;
-constexpr int kSortRoundsBig = 4 * kSortRounds;
-static_assert(kSortTile % kSortThreads == 0 && kSortThreads % 128 == 0 && kSortThreads >= 256, "sort geometry");
-static_assert(kSortThreads * kSortRoundsBig < (1 << kFlagCountBits), "a tile's digit count must fit the packed field");
-
-struct SortShared {
-  uint32_t h[kHistWords];
-  uint32_t cnt[kSortWaves][256];
-  uint32_t start[kSortWaves][256];
-  uint32_t part_tot[kSortGroups][256];
-  uint32_t part_prev[kSortGroups][256];
-  uint32_t digit_off[256];
-  uint32_t wave_sum[4];
-  int gave_up;
-};
-
-struct SortArgs {
-  const float* s;                // scores (first pass only)
-  const uint32_t* keys_in;       // (key, index) pairs of the previous pass
-  const uint32_t* idx_in;
-  int T, shift, n_tiles;
-  unsigned long long* table;     // [n_tiles][128] tagged digit counts
-  unsigned long long* epoch;     // launch counter behind the tags
-  uint32_t* fault;
-  uint32_t* keys_out;
-  uint32_t* idx_out;
-  int32_t* rank_out;             // last pass only
-};
 
 // Ranks of kCountTokens tokens of a short vector (T <= kShortT) by counting: a workgroup reads all keys into LDS,
 // 32 lanes share a token and compare its key with every other one: rank = keys before it in the order
 // (key ascending, index ascending).  T * T comparisons, two vector instructions each, spread over T / 32
-// workgroups: 5 us at 8000 tokens, one launch and one barrier, against 25 us for four sort passes, which
-// are latency from end to end at these sizes.  At 12288 tokens both jobs of a layer step's launch take ~11 us;
-// beyond, the comparisons grow past what the sort takes (16384: ~14 us, 32768: ~55 us).
+// workgroups: 5 us at 8000 tokens, one launch and one barrier.
 constexpr int kCountTokens = kSortThreads / 32;
 struct CountShared {
   uint32_t keys[kShortT];
@@ -81,149 +46,509 @@ __device__ __forceinline__ void rank_count_body(CountShared& sh, const float* __
 }
 inline int rank_count_blocks(int T) { return (T + kCountTokens - 1) / kCountTokens; }
 
-// Tiles of a sort of T scores: kSortTile elements each, or four times that when T would otherwise
-// need more workgroups than `limit`; n_tiles = 0 if even those are too many.
-struct SortPlan {
-  int n_tiles;
-  bool big;
+// ---------------------------------------------------------------------------------------------
+struct DigitShared {
+  uint16_t cnt[kSortWaves][256];                        // pairs per wavefront and digit
+  uint16_t start[kSortWaves][256];                      // their first places
 };
-SortPlan sort_plan(int T, int limit);
-// Arguments of pass `pass` (0..3) of the sort of s[0..T) into rank_out, using ws's sort buffers.
-SortArgs sort_pass_args(const Workspace& ws, const float* s, int T, int n_tiles, int32_t* rank_out, int pass);
 
-// One pass for tile `me` (kSortThreads threads, R elements each).
-template <int R, bool FIRST, bool LAST>
-__device__ __forceinline__ void sort_pass_body(SortShared& sh, const SortArgs& a, int me) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const unsigned long long tag = *a.epoch + 1ull;
-
-  // this wave's elements: issue every load before anything waits on one
-  constexpr int kTile = kSortThreads * R, kPerWave = 64 * R;
-  uint32_t key[R], idx[R], off[R];
-  const int base = me * kTile + wave * kPerWave;
+// Sorts n <= PER * kSortThreads pairs in LDS by key, equal keys in the order they are in: LSD radix passes of 8 bits over the
+// bits in which the keys differ, equal digits of a wavefront ranked by ballots.  For what equal-width bins cannot
+// tell apart: repeated or nearly equal keys.  Two barriers a pass: a wavefront clears and fills its own row of counts,
+// and every wavefront works out its own first places from all rows.
+template <int PER, typename Tok>
+__device__ __forceinline__ void sort_by_digits(uint32_t* key, Tok* tok, DigitShared& sh, uint32_t* red, int n) {
+  const int tid = threadIdx.x, wave = uniform_wave(), lane = tid & 63;
+  const int rounds = (n + kSortThreads - 1) / kSortThreads;                  // of 64 pairs per wavefront
+  uint32_t lo = 0xffffffffu, hi = 0u;
+  for (int i = tid; i < n; i += kSortThreads) {
+    lo = min(lo, key[i]);
+    hi = max(hi, key[i]);
+  }
+  block_min_max(red, lo, hi);
+  const int bits = hi == lo ? 0 : 32 - __clz((int)(hi - lo)), n_pass = (bits + 7) / 8;
+  uint2* my_cnt = reinterpret_cast<uint2*>(&sh.cnt[wave][4 * lane]);         // digits 4 lane .. 4 lane + 3
+  for (int pass = 0; pass < n_pass; ++pass) {           // uniform
+    const int shift = 8 * pass;
+    int e = wave * 64 * rounds + lane;                  // this thread's pair r: e + 64 r
+    asm volatile("" : "+v"(e));                         // addresses are worked out per pass, not held through it
+    uint32_t k[PER], t[PER], off[PER];
+    *my_cnt = make_uint2(0u, 0u);
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int e = base + r * 64 + lane;
-    key[r] = 0;
-    idx[r] = 0;
-    if (e < a.T) {
-      key[r] = FIRST ? order_key(a.s[e]) : a.keys_in[e];
-      idx[r] = FIRST ? (uint32_t)e : a.idx_in[e];
+    for (int r = 0; r < PER; ++r) {
+      k[r] = lo;
+      t[r] = 0;
+      off[r] = 0;
+      if (r < rounds) {                                 // uniform
+        const bool valid = e + 64 * r < n;
+        if (valid) {
+          k[r] = key[e + 64 * r];
+          t[r] = tok[e + 64 * r];
+        }
+        const uint32_t d = ((k[r] - lo) >> shift) & 255u;
+        uint64_t peers = __ballot(valid);
+        for (int b = 0; b < 8; ++b) {
+          const bool bit = (d >> b) & 1u;
+          const uint64_t bal = __ballot(bit);
+          peers &= bit ? bal : ~bal;
+        }
+        const uint32_t before = lanes_below(peers);
+        uint32_t old = 0;
+        if (valid) old = sh.cnt[wave][d];
+        if (valid && before == 0) sh.cnt[wave][d] = (uint16_t)(old + (uint32_t)__popcll(peers));
+        off[r] = old + before;
+      }
+    }
+    __syncthreads();                                    // all counts are there, all pairs are read
+    // two digits a word: sums stay below 2^16
+    uint2 tot = make_uint2(0u, 0u), prev = tot;
+#pragma unroll 8
+    for (int w = 0; w < kSortWaves; ++w) {
+      if (w == wave) prev = tot;
+      const uint2 c = *reinterpret_cast<const uint2*>(&sh.cnt[w][4 * lane]);
+      tot.x += c.x;
+      tot.y += c.y;
+    }
+    const uint32_t t0 = tot.x & 0xffffu, t1 = tot.x >> 16, t2 = tot.y & 0xffffu, t3 = tot.y >> 16, sum = t0 + t1 + t2 + t3;
+    const uint32_t s0 = wave_prefix_sum(sum) - sum, s1 = s0 + t0, s2 = s1 + t1;
+    *reinterpret_cast<uint2*>(&sh.start[wave][4 * lane]) = make_uint2(prev.x + (s0 | (s1 << 16)), prev.y + (s2 | ((s2 + t2) << 16)));
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+      if (r < rounds && e + 64 * r < n) {
+        const uint32_t dest = sh.start[wave][((k[r] - lo) >> shift) & 255u] + off[r];   // < n
+        key[dest] = k[r];
+        tok[dest] = (Tok)t[r];
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+struct RankArgs {
+  const float* s;                // scores
+  const uint32_t* sample;        // n_s keys of s left behind by its producer, or null: taken from s
+  int n_s, stride;               // the sample: keys and the stride between their positions
+  int T, n_tiles, tile_log;      // tiles of 2^tile_log tokens
+  int tile_step;                 // a power of two, at least half of n_tiles
+  int n_buckets;
+  uint2* pairs;                  // [T] (key, token), grouped by bucket inside each tile
+  uint32_t* count;               // [n_tiles][n_buckets] a tile's first place of the bucket | its tokens of the bucket << 16
+  uint32_t* edge;                // [n_buckets + 1] first key of each bucket; the last one's last key
+  int32_t* rank_out;
+};
+
+constexpr int kSortedSample = 4096;                     // most keys of a sample that is sorted
+struct PartShared {
+  SampleShared s;                                       // bin: the sample's counts, then the bucket of each bin
+  union {
+    uint16_t cnt[kSortWaves][kRankMaxBuckets];          // tokens per wavefront and bucket, then their first places
+    struct {                                            // a sample to be sorted (its numbers in s.bin)
+      uint32_t key[kSortedSample];
+      DigitShared digit;
+    };
+  };
+};
+static_assert(sizeof(uint16_t) * kSortedSample <= sizeof(SampleShared::bin) && kSortedSample >= 4 * kRankMaxBuckets &&
+                  sizeof(uint2) * kRankMaxBuckets <= sizeof(SampleShared::bin), "a sorted sample's numbers, then its borders, are held in bin");
+
+// Launch 1 for tile `me` (kSortThreads threads, R tokens each): the tile's (key, token) pairs, grouped by bucket and
+// in token order inside one, go to the tile's own stretch of `pairs`, and where each bucket's begin to `count`.
+// Every tile works out the same bucket borders from the same sample, so tiles agree on nothing else and wait for
+// nobody.  Bound by latency: the loads, three counts with a scan each, the stores.
+// Borders are those of the sample's histogram bins: bucket b holds the bins whose first sampled key has a place in
+// [b, b + 1) n_s / B.  Where a bin holds three buckets' worth or more (scores that repeat, or that a few outliers push
+// together) the sample is sorted instead, and every n_s / B-th pair (key, token) of it is a border: equal scores are
+// then shared out by token.
+template <int R>
+__device__ __forceinline__ void partition_body(PartShared& sh, const RankArgs& a, int me) {
+  const int tid = threadIdx.x, wave = uniform_wave(), lane = tid & 63, T = a.T, B = a.n_buckets;
+  constexpr int kTile = kSortThreads * R;
+  const int e0 = me * kTile + wave * (64 * R) + lane;   // this thread's token r: e0 + 64 r
+  float f[R];
+  uint32_t v[kSamplePer];
+#pragma unroll
+  for (int r = 0; r < R; ++r) f[r] = a.s[min(e0 + 64 * r, T - 1)];
+  load_sample(a.s, a.sample, a.n_s, a.stride, v);
+  uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+  for (int u = 0; u < kSamplePer; ++u) {
+    lo = min(lo, v[u]);
+    hi = max(hi, v[u]);
+  }
+  block_min_max(sh.s.red, lo, hi);
+  const int shift = bin_shift(lo, hi, kSampleBinBits);
+  sample_count(sh.s, v, a.n_s, lo, hi, shift);
+  const uint4 c = sh.s.bin[tid];
+  uint32_t first, total, most;
+  block_scan<true>(sh.s.red, c.x + c.y + c.z + c.w, max(max(c.x, c.y), max(c.z, c.w)), first, total, most);
+  const bool sorted = B > 1 && most * (uint32_t)B > 3u * (uint32_t)a.n_s;      // uniform
+  uint32_t* lut = &sh.s.bin[0].x;
+  uint2* border = reinterpret_cast<uint2*>(sh.s.bin);   // [b]: first pair of bucket b, b > 0
+  if (!sorted) {
+    const float per_key = (float)B / (float)a.n_s;      // monotone in `first` whatever the rounding
+    const uint32_t f1 = first + c.x, f2 = f1 + c.y, f3 = f2 + c.z, top = (uint32_t)(B - 1);
+    const uint32_t bucket[4] = {min((uint32_t)((float)first * per_key), top), min((uint32_t)((float)f1 * per_key), top),
+                                min((uint32_t)((float)f2 * per_key), top), min((uint32_t)((float)f3 * per_key), top)};
+    sh.s.bin[tid] = make_uint4(bucket[0], bucket[1], bucket[2], bucket[3]);   // own counts only were read
+    __syncthreads();
+    if (me == 0) {
+      // first key of every bucket (empty ones: of the next that is not); bins behind the last key's: that key
+      uint32_t prev = tid == 0 ? 0xffffffffu : lut[4 * tid - 1];             // + 1 = 0: bucket 0 begins with bin 0
+      const uint32_t past = (hi - lo) >> shift;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t j = (uint32_t)(4 * tid + i);
+        for (uint32_t b = prev + 1u; b <= bucket[i]; ++b) a.edge[b] = j <= past ? lo + (j << shift) : hi;
+        prev = bucket[i];
+      }
+      if (tid == kSortThreads - 1)
+        for (uint32_t b = prev + 1u; b <= (uint32_t)B; ++b) a.edge[b] = hi;
+    }
+  } else {
+    // one of every 2^thin keys of it: four a bucket are enough here, and sorting costs what it sorts (all 4096, 128 K
+    // scores, a third of them equal: 55 us the ranking, with 1024 of them 50)
+    const int need = max(4 * B, 1024);
+    const int thin = a.n_s >= 8 * need ? 3 : a.n_s >= 4 * need ? 2 : a.n_s >= 2 * need ? 1 : 0;
+    const int n_s = min(a.n_s >> thin, kSortedSample);
+    uint16_t* num = reinterpret_cast<uint16_t*>(sh.s.bin);
+    __syncthreads();                                    // the counts were read
+#pragma unroll
+    for (int u = 0; u < kSamplePer; ++u) {
+      const int j = tid + u * kSortThreads, i = j >> thin;
+      const uint32_t pick = (uint32_t)i * 2654435761u >> 24;                 // any of the group's, for periodic scores
+      if ((((uint32_t)j ^ pick) & ((1u << thin) - 1u)) == 0u && i < n_s) {
+        sh.key[i] = v[u];
+        num[i] = (uint16_t)j;
+      }
+    }
+    __syncthreads();
+    sort_by_digits<kSortedSample / kSortThreads>(sh.key, num, sh.digit, sh.s.red, n_s);
+    uint2 mine = make_uint2(0u, 0u);
+    if (tid < B) {
+      const int i = (int)((uint32_t)tid * (uint32_t)n_s / (uint32_t)B);
+      const uint32_t j = num[i];
+      mine = make_uint2(sh.key[i], a.sample != nullptr ? j * (uint32_t)a.stride : sample_position(j, a.stride));
+    }
+    __syncthreads();                                    // num and key are read
+    if (tid < B) border[tid] = mine;
+    if (me == 0) {
+      if (tid < B) a.edge[tid] = mine.x;                // bucket 0: the sample's first key
+      if (tid == 0) a.edge[B] = hi;
     }
   }
-  hist_clear(sh.h, tid, kSortThreads);
-  if (tid == 0) sh.gave_up = 0;
+  {
+    // clear the wavefronts' counts
+    uint32_t* w = reinterpret_cast<uint32_t*>(&sh.cnt[0][0]);
 #pragma unroll
-  for (int w = 0; w < kSortWaves; ++w)
-    if (tid < 256) sh.cnt[w][tid] = 0;
+    for (int i = 0; i < (int)(sizeof(sh.cnt) / 4 / kSortThreads); ++i) w[i * kSortThreads + tid] = 0u;
+  }
   __syncthreads();
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-    if (base + r * 64 + lane < a.T) hist_add(sh.h, tid, (key[r] >> a.shift) & 255u);
-  __syncthreads();
-  // publish this tile's counts, two digits per word
-  if (tid < 128)
-    flag_publish(&a.table[(int64_t)me * 128 + tid], tag, hist_total(sh.h, 2 * tid), hist_total(sh.h, 2 * tid + 1));
 
-  // Places inside the tile, while the counts travel (the exchange below takes ~2 us at 64 tiles, 7 us at 256;
-  // ranking after it instead cost 0.8 us per pass at 131 040 tokens, 9.1 against 8.2).
-  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  // places inside the tile: equal buckets of a wavefront are ranked by ballots, stable by construction
+  const int n_bits = B > 1 ? 32 - __clz(B - 1) : 0;
+  uint32_t key[R], d[R], off[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int e = base + r * 64 + lane;
-    const bool valid = e < a.T;
-    const uint32_t d = (key[r] >> a.shift) & 255u;
-    uint64_t peers = __ballot(valid);
+    key[r] = order_key(f[r]);
+    if (!sorted) {                                      // uniform
+      d[r] = lut[clamped_bin(key[r], lo, hi, shift)];
+    } else {
+      const uint32_t t = (uint32_t)(e0 + 64 * r);
+      int b = 0;                                        // last border that is not behind the pair
+      for (int step = kRankMaxBuckets / 2; step > 0; step >>= 1) {
+        if (b + step < B) {
+          const uint2 x = border[b + step];
+          if (x.x < key[r] || (x.x == key[r] && x.y <= t)) b += step;
+        }
+      }
+      d[r] = (uint32_t)b;
+    }
+  }
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const bool bit = (d >> b) & 1u;
+  for (int r = 0; r < R; ++r) {
+    const bool valid = e0 + 64 * r < T;
+    uint64_t peers = __ballot(valid);
+    for (int b = 0; b < n_bits; ++b) {
+      const bool bit = (d[r] >> b) & 1u;
       const uint64_t bal = __ballot(bit);
       peers &= bit ? bal : ~bal;
     }
-    const uint32_t before = __popcll(peers & lt_mask);
+    const uint32_t before = lanes_below(peers);
     uint32_t old = 0;
-    if (valid) old = sh.cnt[wave][d];
-    if (valid && before == 0) sh.cnt[wave][d] = old + (uint32_t)__popcll(peers);
+    if (valid) old = sh.cnt[wave][d[r]];
+    if (valid && before == 0) sh.cnt[wave][d[r]] = (uint16_t)(old + (uint32_t)__popcll(peers));
     off[r] = old + before;
   }
-
-  // every tile's counts of digits 2w, 2w+1 (w = tid % 128); the thread groups share the tiles
-  {
-    const int w = tid & 127, grp = tid >> 7;
-    uint32_t tot0 = 0, tot1 = 0, prev0 = 0, prev1 = 0;
-    bool failed = false;
-    for (int t0 = grp; t0 < a.n_tiles; t0 += kSortGroups * kSortPoll) {
-      unsigned long long v[kSortPoll];
-      failed |= !flag_poll_batch<kSortGroups, kSortPoll>(a.table + w, 128, t0, a.n_tiles, tag, v);
+  __syncthreads();
+  uint32_t tot = 0;
+  if (tid < B) {
 #pragma unroll
-      for (int u = 0; u < kSortPoll; ++u) {
-        const int t = t0 + u * kSortGroups;
-        if (t < a.n_tiles) {
-          const uint32_t c0 = flag_count0(v[u]), c1 = flag_count1(v[u]);
-          tot0 += c0;
-          tot1 += c1;
-          prev0 += (t < me) ? c0 : 0u;
-          prev1 += (t < me) ? c1 : 0u;
-        }
-      }
-    }
-    sh.part_tot[grp][2 * w] = tot0;
-    sh.part_tot[grp][2 * w + 1] = tot1;
-    sh.part_prev[grp][2 * w] = prev0;
-    sh.part_prev[grp][2 * w + 1] = prev1;
-    if (failed) {
-      sh.gave_up = 1;
-      *a.fault = 1u;
-    }
+    for (int w = 0; w < kSortWaves; ++w) tot += sh.cnt[w][tid];
   }
-  __syncthreads();
-  if (sh.gave_up) return;                               // uniform: nothing is scattered by this workgroup
-  if (me == 0 && tid == 0) *a.epoch = tag;             // every workgroup has read the old value by now
-
-  // digit `tid` (first 256 threads): total over all tiles, exclusive scan over the digits
-  if (tid < 256) {
-    uint32_t tot = 0, prev = 0;
-#pragma unroll
-    for (int g = 0; g < kSortGroups; ++g) {
-      tot += sh.part_tot[g][tid];
-      prev += sh.part_prev[g][tid];
-    }
-    const uint32_t incl = wave_prefix_sum(tot);
-    if (lane == 63) sh.wave_sum[wave] = incl;
-    sh.part_tot[0][tid] = incl - tot;                   // exclusive within the wave (own group row is consumed)
-    sh.part_prev[0][tid] = prev;
-  }
-  __syncthreads();
-  if (tid < 256) {
-    uint32_t digit_base = sh.part_tot[0][tid];
-    for (int w = 0; w < wave; ++w) digit_base += sh.wave_sum[w];
-    sh.digit_off[tid] = digit_base + sh.part_prev[0][tid];   // first destination of digit `tid` in this tile
-  }
-
-  __syncthreads();
-  if (tid < 256) {
-    uint32_t run = sh.digit_off[tid];
+  uint32_t start;
+  block_scan<true>(sh.s.red, tot, 0u, start, total, most);
+  if (tid < B) {
+    a.count[(int64_t)me * B + tid] = start | (tot << 16);
+    uint32_t run = start;
 #pragma unroll
     for (int w = 0; w < kSortWaves; ++w) {
-      sh.start[w][tid] = run;
-      run += sh.cnt[w][tid];
+      const uint32_t c = sh.cnt[w][tid];
+      sh.cnt[w][tid] = (uint16_t)run;
+      run += c;
     }
   }
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int e = base + r * 64 + lane;
-    if (e < a.T) {
-      const uint32_t d = (key[r] >> a.shift) & 255u;
-      const uint32_t dest = sh.start[wave][d] + off[r];
-      if (LAST) {
-        a.rank_out[idx[r]] = (int32_t)dest;
-      } else {
-        a.keys_out[dest] = key[r];
-        a.idx_out[dest] = idx[r];
-      }
+    const int e = e0 + 64 * r;
+    if (e < T) {
+      const int dest = me * kTile + (int)(sh.cnt[wave][d[r]] + off[r]);
+      if (dest < T) a.pairs[dest] = make_uint2(key[r], (uint32_t)e);          // always true
     }
   }
 }
+
+// ---------------------------------------------------------------------------------------------
+constexpr int kBucketCap = 7168;                        // pairs one workgroup orders in LDS: two workgroups a compute unit
+constexpr int kBucketPer = kBucketCap / kSortThreads;
+constexpr int kBucketBins = 2 * kSortThreads;           // two per thread
+constexpr int kBucketBinBits = 11;
+constexpr uint32_t kBinMax = 64;                        // longest bin that is ordered by comparing its keys
+static_assert(kBucketBins == 1 << kBucketBinBits, "bucket bins");
+
+struct BucketShared {
+  uint32_t key[kBucketCap];
+  uint32_t tok[kBucketCap];
+  union {
+    uint32_t bin[kBucketBins + 1];
+    DigitShared digit;
+  };
+  uint32_t red[2 * kSortWaves];
+  uint32_t seg_off[kRankMaxTiles + 1];                  // place of each tile's pairs in the bucket
+  uint32_t seg_src[kRankMaxTiles];                      // ... and in `pairs`
+  RankArgs args;                                        // operands of bucket_by_ranges
+  uint32_t n, base;
+};
+
+// Ranks of the bucket's n <= R * kSortThreads pairs in sh.key / sh.tok, whose keys lie in or near [lo, hi]: that range is cut
+// into 2048 bins of equal width, a key's place is its bin's first plus the smaller keys of its bin.  sh.bin is clear.
+// A count, a scan and a short loop over the own bin; the order of the atomic additions decides only where inside its
+// bin a key waits to be compared.  Returns false, with sh.key and sh.tok as they were, where a bin is longer than kBinMax.
+template <int R>
+__device__ __forceinline__ bool bucket_by_bins(BucketShared& sh, int n, uint32_t lo, uint32_t hi, uint32_t base, int T,
+                                               int32_t* __restrict__ rank_out) {
+  const int tid = threadIdx.x, shift = bin_shift(lo, hi, kBucketBinBits);
+  uint32_t key[R], tok[R], slot[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int e = min(tid + r * kSortThreads, n - 1);
+    key[r] = sh.key[e];
+    tok[r] = sh.tok[e];
+    slot[r] = 0;
+    if (tid + r * kSortThreads < n) slot[r] = atomicAdd(&sh.bin[clamped_bin(key[r], lo, hi, shift)], 1u);
+    if (R > 2) __builtin_amdgcn_sched_barrier(0);       // one element's temporaries at a time: 64 registers are all there are
+  }
+  __syncthreads();
+  const uint32_t c0 = sh.bin[2 * tid], c1 = sh.bin[2 * tid + 1];
+  uint32_t first, total, most;
+  block_scan<true>(sh.red, c0 + c1, max(c0, c1), first, total, most);
+  if (most > kBinMax) return false;                     // uniform
+  sh.bin[2 * tid] = first;
+  sh.bin[2 * tid + 1] = first + c0;
+  if (tid == 0) sh.bin[kBucketBins] = (uint32_t)n;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (tid + r * kSortThreads < n) {
+      const uint32_t i = sh.bin[clamped_bin(key[r], lo, hi, shift)] + slot[r];   // < n
+      sh.key[i] = key[r];
+      sh.tok[i] = tok[r];
+    }
+    if (R > 2) __builtin_amdgcn_sched_barrier(0);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (tid + r * kSortThreads < n) {
+      const uint32_t b = clamped_bin(key[r], lo, hi, shift), i0 = sh.bin[b], i1 = sh.bin[b + 1];
+      uint32_t c = base + i0;
+      if (i1 - i0 > 1u)
+#pragma unroll 1
+        for (uint32_t i = i0; i < i1; i += 4u) {        // four at a time: a bin's length in memory round trips otherwise
+#pragma unroll
+          for (uint32_t q = 0; q < 4u; ++q) {
+            const uint32_t j = min(i + q, i1 - 1u), k = sh.key[j], t = sh.tok[j];
+            c += (i + q < i1 && (k < key[r] || (k == key[r] && t < tok[r]))) ? 1u : 0u;
+          }
+        }
+      if (tok[r] < (uint32_t)T) rank_out[tok[r]] = (int32_t)c;               // always true
+    }
+    if (R > 2) __builtin_amdgcn_sched_barrier(0);
+  }
+  return true;
+}
+
+// Pair number i of the bucket (i < seg_off[n_tiles]).
+__device__ __forceinline__ uint2 bucket_pair(const BucketShared& sh, const RankArgs& a, uint32_t i) {
+  int t = 0;                                            // last tile whose pairs begin at or before i
+  for (int step = a.tile_step; step > 0; step >>= 1)
+    if (t + step < a.n_tiles && sh.seg_off[t + step] <= i) t += step;
+  const uint32_t p = sh.seg_src[t] + (i - sh.seg_off[t]);
+  return a.pairs[min(p, (uint32_t)a.T - 1u)];           // p < T
+}
+
+// Next range [from, to] of a large bucket's keys, `from` given: as many bins as LDS holds the pairs of, or (true) the
+// single key from = to, which has more.  At least one pair has a key >= from; returns with to < from if none has.
+__device__ __forceinline__ bool next_range(BucketShared& sh, const RankArgs& a, uint32_t n, uint32_t& from, uint32_t& to) {
+  const int tid = threadIdx.x;
+  to = 0xffffffffu;
+  for (;;) {                                            // at most three trips: 11 bits of the range each
+    const int shift = bin_shift(from, to, kBucketBinBits);
+    __syncthreads();
+    sh.bin[2 * tid] = 0;
+    sh.bin[2 * tid + 1] = 0;
+    __syncthreads();
+    for (uint32_t i = tid; i < n; i += kSortThreads) {
+      const uint32_t k = bucket_pair(sh, a, i).x;
+      if (k >= from && k <= to) atomicAdd(&sh.bin[(k - from) >> shift], 1u);
+    }
+    __syncthreads();
+    const uint32_t c0 = sh.bin[2 * tid], c1 = sh.bin[2 * tid + 1];
+    uint32_t first, total, most;
+    block_scan<true>(sh.red, c0 + c1, 0u, first, total, most);
+    // leading bins that fit together, and how many pairs they hold
+    const uint32_t i0 = first + c0, i1 = i0 + c1;
+    uint32_t fit = i1 <= (uint32_t)kBucketCap ? 2u * tid + 2u : i0 <= (uint32_t)kBucketCap ? 2u * tid + 1u : 0u;
+    uint32_t held = i1 <= (uint32_t)kBucketCap ? i1 : i0 <= (uint32_t)kBucketCap ? i0 : 0u;
+    uint32_t lowest = 0u;
+    block_min_max(sh.red, lowest, fit);
+    block_min_max(sh.red, lowest, held);
+    if (total == 0u) {                                  // cannot happen
+      to = from - 1u;
+      return false;
+    }
+    if (held > 0u) {
+      if (fit < (uint32_t)kBucketBins) to = min(to, from + (fit << shift) - 1u);
+      return false;
+    }
+    // the first bin that holds anything holds too much
+    const uint32_t mask = (1u << shift) - 1u;
+    from += fit << shift;
+    to = to - from < mask ? to : from + mask;
+    if (shift == 0) return true;
+  }
+}
+
+// Buckets that bins do not order: many keys equal, or so close that the sample's bins do not tell them apart.  Up to
+// what LDS holds (the pairs are there) they are ordered by digits.  Larger ones take their keys in ascending
+// ranges that LDS holds, or single keys, whose order is the token order; each range costs two or more sweeps over the
+// bucket's pairs by this one workgroup (128 K equal scores: one sweep to find that out, one to write the ranks).
+// A function of its own, with its operands in LDS: inlined, it cost the ordinary path 60 registers or its spills.
+__device__ __forceinline__ void bucket_by_ranges(BucketShared& sh) {
+  const RankArgs& a = sh.args;
+  const uint32_t n = sh.n, base = sh.base;
+  const bool in_lds = n <= (uint32_t)kBucketCap;
+  uint32_t from = 0, to = 0xffffffffu, done = 0;        // keys below `from` are ranked: `done` of them
+  while (done < n) {                                    // uniform; every trip ranks at least one pair or ends the loop
+    uint32_t m = n;                                     // pairs of this trip
+    bool single = false;
+    if (!in_lds) {
+      single = next_range(sh, a, n, from, to);
+      // in token order: the pairs of the range to LDS, or the ranks of the single key
+      m = 0;
+      for (uint32_t i0 = 0; i0 < n; i0 += kSortThreads) {
+        const uint32_t i = i0 + threadIdx.x;
+        uint2 p = make_uint2(0u, 0u);
+        if (i < n) p = bucket_pair(sh, a, i);
+        const bool in = i < n && p.x >= from && p.x <= to;
+        uint32_t at, total, most;
+        block_scan<true>(sh.red, in ? 1u : 0u, 0u, at, total, most);
+        at += m;
+        if (in && single && p.y < (uint32_t)a.T) a.rank_out[p.y] = (int32_t)(base + done + at);
+        if (in && !single && at < (uint32_t)kBucketCap) {
+          sh.key[at] = p.x;
+          sh.tok[at] = p.y;
+        }
+        m += total;
+      }
+      if (m == 0u) return;                              // cannot happen
+      __syncthreads();
+    }
+    if (!single) {
+      const uint32_t held = min(m, (uint32_t)kBucketCap);
+      sort_by_digits<kBucketPer>(sh.key, sh.tok, sh.digit, sh.red, (int)held);
+      for (uint32_t i = threadIdx.x; i < held; i += kSortThreads) {
+        const uint32_t tok = sh.tok[i];
+        if (tok < (uint32_t)a.T) a.rank_out[tok] = (int32_t)(base + done + i);   // always true
+      }
+    }
+    __syncthreads();
+    done += m;
+    from = to + 1u;                                     // to = 2^32 - 1: nothing is left
+  }
+}
+
+// Launch 2 for bucket b: collects its pairs, a stretch from every tile, and writes their ranks.  The tiles' counts say
+// where the stretches are and how many tokens come before the bucket.
+__device__ __forceinline__ void bucket_body(BucketShared& sh, const RankArgs& a, int b) {
+  const int tid = threadIdx.x, B = a.n_buckets, n_tiles = a.n_tiles;
+  uint32_t start = 0, cnt = 0;
+  if (tid < n_tiles) {                                  // n_tiles <= kRankMaxTiles <= kSortThreads
+    const uint32_t w = a.count[(int64_t)tid * B + b];
+    start = w & 0xffffu;
+    cnt = w >> 16;
+  }
+  uint32_t lo = a.edge[b], hi = a.edge[b + 1];
+  if (b + 1 < B && hi > lo) hi -= 1u;
+  sh.bin[2 * tid] = 0;
+  sh.bin[2 * tid + 1] = 0;
+  uint32_t at, n, base;
+  block_scan<false>(sh.red, cnt, start, at, n, base);
+  if (tid < n_tiles) {
+    sh.seg_off[tid] = at;
+    sh.seg_src[tid] = ((uint32_t)tid << a.tile_log) + start;
+  }
+  if (tid == 0) sh.seg_off[n_tiles] = n;
+  __syncthreads();
+  if (n == 0u) return;                                  // uniform
+  const bool in_lds = n <= (uint32_t)kBucketCap;        // uniform
+  if (in_lds) {
+    // pair by pair, each looking up its tile: stretches may be as uneven as they like (a bucket of equal scores is a
+    // run of tokens)
+    for (uint32_t i = tid; i < n; i += 2 * kSortThreads) {
+      const uint32_t i2 = i + kSortThreads < n ? i + kSortThreads : i;
+      const uint2 p = bucket_pair(sh, a, i), p2 = bucket_pair(sh, a, i2);
+      sh.key[i] = p.x;
+      sh.tok[i] = p.y;
+      sh.key[i2] = p2.x;
+      sh.tok[i2] = p2.y;
+    }
+    __syncthreads();
+    if (b == 0 || b + 1 == B) {
+      // the outermost buckets reach beyond the sample's first and last key, by any distance
+      for (uint32_t i = tid; i < n; i += kSortThreads) {
+        lo = min(lo, sh.key[i]);
+        hi = max(hi, sh.key[i]);
+      }
+      block_min_max(sh.red, lo, hi);
+    }
+    if (n <= 2u * kSortThreads ? bucket_by_bins<2>(sh, (int)n, lo, hi, base, a.T, a.rank_out)
+                               : bucket_by_bins<kBucketPer>(sh, (int)n, lo, hi, base, a.T, a.rank_out))
+      return;
+  }
+  if (tid == 0) {
+    sh.args = a;
+    sh.n = n;
+    sh.base = base;
+  }
+  __syncthreads();
+  bucket_by_ranges(sh);
+}
+
+// Geometry of a ranking of T scores (T <= kRankMaxT), without its operands.
+RankArgs rank_plan(int T);
+// ... with the workspace's buffers.  sample: rank_plan(T).n_s keys of s in compact form, or null.
+RankArgs rank_args(const Workspace& ws, const float* s, int T, const uint32_t* sample, int32_t* rank_out);
 
 }  // namespace asl

@@ -1,0 +1,161 @@
+// A row's sample in LDS: what the top-k takes its bound from (select_body.h) and the ranking the borders of its
+// buckets (rank_body.h).  Every workgroup that needs either works it out from the same few thousand sampled keys: one
+// histogram of 4096 bins of equal width over the sample's range resolves both (~1.5 us beside the workgroup's own
+// loads), where a launch in front of it that did so once per row took 8 us, boundary included.
+#pragma once
+#include "asl_internal.h"
+
+namespace asl {
+
+constexpr int kRowThreads = 1024;                      // workgroup of the ranking and of the selection kernels
+constexpr int kRowWaves = kRowThreads / 64;
+constexpr int kSampleBins = 4 * kRowThreads;           // four neighbouring bins per thread
+constexpr int kSampleBinBits = 12;
+constexpr int kSamplePer = kSelMaxSample / kRowThreads;
+static_assert(kSampleBins == 1 << kSampleBinBits && kSelMaxSample % kRowThreads == 0, "sample geometry");
+
+struct SampleShared {
+  uint4 bin[kRowThreads];                              // [kSampleBins]
+  uint32_t red[2 * kRowWaves];
+  uint32_t out[4];
+};
+
+// Position of sampled key j, one per stride: a scattered place of it, so that a periodic row does not meet a regular sample.
+__device__ __forceinline__ uint32_t sample_position(uint32_t j, int stride) {
+  return j * (uint32_t)stride + (((j * 2654435761u >> 16) * (uint32_t)stride) >> 16);   // < (j + 1) * stride
+}
+
+// Keys u * kRowThreads + tid of a sample of n_s keys (positions past its end repeat its last key): compact in
+// `sample`, or, where that is null, read from the row itself.  All loads are in flight together.
+__device__ __forceinline__ void load_sample(const float* __restrict__ row, const uint32_t* __restrict__ sample, int n_s, int stride,
+                                            uint32_t (&v)[kSamplePer]) {
+  const int tid = threadIdx.x;
+  if (sample != nullptr) {
+#pragma unroll
+    for (int u = 0; u < kSamplePer; ++u) v[u] = sample[min(tid + u * kRowThreads, n_s - 1)];
+  } else {
+    float f[kSamplePer];
+#pragma unroll
+    for (int u = 0; u < kSamplePer; ++u) {
+      const uint32_t j = (uint32_t)min(tid + u * kRowThreads, n_s - 1);
+      f[u] = row[sample_position(j, stride)];
+    }
+#pragma unroll
+    for (int u = 0; u < kSamplePer; ++u) v[u] = order_key(f[u]);
+  }
+}
+
+// The wavefronts' totals red[0 .. kRowWaves - 1], one per lane of a row of 16, summed along the row; lane 15 of the
+// result has the sum.  (Every thread reading all totals held 32 registers and as many masks.)
+static_assert(kRowWaves == 16, "one row of lanes");
+__device__ __forceinline__ uint32_t row_prefix_sum(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);   // row_shr:1
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);   // row_shr:2
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);   // row_shr:4
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);   // row_shr:8
+  return x;
+}
+__device__ __forceinline__ int uniform_wave() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
+
+// Smallest and largest of the workgroup's values.
+__device__ __forceinline__ void block_min_max(uint32_t* red, uint32_t& lo, uint32_t& hi) {
+  const int wave = uniform_wave(), lane = threadIdx.x & 63;
+  lo = wave_min(lo);
+  hi = wave_max(hi);
+  __syncthreads();                                     // red may still be in use
+  if (lane == 0) {
+    red[wave] = lo;
+    red[kRowWaves + wave] = hi;
+  }
+  __syncthreads();
+  lo = wave_min(red[lane & (kRowWaves - 1)]);
+  hi = wave_max(red[kRowWaves + (lane & (kRowWaves - 1))]);
+}
+
+// Exclusive prefix over the workgroup's threads of `x`, its total, and the total of `y` (MAX: its largest).
+template <bool MAX>
+__device__ __forceinline__ void block_scan(uint32_t* red, uint32_t x, uint32_t y, uint32_t& excl, uint32_t& total, uint32_t& y_total) {
+  const int wave = uniform_wave(), lane = threadIdx.x & 63;
+  const uint32_t incl = wave_prefix_sum(x), yw = MAX ? wave_max(y) : wave_sum(y);
+  __syncthreads();                                     // red may still be in use
+  if (lane == 63) {
+    red[wave] = incl;
+    red[kRowWaves + wave] = yw;
+  }
+  __syncthreads();
+  const uint32_t before = row_prefix_sum(red[lane & (kRowWaves - 1)]), ys = red[kRowWaves + (lane & (kRowWaves - 1))];
+  total = (uint32_t)__builtin_amdgcn_readlane((int)before, kRowWaves - 1);
+  excl = incl - x + (wave == 0 ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)before, wave - 1));
+  y_total = MAX ? wave_max(ys) : (uint32_t)__builtin_amdgcn_readlane((int)row_prefix_sum(ys), kRowWaves - 1);
+}
+
+// Shift that maps key - lo, for keys in [lo, hi], to fewer than 2^bits bins.
+__device__ __forceinline__ int bin_shift(uint32_t lo, uint32_t hi, int bits) {
+  const uint32_t span = hi - lo;
+  const int b = span == 0 ? 0 : 32 - __clz((int)span);
+  return b > bits ? b - bits : 0;
+}
+__device__ __forceinline__ uint32_t clamped_bin(uint32_t key, uint32_t lo, uint32_t hi, int shift) {
+  return (min(max(key, lo), hi) - lo) >> shift;
+}
+
+// Counts the sample's keys in [lo, hi] in bins of width 2^shift from lo.
+__device__ __forceinline__ void sample_count(SampleShared& sh, const uint32_t (&v)[kSamplePer], int n_s, uint32_t lo, uint32_t hi, int shift) {
+  const int tid = threadIdx.x;
+  uint32_t* bin = &sh.bin[0].x;
+  sh.bin[tid] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kSamplePer; ++u)
+    if (tid + u * kRowThreads < n_s && v[u] >= lo && v[u] <= hi) atomicAdd(&bin[(v[u] - lo) >> shift], 1u);
+  __syncthreads();
+}
+
+// The m-th smallest key of the sample (1 <= m <= n_s), rounded up to its bin's last key: `bound` lets at most `slack`
+// more of the sample's keys pass (further rounds, 4096 bins within the bin, until that holds).  `below`: the first
+// key of the bin that holds the m_low-th key (m_low <= m).
+__device__ __forceinline__ void sample_bound(SampleShared& sh, const uint32_t (&v)[kSamplePer], int n_s, uint32_t m, uint32_t m_low,
+                                             uint32_t slack, uint32_t& bound, uint32_t& below) {
+  const int tid = threadIdx.x;
+  uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+  for (int u = 0; u < kSamplePer; ++u) {
+    lo = min(lo, v[u]);
+    hi = max(hi, v[u]);
+  }
+  block_min_max(sh.red, lo, hi);
+  below = lo;
+  for (int round = 0;; ++round) {
+    const int shift = bin_shift(lo, hi, kSampleBinBits);
+    sample_count(sh, v, n_s, lo, hi, shift);
+    const uint4 c = sh.bin[tid];
+    uint32_t excl, total, most;
+    block_scan<true>(sh.red, c.x + c.y + c.z + c.w, 0u, excl, total, most);
+    const uint32_t cs[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t incl = excl + cs[q];
+      if (excl < m && m <= incl) {                     // exactly one bin of the workgroup
+        sh.out[0] = (uint32_t)(4 * tid + q);
+        sh.out[1] = m - excl;
+        sh.out[2] = incl - m;
+      }
+      if (excl < m_low && m_low <= incl) sh.out[3] = (uint32_t)(4 * tid + q);
+      excl = incl;
+    }
+    __syncthreads();
+    const uint32_t first = lo + (sh.out[0] << shift), mask = (1u << shift) - 1u,
+                   last = hi - first < mask ? hi : first + mask, over = sh.out[2];
+    if (round == 0) below = lo + (sh.out[3] << shift);
+    if (over <= slack || shift == 0) {                 // uniform
+      bound = last;
+      return;
+    }
+    m = sh.out[1];
+    m_low = 0;
+    lo = first;
+    hi = last;
+  }
+}
+
+}  // namespace asl

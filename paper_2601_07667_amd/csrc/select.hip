@@ -64,7 +64,6 @@ SelectArgs select_args(const Workspace& ws, const float* scores, int T, int k, i
   a.m = sel_sample_rank(T, k, a.n_s, run);
   a.slack = sel_bound_slack(T, a.m, a.n_s, run);
   a.bound = ws.sel_bound;
-  a.thr = ws.sel_thr;
   a.cand_key = ws.sel_cand_key;
   a.cand_idx = ws.sel_cand_idx;
   a.seg_count = ws.sel_seg_count;
@@ -72,11 +71,16 @@ SelectArgs select_args(const Workspace& ws, const float* scores, int T, int k, i
   return a;
 }
 
-hipError_t launch_select(const Workspace& ws, const float* scores, int rows, int T, int k, int W,
-                         int32_t* idx_out, hipStream_t st) {
+hipError_t launch_finish(const Workspace& ws, int kernel_id, const SelectArgs& a, int rows, hipStream_t st) {
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(select_finish_kernel),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFinishLdsBytes);
   if (attr != hipSuccess) return attr;
+  ASL_LAUNCH(ws.prof, kernel_id, st, select_finish_kernel, dim3(rows), dim3(kFinThreads), kFinishLdsBytes, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_select(const Workspace& ws, const float* scores, int rows, int T, int k, int W,
+                         int32_t* idx_out, hipStream_t st) {
   // rows beyond what the candidate buffers hold at once take further rounds of the three launches
   const int rows_per_round = ws.sel_rows;
   for (int row0 = 0; row0 < rows; row0 += rows_per_round) {
@@ -99,7 +103,8 @@ hipError_t launch_select(const Workspace& ws, const float* scores, int rows, int
       ASL_LAUNCH(ws.prof, kKernSelHist, st, (select_filter_kernel<kFinThreads, true>), fgrid, dim3(kFinThreads), 0, st, a);
     else
       ASL_LAUNCH(ws.prof, kKernSelHist, st, (select_filter_kernel<kFinThreads, false>), fgrid, dim3(kFinThreads), 0, st, a);
-    ASL_LAUNCH(ws.prof, kKernSelWrite, st, select_finish_kernel, dim3(nr), dim3(kFinThreads), kFinishLdsBytes, st, a);
+    const hipError_t e = launch_finish(ws, kKernSelWrite, a, nr, st);
+    if (e != hipSuccess) return e;
   }
   return hipGetLastError();
 }

@@ -140,7 +140,6 @@ struct SelectArgs {
   int n_s, stride;               // the sample: keys and the stride between their positions
   int m, slack;                  // rank of the bound in the sample, sample keys it may let pass beyond (see select_bound.h)
   uint32_t* bound;               // [rows]
-  uint32_t* thr;                 // [rows][2] (threshold key, kept ties) when step 3 spans two launches
   uint32_t* cand_key;            // [rows][n_tiles][kSelSegment]
   uint32_t* cand_idx;
   uint32_t* seg_count;           // [rows][n_tiles]
@@ -205,11 +204,6 @@ __device__ __forceinline__ KeepTest keep_test(uint32_t bound) {
   return t;
 }
 __device__ __forceinline__ bool keeps(const KeepTest& t, float score) { return (__float_as_uint(score) - t.lo) <= t.span; }
-// Set bits of a wavefront ballot that belong to lanes below the calling one.
-__device__ __forceinline__ uint32_t lanes_below(uint64_t ballot) {
-  return __builtin_amdgcn_mbcnt_hi((uint32_t)(ballot >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ballot, 0u));
-}
-
 struct FilterShared {
   uint32_t wave_tot[kFinWaves];
 };
@@ -346,8 +340,7 @@ struct FinishShared {
 };
 constexpr size_t kFinishLdsBytes = sizeof(FinishShared) + 2 * (size_t)kSelCandCap * sizeof(uint32_t);
 
-// Step 3 has two halves, usable from one kernel or from two consecutive launches.
-// Common start: offsets of the tiles' candidates in the row's candidate sequence and, unless the
+// Step 3 begins with the offsets of the tiles' candidates in the row's candidate sequence and, unless the
 // whole row has to be taken instead (sh.whole_row), the candidates copied into LDS.  Returns the
 // number of candidates.
 __device__ __forceinline__ int finish_load(FinishShared& sh, uint32_t* lds_cand, const SelectArgs& a, int row) {
@@ -418,18 +411,14 @@ __device__ __forceinline__ int finish_load(FinishShared& sh, uint32_t* lds_cand,
 }
 
 // First half: the k-th smallest key of the row and how many keys equal to it are kept.
-// n: finish_load's result.  With `publish` the pair is also stored for a later launch.
+// n: finish_load's result.
 __device__ __forceinline__ void finish_threshold(FinishShared& sh, const uint32_t* lds_cand, const SelectArgs& a, int row,
-                                                 int n, bool publish, uint32_t& thr, uint32_t& k_rem) {
+                                                 int n, uint32_t& thr, uint32_t& k_rem) {
   if (!sh.whole_row) {                                 // uniform
     radix_select_block(n, (uint32_t)a.k, [&](int i) { return lds_cand[i]; }, sh.h, sh.sm, thr, k_rem);
   } else {
     const float* sr = a.scores + (int64_t)row * a.T;
     radix_select_block(a.T, (uint32_t)a.k, [&](int i) { return order_key(sr[i]); }, sh.h, sh.sm, thr, k_rem);
-  }
-  if (publish && threadIdx.x == 0) {
-    a.thr[2 * row] = thr;
-    a.thr[2 * row + 1] = k_rem;
   }
 }
 
@@ -454,20 +443,8 @@ __device__ __forceinline__ void finish_write(FinishShared& sh, const uint32_t* l
 __device__ __forceinline__ void select_finish_body(FinishShared& sh, uint32_t* lds_cand, const SelectArgs& a, int row) {
   const int n = finish_load(sh, lds_cand, a, row);
   uint32_t thr, k_rem;
-  finish_threshold(sh, lds_cand, a, row, n, false, thr, k_rem);
+  finish_threshold(sh, lds_cand, a, row, n, thr, k_rem);
   finish_write(sh, lds_cand, a, row, n, thr, k_rem);
-}
-
-// Step 3 over two launches: the first stores (threshold key, kept ties) of every row in a.thr ...
-__device__ __forceinline__ void select_threshold_body(FinishShared& sh, uint32_t* lds_cand, const SelectArgs& a, int row) {
-  const int n = finish_load(sh, lds_cand, a, row);
-  uint32_t thr, k_rem;
-  finish_threshold(sh, lds_cand, a, row, n, true, thr, k_rem);
-}
-// ... the second loads the candidates again and writes the indices.
-__device__ __forceinline__ void select_write_body(FinishShared& sh, uint32_t* lds_cand, const SelectArgs& a, int row) {
-  const int n = finish_load(sh, lds_cand, a, row);
-  finish_write(sh, lds_cand, a, row, n, a.thr[2 * row], a.thr[2 * row + 1]);
 }
 
 // All three steps for a row of at most kShortT scores, one workgroup per row: every token is a candidate.
@@ -499,5 +476,8 @@ __device__ __forceinline__ void select_short_body(ShortSelectShared& sh, const S
 // Arguments of a select over `rows` rows of scores (buffers from the workspace; rows <= ws.sel_rows).
 SelectArgs select_args(const Workspace& ws, const float* scores, int T, int k, int W, int32_t* idx_out,
                        bool have_sample);
+
+// Launches step 3 for `rows` rows, to be timed as kernel `kernel_id`.
+hipError_t launch_finish(const Workspace& ws, int kernel_id, const SelectArgs& a, int rows, hipStream_t st);
 
 }  // namespace asl

@@ -94,6 +94,44 @@ def test_rank_beyond_the_small_tile_limit(gpu_device, T):
     c.close()
 
 
+def _rank_sample_positions(T):
+    """Where a ranking of T > 12288 scores takes its sample from a vector that nobody left one of."""
+    n = min(8192, max(1024, T // 32))
+    j, stride = np.arange(n, dtype=np.uint64), T // n
+    return (j * stride + (((j * 2654435761 % 2 ** 32) >> 16) * stride >> 16)).astype(np.int64)
+
+
+@pytest.mark.parametrize("T", [12289, 131072, 262145])
+@pytest.mark.parametrize("kind", ["lognormal", "two-signs", "equal", "third-zero", "few", "sorted", "outliers",
+                                  "unsampled-equal", "unsampled-close"])
+def test_rank_buckets(gpu_device, T, kind):
+    """Scores that fill the ranking's buckets evenly, that its sample's bins do not tell apart (the sample is sorted), and
+    that the sample misses (a bucket of more pairs than LDS holds): integers, exact.  Sizes: the smallest that
+    takes buckets, the 2048-token tiles' and the first of the 4096-token tiles, with one token in the last."""
+    rng = np.random.default_rng(T)
+    s = np.exp(2 * rng.standard_normal(T)).astype(np.float32)
+    if kind == "two-signs":
+        s = rng.standard_normal(T).astype(np.float32)
+    elif kind == "equal":
+        s[:] = 0.25
+    elif kind == "third-zero":
+        s[rng.random(T) < 1 / 3] = 0.0
+    elif kind == "few":
+        s = np.round(3 * rng.standard_normal(T)).astype(np.float32)
+    elif kind == "sorted":
+        s = np.sort(s)
+    elif kind == "outliers":
+        s = (1e-3 * (1 + 0.02 * rng.standard_normal(T))).astype(np.float32)
+        s[::T // 40] = 50.0
+    elif kind.startswith("unsampled"):
+        rest = np.ones(T, dtype=bool)
+        rest[_rank_sample_positions(T)] = False
+        s[rest] = 0.5 if kind == "unsampled-equal" else 0.5 + 1e-6 * np.round(rng.random(int(rest.sum())) * 10)
+    c = asl.Asl(T, 1, 32)
+    _rank_case(c, gpu_device, s)
+    c.close()
+
+
 def test_rank_special(ctx, gpu_device):
     T = 5000
     _rank_case(ctx, gpu_device, np.ones(T, dtype=np.float32))                               # all equal
