@@ -219,8 +219,8 @@ asl_status asl_gather_rows(asl_ctx* ctx, const void* src, int64_t src_row_stride
 /* One layer of Alg. 1 + Alg. 2 in a single call: asl_score_layer, asl_rank_stat, asl_select_topk
  * (Hk per-head rows + the all-head row) and asl_gather_kv (per-head rows), with the same results as
  * the single calls.  After the scoring, ranking and top-k + compaction are independent; the call
- * runs them side by side on `stream`: the two stages of the ranking share launches with the first stages of the
- * top-k, a last launch has the statistic (below l_min the note that it was not evaluated) beside the
+ * runs them side by side in three launches on `stream`: two that each carry a stage of the ranking and one of the
+ * top-k, and one with the statistic (below l_min the note that it was not evaluated) beside the
  * compaction.  Contexts of up to 12288 past tokens take one launch for the ranking and the top-k.
  *   scores  [Hk+1, T] f32 out: rows 0..Hk-1 = P (per KV head), row Hk = s (all heads).
  *   idx_out [Hk+1, k+W] int32 out: rows 0..Hk-1 = Alg. 1's per-head I, row Hk = Alg. 2's select_idx

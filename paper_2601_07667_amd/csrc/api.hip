@@ -50,9 +50,8 @@ size_t carve(char* base, int32_t max_seq_len, int32_t max_kv_heads, int32_t max_
   const size_t sel_tiles = (N + asl::kSelTile - 1) / asl::kSelTile;
   w.sel_rows = (int)(rows < (size_t)asl::kSelMaxRowsAtOnce ? rows : (size_t)asl::kSelMaxRowsAtOnce);
   w.sel_sample = (uint32_t*)take((size_t)w.sel_rows * asl::kSelMaxSample * sizeof(uint32_t));
-  w.sel_bound = (uint32_t*)take((size_t)w.sel_rows * sizeof(uint32_t));
-  w.sel_cand_key = (uint32_t*)take((size_t)w.sel_rows * sel_tiles * asl::kSelSegment * sizeof(uint32_t));
-  w.sel_cand_idx = (uint32_t*)take((size_t)w.sel_rows * sel_tiles * asl::kSelSegment * sizeof(uint32_t));
+  w.sel_bound = (uint32_t*)take((size_t)w.sel_rows * 2 * sizeof(uint32_t));
+  w.sel_cand = (uint2*)take((size_t)w.sel_rows * sel_tiles * asl::kSelSegment * sizeof(uint2));
   w.sel_seg_count = (uint32_t*)take((size_t)w.sel_rows * sel_tiles * sizeof(uint32_t));
   w.var_table = (unsigned long long*)take((size_t)asl::kVarMaxBlocks * 4 * sizeof(unsigned long long));
   w.var_epoch = (unsigned long long*)take(sizeof(unsigned long long));

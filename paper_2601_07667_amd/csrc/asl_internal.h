@@ -61,9 +61,8 @@ struct Workspace {
   uint32_t* rank_sample;   // [kSelMaxSample] sampled keys of a vector that nobody left a sample of
   // select
   uint32_t* sel_sample;    // [sel_rows][kSelMaxSample] sampled keys of freshly pooled score rows
-  uint32_t* sel_bound;     // [sel_rows] key bound guessed from the row's sample
-  uint32_t* sel_cand_key;  // [sel_rows][n_tiles][kSelSegment] keys that passed the bound, in token order
-  uint32_t* sel_cand_idx;  // same shape: their token indices
+  uint32_t* sel_bound;     // [sel_rows][2] key bound guessed from the row's sample, and where its threshold is looked for from
+  uint2* sel_cand;         // [sel_rows][n_tiles][kSelSegment] (key, token) of the keys that passed the bound, in token order
   uint32_t* sel_seg_count; // [sel_rows][n_tiles] entries used in each segment
   int sel_rows;            // rows the candidate buffers hold at once
   // rank variance
@@ -250,7 +249,7 @@ struct GatherArgs {
 hipError_t launch_gather(Prof* prof, const GatherArgs& args, int Hk, int n_layers, hipStream_t st);
 bool gather_prepare(GatherArgs& a);   // sets cpr_shift; returns whether cpr is a power of two
 // Ranking sort of the last of `rows` score rows + top-k of all rows + optional statistic and KV
-// compaction in four launches (two for short contexts) on one stream (tail.hip); *taken = false when the sizes do not fit and nothing was launched.
+// compaction in three launches (two for short contexts) on one stream (tail.hip); *taken = false when the sizes do not fit and nothing was launched.
 struct RankvarArgs;
 hipError_t launch_tail(const Workspace& ws, const float* scores, int rows, int T, int k, int W, int32_t* rank_row,
                        int32_t* idx_out, const GatherArgs* gather, int Hk, bool have_sample, const RankvarArgs& stat,

@@ -46,11 +46,13 @@ __global__ void __launch_bounds__(kSortThreads) rank_count_kernel(const float* _
 RankArgs rank_plan(int T) {
   RankArgs a = {};
   a.T = T;
-  a.tile_log = T <= 262144 ? 11 : T <= 1048576 ? 12 : 13;
+  a.tile_log = T <= 131072 ? 11 : T <= 1048576 ? 12 : 13;     // up to 64 tiles, then up to 256
   a.n_tiles = (T + (1 << a.tile_log) - 1) >> a.tile_log;
   a.tile_step = 1;
   while (2 * a.tile_step < a.n_tiles) a.tile_step *= 2;
+  // ~512 tokens a bucket, more where that keeps them to one workgroup per compute unit (240, beside the top-k's) ...
   a.n_buckets = (T + 511) / 512;
+  if (a.n_buckets > 240) a.n_buckets = T <= 264000 ? 240 : (T + 1023) / 1024;
   if (a.n_buckets > kRankMaxBuckets) a.n_buckets = kRankMaxBuckets;
   a.n_s = sel_sample_size(T);
   if (a.n_s > T) a.n_s = T;

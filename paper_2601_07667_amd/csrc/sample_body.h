@@ -25,24 +25,26 @@ __device__ __forceinline__ uint32_t sample_position(uint32_t j, int stride) {
   return j * (uint32_t)stride + (((j * 2654435761u >> 16) * (uint32_t)stride) >> 16);   // < (j + 1) * stride
 }
 
-// Keys u * kRowThreads + tid of a sample of n_s keys (positions past its end repeat its last key): compact in
+// Keys u * kRowThreads + tid of a sample of n_s keys (positions past its end repeat another of its keys): compact in
 // `sample`, or, where that is null, read from the row itself.  All loads are in flight together.
 __device__ __forceinline__ void load_sample(const float* __restrict__ row, const uint32_t* __restrict__ sample, int n_s, int stride,
                                             uint32_t (&v)[kSamplePer]) {
   const int tid = threadIdx.x;
   if (sample != nullptr) {
 #pragma unroll
-    for (int u = 0; u < kSamplePer; ++u) v[u] = sample[min(tid + u * kRowThreads, n_s - 1)];
+    for (int u = 0; u < kSamplePer; ++u)
+      if (u * kRowThreads < n_s) v[u] = sample[min(tid + u * kRowThreads, n_s - 1)];          // uniform
   } else {
     float f[kSamplePer];
 #pragma unroll
-    for (int u = 0; u < kSamplePer; ++u) {
-      const uint32_t j = (uint32_t)min(tid + u * kRowThreads, n_s - 1);
-      f[u] = row[sample_position(j, stride)];
-    }
+    for (int u = 0; u < kSamplePer; ++u)
+      if (u * kRowThreads < n_s) f[u] = row[sample_position((uint32_t)min(tid + u * kRowThreads, n_s - 1), stride)];
 #pragma unroll
-    for (int u = 0; u < kSamplePer; ++u) v[u] = order_key(f[u]);
+    for (int u = 0; u < kSamplePer; ++u) v[u] = u * kRowThreads < n_s ? order_key(f[u]) : 0u;
   }
+#pragma unroll
+  for (int u = 1; u < kSamplePer; ++u)
+    if (u * kRowThreads >= n_s) v[u] = v[0];
 }
 
 // The wavefronts' totals red[0 .. kRowWaves - 1], one per lane of a row of 16, summed along the row; lane 15 of the

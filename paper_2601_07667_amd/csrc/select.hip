@@ -3,17 +3,20 @@
 // Alg. 2 steps 11-12 on the all-head scores).
 //
 // Exact selection in three small launches that read the scores once and never wait for each other:
-//  1. guess    one workgroup per row looks at an evenly strided sample of the row (read from the
-//              scores, or left behind in compact form by the pooling kernel that produced them)
+//  1. guess    one workgroup per row looks at a strided sample of the row
 //              and takes the sample's m-th smallest key (keys are an order-preserving transform of the scores,
 //              ascending key = descending score) as a bound that, with m a few standard deviations
 //              above the expected number of top-k members in the sample, admits at least k keys
-//              of the row and not many more;
+//              of the row and not many more; the key as far on the other side says where the row's k-th is likely;
 //  2. filter   one workgroup per tile of 4096 tokens keeps the tile's keys <= the bound, in token
-//              order, in the tile's own segment of a candidate buffer (no offsets to agree on);
+//              order, in the tile's own segment of a candidate buffer (no offsets to agree on).  Where the pooling
+//              kernel left the sample behind in compact form (layer steps) the filter's workgroups take the bound from
+//              it themselves and there is no launch 1;
 //  3. finish   one workgroup per row loads the row's candidates (a few thousand) into LDS, finds
-//              the k-th smallest key among them by radix select, and writes the kept tokens in
-//              order.
+//              the k-th smallest key among them (finish_threshold), and writes the kept tokens in order.
+// (With four radix passes for the bound and for the threshold instead of one histogram each, 256 rows of 131040 scores
+// took 57.2 us, now 48.7; a layer step's tail with the bound in a launch of its own and the finish in another 37 us,
+// now 26.)
 // The bound is only a guess: if fewer than k keys passed it, or a tile's or the row's candidates
 // do not fit their buffers, step 3 runs the same selection over the whole row straight from the
 // scores instead (slower, same result).  The result therefore never depends on the sample.
@@ -33,15 +36,14 @@ __global__ void __launch_bounds__(kFinThreads) select_guess_kernel(SelectArgs a)
 // ones for a few rows (one round of workgroups: the shorter each one's share, the sooner it ends).
 template <int NT, bool VEC>
 __global__ void __launch_bounds__(NT) select_filter_kernel(SelectArgs a) {
-  __shared__ FilterShared sh;
-  select_filter_body<NT, VEC>(sh, a, (int)blockIdx.y, (int)blockIdx.x);
+  __shared__ FilterShared<false> sh;
+  select_filter_body<NT, VEC, false>(sh, a, (int)blockIdx.y, (int)blockIdx.x);
 }
 
-// dynamic LDS: kFinishLdsBytes
-__global__ void __launch_bounds__(kFinThreads) select_finish_kernel(SelectArgs a) {
+// dynamic LDS: finish_lds_bytes(a.cand_cap)
+__global__ void __launch_bounds__(kFinThreads, 8) select_finish_kernel(SelectArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_dyn[];
-  FinishShared& sh = *reinterpret_cast<FinishShared*>(lds_dyn);
-  select_finish_body(sh, reinterpret_cast<uint32_t*>(lds_dyn + sizeof(FinishShared)), a, (int)blockIdx.x);
+  select_finish_body(lds_dyn, a, (int)blockIdx.x);
 }
 
 __global__ void __launch_bounds__(kFinThreads) select_short_kernel(SelectArgs a) {
@@ -63,24 +65,20 @@ SelectArgs select_args(const Workspace& ws, const float* scores, int T, int k, i
   a.n_s = sel_sample_size(T) / run * run;
   a.m = sel_sample_rank(T, k, a.n_s, run);
   a.slack = sel_bound_slack(T, a.m, a.n_s, run);
+  a.m_low = sel_sample_rank_low(T, k, a.n_s, run);
+  a.cand_cap = sel_cand_cap(T, a.m, a.slack, a.n_s, run);
   a.bound = ws.sel_bound;
-  a.cand_key = ws.sel_cand_key;
-  a.cand_idx = ws.sel_cand_idx;
+  a.cand = ws.sel_cand;
   a.seg_count = ws.sel_seg_count;
   a.idx_out = idx_out;
   return a;
 }
 
-hipError_t launch_finish(const Workspace& ws, int kernel_id, const SelectArgs& a, int rows, hipStream_t st) {
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(select_finish_kernel),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFinishLdsBytes);
-  if (attr != hipSuccess) return attr;
-  ASL_LAUNCH(ws.prof, kernel_id, st, select_finish_kernel, dim3(rows), dim3(kFinThreads), kFinishLdsBytes, st, a);
-  return hipGetLastError();
-}
-
 hipError_t launch_select(const Workspace& ws, const float* scores, int rows, int T, int k, int W,
                          int32_t* idx_out, hipStream_t st) {
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(select_finish_kernel),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)finish_lds_bytes(kSelCandCap));
+  if (attr != hipSuccess) return attr;
   // rows beyond what the candidate buffers hold at once take further rounds of the three launches
   const int rows_per_round = ws.sel_rows;
   for (int row0 = 0; row0 < rows; row0 += rows_per_round) {
@@ -103,8 +101,7 @@ hipError_t launch_select(const Workspace& ws, const float* scores, int rows, int
       ASL_LAUNCH(ws.prof, kKernSelHist, st, (select_filter_kernel<kFinThreads, true>), fgrid, dim3(kFinThreads), 0, st, a);
     else
       ASL_LAUNCH(ws.prof, kKernSelHist, st, (select_filter_kernel<kFinThreads, false>), fgrid, dim3(kFinThreads), 0, st, a);
-    const hipError_t e = launch_finish(ws, kKernSelWrite, a, nr, st);
-    if (e != hipSuccess) return e;
+    ASL_LAUNCH(ws.prof, kKernSelWrite, st, select_finish_kernel, dim3(nr), dim3(kFinThreads), finish_lds_bytes(a.cand_cap), st, a);
   }
   return hipGetLastError();
 }

@@ -1,44 +1,19 @@
 // Device code of asl_select's three kernels (see select.hip for the method), written as functions
 // over explicit shared-state structs so that another kernel can host them beside a second body.
 #pragma once
-#include "asl_internal.h"
+#include "sample_body.h"
 
 namespace asl {
 
-constexpr int kFinThreads = 1024;                      // workgroup of all three kernels
+constexpr int kFinThreads = kRowThreads;               // workgroup of all three kernels
 constexpr int kFinWaves = kFinThreads / 64;
-constexpr int kFinPerThread = 8;                       // consecutive elements per thread in the ordered write
 constexpr int kFilterThreads = 256;                    // filter workgroup of its own launch over many tiles ...
 constexpr int kFilterSmallFrom = 2048;                 // ... (rows x tiles per row) from this many on; kFinThreads below
+constexpr int kFilterMostTiles = 4;                    // tiles of one workgroup that takes the bound itself
 constexpr uint32_t kSegOverflow = 0xffffffffu;         // a tile's count when its segment was too small
 static_assert(kSelTile % kFinThreads == 0 && kSelTile % kFilterThreads == 0, "filter tile geometry");
 
 static_assert(kSelMaxSample % kFinThreads == 0, "the bound kernel's threads share the sample evenly");
-
-// Exclusive prefix over the workgroup's threads of two counters (kFinThreads threads), plus totals.
-__device__ __forceinline__ void block_scan2(uint32_t a, uint32_t b, uint32_t* sm /* 2*kFinWaves+2 */,
-                                            uint32_t& a_excl, uint32_t& b_excl, uint32_t& a_tot, uint32_t& b_tot) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const uint32_t ai = wave_prefix_sum(a), bi = wave_prefix_sum(b);
-  __syncthreads();                                     // sm may still be in use
-  if (lane == 63) {
-    sm[wave] = ai;
-    sm[kFinWaves + wave] = bi;
-  }
-  __syncthreads();
-  uint32_t ab = 0, bb = 0, at = 0, bt = 0;
-  for (int w = 0; w < kFinWaves; ++w) {
-    const uint32_t x = sm[w], y = sm[kFinWaves + w];
-    ab += (w < wave) ? x : 0u;
-    bb += (w < wave) ? y : 0u;
-    at += x;
-    bt += y;
-  }
-  a_excl = ab + ai - a;
-  b_excl = bb + bi - b;
-  a_tot = at;
-  b_tot = bt;
-}
 
 // Radix select over n keys read through `key_at(i)`: returns the k-th smallest key (1 <= k <= n)
 // and how many of the keys equal to it belong to the k smallest (k_rem >= 1).  All kFinThreads
@@ -139,49 +114,42 @@ struct SelectArgs {
   int T, n_tiles, k, W;
   int n_s, stride;               // the sample: keys and the stride between their positions
   int m, slack;                  // rank of the bound in the sample, sample keys it may let pass beyond (see select_bound.h)
-  uint32_t* bound;               // [rows]
-  uint32_t* cand_key;            // [rows][n_tiles][kSelSegment]
-  uint32_t* cand_idx;
+  int m_low;                     // rank of a sample key that is hardly behind the row's k-th
+  int cand_cap;                  // candidates of one row that step 3 holds in LDS
+  uint32_t* bound;               // [rows][2] the bound, and a key that the k-th is hardly below
+  uint2* cand;                   // [rows][n_tiles][kSelSegment] (key, token)
   uint32_t* seg_count;           // [rows][n_tiles]
   int32_t* idx_out;              // [rows][k + W]
 };
 
 struct GuessShared {
-  uint32_t samp[kSelMaxSample];
-  uint32_t h[kHistWords];
-  uint32_t sm[2 * kFinWaves + 2];
+  SampleShared s;
 };
 
-// Step 1: bound[row] = the m-th smallest key of the row's strided sample, or a key that up to sel_bound_slack more
-// of the sample's keys do not exceed (which saves one or two of the four digit passes); 0xffffffff: admit all.
+// The row's bound and the key the threshold is looked for from, from the sample keys v.
+__device__ __forceinline__ void select_bound(SampleShared& sh, const SelectArgs& a, const uint32_t (&v)[kSamplePer], uint32_t& bound,
+                                             uint32_t& below) {
+  bound = 0xffffffffu;
+  below = 0u;
+  if (a.m < a.n_s) sample_bound(sh, v, a.n_s, (uint32_t)a.m, (uint32_t)a.m_low, (uint32_t)a.slack, bound, below);   // uniform
+}
+
+// Step 1 on its own, from the scores: runs of kSelSampleRun neighbouring keys.
 __device__ __forceinline__ void select_guess_body(GuessShared& sh, const SelectArgs& a, int row) {
-  const int tid = threadIdx.x, n_s = a.n_s, stride = a.stride, m = a.m;
-  if (m >= n_s) {                                      // uniform
-    if (tid == 0) a.bound[row] = 0xffffffffu;
-    return;
+  const int tid = threadIdx.x, n_s = a.n_s, stride = a.stride;
+  const float* sr = a.scores + (int64_t)row * a.T;
+  uint32_t v[kSamplePer];
+#pragma unroll
+  for (int u = 0; u < kSamplePer; ++u) {               // key j = member j % run of run j / run
+    const int j = min(tid + u * kFinThreads, n_s - 1);
+    v[u] = order_key(sr[(j / kSelSampleRun) * (kSelSampleRun * stride) + (j % kSelSampleRun)]);
   }
-  // Every thread's keys are loaded before the first is stored (positions past the sample re-read its
-  // last key): one memory round trip for the whole sample.
-  constexpr int kSampPer = kSelMaxSample / kFinThreads;
-  uint32_t v[kSampPer];
-  if (a.sample != nullptr) {                           // the producer of the scores left the sample behind
-    const uint32_t* sp = a.sample + (int64_t)row * kSelMaxSample;
-#pragma unroll
-    for (int u = 0; u < kSampPer; ++u) v[u] = sp[min(tid + u * kFinThreads, n_s - 1)];
-  } else {
-    const float* sr = a.scores + (int64_t)row * a.T;
-#pragma unroll
-    for (int u = 0; u < kSampPer; ++u) {               // key j = member j % run of run j / run
-      const int j = min(tid + u * kFinThreads, n_s - 1);
-      v[u] = order_key(sr[(j / kSelSampleRun) * (kSelSampleRun * stride) + (j % kSelSampleRun)]);
-    }
+  uint32_t bound, below;
+  select_bound(sh.s, a, v, bound, below);
+  if (tid == 0) {
+    a.bound[2 * row] = bound;
+    a.bound[2 * row + 1] = below;
   }
-#pragma unroll
-  for (int u = 0; u < kSampPer; ++u)
-    if (tid + u * kFinThreads < n_s) sh.samp[tid + u * kFinThreads] = v[u];
-  uint32_t thr, k_rem;
-  radix_select_block(n_s, (uint32_t)m, [&](int i) { return sh.samp[i]; }, sh.h, sh.sm, thr, k_rem, (uint32_t)a.slack);
-  if (tid == 0) a.bound[row] = thr;
 }
 
 // key(score) <= bound, decided on the score's bits without forming the key: non-negative scores
@@ -204,116 +172,148 @@ __device__ __forceinline__ KeepTest keep_test(uint32_t bound) {
   return t;
 }
 __device__ __forceinline__ bool keeps(const KeepTest& t, float score) { return (__float_as_uint(score) - t.lo) <= t.span; }
-struct FilterShared {
-  uint32_t wave_tot[kFinWaves];
+
+template <bool INSIDE> struct FilterShared {
+  uint32_t wave_tot[1][kFinWaves];
+};
+template <> struct FilterShared<true> {
+  uint32_t wave_tot[kFilterMostTiles][kFinWaves];
+  SampleShared s;
 };
 
 // Step 2: the tile's keys <= bound, in token order, to the tile's segment of the candidate buffer.
 // NT threads per workgroup: each wavefront takes kSelTile / (NT / 64) consecutive tokens.
 // VEC: a lane reads four neighbouring scores with one 16-byte load (the row must start on a 16-byte
 // boundary: T % 4 == 0 and an aligned base); otherwise one score per load.
-template <int NT, bool VEC>
-__device__ __forceinline__ void select_filter_body(FilterShared& sh, const SelectArgs& a, int row, int tile) {
+// INSIDE (NT = kFinThreads): the sample is there in compact form and the workgroup takes the bound from it
+// (step 1) beside its own loads; the row's first one stores it for step 3.  TILES: consecutive tiles of a workgroup,
+// from `tile` on: a bound costs as much as two of them.
+template <int NT, bool VEC, bool INSIDE, int TILES = 1>
+__device__ __forceinline__ void select_filter_body(FilterShared<INSIDE>& sh, const SelectArgs& a, int row, int tile) {
   constexpr int kWaves = NT / 64, kSelPerWave = kSelTile / kWaves;
   constexpr int kPer = VEC ? 4 : 1;                     // neighbouring tokens per lane and round
   constexpr int kSelRounds = kSelPerWave / (64 * kPer);
-  static_assert(kSelRounds >= 1, "filter tile geometry");
+  static_assert(kSelRounds >= 1 && (TILES == 1 || INSIDE) && TILES <= kFilterMostTiles, "filter tile geometry");
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, T = a.T;
   const float* sr = a.scores + (int64_t)row * T;
-  const int base = tile * kSelTile + wave * kSelPerWave;
-  float sc[kSelRounds][kPer];
+  const int base = tile * kSelTile + wave * kSelPerWave;     // of the first tile
+  float sc[TILES][kSelRounds][kPer];
 #pragma unroll
-  for (int r = 0; r < kSelRounds; ++r) {               // all loads in flight before the first use
-    const int e = base + (r * 64 + lane) * kPer;
-    if (VEC) {
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (e + 3 < T) {
-        v = *reinterpret_cast<const float4*>(sr + e);
-      } else {                                          // the row's last, partial piece
-        if (e < T) v.x = sr[e];
-        if (e + 1 < T) v.y = sr[e + 1];
-        if (e + 2 < T) v.z = sr[e + 2];
+  for (int i = 0; i < TILES; ++i) {
+#pragma unroll
+    for (int r = 0; r < kSelRounds; ++r) {             // all loads in flight before the first use
+      const int e = base + i * kSelTile + (r * 64 + lane) * kPer;
+      if (VEC) {
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (e + 3 < T) {
+          v = *reinterpret_cast<const float4*>(sr + e);
+        } else {                                        // the row's last, partial piece
+          if (e < T) v.x = sr[e];
+          if (e + 1 < T) v.y = sr[e + 1];
+          if (e + 2 < T) v.z = sr[e + 2];
+        }
+        sc[i][r][0] = v.x;
+        sc[i][r][1 % kPer] = v.y;
+        sc[i][r][2 % kPer] = v.z;
+        sc[i][r][3 % kPer] = v.w;
+      } else {
+        sc[i][r][0] = (e < T) ? sr[e] : 0.f;
       }
-      sc[r][0] = v.x;
-      sc[r][1 % kPer] = v.y;
-      sc[r][2 % kPer] = v.z;
-      sc[r][3 % kPer] = v.w;
-    } else {
-      sc[r][0] = (e < T) ? sr[e] : 0.f;
     }
   }
-  const KeepTest kt = keep_test(a.bound[row]);
+  uint32_t bound, below;
+  if constexpr (INSIDE) {
+    static_assert(NT == kFinThreads, "the sample is shared out among kFinThreads threads");
+    uint32_t v[kSamplePer];
+    load_sample(nullptr, a.sample + (int64_t)row * kSelMaxSample, a.n_s, a.stride, v);
+    select_bound(sh.s, a, v, bound, below);
+    if (tile == 0 && tid == 0) {
+      a.bound[2 * row] = bound;
+      a.bound[2 * row + 1] = below;
+    }
+  } else {
+    bound = a.bound[2 * row];
+  }
+  const KeepTest kt = keep_test(bound);
   // per round: which of the lane's tokens are kept (bit j), how many lower lanes keep, the round's total
-  uint32_t kept[kSelRounds], before[kSelRounds], round_tot[kSelRounds];
-  uint32_t w_cnt = 0;
+  uint32_t kept[TILES][kSelRounds], before[TILES][kSelRounds], round_tot[TILES][kSelRounds];
 #pragma unroll
-  for (int r = 0; r < kSelRounds; ++r) {
-    const int e0 = base + (r * 64 + lane) * kPer;
-    kept[r] = 0;
-    before[r] = 0;
-    round_tot[r] = 0;
+  for (int i = 0; i < TILES; ++i) {
+    uint32_t w_cnt = 0;
 #pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-      const bool keep = (e0 + j < T) && keeps(kt, sc[r][j]);
-      const uint64_t bal = __ballot(keep);
-      kept[r] |= keep ? (1u << j) : 0u;
-      before[r] += lanes_below(bal);
-      round_tot[r] += (uint32_t)__popcll(bal);
+    for (int r = 0; r < kSelRounds; ++r) {
+      const int e0 = base + i * kSelTile + (r * 64 + lane) * kPer;
+      kept[i][r] = 0;
+      before[i][r] = 0;
+      round_tot[i][r] = 0;
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        const bool keep = (e0 + j < T) && keeps(kt, sc[i][r][j]);
+        const uint64_t bal = __ballot(keep);
+        kept[i][r] |= keep ? (1u << j) : 0u;
+        before[i][r] += lanes_below(bal);
+        round_tot[i][r] += (uint32_t)__popcll(bal);
+      }
+      w_cnt += round_tot[i][r];
     }
-    w_cnt += round_tot[r];
+    if (lane == 0) sh.wave_tot[i][wave] = w_cnt;
   }
-  if (lane == 0) sh.wave_tot[wave] = w_cnt;
   __syncthreads();
-  uint32_t run = 0, total = 0;
-  for (int w = 0; w < kWaves; ++w) {
-    run += (w < wave) ? sh.wave_tot[w] : 0u;
-    total += sh.wave_tot[w];
-  }
-  const int64_t seg = ((int64_t)row * a.n_tiles + tile);
-  if (tid == 0) a.seg_count[seg] = (total > (uint32_t)kSelSegment) ? kSegOverflow : total;
-  if (total > (uint32_t)kSelSegment) return;           // uniform: the finish step takes the whole row instead
-  uint32_t* ck = a.cand_key + seg * kSelSegment;
-  uint32_t* ci = a.cand_idx + seg * kSelSegment;
 #pragma unroll
-  for (int r = 0; r < kSelRounds; ++r) {
-    // token order inside a round: lane by lane, a lane's kPer tokens in a row.  Few tokens are kept:
-    // the loop runs as often as the busiest lane has kept tokens.
-    const int e0 = base + (r * 64 + lane) * kPer;
-    uint32_t pos = run + before[r], m = kept[r];
-    while (m != 0u) {
-      const int j = __ffs((int)m) - 1;
-      const float f = (j == 0) ? sc[r][0] : (j == 1) ? sc[r][1 % kPer] : (j == 2) ? sc[r][2 % kPer] : sc[r][3 % kPer];
-      ck[pos] = order_key(f);
-      ci[pos] = (uint32_t)(e0 + j);
-      ++pos;
-      m &= m - 1u;
+  for (int i = 0; i < TILES; ++i) {
+    if (tile + i >= a.n_tiles) break;                   // uniform
+    uint32_t run = 0, total = 0;
+    for (int w = 0; w < kWaves; ++w) {
+      run += (w < wave) ? sh.wave_tot[i][w] : 0u;
+      total += sh.wave_tot[i][w];
     }
-    run += round_tot[r];
+    const int64_t seg = ((int64_t)row * a.n_tiles + tile + i);
+    if (tid == 0) a.seg_count[seg] = (total > (uint32_t)kSelSegment) ? kSegOverflow : total;
+    if (total > (uint32_t)kSelSegment) continue;        // uniform: the finish step takes the whole row instead
+    uint2* cand = a.cand + seg * kSelSegment;
+#pragma unroll
+    for (int r = 0; r < kSelRounds; ++r) {
+      // token order inside a round: lane by lane, a lane's kPer tokens in a row.  Few tokens are kept:
+      // the loop runs as often as the busiest lane has kept tokens.
+      const int e0 = base + i * kSelTile + (r * 64 + lane) * kPer;
+      uint32_t pos = run + before[i][r], m = kept[i][r];
+      while (m != 0u) {
+        const int j = __ffs((int)m) - 1;
+        const float f = (j == 0) ? sc[i][r][0] : (j == 1) ? sc[i][r][1 % kPer] : (j == 2) ? sc[i][r][2 % kPer] : sc[i][r][3 % kPer];
+        cand[pos] = make_uint2(order_key(f), (uint32_t)(e0 + j));
+        ++pos;
+        m &= m - 1u;
+      }
+      run += round_tot[i][r];
+    }
   }
 }
 
 // Ordered write of the kept elements of a sequence of n (key, token) pairs given in token order:
 // kept = key < thr, or key == thr and fewer than k_rem equal keys precede it.
-template <typename KeyAt, typename TokAt>
-__device__ __forceinline__ void ordered_write(int n, uint32_t thr, uint32_t k_rem, int k, KeyAt key_at, TokAt tok_at,
-                                              uint32_t* sm, int32_t* __restrict__ out) {
+// PER consecutive elements per thread and round.
+// load(i0, key): the keys of elements i0 .. i0 + PER - 1; those from n on may be anything.
+template <int PER, typename Load, typename TokAt>
+__device__ __forceinline__ void ordered_write(int n, uint32_t thr, uint32_t k_rem, int k, Load load, TokAt tok_at,
+                                              uint32_t* red, int32_t* __restrict__ out) {
   const int tid = threadIdx.x;
+  static_assert(kFinThreads * PER < 65536, "a round's two counts share a word");
   uint32_t lt_base = 0, eq_base = 0;
-  for (int c0 = 0; c0 < n; c0 += kFinThreads * kFinPerThread) {
-    const int i0 = c0 + tid * kFinPerThread;
-    uint32_t key[kFinPerThread];
-    uint32_t lt = 0, eq = 0;
+  for (int c0 = 0; c0 < n; c0 += kFinThreads * PER) {
+    const int i0 = c0 + tid * PER;
+    uint32_t key[PER];
+    uint32_t cnt = 0;                                  // keys below the threshold | keys equal to it << 16
+    if (i0 < n) load(i0, key);
 #pragma unroll
-    for (int j = 0; j < kFinPerThread; ++j) {
-      key[j] = (i0 + j < n) ? key_at(i0 + j) : 0xffffffffu;
-      lt += (i0 + j < n && key[j] < thr) ? 1u : 0u;
-      eq += (i0 + j < n && key[j] == thr) ? 1u : 0u;
+    for (int j = 0; j < PER; ++j) {
+      cnt += (i0 + j < n && key[j] < thr) ? 1u : 0u;
+      cnt += (i0 + j < n && key[j] == thr) ? 65536u : 0u;
     }
-    uint32_t lt_excl, eq_excl, lt_tot, eq_tot;
-    block_scan2(lt, eq, sm, lt_excl, eq_excl, lt_tot, eq_tot);
-    uint32_t lt_run = lt_base + lt_excl, eq_run = eq_base + eq_excl;
+    uint32_t excl, total, none;
+    block_scan<true>(red, cnt, 0u, excl, total, none);
+    uint32_t lt_run = lt_base + (excl & 0xffffu), eq_run = eq_base + (excl >> 16);
 #pragma unroll
-    for (int j = 0; j < kFinPerThread; ++j) {
+    for (int j = 0; j < PER; ++j) {
       if (i0 + j < n) {
         const bool is_lt = key[j] < thr, is_eq = key[j] == thr;
         if (is_lt || (is_eq && eq_run < k_rem)) {
@@ -324,84 +324,89 @@ __device__ __forceinline__ void ordered_write(int n, uint32_t thr, uint32_t k_re
         eq_run += is_eq ? 1u : 0u;
       }
     }
-    lt_base += lt_tot;
-    eq_base += eq_tot;
+    lt_base += total & 0xffffu;
+    eq_base += total >> 16;
   }
 }
 
-// Shared state of step 3; kSelCandCap candidate keys, then kSelCandCap candidate tokens, follow it in
+// Shared state of step 3; a.cand_cap candidate keys, then as many candidate tokens, follow it in
 // the workgroup's dynamic LDS.
+constexpr int kFinBins = 2 * kFinThreads;               // two per thread
+constexpr int kFinBinBits = 11;
+constexpr uint32_t kFinListMax = 64;
+static_assert(kFinBins == 1 << kFinBinBits && kFinBins <= kHistWords, "the bins share the histogram's memory");
 struct FinishShared {
   uint32_t h[kHistWords];
   uint32_t sm[2 * kFinWaves + 2];
+  uint32_t list[kFinListMax];
+  uint32_t pick[4];
   uint32_t seg_off[kSelMaxRowTiles + 1];
   int whole_row;
-  uint32_t pad[2];
 };
-constexpr size_t kFinishLdsBytes = sizeof(FinishShared) + 2 * (size_t)kSelCandCap * sizeof(uint32_t);
+constexpr size_t finish_lds_bytes(int cand_cap) { return (sizeof(FinishShared) + 15) / 16 * 16 + 2 * (size_t)cand_cap * sizeof(uint32_t); }
+__device__ __forceinline__ uint32_t* finish_cand(void* lds) {
+  return reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(lds) + (sizeof(FinishShared) + 15) / 16 * 16);
+}
 
 // Step 3 begins with the offsets of the tiles' candidates in the row's candidate sequence and, unless the
 // whole row has to be taken instead (sh.whole_row), the candidates copied into LDS.  Returns the
 // number of candidates.
 __device__ __forceinline__ int finish_load(FinishShared& sh, uint32_t* lds_cand, const SelectArgs& a, int row) {
-  const int tid = threadIdx.x, n_tiles = a.n_tiles, k = a.k;
+  const int tid = threadIdx.x, n_tiles = a.n_tiles, k = a.k, wave = uniform_wave(), lane = tid & 63;
+  uint32_t c = 0;                                       // thread t takes tile t's count
+  if (tid < n_tiles && n_tiles <= kSelMaxRowTiles) c = a.seg_count[(int64_t)row * n_tiles + tid];
+  sh.h[2 * tid] = 0;                                    // finish_threshold's bins
+  sh.h[2 * tid + 1] = 0;
+  if (tid == 0) sh.pick[3] = 0;
   {
-    uint32_t c = 0, over = 0;                          // thread t takes tile t
-    if (tid < n_tiles && n_tiles <= kSelMaxRowTiles) {
-      c = a.seg_count[(int64_t)row * n_tiles + tid];
-      over = (c == kSegOverflow) ? 1u : 0u;
-      c = over ? 0u : c;
-    }
-    uint32_t c_excl, o_excl, c_tot, o_tot;
-    block_scan2(c, over, sh.sm, c_excl, o_excl, c_tot, o_tot);
+    const uint32_t over = (c == kSegOverflow) ? 1u : 0u;
+    c = over ? 0u : c;
+    uint32_t c_excl, c_tot, any_over;
+    block_scan<true>(sh.sm, c, over, c_excl, c_tot, any_over);
     if (tid < n_tiles && n_tiles <= kSelMaxRowTiles) sh.seg_off[tid] = c_excl;
     if (tid == 0) {
       if (n_tiles <= kSelMaxRowTiles) sh.seg_off[n_tiles] = c_tot;
-      sh.whole_row = (n_tiles > kSelMaxRowTiles || o_tot != 0 || c_tot < (uint32_t)k || c_tot > (uint32_t)kSelCandCap) ? 1 : 0;
+      sh.whole_row = (n_tiles > kSelMaxRowTiles || any_over != 0 || c_tot < (uint32_t)k || c_tot > (uint32_t)a.cand_cap) ? 1 : 0;
     }
   }
   __syncthreads();
   if (sh.whole_row) return 0;                          // uniform
   uint32_t* lk = lds_cand;
-  uint32_t* li = lds_cand + kSelCandCap;
-  // Wavefront w copies tiles w, w + kFinWaves, ..., two tiles and 128 candidates of each at a time:
-  // the eight loads of such a step are in flight together (a tile holds ~100 candidates at the
-  // usual budgets, so a row takes one memory round trip instead of one per tile and 64 candidates).
-  const int lane = tid & 63;
-  for (int t0 = tid >> 6; t0 < n_tiles; t0 += 2 * kFinWaves) {
-    uint32_t o[2], c[2];
-    int64_t seg[2];
+  uint32_t* li = lds_cand + a.cand_cap;
+  // Wavefront w copies tiles w, w + kFinWaves, ..., two tiles and kBatch candidates of each at a time, whose loads
+  // are in flight together (a tile holds ~100 candidates at the usual budgets, ~400 at the largest).
+  constexpr int kDeep = 4, kBatch = 64 * kDeep;
+  const uint2* row_cand = a.cand + (int64_t)row * n_tiles * kSelSegment;
+  for (int t0 = wave; t0 < n_tiles; t0 += 2 * kFinWaves) {
+    uint32_t o[2], n[2];
+    const uint2* seg[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const int t = t0 + q * kFinWaves;
       const bool in = t < n_tiles;
       o[q] = in ? sh.seg_off[t] : 0u;
-      c[q] = in ? sh.seg_off[t + 1] - o[q] : 0u;
-      seg[q] = ((int64_t)row * n_tiles + (in ? t : 0)) * kSelSegment;
+      n[q] = in ? sh.seg_off[t + 1] - o[q] : 0u;
+      seg[q] = row_cand + (int64_t)(in ? t : 0) * kSelSegment;
     }
-    const uint32_t c_max = c[0] > c[1] ? c[0] : c[1];
-    for (uint32_t j0 = 0; j0 < c_max; j0 += 128) {
-      uint32_t kk[2][2], ii[2][2];
+    const uint32_t n_max = n[0] > n[1] ? n[0] : n[1];
+    for (uint32_t j0 = 0; j0 < n_max; j0 += kBatch) {
+      uint2 x[2][kDeep];
 #pragma unroll
       for (int q = 0; q < 2; ++q)
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < kDeep; ++u) {
           const uint32_t j = j0 + u * 64 + lane;
-          kk[q][u] = 0;
-          ii[q][u] = 0;
-          if (j < c[q]) {
-            kk[q][u] = a.cand_key[seg[q] + j];
-            ii[q][u] = a.cand_idx[seg[q] + j];
-          }
+          x[q][u] = make_uint2(0u, 0u);
+          if (j < n[q]) x[q][u] = seg[q][j];
         }
 #pragma unroll
       for (int q = 0; q < 2; ++q)
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < kDeep; ++u) {
           const uint32_t j = j0 + u * 64 + lane;
-          if (j < c[q]) {
-            lk[o[q] + j] = kk[q][u];
-            li[o[q] + j] = ii[q][u];
+          if (j < n[q]) {
+            lk[o[q] + j] = x[q][u].x;
+            li[o[q] + j] = x[q][u].y;
           }
         }
     }
@@ -410,47 +415,120 @@ __device__ __forceinline__ int finish_load(FinishShared& sh, uint32_t* lds_cand,
   return (int)sh.seg_off[n_tiles];
 }
 
-// First half: the k-th smallest key of the row and how many keys equal to it are kept.
-// n: finish_load's result.
+// The k-th smallest of the row's keys and how many keys equal to it are kept.  n: finish_load's result.
+// The k-th key is hardly outside [below, bound] (both from the sample): 2048 bins of equal width there, and the few keys
+// of the bin that holds the k-th compared with each other.  Where the k-th is before them or its bin holds more than
+// kFinListMax, and for whole rows, the radix select.
 __device__ __forceinline__ void finish_threshold(FinishShared& sh, const uint32_t* lds_cand, const SelectArgs& a, int row,
-                                                 int n, uint32_t& thr, uint32_t& k_rem) {
-  if (!sh.whole_row) {                                 // uniform
-    radix_select_block(n, (uint32_t)a.k, [&](int i) { return lds_cand[i]; }, sh.h, sh.sm, thr, k_rem);
-  } else {
+                                                 int n, uint32_t bound, uint32_t below, uint32_t& thr, uint32_t& k_rem) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (sh.whole_row) {                                  // uniform
     const float* sr = a.scores + (int64_t)row * a.T;
     radix_select_block(a.T, (uint32_t)a.k, [&](int i) { return order_key(sr[i]); }, sh.h, sh.sm, thr, k_rem);
+    return;
   }
+  const int shift = bin_shift(below, bound, kFinBinBits);
+  uint32_t lower = 0;                                   // keys before `below`: most of the k, so not by atomics on one word
+  for (int i = tid; i < n; i += kFinThreads) {
+    const uint32_t key = lds_cand[i];
+    if (key < below)
+      ++lower;
+    else
+      atomicAdd(&sh.h[clamped_bin(key, below, bound, shift)], 1u);
+  }
+  __syncthreads();
+  const uint32_t c0 = sh.h[2 * tid], c1 = sh.h[2 * tid + 1], kk = (uint32_t)a.k;
+  uint32_t excl, total;
+  block_scan<false>(sh.sm, c0 + c1, lower, excl, total, lower);
+  excl += lower;
+  if (tid == 0 && lower >= kk) {                        // the k-th is before `below`
+    sh.pick[1] = kk;
+    sh.pick[2] = kFinListMax + 1u;
+  }
+  if (excl < kk && kk <= excl + c0) {                   // one bin of the workgroup (n >= k)
+    sh.pick[0] = 2u * tid;
+    sh.pick[1] = kk - excl;
+    sh.pick[2] = c0;
+  } else if (excl + c0 < kk && kk <= excl + c0 + c1) {
+    sh.pick[0] = 2u * tid + 1u;
+    sh.pick[1] = kk - excl - c0;
+    sh.pick[2] = c1;
+  }
+  __syncthreads();
+  const uint32_t d = sh.pick[0], c = sh.pick[2];
+  k_rem = sh.pick[1];
+  if (c > kFinListMax) {                                // uniform
+    radix_select_block(n, kk, [&](int i) { return lds_cand[i]; }, sh.h, sh.sm, thr, k_rem);
+    return;
+  }
+  for (int i = tid; i < n; i += kFinThreads) {
+    const uint32_t key = lds_cand[i];
+    if (key >= below && clamped_bin(key, below, bound, shift) == d) sh.list[atomicAdd(&sh.pick[3], 1u)] = key;   // c of them
+  }
+  __syncthreads();
+  // every wavefront for itself (no further barrier)
+  const uint32_t key = sh.list[min((uint32_t)lane, c - 1u)];
+  uint32_t less = 0, same = 0;
+  for (uint32_t j = 0; j < c; ++j) {
+    const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)key, (int)j);
+    less += x < key ? 1u : 0u;
+    same += x == key ? 1u : 0u;
+  }
+  const uint64_t hit = __ballot((uint32_t)lane < c && less < k_rem && k_rem <= less + same);
+  const int who = hit != 0ull ? __ffsll((unsigned long long)hit) - 1 : 0;    // never zero
+  thr = (uint32_t)__builtin_amdgcn_readlane((int)key, who);
+  k_rem -= (uint32_t)__builtin_amdgcn_readlane((int)less, who);
 }
 
-// Second half: the kept tokens in ascending order, then the window tokens.
+// The kept tokens in ascending order, then the window tokens.
 __device__ __forceinline__ void finish_write(FinishShared& sh, const uint32_t* lds_cand, const SelectArgs& a, int row,
                                              int n, uint32_t thr, uint32_t k_rem) {
   const int tid = threadIdx.x, T = a.T, k = a.k, W = a.W;
   int32_t* out = a.idx_out + (int64_t)row * (k + W);
-  if (!sh.whole_row) {                                 // uniform
-    const uint32_t* lk = lds_cand;
-    const uint32_t* li = lds_cand + kSelCandCap;
-    ordered_write(n, thr, k_rem, k, [&](int i) { return lk[i]; }, [&](int i) { return li[i]; }, sh.sm, out);
-  } else {
+  const uint32_t* li = lds_cand + a.cand_cap;
+  if (sh.whole_row) {                                  // uniform
     const float* sr = a.scores + (int64_t)row * T;
-    ordered_write(T, thr, k_rem, k, [&](int i) { return order_key(sr[i]); }, [&](int i) { return (uint32_t)i; }, sh.sm, out);
+    ordered_write<8>(T, thr, k_rem, k, [&](int i0, uint32_t* key) {
+      for (int j = 0; j < 8; ++j) key[j] = order_key(sr[min(i0 + j, T - 1)]);
+    }, [&](int i) { return (uint32_t)i; }, sh.sm, out);
+  } else {
+    // four keys per LDS read: cand_cap is a multiple of eight
+    const uint4* lk = reinterpret_cast<const uint4*>(lds_cand);
+    auto four = [&](int i0, uint32_t* key) {
+      const uint4 x = lk[i0 / 4];
+      key[0] = x.x;
+      key[1] = x.y;
+      key[2] = x.z;
+      key[3] = x.w;
+    };
+    auto tok = [&](int i) { return li[i]; };
+    if (n <= 4 * kFinThreads)
+      ordered_write<4>(n, thr, k_rem, k, four, tok, sh.sm, out);
+    else
+      ordered_write<8>(n, thr, k_rem, k, [&](int i0, uint32_t* key) {
+        four(i0, key);
+        four(i0 + 4, key + 4);
+      }, tok, sh.sm, out);
   }
   // window tokens T .. T+W-1 (Alg. 1 step 10: Concat with I_w)
   for (int i = tid; i < W; i += kFinThreads) out[k + i] = T + i;
 }
 
-// Step 3 in one kernel: one workgroup per row.
-__device__ __forceinline__ void select_finish_body(FinishShared& sh, uint32_t* lds_cand, const SelectArgs& a, int row) {
+// Step 3: one workgroup per row.
+__device__ __forceinline__ void select_finish_body(void* lds, const SelectArgs& a, int row) {
+  FinishShared& sh = *static_cast<FinishShared*>(lds);
+  uint32_t* lds_cand = finish_cand(lds);
+  const uint32_t bound = a.bound[2 * row], below = a.bound[2 * row + 1];
   const int n = finish_load(sh, lds_cand, a, row);
   uint32_t thr, k_rem;
-  finish_threshold(sh, lds_cand, a, row, n, thr, k_rem);
+  finish_threshold(sh, lds_cand, a, row, n, bound, below, thr, k_rem);
   finish_write(sh, lds_cand, a, row, n, thr, k_rem);
 }
 
 // All three steps for a row of at most kShortT scores, one workgroup per row: every token is a candidate.
 // Latency-bound like the finish step; it replaces three launches (64 rows of 8000 scores: 25.0 -> 11 us).
 struct ShortSelectShared {
-  uint32_t keys[kShortT];
+  __align__(16) uint32_t keys[kShortT];
   uint32_t h[kHistWords];
   uint32_t sm[2 * kFinWaves + 2];
 };
@@ -469,15 +547,14 @@ __device__ __forceinline__ void select_short_body(ShortSelectShared& sh, const S
   uint32_t thr, k_rem;
   radix_select_block(T, (uint32_t)a.k, [&](int i) { return sh.keys[i]; }, sh.h, sh.sm, thr, k_rem);
   int32_t* out = a.idx_out + (int64_t)row * (a.k + a.W);
-  ordered_write(T, thr, k_rem, a.k, [&](int i) { return sh.keys[i]; }, [&](int i) { return (uint32_t)i; }, sh.sm, out);
+  ordered_write<4>(T, thr, k_rem, a.k, [&](int i0, uint32_t* key) {
+    for (int j = 0; j < 4; ++j) key[j] = sh.keys[i0 + j];   // i0 + 3 < kShortT
+  }, [&](int i) { return (uint32_t)i; }, sh.sm, out);
   for (int i = tid; i < a.W; i += kFinThreads) out[a.k + i] = T + i;   // window tokens (Alg. 1 step 10)
 }
 
 // Arguments of a select over `rows` rows of scores (buffers from the workspace; rows <= ws.sel_rows).
 SelectArgs select_args(const Workspace& ws, const float* scores, int T, int k, int W, int32_t* idx_out,
                        bool have_sample);
-
-// Launches step 3 for `rows` rows, to be timed as kernel `kernel_id`.
-hipError_t launch_finish(const Workspace& ws, int kernel_id, const SelectArgs& a, int rows, hipStream_t st);
 
 }  // namespace asl

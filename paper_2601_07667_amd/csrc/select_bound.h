@@ -21,7 +21,8 @@ constexpr int kSelMaxSample = 8192;    // sampled keys per row
 inline int sel_sample_size(int T) {
   int n = T / 32;
   n = n < 1024 ? 1024 : n;
-  return n > kSelMaxSample ? kSelMaxSample : n;
+  const int most = T <= 262144 ? kSelMaxSample / 2 : kSelMaxSample;   // the whole is for the ranking's 1024 buckets
+  return n > most ? most : n;
 }
 inline int sel_sample_stride(int T) { return T / sel_sample_size(T); }
 // Rank m of the sample key taken as the bound: f = n_s / T of the row is sampled, the top-k members
@@ -33,6 +34,12 @@ inline int sel_sample_rank(int T, int k, int n_s, int run) {
   const float kf = (float)k * (float)n_s / (float)T;
   const int m = (int)(kf + 5.0f * sqrtf((float)run * kf) + 4.0f);
   return m;                                            // >= n_s means: no usable bound, admit everything
+}
+// Rank of a sample key that is behind the row's k-th with probability < 1e-6, by the same estimate; at least 1.
+inline int sel_sample_rank_low(int T, int k, int n_s, int run) {
+  const float kf = (float)k * (float)n_s / (float)T;
+  const int m = (int)(kf - 5.0f * sqrtf((float)run * kf) - 4.0f);
+  return m < 1 ? 1 : m;
 }
 // How many sample keys beyond the m-th the bound may let pass: m / 8, and no more than the candidate buffers
 // hold.  The m-th sample key admits m T / n_s tokens with standard deviation T / n_s sqrt(c m), c as above; a row's
@@ -50,6 +57,13 @@ inline int sel_bound_slack(int T, int m, int n_s, int run) {
   const float row = (row_room - 3.0f * row_dev) / per_key, tile = (tile_room - 4.0f * tile_dev) / per_key_tile;
   const float cap = row < tile ? row : tile;
   return cap <= 0.f ? 0 : ((float)s < cap ? s : (int)cap);
+}
+// Candidates of a row that the finishing workgroup makes room for: half of kSelCandCap where the bound admits more than
+// that once in 10^6 rows at most, since two workgroups then share a compute unit (a row with more is selected from
+// global memory).
+inline int sel_cand_cap(int T, int m, int slack, int n_s, int run) {
+  const float per_key = (float)T / (float)n_s;
+  return (float)(m + slack) * per_key + 5.0f * per_key * sqrtf((float)run * (float)m) <= (float)(kSelCandCap / 2) ? kSelCandCap / 2 : kSelCandCap;
 }
 // Without a prepared sample the bound kernel reads runs of kSelSampleRun neighbouring keys, one run
 // per kSelSampleRun sample strides: the same number of keys from a quarter of the cache lines.

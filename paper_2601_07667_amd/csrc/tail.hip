@@ -1,4 +1,4 @@
-// The part of a layer step that follows the scoring, in four launches on one stream (two for short contexts).
+// The part of a layer step that follows the scoring, in three launches on one stream (two for short contexts).
 //
 // After the scores are pooled two independent chains remain: the ranking (partition, buckets: Alg. 1 step 11) with the
 // statistic (Alg. 2 steps 4-10), and the top-k + KV compaction (bound, filter, finish, gather: Alg. 1
@@ -6,6 +6,8 @@
 // stream) or pay two cross-queue synchronisations per layer (two streams).  Here the stages share launches:
 // the two jobs of a launch are independent, and every stage depends only on earlier launches, which the launch
 // boundary orders.  The bodies are the same device functions the single-call kernels use.
+#include <type_traits>
+
 #include "gather_body.h"
 #include "rank_body.h"
 #include "rankvar_body.h"
@@ -15,10 +17,11 @@ namespace asl {
 
 static_assert(kSortThreads == kFinThreads, "both jobs of a launch use the same workgroup size");
 constexpr int kTailThreads = kSortThreads;
+constexpr int kTailUnits = 256;                       // compute units of an MI355X
 
-union PartGuessShared {
+union PartFilterShared {
   PartShared part;
-  GuessShared guess;
+  FilterShared<true> filter;
 };
 
 // Short contexts (T <= kShortT): ranking by counting and the top-k of every row in one launch instead of the
@@ -36,36 +39,36 @@ __global__ void __launch_bounds__(kTailThreads) tail_short_kernel(const float* s
     rank_count_body(sh.count, s_all, se.T, rank_row, b - rows);
 }
 
-// launch 0: the ranking's partition | top-k bound (one workgroup per score row)
-template <int R>
-__global__ void __launch_bounds__(kTailThreads) tail0_kernel(RankArgs ra, SelectArgs se) {
-  __shared__ PartGuessShared sh;
+// launch 0: the ranking's partition | top-k bound and filter (TILES tiles of a score row per workgroup; VEC: 16-byte
+// loads, for rows that start on 16-byte boundaries)
+template <int R, bool VEC, int TILES>
+__global__ void __launch_bounds__(kTailThreads, 8) tail0_kernel(RankArgs ra, SelectArgs se) {
+  __shared__ PartFilterShared sh;
   const int b = (int)blockIdx.x;
-  if (b < ra.n_tiles)
+  if (b < ra.n_tiles) {
     partition_body<R>(sh.part, ra, b);
-  else
-    select_guess_body(sh.guess, se, b - ra.n_tiles);
-}
-
-// launch 1: the ranking's buckets | top-k filter (one workgroup per tile of a score row; VEC: 16-byte loads,
-// for rows that start on 16-byte boundaries); dynamic LDS sizeof(BucketShared)
-template <bool VEC>
-__global__ void __launch_bounds__(kTailThreads, 8) tail1_kernel(RankArgs ra, SelectArgs se) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_dyn[];
-  const int b = (int)blockIdx.x;
-  if (b < ra.n_buckets) {
-    bucket_body(*reinterpret_cast<BucketShared*>(lds_dyn), ra, b);
   } else {
-    const int j = b - ra.n_buckets;
-    select_filter_body<kTailThreads, VEC>(*reinterpret_cast<FilterShared*>(lds_dyn), se, j / se.n_tiles, j % se.n_tiles);
+    const int j = b - ra.n_tiles, per_row = (se.n_tiles + TILES - 1) / TILES;
+    select_filter_body<kTailThreads, VEC, true, TILES>(sh.filter, se, j / per_row, (j % per_row) * TILES);
   }
 }
 
-// launch 3: rank-variance statistic over the ring that now holds this layer's ranks (its first
+// launch 1: top-k finish (one workgroup per score row, the longer ones, first) | the ranking's buckets;
+// dynamic LDS for the larger of the two
+__global__ void __launch_bounds__(kTailThreads, 8) tail1_kernel(RankArgs ra, SelectArgs se, int rows) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_dyn[];
+  const int b = (int)blockIdx.x;
+  if (b < rows)
+    select_finish_body(lds_dyn, se, b);
+  else
+    bucket_body(*reinterpret_cast<BucketShared*>(lds_dyn), ra, b - rows);
+}
+
+// launch 2: rank-variance statistic over the ring that now holds this layer's ranks (its first
 // n_stat workgroups; workgroup 0 waits for the others) | KV compaction with the per-head indices of
-// launch 2 (gx blocks per (head, tensor) slab)
+// launch 1 (gx blocks per (head, tensor) slab)
 template <bool POW2>
-__global__ void __launch_bounds__(kVarThreads) tail3_kernel(RankvarArgs ra, int n_stat, GatherArgs ga, int gx, int Hk) {
+__global__ void __launch_bounds__(kVarThreads) tail2_kernel(RankvarArgs ra, int n_stat, GatherArgs ga, int gx, int Hk) {
   __shared__ RankvarShared sh;
   const int b = (int)blockIdx.x;
   if (b < n_stat) {
@@ -81,28 +84,37 @@ __global__ void __launch_bounds__(kVarThreads) tail3_kernel(RankvarArgs ra, int 
   }
 }
 
-// Launches 0 to 2 (launch 2: the top-k's finish alone).
+// Launches 0 and 1.
+template <bool VEC>
 static hipError_t launch_rank_select(const Workspace& ws, const SelectArgs& se, const RankArgs& ra, int rows, hipStream_t st) {
-  static const hipError_t attr = [] {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(tail1_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             (int)sizeof(BucketShared));
-    return e != hipSuccess ? e
-                           : hipFuncSetAttribute(reinterpret_cast<const void*>(tail1_kernel<false>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(BucketShared));
-  }();
+  constexpr size_t kMost = finish_lds_bytes(kSelCandCap) > sizeof(BucketShared) ? finish_lds_bytes(kSelCandCap) : sizeof(BucketShared);
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(tail1_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                     (int)kMost);
   if (attr != hipSuccess) return attr;
-  const dim3 block(kTailThreads), grid0(ra.n_tiles + rows), grid1(ra.n_buckets + rows * se.n_tiles);
+  const dim3 block(kTailThreads), grid1(rows + ra.n_buckets);
+  // Tiles per filtering workgroup: as few as leave launch 0 one workgroup per compute unit; two on a unit slow down each
+  // other's barriers and scans (launch 0 of the 8B shape: 128K 12.0 us with one tile each and 352 workgroups, 10.0 with
+  // 208; 256K 18.6 us with 704, 15.0 with 208).
+  auto grid0 = [&](int tiles) { return ra.n_tiles + rows * ((se.n_tiles + tiles - 1) / tiles); };
+  const int tiles = grid0(1) <= kTailUnits ? 1 : grid0(2) <= kTailUnits ? 2 : kFilterMostTiles;
+  auto launch0 = [&](auto r) {
+    constexpr int R = decltype(r)::value;
+    if (tiles == 1)
+      ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<R, VEC, 1>), dim3(grid0(1)), block, 0, st, ra, se);
+    else if (tiles == 2)
+      ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<R, VEC, 2>), dim3(grid0(2)), block, 0, st, ra, se);
+    else
+      ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<R, VEC, 4>), dim3(grid0(4)), block, 0, st, ra, se);
+  };
   if (ra.tile_log == 11)
-    ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<2>), grid0, block, 0, st, ra, se);
+    launch0(std::integral_constant<int, 2>());
   else if (ra.tile_log == 12)
-    ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<4>), grid0, block, 0, st, ra, se);
+    launch0(std::integral_constant<int, 4>());
   else
-    ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<8>), grid0, block, 0, st, ra, se);
-  if (se.T % 4 == 0 && reinterpret_cast<uintptr_t>(se.scores) % 16 == 0)
-    ASL_LAUNCH(ws.prof, kKernTail, st, (tail1_kernel<true>), grid1, block, sizeof(BucketShared), st, ra, se);
-  else
-    ASL_LAUNCH(ws.prof, kKernTail, st, (tail1_kernel<false>), grid1, block, sizeof(BucketShared), st, ra, se);
-  return launch_finish(ws, kKernTail, se, rows, st);
+    launch0(std::integral_constant<int, 8>());
+  const size_t fin = finish_lds_bytes(se.cand_cap), lds = fin > sizeof(BucketShared) ? fin : sizeof(BucketShared);
+  ASL_LAUNCH(ws.prof, kKernTail, st, tail1_kernel, grid1, block, lds, st, ra, se, rows);
+  return hipGetLastError();
 }
 
 // The last launch: statistic (or the note that it is not evaluated yet) beside the compaction, which may be
@@ -117,11 +129,11 @@ static hipError_t launch_stat_gather(const Workspace& ws, const GatherArgs* gath
     const int n_stat = stat.skip != 0 ? 1 : rankvar_blocks(stat.T);
     const dim3 grid4(n_stat + gx * Hk * ga.n_tensors);
     if (gx == 0)
-      ASL_LAUNCH(ws.prof, kKernRankvar, st, (tail3_kernel<true>), dim3(n_stat), dim3(kVarThreads), 0, st, stat, n_stat, ga, 1, Hk);
+      ASL_LAUNCH(ws.prof, kKernRankvar, st, (tail2_kernel<true>), dim3(n_stat), dim3(kVarThreads), 0, st, stat, n_stat, ga, 1, Hk);
     else if (pow2)
-      ASL_LAUNCH(ws.prof, kKernTail, st, (tail3_kernel<true>), grid4, dim3(kVarThreads), 0, st, stat, n_stat, ga, gx, Hk);
+      ASL_LAUNCH(ws.prof, kKernTail, st, (tail2_kernel<true>), grid4, dim3(kVarThreads), 0, st, stat, n_stat, ga, gx, Hk);
     else
-      ASL_LAUNCH(ws.prof, kKernTail, st, (tail3_kernel<false>), grid4, dim3(kVarThreads), 0, st, stat, n_stat, ga, gx, Hk);
+      ASL_LAUNCH(ws.prof, kKernTail, st, (tail2_kernel<false>), grid4, dim3(kVarThreads), 0, st, stat, n_stat, ga, gx, Hk);
     return hipGetLastError();
   }
   if (stat.skip != 0) return launch_stat_skip(ws.prof, stat.out, stat.state, stat.layer_idx, stat.l_obs, stat.push, st);
@@ -146,7 +158,9 @@ hipError_t launch_tail(const Workspace& ws, const float* scores, int rows, int T
     e = hipGetLastError();
   } else {
     const uint32_t* sample = have_sample ? ws.sel_sample + (int64_t)(rows - 1) * kSelMaxSample : nullptr;
-    e = launch_rank_select(ws, se, rank_args(ws, s_all, T, sample, rank_row), rows, st);
+    const RankArgs ra = rank_args(ws, s_all, T, sample, rank_row);
+    e = T % 4 == 0 && reinterpret_cast<uintptr_t>(scores) % 16 == 0 ? launch_rank_select<true>(ws, se, ra, rows, st)
+                                                                    : launch_rank_select<false>(ws, se, ra, rows, st);
   }
   return e != hipSuccess ? e : launch_stat_gather(ws, gather, Hk, stat, st);
 }

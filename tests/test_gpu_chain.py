@@ -436,6 +436,17 @@ def test_layer_step_at_bench_size_and_beyond(gpu_device):
                      layer_idx=3)
 
 
+@pytest.mark.parametrize("Hk,N,budget", [(16, 75017, 2048),     # two filter tiles per workgroup, the last one alone
+                                         (32, 60017, 777),      # four, the last workgroup of a row with three
+                                         (16, 75020, 8192),     # rows on 16-byte boundaries, large budget
+                                         (2, 131072 + 17, 64),  # the first size with ranking tiles of 4096
+                                         (1, 12289 + 16, 8192)])
+def test_layer_step_geometries(gpu_device, Hk, N, budget):
+    """Sizes at which the shared launches change how they are cut: against the single calls, bit for bit."""
+    sh = synth.Shape(Hq=Hk, Hk=Hk, d=64, N=N, W=16, S=7, budget=budget)
+    _layer_step_case(gpu_device, synth.iid_layer(sh, N + Hk, name=f"geometry-{Hk}-{N}"))
+
+
 def test_layer_step_is_reproducible(gpu_device):
     """200 repetitions of asl_layer_step on the C3 layer, and of the single ranking and top-k calls on its
     scores: every output has the same bits every time (the workgroups of the ranking and statistic
