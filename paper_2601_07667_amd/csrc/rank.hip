@@ -9,7 +9,7 @@
 //                their ranks: what comes before the bucket is the sum of the tiles' notes.
 // The sample decides only how even the buckets are; a bucket that outgrows LDS is ordered from memory.
 // (Four passes of an LSD radix sort with the tiles' counts exchanged inside each launch took 33.5 us at 131040 tokens
-// and 101 us at a million; this takes 16 and 37.)
+// and 101 us at a million; this takes 16 and 31.)
 //
 // Short vectors (kShortT) are ranked by counting instead, in one launch (rank_count_body), unless the ranks
 // overwrite the scores.
@@ -50,9 +50,12 @@ RankArgs rank_plan(int T) {
   a.n_tiles = (T + (1 << a.tile_log) - 1) >> a.tile_log;
   a.tile_step = 1;
   while (2 * a.tile_step < a.n_tiles) a.tile_step *= 2;
-  // ~512 tokens a bucket, more where that keeps them to one workgroup per compute unit (240, beside the top-k's) ...
+  // ~512 tokens a bucket, more where that keeps them to one round of workgroups: one per compute unit (240, beside the
+  // top-k's) up to ~1100 tokens a bucket, two up to 2048, which is the most that four pairs a thread take without many
+  // buckets going beyond.  Ranking + statistic, us, with 512 buckets and with one per 1024 tokens: 400 K tokens 28.8, 29.3;
+  // 700 K 36.0, 39.7; 1 M 43.5, 57.7; 2 M 135, 72.7 (there: 1024).
   a.n_buckets = (T + 511) / 512;
-  if (a.n_buckets > 240) a.n_buckets = T <= 264000 ? 240 : (T + 1023) / 1024;
+  if (a.n_buckets > 240) a.n_buckets = T <= 264000 ? 240 : T <= 512 * 2048 ? 512 : (T + 2047) / 2048;
   if (a.n_buckets > kRankMaxBuckets) a.n_buckets = kRankMaxBuckets;
   a.n_s = sel_sample_size(T);
   if (a.n_s > T) a.n_s = T;

@@ -533,8 +533,9 @@ __device__ __forceinline__ void bucket_body(BucketShared& sh, const RankArgs& a,
       }
       block_min_max(sh.red, lo, hi);
     }
-    if (n <= 2u * kSortThreads ? bucket_by_bins<2>(sh, (int)n, lo, hi, base, a.T, a.rank_out)
-                               : bucket_by_bins<kBucketPer>(sh, (int)n, lo, hi, base, a.T, a.rank_out))
+    if (n <= 2u * kSortThreads   ? bucket_by_bins<2>(sh, (int)n, lo, hi, base, a.T, a.rank_out)
+        : n <= 4u * kSortThreads ? bucket_by_bins<4>(sh, (int)n, lo, hi, base, a.T, a.rank_out)
+                                 : bucket_by_bins<kBucketPer>(sh, (int)n, lo, hi, base, a.T, a.rank_out))
       return;
   }
   if (tid == 0) {
