@@ -11,8 +11,7 @@
 // (Four passes of an LSD radix sort with the tiles' counts exchanged inside each launch took 33.5 us at 131040 tokens
 // and 101 us at a million; this takes 16 and 31.)
 //
-// Short vectors (kShortT) are ranked by counting instead, in one launch (rank_count_body), unless the ranks
-// overwrite the scores.
+// Short vectors (kShortT) are ranked in one launch instead (rank_short_body), unless the ranks overwrite the scores.
 #include <cstdio>
 #include <mutex>
 
@@ -38,9 +37,10 @@ __global__ void __launch_bounds__(kSortThreads, 8) rank_bucket_kernel(RankArgs a
   bucket_body(*reinterpret_cast<BucketShared*>(lds_dyn), a, (int)blockIdx.x);
 }
 
-__global__ void __launch_bounds__(kSortThreads) rank_count_kernel(const float* __restrict__ s, int T, int32_t* __restrict__ rank_out) {
-  __shared__ CountShared sh;
-  rank_count_body(sh, s, T, rank_out, (int)blockIdx.x);
+// dynamic LDS: sizeof(ShortRankShared)
+__global__ void __launch_bounds__(kSortThreads) rank_short_kernel(const float* __restrict__ s, int T, int32_t* __restrict__ rank_out) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_dyn[];
+  rank_short_body(*reinterpret_cast<ShortRankShared*>(lds_dyn), s, T, rank_out, (int)blockIdx.x);
 }
 
 RankArgs rank_plan(int T) {
@@ -79,12 +79,16 @@ RankArgs rank_args(const Workspace& ws, const float* s, int T, const uint32_t* s
 constexpr int64_t kSampleDirect = 64 * 4096;
 
 hipError_t launch_rank(const Workspace& ws, const float* s, int T, int32_t* rank_out, hipStream_t st) {
-  // Counting workgroups read all scores while others already write ranks; the partition reads them in its first launch
+  // The workgroups of the one launch read all scores while others already write ranks; the partition reads them in its first launch
   // and writes ranks in its last, so it takes the calls that rank a vector in place.
   const uintptr_t s0 = reinterpret_cast<uintptr_t>(s), r0 = reinterpret_cast<uintptr_t>(rank_out), bytes = (uintptr_t)T * 4;
   const bool in_place = s0 < r0 + bytes && r0 < s0 + bytes;
   if (T <= kShortT && !in_place) {
-    ASL_LAUNCH(ws.prof, kKernSortScatter, st, rank_count_kernel, dim3(rank_count_blocks(T)), dim3(kSortThreads), 0, st, s, T, rank_out);
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(rank_short_kernel),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(ShortRankShared));
+    if (attr != hipSuccess) return attr;
+    ASL_LAUNCH(ws.prof, kKernSortScatter, st, rank_short_kernel, dim3(short_rank_blocks(T)), dim3(kSortThreads), sizeof(ShortRankShared), st,
+               s, T, rank_out);
     return hipGetLastError();
   }
   if (T > kRankMaxT) return hipErrorInvalidConfiguration;

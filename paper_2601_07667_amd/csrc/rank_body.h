@@ -8,45 +8,6 @@ namespace asl {
 constexpr int kSortThreads = kRowThreads;
 constexpr int kSortWaves = kSortThreads / 64;
 
-// Ranks of kCountTokens tokens of a short vector (T <= kShortT) by counting: a workgroup reads all keys into LDS,
-// 32 lanes share a token and compare its key with every other one: rank = keys before it in the order
-// (key ascending, index ascending).  T * T comparisons, two vector instructions each, spread over T / 32
-// workgroups: 5 us at 8000 tokens, one launch and one barrier.
-constexpr int kCountTokens = kSortThreads / 32;
-struct CountShared {
-  uint32_t keys[kShortT];
-};
-__device__ __forceinline__ void rank_count_body(CountShared& sh, const float* __restrict__ s, int T, int32_t* __restrict__ rank_out,
-                                                int block) {
-  const int tid = threadIdx.x, lane = tid & 31;
-  constexpr int kPer = kShortT / kSortThreads;
-  static_assert(kShortT % kSortThreads == 0 && kCountTokens == 32, "the keys of a workgroup's tokens are one group of 32");
-  float v[kPer];
-#pragma unroll
-  for (int u = 0; u < kPer; ++u) v[u] = s[min(tid + u * kSortThreads, T - 1)];        // one round trip
-  // positions past the end hold the largest key, which precedes nothing
-#pragma unroll
-  for (int u = 0; u < kPer; ++u) sh.keys[tid + u * kSortThreads] = tid + u * kSortThreads < T ? order_key(v[u]) : 0xffffffffu;
-  __syncthreads();
-  const int i0 = block * kCountTokens, i = i0 + (tid >> 5);
-  const uint32_t ki = sh.keys[i];                       // i < kShortT: see the grid
-  const int n_groups = (T + 31) / 32;                   // groups of 32 keys, one per lane
-  uint32_t before = 0;
-#pragma unroll 8
-  for (int g = 0; g < block; ++g) before += (sh.keys[g * 32 + lane] <= ki) ? 1u : 0u;              // lower indices: ties precede
-#pragma unroll 8
-  for (int g = block + 1; g < n_groups; ++g) before += (sh.keys[g * 32 + lane] < ki) ? 1u : 0u;    // higher indices: ties follow
-  {
-    const uint32_t kj = sh.keys[i0 + lane];
-    before += (kj < ki || (kj == ki && i0 + lane < i)) ? 1u : 0u;
-  }
-#pragma unroll
-  for (int d = 16; d > 0; d >>= 1) before += (uint32_t)__shfl_xor((int)before, d);
-  if (lane == 0 && i < T) rank_out[i] = (int32_t)before;
-}
-inline int rank_count_blocks(int T) { return (T + kCountTokens - 1) / kCountTokens; }
-
-// ---------------------------------------------------------------------------------------------
 struct DigitShared {
   uint16_t cnt[kSortWaves][256];                        // pairs per wavefront and digit
   uint16_t start[kSortWaves][256];                      // their first places
@@ -121,6 +82,155 @@ __device__ __forceinline__ void sort_by_digits(uint32_t* key, Tok* tok, DigitSha
       }
     }
     __syncthreads();
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+constexpr uint32_t kBinMax = 64;                        // longest bin that is ordered by comparing its keys
+
+// Short vectors (T <= kShortT), in one launch and with nothing exchanged between workgroups: every workgroup reads all
+// keys.  Two ways:
+//  - by counting: a token's 32 lanes compare its key with every other one, rank = keys before it in the order (key
+//    ascending, index ascending), 32 tokens a workgroup.  T^2 comparisons of two vector instructions.
+//  - by bins: the workgroup counts all keys in 4096 bins of equal width between the smallest and the largest; of those bins
+//    that begin at its 64 places of the order it groups the keys in LDS, and a thread per key compares it with the others of
+//    its bin.  Bound by latency (eight barriers).  Where some bin is longer than kBinMax (repeated or outlying scores) the
+//    workgroup ranks 64 tokens by counting instead.
+// Counting takes the sizes up to kCountT (one call, us, counting and bins: 2000 tokens 4.1, 5.9; 8000 8.4, 6.9;
+// 12000 17.0, 7.6; 12000 of which a third are equal 17.0, 23.1).
+constexpr int kCountTokens = kSortThreads / 32;
+constexpr int kCountT = 5120;
+constexpr int kShortPlaces = 2 * kCountTokens;
+constexpr int kShortPer = kShortT / kSortThreads;
+static_assert(kShortT % kSortThreads == 0 && kCountTokens == 32, "the keys of a workgroup's tokens are one group of 32");
+struct ShortRankShared {
+  uint32_t keys[kShortT];                               // by counting
+  union {
+    uint4 bin4[kSampleBins / 4 + 1];                    // four bins a thread: their counts, then their first places and the last one's end
+    uint32_t bin[kSampleBins + 4];
+  };
+  uint32_t key[kShortPlaces + kBinMax];                 // by bins: this workgroup's keys ...
+  uint32_t tok[kShortPlaces + kBinMax];                 // ... and tokens
+  uint32_t red[2 * kSortWaves];
+  uint32_t from, to;                                    // the places whose bins begin at this workgroup's
+};
+inline int short_rank_blocks(int T) { return T <= kCountT ? (T + kCountTokens - 1) / kCountTokens : (T + kShortPlaces - 1) / kShortPlaces; }
+
+// Ranks of tokens 32 group .. 32 group + 31 by counting.  keys: all T of them; up to the next multiple of 32 the largest
+// key, which precedes nothing.
+__device__ __forceinline__ void count_ranks(const uint32_t* keys, int T, int group, int32_t* __restrict__ rank_out) {
+  const int tid = threadIdx.x, lane = tid & 31, n_groups = (T + 31) / 32;
+  const int i0 = group * kCountTokens, i = i0 + (tid >> 5);
+  const uint32_t ki = keys[i];                          // i < kShortT
+  uint32_t before = 0;
+#pragma unroll 8
+  for (int g = 0; g < group; ++g) before += (keys[g * 32 + lane] <= ki) ? 1u : 0u;              // lower indices: ties precede
+#pragma unroll 8
+  for (int g = group + 1; g < n_groups; ++g) before += (keys[g * 32 + lane] < ki) ? 1u : 0u;    // higher indices: ties follow
+  {
+    const uint32_t kj = keys[i0 + lane];
+    before += (kj < ki || (kj == ki && i0 + lane < i)) ? 1u : 0u;
+  }
+#pragma unroll
+  for (int d = 16; d > 0; d >>= 1) before += (uint32_t)__shfl_xor((int)before, d);
+  if (lane == 0 && i < T) rank_out[i] = (int32_t)before;
+}
+
+__device__ __forceinline__ void rank_short_body(ShortRankShared& sh, const float* __restrict__ s, int T, int32_t* __restrict__ rank_out,
+                                                int b) {
+  const int tid = threadIdx.x;
+  uint32_t key[kShortPer], slot[kShortPer];
+  {
+    float f[kShortPer];
+#pragma unroll
+    for (int u = 0; u < kShortPer; ++u) f[u] = u * kSortThreads < T ? s[min(tid + u * kSortThreads, T - 1)] : 0.f;   // one round trip
+#pragma unroll
+    for (int u = 0; u < kShortPer; ++u) key[u] = order_key(f[u]);
+  }
+  auto all_keys = [&] {
+#pragma unroll
+    for (int u = 0; u < kShortPer; ++u)
+      if (u * kSortThreads < T) sh.keys[tid + u * kSortThreads] = tid + u * kSortThreads < T ? key[u] : 0xffffffffu;
+    __syncthreads();
+  };
+  if (T <= kCountT) {                                   // uniform
+    all_keys();
+    count_ranks(sh.keys, T, b, rank_out);
+    return;
+  }
+  const uint32_t p0 = (uint32_t)(b * kShortPlaces), p1 = min(p0 + (uint32_t)kShortPlaces, (uint32_t)T);
+  sh.bin4[tid] = make_uint4(0u, 0u, 0u, 0u);
+  if (tid == 0) {
+    sh.from = p0;
+    sh.to = p1;
+  }
+  uint32_t lo = key[0], hi = key[0];                    // positions past the end repeat the last key
+#pragma unroll
+  for (int u = 1; u < kShortPer; ++u)
+    if (u * kSortThreads < T) {                         // uniform
+      lo = min(lo, key[u]);
+      hi = max(hi, key[u]);
+    }
+  block_min_max(sh.red, lo, hi);
+  if (lo == hi) {                                       // uniform: all scores are equal
+    if (tid < kShortPlaces && p0 + tid < p1) rank_out[p0 + tid] = (int32_t)(p0 + tid);
+    return;
+  }
+  const int shift = bin_shift(lo, hi, kSampleBinBits);
+  uint32_t* bin = sh.bin;
+#pragma unroll
+  for (int u = 0; u < kShortPer; ++u) {
+    slot[u] = 0;
+    if (tid + u * kSortThreads < T) slot[u] = atomicAdd(&bin[(key[u] - lo) >> shift], 1u);
+  }
+  __syncthreads();
+  const uint4 c = sh.bin4[tid];
+  uint32_t first, total, most;
+  block_scan<true>(sh.red, c.x + c.y + c.z + c.w, max(max(c.x, c.y), max(c.z, c.w)), first, total, most);
+  if (most > kBinMax) {                                 // uniform
+    all_keys();
+    count_ranks(sh.keys, T, 2 * b, rank_out);
+    if ((2 * b + 1) * kCountTokens < T) count_ranks(sh.keys, T, 2 * b + 1, rank_out);
+    return;
+  }
+  const uint32_t cs[4] = {c.x, c.y, c.z, c.w};
+  uint32_t at4[5] = {first, 0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    at4[q + 1] = at4[q] + cs[q];
+    if (at4[q] < p0 && p0 < at4[q + 1]) sh.from = at4[q + 1];      // a bin of the workgroup before reaches into these places
+    if (at4[q] < p1 && p1 < at4[q + 1]) sh.to = at4[q + 1];
+  }
+  sh.bin4[tid] = make_uint4(at4[0], at4[1], at4[2], at4[3]);       // own counts only were read
+  if (tid == 0) bin[kSampleBins] = (uint32_t)T;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kShortPer; ++u) {
+    if (tid + u * kSortThreads < T) {
+      const uint32_t at = bin[(key[u] - lo) >> shift];
+      if (at >= p0 && at < p1) {
+        const uint32_t i = min(at - p0 + slot[u], (uint32_t)kShortPlaces + kBinMax - 1u);   // smaller by itself
+        sh.key[i] = key[u];
+        sh.tok[i] = (uint32_t)(tid + u * kSortThreads);
+      }
+    }
+  }
+  __syncthreads();
+  // a thread per place: few keys are this workgroup's, and a wavefront that went through its own again would run the
+  // comparison once for each (12000 tokens: 28 us the ranking and its statistic, so 18)
+  const uint32_t i = sh.from - p0 + tid;
+  if (i < sh.to - p0) {                                 // at most kShortPlaces + kBinMax places, from <= to
+    const uint32_t k = sh.key[i], t = sh.tok[i], d = (k - lo) >> shift, i0 = bin[d] - p0, i1 = bin[d + 1u] - p0;
+    uint32_t before = 0;
+    if (i1 - i0 > 1u)
+      for (uint32_t j0 = i0; j0 < i1; j0 += 4u) {
+#pragma unroll
+        for (uint32_t q = 0; q < 4u; ++q) {
+          const uint32_t j = min(j0 + q, i1 - 1u), kj = sh.key[j], tj = sh.tok[j];
+          before += (j0 + q < i1 && (kj < k || (kj == k && tj < t))) ? 1u : 0u;
+        }
+      }
+    rank_out[t] = (int32_t)(p0 + i0 + before);
   }
 }
 
@@ -314,7 +424,6 @@ constexpr int kBucketCap = 7168;                        // pairs one workgroup o
 constexpr int kBucketPer = kBucketCap / kSortThreads;
 constexpr int kBucketBins = 2 * kSortThreads;           // two per thread
 constexpr int kBucketBinBits = 11;
-constexpr uint32_t kBinMax = 64;                        // longest bin that is ordered by comparing its keys
 static_assert(kBucketBins == 1 << kBucketBinBits, "bucket bins");
 
 struct BucketShared {

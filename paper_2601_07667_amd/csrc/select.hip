@@ -46,9 +46,10 @@ __global__ void __launch_bounds__(kFinThreads, 8) select_finish_kernel(SelectArg
   select_finish_body(lds_dyn, a, (int)blockIdx.x);
 }
 
+// dynamic LDS: sizeof(ShortSelectShared)
 __global__ void __launch_bounds__(kFinThreads) select_short_kernel(SelectArgs a) {
-  __shared__ ShortSelectShared sh;
-  select_short_body(sh, a, (int)blockIdx.x);
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_dyn[];
+  select_short_body(*reinterpret_cast<ShortSelectShared*>(lds_dyn), a, (int)blockIdx.x);
 }
 
 SelectArgs select_args(const Workspace& ws, const float* scores, int T, int k, int W, int32_t* idx_out,
@@ -79,13 +80,16 @@ hipError_t launch_select(const Workspace& ws, const float* scores, int rows, int
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(select_finish_kernel),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)finish_lds_bytes(kSelCandCap));
   if (attr != hipSuccess) return attr;
+  static const hipError_t attr_short = hipFuncSetAttribute(reinterpret_cast<const void*>(select_short_kernel),
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(ShortSelectShared));
+  if (attr_short != hipSuccess) return attr_short;
   // rows beyond what the candidate buffers hold at once take further rounds of the three launches
   const int rows_per_round = ws.sel_rows;
   for (int row0 = 0; row0 < rows; row0 += rows_per_round) {
     const int nr = rows - row0 < rows_per_round ? rows - row0 : rows_per_round;
     const SelectArgs a = select_args(ws, scores + (int64_t)row0 * T, T, k, W, idx_out + (int64_t)row0 * (k + W), false);
     if (T <= kShortT) {
-      ASL_LAUNCH(ws.prof, kKernSelWrite, st, select_short_kernel, dim3(nr), dim3(kFinThreads), 0, st, a);
+      ASL_LAUNCH(ws.prof, kKernSelWrite, st, select_short_kernel, dim3(nr), dim3(kFinThreads), sizeof(ShortSelectShared), st, a);
       continue;
     }
     ASL_LAUNCH(ws.prof, kKernSelHist, st, select_guess_kernel, dim3(nr), dim3(kFinThreads), 0, st, a);

@@ -415,13 +415,30 @@ __device__ __forceinline__ int finish_load(FinishShared& sh, uint32_t* lds_cand,
   return (int)sh.seg_off[n_tiles];
 }
 
+// The k_rem-th smallest of the c <= kFinListMax listed keys, and (k_rem) how many of those equal to it are kept.  Every
+// wavefront for itself.
+__device__ __forceinline__ void pick_listed(const uint32_t* list, uint32_t c, uint32_t& thr, uint32_t& k_rem) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t key = list[min((uint32_t)lane, c - 1u)];
+  uint32_t less = 0, same = 0;
+  for (uint32_t j = 0; j < c; ++j) {
+    const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)key, (int)j);
+    less += x < key ? 1u : 0u;
+    same += x == key ? 1u : 0u;
+  }
+  const uint64_t hit = __ballot((uint32_t)lane < c && less < k_rem && k_rem <= less + same);
+  const int who = hit != 0ull ? __ffsll((unsigned long long)hit) - 1 : 0;    // never zero
+  thr = (uint32_t)__builtin_amdgcn_readlane((int)key, who);
+  k_rem -= (uint32_t)__builtin_amdgcn_readlane((int)less, who);
+}
+
 // The k-th smallest of the row's keys and how many keys equal to it are kept.  n: finish_load's result.
 // The k-th key is hardly outside [below, bound] (both from the sample): 2048 bins of equal width there, and the few keys
 // of the bin that holds the k-th compared with each other.  Where the k-th is before them or its bin holds more than
 // kFinListMax, and for whole rows, the radix select.
 __device__ __forceinline__ void finish_threshold(FinishShared& sh, const uint32_t* lds_cand, const SelectArgs& a, int row,
                                                  int n, uint32_t bound, uint32_t below, uint32_t& thr, uint32_t& k_rem) {
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x;
   if (sh.whole_row) {                                  // uniform
     const float* sr = a.scores + (int64_t)row * a.T;
     radix_select_block(a.T, (uint32_t)a.k, [&](int i) { return order_key(sr[i]); }, sh.h, sh.sm, thr, k_rem);
@@ -466,18 +483,7 @@ __device__ __forceinline__ void finish_threshold(FinishShared& sh, const uint32_
     if (key >= below && clamped_bin(key, below, bound, shift) == d) sh.list[atomicAdd(&sh.pick[3], 1u)] = key;   // c of them
   }
   __syncthreads();
-  // every wavefront for itself (no further barrier)
-  const uint32_t key = sh.list[min((uint32_t)lane, c - 1u)];
-  uint32_t less = 0, same = 0;
-  for (uint32_t j = 0; j < c; ++j) {
-    const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)key, (int)j);
-    less += x < key ? 1u : 0u;
-    same += x == key ? 1u : 0u;
-  }
-  const uint64_t hit = __ballot((uint32_t)lane < c && less < k_rem && k_rem <= less + same);
-  const int who = hit != 0ull ? __ffsll((unsigned long long)hit) - 1 : 0;    // never zero
-  thr = (uint32_t)__builtin_amdgcn_readlane((int)key, who);
-  k_rem -= (uint32_t)__builtin_amdgcn_readlane((int)less, who);
+  pick_listed(sh.list, c, thr, k_rem);
 }
 
 // The kept tokens in ascending order, then the window tokens.
@@ -525,31 +531,94 @@ __device__ __forceinline__ void select_finish_body(void* lds, const SelectArgs& 
   finish_write(sh, lds_cand, a, row, n, thr, k_rem);
 }
 
-// All three steps for a row of at most kShortT scores, one workgroup per row: every token is a candidate.
-// Latency-bound like the finish step; it replaces three launches (64 rows of 8000 scores: 25.0 -> 11 us).
+// All three steps for a row of at most kShortT scores, one workgroup per row: every token is a candidate.  The threshold
+// as in the finish step, in 4096 bins between the row's smallest and largest key; the radix select where the k-th's bin
+// holds more than kFinListMax.  Bound by latency (8 rows, us, with the radix select for all and so: 2000 scores 7.4, 5.7;
+// 8000 10.4, 7.1; 12000 12.9, 7.9; 12000 of a few values 12.9, 16.7: equal keys are counted one after the other).
 struct ShortSelectShared {
-  __align__(16) uint32_t keys[kShortT];
-  uint32_t h[kHistWords];
+  uint4 keys[kShortT / 4];
+  union {
+    uint4 bin[kFinThreads];
+    uint32_t h[kHistWords];
+  };
   uint32_t sm[2 * kFinWaves + 2];
+  uint32_t list[kFinListMax];
+  uint32_t pick[4];
 };
 __device__ __forceinline__ void select_short_body(ShortSelectShared& sh, const SelectArgs& a, int row) {
   const int tid = threadIdx.x, T = a.T;
   constexpr int kPer = kShortT / kFinThreads;
-  static_assert(kShortT % kFinThreads == 0, "the threads share the row evenly");
+  static_assert(kShortT % kFinThreads == 0 && kPer % 4 == 0, "the threads share the row evenly");
   const float* sr = a.scores + (int64_t)row * T;
-  float v[kPer];
+  uint32_t* keys = &sh.keys[0].x;
+  uint32_t key[kPer], lo = 0xffffffffu, hi = 0u, thr, k_rem;
+  {
+    float f[kPer];
 #pragma unroll
-  for (int u = 0; u < kPer; ++u) v[u] = sr[min(tid + u * kFinThreads, T - 1)];   // one round trip
+    for (int u = 0; u < kPer; ++u) f[u] = u * kFinThreads < T ? sr[min(tid + u * kFinThreads, T - 1)] : 0.f;   // one round trip
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) key[u] = order_key(f[u]);
+  }
+  sh.bin[tid] = make_uint4(0u, 0u, 0u, 0u);
+  if (tid == 0) sh.pick[3] = 0;
 #pragma unroll
   for (int u = 0; u < kPer; ++u)
-    if (tid + u * kFinThreads < T) sh.keys[tid + u * kFinThreads] = order_key(v[u]);
+    if (u * kFinThreads < T) {                          // uniform; positions past the end repeat the last key
+      if (tid + u * kFinThreads < T) keys[tid + u * kFinThreads] = key[u];
+      lo = min(lo, key[u]);
+      hi = max(hi, key[u]);
+    }
+  block_min_max(sh.sm, lo, hi);
+  const int shift = bin_shift(lo, hi, kSampleBinBits);
+  uint32_t* bin = &sh.bin[0].x;
+#pragma unroll
+  for (int u = 0; u < kPer; ++u)
+    if (lo != hi && tid + u * kFinThreads < T) atomicAdd(&bin[(key[u] - lo) >> shift], 1u);
   __syncthreads();
-  uint32_t thr, k_rem;
-  radix_select_block(T, (uint32_t)a.k, [&](int i) { return sh.keys[i]; }, sh.h, sh.sm, thr, k_rem);
+  const uint4 c4 = sh.bin[tid];
+  const uint32_t cs[4] = {c4.x, c4.y, c4.z, c4.w}, kk = (uint32_t)a.k;
+  uint32_t excl, total, most;
+  block_scan<true>(sh.sm, c4.x + c4.y + c4.z + c4.w, 0u, excl, total, most);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (excl < kk && kk <= excl + cs[q]) {              // one bin of the workgroup (1 <= k <= T)
+      sh.pick[0] = (uint32_t)(4 * tid + q);
+      sh.pick[1] = kk - excl;
+      sh.pick[2] = cs[q];
+    }
+    excl += cs[q];
+  }
+  __syncthreads();
+  const uint32_t d = sh.pick[0], c = sh.pick[2];
+  k_rem = sh.pick[1];
+  if (lo == hi) {                                       // uniform: all scores are equal, nothing was counted
+    thr = lo;
+    k_rem = kk;
+  } else if (c > kFinListMax) {                         // uniform
+    radix_select_block(T, kk, [&](int i) { return keys[i]; }, sh.h, sh.sm, thr, k_rem);
+  } else {
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+      if (tid + u * kFinThreads < T && (key[u] - lo) >> shift == d) sh.list[atomicAdd(&sh.pick[3], 1u)] = key[u];   // c of them
+    __syncthreads();
+    pick_listed(sh.list, c, thr, k_rem);
+  }
   int32_t* out = a.idx_out + (int64_t)row * (a.k + a.W);
-  ordered_write<4>(T, thr, k_rem, a.k, [&](int i0, uint32_t* key) {
-    for (int j = 0; j < 4; ++j) key[j] = sh.keys[i0 + j];   // i0 + 3 < kShortT
-  }, [&](int i) { return (uint32_t)i; }, sh.sm, out);
+  auto four = [&](int i0, uint32_t* x) {
+    const uint4 v = sh.keys[i0 / 4];                    // i0 + 3 < kShortT
+    x[0] = v.x;
+    x[1] = v.y;
+    x[2] = v.z;
+    x[3] = v.w;
+  };
+  auto tok = [&](int i) { return (uint32_t)i; };
+  if (T <= 4 * kFinThreads)
+    ordered_write<4>(T, thr, k_rem, a.k, four, tok, sh.sm, out);
+  else
+    ordered_write<kPer>(T, thr, k_rem, a.k, [&](int i0, uint32_t* x) {
+#pragma unroll
+      for (int j = 0; j < kPer; j += 4) four(min(i0 + j, kShortT - 4), x + j);
+    }, tok, sh.sm, out);
   for (int i = tid; i < a.W; i += kFinThreads) out[a.k + i] = T + i;   // window tokens (Alg. 1 step 10)
 }
 

@@ -24,19 +24,16 @@ union PartFilterShared {
   FilterShared<true> filter;
 };
 
-// Short contexts (T <= kShortT): ranking by counting and the top-k of every row in one launch instead of the
-// four below, for N = 4096 15 instead of 36 us.  The selecting workgroups, the longer ones, come first.
-union ShortShared {
-  ShortSelectShared select;
-  CountShared count;
-};
+// Short contexts (T <= kShortT): the ranking and the top-k of every row in one launch instead of the two below.  The
+// selecting workgroups, the longer ones, come first.  Dynamic LDS: kTailShortLds.
+constexpr size_t kTailShortLds = sizeof(ShortSelectShared) > sizeof(ShortRankShared) ? sizeof(ShortSelectShared) : sizeof(ShortRankShared);
 __global__ void __launch_bounds__(kTailThreads) tail_short_kernel(const float* s_all, int32_t* rank_row, SelectArgs se, int rows) {
-  __shared__ ShortShared sh;
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_dyn[];
   const int b = (int)blockIdx.x;
   if (b < rows)
-    select_short_body(sh.select, se, b);
+    select_short_body(*reinterpret_cast<ShortSelectShared*>(lds_dyn), se, b);
   else
-    rank_count_body(sh.count, s_all, se.T, rank_row, b - rows);
+    rank_short_body(*reinterpret_cast<ShortRankShared*>(lds_dyn), s_all, se.T, rank_row, b - rows);
 }
 
 // launch 0: the ranking's partition | top-k bound and filter (TILES tiles of a score row per workgroup; VEC: 16-byte
@@ -153,8 +150,11 @@ hipError_t launch_tail(const Workspace& ws, const float* scores, int rows, int T
   const SelectArgs se = select_args(ws, scores, T, k, W, idx_out, have_sample);
   hipError_t e;
   if (T <= kShortT) {
-    ASL_LAUNCH(ws.prof, kKernTail, st, tail_short_kernel, dim3(rows + rank_count_blocks(T)), dim3(kTailThreads), 0, st, s_all,
-               rank_row, se, rows);
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(tail_short_kernel),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTailShortLds);
+    if (attr != hipSuccess) return attr;
+    ASL_LAUNCH(ws.prof, kKernTail, st, tail_short_kernel, dim3(rows + short_rank_blocks(T)), dim3(kTailThreads), kTailShortLds, st,
+               s_all, rank_row, se, rows);
     e = hipGetLastError();
   } else {
     const uint32_t* sample = have_sample ? ws.sel_sample + (int64_t)(rows - 1) * kSelMaxSample : nullptr;

@@ -165,8 +165,8 @@ def test_rank_and_select_at_tile_boundaries(ctx, gpu_device, T):
         _select_case(ctx, gpu_device, np.stack([s, -s]), budget, 8)
 
 
-# Up to 12288 scores are ranked by counting (32 tokens per workgroup) and selected from by one workgroup per
-# row; above, the sort (tiles of 2048) and the bound / filter / finish launches (tiles of 4096) take over.
+# Up to 12288 scores are ranked in one launch (128 places per workgroup) and selected from by one workgroup per
+# row; above, the partition (tiles of 2048) and the bound / filter / finish launches (tiles of 4096) take over.
 @pytest.mark.parametrize("T", [31, 32, 33, 95, 1023, 1025, 8192, 12256, 12257, 12287, 12288, 12289, 14335, 14336, 14337,
                                16383, 16384, 16385])
 def test_short_vectors_and_their_limit(ctx, gpu_device, T):
@@ -181,6 +181,33 @@ def test_short_vectors_and_their_limit(ctx, gpu_device, T):
         _rank_case(ctx, gpu_device, v)
     for budget in (9, T // 3 + 8, T + 8):                                   # k = 1, ~T/3, T
         _select_case(ctx, gpu_device, np.stack([s, -s, wild]), budget, 8)
+
+
+@pytest.mark.parametrize("T", [1, 2, 127, 128, 129, 255, 257, 1024, 4095, 4097, 9994, 12287, 12288])
+@pytest.mark.parametrize("kind", ["lognormal", "pairs", "third-zero", "outlier"])
+def test_short_vectors_by_bins(ctx, gpu_device, T, kind):
+    """Short vectors whose scores their 4096 bins tell apart (with equal neighbours, so that bins of a few keys straddle
+    the workgroups' places) and whose do not (repeated scores; one outlier that pushes the others into one bin): integers, exact."""
+    rng = np.random.default_rng(T)
+    s = np.exp(2 * rng.standard_normal(T)).astype(np.float32)
+    if kind == "pairs":
+        s = s[rng.permutation(T) // 3]
+    elif kind == "third-zero":
+        s[rng.random(T) < 1 / 3] = 0.0
+    elif kind == "outlier":
+        s = (1 + 1e-5 * rng.random(T)).astype(np.float32)
+        s[T // 2] = -3e38
+    _rank_case(ctx, gpu_device, s)
+    for budget in sorted({9, T // 3 + 9, T + 8}):                           # k = 1, ~T/3, T
+        _select_case(ctx, gpu_device, np.stack([s, -s]), budget, 8)
+
+
+@pytest.mark.parametrize("T", [264000, 264001, 1048576, 1048577])
+def test_rank_where_the_bucket_count_changes(gpu_device, T):
+    """The last size of 240 buckets, the first and last of 512 and the first beyond, scores mostly distinct: exact."""
+    c = asl.Asl(T, 1, 32)
+    _rank_case(c, gpu_device, np.exp(2 * np.random.default_rng(T).standard_normal(T)).astype(np.float32))
+    c.close()
 
 
 # ----------------------------------------------------------------------------- statistic
