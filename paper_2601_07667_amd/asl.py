@@ -120,8 +120,12 @@ def _ptr(t) -> Optional[int]:
 
 
 def _stream() -> int:
+    """Handle of the calling thread's current stream on its current device, without the Stream object that
+    torch.cuda.current_stream() makes (2.9 us of a call whose one launch takes 2.5; so 0.1 us)."""
     import torch
-    return torch.cuda.current_stream().cuda_stream
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def make_params(Hq: int, Hk: int, d: int, N: int, W: int, S: int, budget: int, dtype: int = ASL_BF16,
