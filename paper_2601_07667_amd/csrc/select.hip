@@ -20,7 +20,7 @@
 // The bound is only a guess: if fewer than k keys passed it, or a tile's or the row's candidates
 // do not fit their buffers, step 3 runs the same selection over the whole row straight from the
 // scores instead (slower, same result).  The result therefore never depends on the sample.
-// Rows of at most kShortT scores need no bound: one launch, one workgroup per row, all tokens in LDS.
+// Rows of at most kSelMidT scores (many rows: kSelShortT; in a layer step: kShortT) need no bound: one launch, one workgroup per row, all tokens in LDS.
 // Integer work throughout: nothing depends on scheduling.
 #include "select_body.h"
 
@@ -46,10 +46,20 @@ __global__ void __launch_bounds__(kFinThreads, 8) select_finish_kernel(SelectArg
   select_finish_body(lds_dyn, a, (int)blockIdx.x);
 }
 
-// dynamic LDS: sizeof(ShortSelectShared)
+// dynamic LDS: sizeof(ShortSelectShared<PER>)
+template <int PER>
 __global__ void __launch_bounds__(kFinThreads) select_short_kernel(SelectArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_dyn[];
-  select_short_body(*reinterpret_cast<ShortSelectShared*>(lds_dyn), a, (int)blockIdx.x);
+  select_short_body<PER>(*reinterpret_cast<ShortSelectShared<PER>*>(lds_dyn), a, (int)blockIdx.x);
+}
+template <int PER>
+static hipError_t launch_select_short(Prof* prof, const SelectArgs& a, int rows, hipStream_t st) {
+  constexpr size_t lds = sizeof(ShortSelectShared<PER>);
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(select_short_kernel<PER>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (attr != hipSuccess) return attr;
+  ASL_LAUNCH(prof, kKernSelWrite, st, select_short_kernel<PER>, dim3(rows), dim3(kFinThreads), lds, st, a);
+  return hipGetLastError();
 }
 
 SelectArgs select_args(const Workspace& ws, const float* scores, int T, int k, int W, int32_t* idx_out,
@@ -80,16 +90,15 @@ hipError_t launch_select(const Workspace& ws, const float* scores, int rows, int
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(select_finish_kernel),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)finish_lds_bytes(kSelCandCap));
   if (attr != hipSuccess) return attr;
-  static const hipError_t attr_short = hipFuncSetAttribute(reinterpret_cast<const void*>(select_short_kernel),
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(ShortSelectShared));
-  if (attr_short != hipSuccess) return attr_short;
   // rows beyond what the candidate buffers hold at once take further rounds of the three launches
   const int rows_per_round = ws.sel_rows;
   for (int row0 = 0; row0 < rows; row0 += rows_per_round) {
     const int nr = rows - row0 < rows_per_round ? rows - row0 : rows_per_round;
     const SelectArgs a = select_args(ws, scores + (int64_t)row0 * T, T, k, W, idx_out + (int64_t)row0 * (k + W), false);
-    if (T <= kShortT) {
-      ASL_LAUNCH(ws.prof, kKernSelWrite, st, select_short_kernel, dim3(nr), dim3(kFinThreads), sizeof(ShortSelectShared), st, a);
+    if (T <= kSelMidT || (T <= kSelShortT && rows >= kSelShortRows)) {
+      const hipError_t e = T <= kShortT ? launch_select_short<kShortT / kFinThreads>(ws.prof, a, nr, st)
+                                        : launch_select_short<kSelShortT / kFinThreads>(ws.prof, a, nr, st);
+      if (e != hipSuccess) return e;
       continue;
     }
     ASL_LAUNCH(ws.prof, kKernSelHist, st, select_guess_kernel, dim3(nr), dim3(kFinThreads), 0, st, a);

@@ -531,12 +531,15 @@ __device__ __forceinline__ void select_finish_body(void* lds, const SelectArgs& 
   finish_write(sh, lds_cand, a, row, n, thr, k_rem);
 }
 
-// All three steps for a row of at most kShortT scores, one workgroup per row: every token is a candidate.  The threshold
-// as in the finish step, in 4096 bins between the row's smallest and largest key; the radix select where the k-th's bin
-// holds more than kFinListMax.  Bound by latency (8 rows, us, with the radix select for all and so: 2000 scores 7.4, 5.7;
-// 8000 10.4, 7.1; 12000 12.9, 7.9; 12000 of a few values 12.9, 16.7: equal keys are counted one after the other).
+// All three steps for a row of at most PER * kFinThreads scores, one workgroup per row: every token is a candidate.  The
+// threshold as in the finish step, in 4096 bins between the row's smallest and largest key; the radix select where the k-th's
+// bin holds more than kFinListMax.  Bound by latency.  8 rows, us, with the radix select for all and so: 2000 scores 7.4,
+// 5.7; 8000 10.4, 7.1; 12000 12.9, 7.9; 12000 of a few
+// values 12.9, 16.6 (equal keys are counted one after the other; kept apart by ballots they cost ordinary rows 1 to 2.5 us).
+// PER keys a thread.
+template <int PER>
 struct ShortSelectShared {
-  uint4 keys[kShortT / 4];
+  uint4 keys[PER * kFinThreads / 4];
   union {
     uint4 bin[kFinThreads];
     uint32_t h[kHistWords];
@@ -545,10 +548,11 @@ struct ShortSelectShared {
   uint32_t list[kFinListMax];
   uint32_t pick[4];
 };
-__device__ __forceinline__ void select_short_body(ShortSelectShared& sh, const SelectArgs& a, int row) {
+template <int PER>
+__device__ __forceinline__ void select_short_body(ShortSelectShared<PER>& sh, const SelectArgs& a, int row) {
   const int tid = threadIdx.x, T = a.T;
-  constexpr int kPer = kShortT / kFinThreads;
-  static_assert(kShortT % kFinThreads == 0 && kPer % 4 == 0, "the threads share the row evenly");
+  constexpr int kPer = PER, kMost = PER * kFinThreads, kWrite = PER <= 16 ? PER : 16;      // keys a thread writes together
+  static_assert(PER % 4 == 0 && PER % kWrite == 0, "four keys per read");
   const float* sr = a.scores + (int64_t)row * T;
   uint32_t* keys = &sh.keys[0].x;
   uint32_t key[kPer], lo = 0xffffffffu, hi = 0u, thr, k_rem;
@@ -605,7 +609,7 @@ __device__ __forceinline__ void select_short_body(ShortSelectShared& sh, const S
   }
   int32_t* out = a.idx_out + (int64_t)row * (a.k + a.W);
   auto four = [&](int i0, uint32_t* x) {
-    const uint4 v = sh.keys[i0 / 4];                    // i0 + 3 < kShortT
+    const uint4 v = sh.keys[i0 / 4];                    // i0 + 3 < kMost
     x[0] = v.x;
     x[1] = v.y;
     x[2] = v.z;
@@ -615,9 +619,9 @@ __device__ __forceinline__ void select_short_body(ShortSelectShared& sh, const S
   if (T <= 4 * kFinThreads)
     ordered_write<4>(T, thr, k_rem, a.k, four, tok, sh.sm, out);
   else
-    ordered_write<kPer>(T, thr, k_rem, a.k, [&](int i0, uint32_t* x) {
+    ordered_write<kWrite>(T, thr, k_rem, a.k, [&](int i0, uint32_t* x) {
 #pragma unroll
-      for (int j = 0; j < kPer; j += 4) four(min(i0 + j, kShortT - 4), x + j);
+      for (int j = 0; j < kWrite; j += 4) four(min(i0 + j, kMost - 4), x + j);
     }, tok, sh.sm, out);
   for (int i = tid; i < a.W; i += kFinThreads) out[a.k + i] = T + i;   // window tokens (Alg. 1 step 10)
 }

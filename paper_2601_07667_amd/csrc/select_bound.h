@@ -14,8 +14,12 @@ constexpr int kSelTile = ASL_SEL_TILE;     // elements per select workgroup tile
 constexpr int kSelSegment = kSelTile / 2;   // candidate slots per select tile
 constexpr int kSelCandCap = 16384;     // candidates of one row the finishing workgroup holds in LDS
 
-constexpr int kShortT = 12288;           // longest score vector that one workgroup holds in LDS (below 64 KB with the
-                                         // selection's counters): ranked and selected from in one launch
+constexpr int kShortT = 12288;           // longest score vector that is ranked and selected from in one launch, every
+                                         // workgroup with all of it
+// The top-k on its own takes longer ones so too, up to what fits a workgroup's LDS: kSelMidT scores always, kSelShortT from
+// kSelShortRows rows on (a call, us, with bound, filter and finish, and so: 8 rows of 16000 16.1, 11.9; 130 rows of 20000
+// 20.2, 15.5; 256 of 30000 27.8, 20.7; 64 of 30000 18.6, 17.0; with fewer rows of that length there is nothing left to gain).
+constexpr int kSelMidT = 16384, kSelShortT = 32768, kSelShortRows = 64;
 // n_s = sel_sample_size(T) keys of a row at positions j * sel_sample_stride(T), j < n_s, for T > kShortT.
 constexpr int kSelMaxSample = 8192;    // sampled keys per row
 inline int sel_sample_size(int T) {

@@ -26,12 +26,12 @@ union PartFilterShared {
 
 // Short contexts (T <= kShortT): the ranking and the top-k of every row in one launch instead of the two below.  The
 // selecting workgroups, the longer ones, come first.  Dynamic LDS: kTailShortLds.
-constexpr size_t kTailShortLds = sizeof(ShortSelectShared) > sizeof(ShortRankShared) ? sizeof(ShortSelectShared) : sizeof(ShortRankShared);
+constexpr size_t kTailShortLds = sizeof(ShortSelectShared<kShortPer>) > sizeof(ShortRankShared) ? sizeof(ShortSelectShared<kShortPer>) : sizeof(ShortRankShared);
 __global__ void __launch_bounds__(kTailThreads) tail_short_kernel(const float* s_all, int32_t* rank_row, SelectArgs se, int rows) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_dyn[];
   const int b = (int)blockIdx.x;
   if (b < rows)
-    select_short_body(*reinterpret_cast<ShortSelectShared*>(lds_dyn), se, b);
+    select_short_body<kShortPer>(*reinterpret_cast<ShortSelectShared<kShortPer>*>(lds_dyn), se, b);
   else
     rank_short_body(*reinterpret_cast<ShortRankShared*>(lds_dyn), s_all, se.T, rank_row, b - rows);
 }

@@ -183,23 +183,41 @@ def test_short_vectors_and_their_limit(ctx, gpu_device, T):
         _select_case(ctx, gpu_device, np.stack([s, -s, wild]), budget, 8)
 
 
-@pytest.mark.parametrize("T", [1, 2, 127, 128, 129, 255, 257, 1024, 4095, 4097, 9994, 12287, 12288])
-@pytest.mark.parametrize("kind", ["lognormal", "pairs", "third-zero", "outlier"])
+@pytest.mark.parametrize("T", [1, 2, 127, 128, 129, 255, 257, 1024, 5120, 5121, 9994, 12287, 12288, 12289, 16385, 32736, 32767,
+                               32768, 32769])
+@pytest.mark.parametrize("kind", ["lognormal", "pairs", "third-zero", "few", "two", "outlier"])
 def test_short_vectors_by_bins(ctx, gpu_device, T, kind):
-    """Short vectors whose scores their 4096 bins tell apart (with equal neighbours, so that bins of a few keys straddle
-    the workgroups' places) and whose do not (repeated scores; one outlier that pushes the others into one bin): integers, exact."""
+    """Vectors up to and just beyond what one workgroup takes, whose scores their bins tell apart (with equal neighbours, so
+    that bins of a few keys straddle the workgroups' places) and whose do not: repeated scores, in one, some or all bins,
+    and one outlier that pushes different scores into one bin.  Integers, exact."""
     rng = np.random.default_rng(T)
     s = np.exp(2 * rng.standard_normal(T)).astype(np.float32)
     if kind == "pairs":
         s = s[rng.permutation(T) // 3]
     elif kind == "third-zero":
         s[rng.random(T) < 1 / 3] = 0.0
+    elif kind == "few":
+        s = np.round(3 * rng.standard_normal(T)).astype(np.float32)
+    elif kind == "two":
+        s = np.where(rng.random(T) < 0.5, 0.25, 0.5).astype(np.float32)
     elif kind == "outlier":
         s = (1 + 1e-5 * rng.random(T)).astype(np.float32)
         s[T // 2] = -3e38
     _rank_case(ctx, gpu_device, s)
     for budget in sorted({9, T // 3 + 9, T + 8}):                           # k = 1, ~T/3, T
         _select_case(ctx, gpu_device, np.stack([s, -s]), budget, 8)
+
+
+@pytest.mark.parametrize("rows,T", [(63, 16385), (64, 16385), (64, 32768), (64, 32769)])
+def test_select_rows_one_workgroup_takes(gpu_device, rows, T):
+    """The fewest rows and longest that one workgroup per row selects from, and one beyond each: integers, exact."""
+    rng = np.random.default_rng(rows + T)
+    s = np.exp(2 * rng.standard_normal((rows, T))).astype(np.float32)
+    s[::3, ::4] = 0.0
+    c = asl.Asl(T + 8, rows, rows * 8)
+    for budget in (9, T // 20, T + 8):
+        _select_case(c, gpu_device, s, budget, 8)
+    c.close()
 
 
 @pytest.mark.parametrize("T", [264000, 264001, 1048576, 1048577])
