@@ -423,10 +423,13 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
 // so every caller gets the same bits for the same partials.
 // p points at the row's partial of chunk 0; consecutive chunks are M float2 apart.
 // Batches of kB chunks per lane: all loads of a batch are issued before the first is used.
-// (fold_batch: as many as the registers hold beside the query fragments.)
 // NR rows at once (pointers p[0..NR-1]): the loads of a batch go out for all of them before the first
 // is used, so NR rows cost as many memory round trips as one.
-template <int RB> constexpr int fold_batch() { return RB == 1 ? 48 : 32; }
+// kFoldChunks: most partials that pass 2's workgroups fold themselves, two lanes a row in one round of loads.  Beyond, every
+// workgroup reading all of them costs more than a launch in front of pass 2 that does so once (28 heads, 128K, 128 chunks:
+// 92.7 us the scoring with the fold in two rounds, 88.8 with that launch; 7 heads on one, W = 64, 200K, 256 chunks: 78.3,
+// 67.6; but 64 chunks, 8B shape: 32K 37.2, 37.9).
+constexpr int kFoldChunks = 64;
 template <int NR, int kB>
 __device__ __forceinline__ void combine_rows(const float2* const (&p)[NR], int M, int n_chunks, int half,
                                              float (&out)[NR]) {
@@ -467,27 +470,52 @@ __device__ __forceinline__ void combine_rows(const float2* const (&p)[NR], int M
     out[q] = mm + log2f(zs);
   }
 }
-__device__ __forceinline__ float combine_row(const float2* __restrict__ p, int M, int n_chunks, int half) {
-  const float2* const ps[1] = {p};
-  float out[1];
-  combine_rows<1, fold_batch<1>()>(ps, M, n_chunks, half, out);
-  return out[0];
-}
 
-// The offsets of all Hk*M rows (one wavefront per 32 rows), for callers that want the rows'
-// log-sum-exp: row_const[r] = m + log2(Z) and, as a natural logarithm, lse_out[r].
+// The offsets of all Hk*M rows, 16 rows a workgroup: row_const[r] = m + log2(Z) and, where the rows' log-sum-exp is asked
+// for, as a natural logarithm, lse_out[r].  16 threads share a row, each every 16th chunk; their results are added in a
+// fixed order.
+constexpr int kCombineRows = 16;
 __global__ void __launch_bounds__(256)
 score_combine_kernel(const float* __restrict__ row_part, int Hk, int M, int n_chunks,
                      float* __restrict__ row_const, float* __restrict__ lse_out) {
-  const int lane = threadIdx.x & 63, ln = lane & 31, half = lane >> 5;
-  const int r = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 32 + ln;
-  const int rr = min(r, Hk * M - 1);
+  __shared__ float2 part[4][kCombineRows];
+  const int tid = threadIdx.x, j = tid >> 4, wave = tid >> 6;
+  const int r = blockIdx.x * kCombineRows + (tid & 15), rr = min(r, Hk * M - 1);
   const int g = rr / M, row = rr % M;
   const float2* p = reinterpret_cast<const float2*>(row_part) + (int64_t)g * n_chunks * M + row;
-  const float c = combine_row(p, M, n_chunks, half);
-  if (half == 0 && r < Hk * M) {
-    row_const[r] = c;
-    if (lse_out != nullptr) lse_out[r] = c * kLn2;
+  constexpr int kB = kMaxChunks / 16;
+  float2 v[kB];
+#pragma unroll
+  for (int i = 0; i < kB; ++i) {
+    const int c = j + 16 * i;
+    v[i] = make_float2(kNegBig, 0.f);
+    if (16 * i < n_chunks) v[i] = p[(int64_t)min(c, n_chunks - 1) * M];
+    if (c >= n_chunks) v[i] = make_float2(kNegBig, 0.f);
+  }
+  float m = kNegBig, z = 0.f;
+#pragma unroll
+  for (int i = 0; i < kB; ++i) m = fmaxf(m, v[i].x);
+#pragma unroll
+  for (int i = 0; i < kB; ++i) z += v[i].y * fast_exp2(v[i].x - m);
+  auto add = [&](float mo, float zo, bool first) {
+    const float mm = fmaxf(m, mo), za = z * fast_exp2(m - mm), zb = zo * fast_exp2(mo - mm);
+    z = first ? za + zb : zb + za;
+    m = mm;
+  };
+#pragma unroll
+  for (int d = 16; d < 64; d <<= 1) add(__shfl_xor(m, d), __shfl_xor(z, d), (tid & d) == 0);
+  if ((tid & 63) < 16) part[wave][tid & 15] = make_float2(m, z);
+  __syncthreads();
+  if (tid < 16) {
+    m = part[0][tid].x;
+    z = part[0][tid].y;
+#pragma unroll
+    for (int w = 1; w < 4; ++w) add(part[w][tid].x, part[w][tid].y, true);
+    const float c = m + log2f(z);
+    if (r < Hk * M) {
+      row_const[r] = c;
+      if (lse_out != nullptr) lse_out[r] = c * kLn2;
+    }
   }
 }
 
@@ -592,17 +620,15 @@ score_colsum_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, 
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
       ps[rb] = reinterpret_cast<const float2*>(row_part) + (int64_t)g * n_parts * M + min(row0 + rb * 32 + ln, m1 - 1);
-    // the smallest batch that takes all partials in one round: a batch is worked through whole, whatever it
-    // holds (always 48, pass 2 took 12.1 us at N = 512, 16.4 at 16K, 21.9 at 32K; so 8.7, 14.3, 19.8)
+    // the smallest batch that takes all partials: a batch is worked through whole, whatever it holds (always 48, pass 2
+    // took 12.1 us at N = 512, 16.4 at 16K; so 8.7, 14.3)
     const auto& rows = reinterpret_cast<const float2* const (&)[RB]>(ps);
     if (n_parts <= 2 * 8)
       combine_rows<RB, 8>(rows, M, n_parts, half, mine);
     else if (n_parts <= 2 * 16)
       combine_rows<RB, 16>(rows, M, n_parts, half, mine);
-    else if (n_parts <= 2 * 32 && fold_batch<RB>() > 32)
-      combine_rows<RB, 32>(rows, M, n_parts, half, mine);
     else
-      combine_rows<RB, fold_batch<RB>()>(rows, M, n_parts, half, mine);
+      combine_rows<RB, kFoldChunks / 2>(rows, M, n_parts, half, mine);
   }
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
@@ -771,20 +797,18 @@ static int device_cu_count() {
 // one; 8B shape, 128K layer step: 111.8 us with two, 115.0 with three); of 8 pieces from two tiles each (8 heads, 128
 // rows, 16K: 12.4 us with two, 13.5 with one; 50K: 19.1 with two, 20.5 with three).
 //
-// fold = true: every workgroup of pass 2 first folds one partial per chunk, in rounds of `2 * fold_batch` partials
-// (one round, in smaller batches, up to 64), so that chunks cost pass 2 what they save both passes in tiles.  The
-// chunk count with the least estimated time is taken, from those that fill rounds and the largest one.  Estimated, in
-// us, fitted to graph-replayed calls (1 to 8 KV heads, 16 to 256 rows, d = 64 and 128 in bf16 and some other shapes,
-// 2K to 256K keys, nine chunk counts each: the choice is 0.5 % off the best of the nine on average, at worst 15 %):
-//  - a round beyond the first 64 partials: 4 for the batch of 48, 14 where one wavefront folds rows of 16 pieces or
-//    more, 4.3 for every further one; 1.7 each above 128 rows;
+// fold = true: the rows' partials, one per chunk, are folded by every workgroup of pass 2 (up to kFoldChunks) or by a
+// launch of their own.  The chunk count with the least estimated time is taken.  Estimated, in us, fitted to graph-replayed
+// calls (1 to 8 KV heads, 16 to 448 rows, d = 64 and 128 in bf16 and some fp32, 4K to 200K keys, six chunk counts each):
+//  - the launch that combines partials: 4;
 //  - a tile, both passes: 1.4, or 4.4 in fp32 (four MFMAs per fragment step);
 //  - a unit takes `alone` workgroups before they slow each other down: its share of the stream feeds one with tiles
-//    of 16 KB (1.3 that do little with them), and 5.2 wavefronts with tiles of 8 KB; in fp32 the four matrix pipes
-//    are shared;
-//  - 0.6 for every further workgroup of a unit (start-up).
-// Examples, now and with two workgroups per unit throughout: 4 heads, 32 rows, d = 64, 128K 35.5 and 42.5 us; one
-// head, 32 rows, d = 64, 24K 16.3 and 21.5; two heads, 32 rows, d = 128, 24K 18.7 and 46.5; 8B shape unchanged.
+//    of 16 KB (1.15 of 64 rows a wavefront, 2.5 of one wavefront), and 5.2 wavefronts with tiles of 8 KB; in fp32 the four
+//    matrix pipes are shared;
+//  - 0.6, or 1.5 with 64 rows a wavefront, for every further workgroup of a unit (start-up).
+// Examples, whole call, now and with all folding in pass 2 (fewer chunks): two heads, d = 64, 16 rows, 64K 19.5 and 25.9,
+// 200K 34.0 and 41.3; one head, 128 rows, 20K 17.0 and 19.1, 200K 36.4 and 44.9; one head, 448 rows, 20K 28.7 and 35.6;
+// 8B shape unchanged.
 template <typename TE, int P, int NW, int RB>
 static int score_chunks(int Hk, int n_tiles, int n_cu, int resident, bool fold) {
   auto fit = [&](int per_cu) {
@@ -800,7 +824,7 @@ static int score_chunks(int Hk, int n_tiles, int n_cu, int resident, bool fold) 
     }
     return n_tiles >= (P > 8 ? 5 : 2) * fit(2) ? fit(2) : fit(1);
   }
-  const float alone = narrow ? 5.2f / NW : f32 ? (NW == 1 ? 3.5f : 1.0f) : NW == 1 || (NW == 2 && P > 16) ? 1.3f : 1.06f;
+  const float alone = narrow ? 5.2f / NW : f32 ? (NW == 1 ? 3.5f : 1.0f) : NW == 1 ? 2.5f : NW == 2 && P > 16 ? 1.3f : RB > 1 ? 1.15f : 1.06f;
   const int most = fit(3), counts[] = {32, 64, RB > 1 ? 64 : 96, 128, RB > 1 ? 128 : 192, 256, most};
   int best = most;
   float best_us = INFINITY;
@@ -808,12 +832,8 @@ static int score_chunks(int Hk, int n_tiles, int n_cu, int resident, bool fold) 
     if (c > most) continue;
     const float per_unit = (float)c * (float)Hk / (float)n_cu;
     const float tiles = n_tiles <= 2 * c ? (float)((n_tiles + c - 1) / c) : (float)n_tiles / (float)c;
-    const int rounds = (c + 2 * fold_batch<RB>() - 1) / (2 * fold_batch<RB>());
-    float us = tiles * (f32 ? 4.4f : 1.4f) * fmaxf(1.0f, per_unit / alone) + 0.6f * fmaxf(0.0f, per_unit - 1.0f);
-    if (RB > 1)
-      us += 1.7f * (float)(rounds - 1);
-    else if (c > 64)
-      us += (NW == 1 && P >= 16 ? 14.0f : 4.0f) + 4.3f * (float)(rounds - 1);
+    const float us = (c > kFoldChunks ? 4.0f : 0.0f) + tiles * (f32 ? 4.4f : 1.4f) * fmaxf(1.0f, per_unit / alone) +
+                     (RB > 1 ? 1.5f : 0.6f) * fmaxf(0.0f, per_unit - 1.0f);
     if (us < best_us) {
       best_us = us;
       best = c;
@@ -850,25 +870,26 @@ static hipError_t launch_score_mfma(const asl_params& p, const Workspace& ws, co
   }();
   const int n_cu = device_cu_count();
   const int n_chunks = score_chunks<TE, P, NW, RB>(Hk, (N + KT - 1) / KT, n_cu, resident, lse == nullptr);
+  const bool combine = n_chunks > kFoldChunks;
   if (!lse) {
     for (int m0 = 0; m0 < M; m0 += kRows)
       ASL_LAUNCH(ws.prof, kKernRowstats, st, (score_rowstats_kernel<TE, P, NW, RB, PAD>), dim3(Hk * n_chunks), dim3(NW * 64), 0,
                  st, q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, p.window, N, n_cu, n_chunks, c1,
                  ws.row_part);
-    if (lse_out) {                                 // only the row normalisers were asked for
-      const int rows = Hk * M;
-      ASL_LAUNCH(ws.prof, kKernCombine, st, score_combine_kernel, dim3((rows + 127) / 128), dim3(256), 0, st, ws.row_part,
-                         Hk, M, n_chunks, ws.row_const, lse_out);
-      return hipGetLastError();
+    if (lse_out || combine) {
+      ASL_LAUNCH(ws.prof, kKernCombine, st, score_combine_kernel, dim3((Hk * M + kCombineRows - 1) / kCombineRows), dim3(256), 0, st,
+                 ws.row_part, Hk, M, n_chunks, ws.row_const, lse_out);
+      if (lse_out) return hipGetLastError();             // only the row normalisers were asked for
     }
   }
   const int n_tiles2 = (T + KT - 1) / KT;
   const int n_chunks2 = n_chunks < n_tiles2 ? n_chunks : n_tiles2;
-  // without the caller's log-sum-exp every pass-2 workgroup folds pass 1's partials of its own rows
+  // without the caller's log-sum-exp or a launch that combined them every pass-2 workgroup folds pass 1's partials of
+  // its own rows
   for (int m0 = 0; m0 < M; m0 += kRows)
     ASL_LAUNCH(ws.prof, kKernColsum, st, (score_colsum_kernel<TE, P, NW, RB, PAD, DENORM>), dim3(Hk * n_chunks2), dim3(NW * 64), 0, st,
-               q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, N, T, n_cu, c1, lse, kLog2e,
-               lse ? nullptr : ws.row_part, n_chunks, ws.u_group);
+               q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, N, T, n_cu, c1, lse ? lse : ws.row_const, lse ? kLog2e : 1.0f,
+               lse || combine ? nullptr : ws.row_part, n_chunks, ws.u_group);
   return hipGetLastError();
 }
 

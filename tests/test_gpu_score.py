@@ -149,6 +149,17 @@ def test_chunk_counts(gpu_device, Hq, Hk, W, N):
 
 # (tiles, chunks per head) on 256 compute units: partials folded in one round of loads of each batch size and in two,
 # three and four, tile counts that leave ragged shares, and the last tile ragged too
+@pytest.mark.parametrize("Hq,Hk,d,W,N,dtype", [(8, 1, 128, 16, 20001, "bf16"), (4, 2, 64, 16, 65600, "bf16"), (7, 1, 128, 64, 20000, "bf16"),
+                                                (3, 3, 128, 32, 65537, "bf16"), (14, 2, 128, 32, 65536, "bf16"),
+                                                (16, 1, 96, 48, 20000, "bf16"), (4, 2, 64, 32, 20000, "f32")])
+def test_partials_combined_by_a_launch_of_their_own(gpu_device, Hq, Hk, d, W, N, dtype):
+    """More than 64 chunks per KV head: full, padded and fp32 rows, one and several launches of query rows, chunk counts off
+    a multiple of 16."""
+    L = _small(Hq, Hk, d, N, W, dtype=dtype, seed=Hq + N)
+    P, s = _run_score(gpu_device, L)
+    _close_to_64_bits(P, s, L)
+
+
 @pytest.mark.parametrize("Hq,Hk,d,W,N", [
     (1, 1, 64, 16, 64 * 14), (1, 1, 64, 16, 64 * 48), (6, 2, 64, 32, 64 * 95 + 1),       # 14, 48; 96 tiles in 64
     (8, 8, 64, 32, 64 * 2000 + 1),                                                        # 2001 in 96
