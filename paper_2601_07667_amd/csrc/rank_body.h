@@ -266,10 +266,9 @@ static_assert(sizeof(uint16_t) * kSortedSample <= sizeof(SampleShared::bin) && k
 // in token order inside one, go to the tile's own stretch of `pairs`, and where each bucket's begin to `count`.
 // Every tile works out the same bucket borders from the same sample, so tiles agree on nothing else and wait for
 // nobody.  Bound by latency: the loads, three counts with a scan each, the stores.
-// Borders are those of the sample's histogram bins: bucket b holds the bins whose first sampled key has a place in
-// [b, b + 1) n_s / B.  Where a bin holds three buckets' worth or more (scores that repeat, or that a few outliers push
-// together) the sample is sorted instead, and every n_s / B-th pair (key, token) of it is a border: equal scores are
-// then shared out by token.
+// Borders are those of the sample's histogram bins (narrowed to where the keys are, if outliers spread them): bucket b holds the bins whose first sampled key has a place in
+// [b, b + 1) n_s / B.  Where a bin still holds three buckets' worth or more (scores that repeat) the sample is sorted
+// instead, and every n_s / B-th pair (key, token) of it is a border: equal scores are then shared out by token.
 template <int R>
 __device__ __forceinline__ void partition_body(PartShared& sh, const RankArgs& a, int me) {
   const int tid = threadIdx.x, wave = uniform_wave(), lane = tid & 63, T = a.T, B = a.n_buckets;
@@ -287,25 +286,55 @@ __device__ __forceinline__ void partition_body(PartShared& sh, const RankArgs& a
     hi = max(hi, v[u]);
   }
   block_min_max(sh.s.red, lo, hi);
-  const int shift = bin_shift(lo, hi, kSampleBinBits);
-  sample_count(sh.s, v, a.n_s, lo, hi, shift);
-  const uint4 c = sh.s.bin[tid];
+  const uint32_t hi_all = hi;
   uint32_t first, total, most;
-  block_scan<true>(sh.s.red, c.x + c.y + c.z + c.w, max(max(c.x, c.y), max(c.z, c.w)), first, total, most);
-  const bool sorted = B > 1 && most * (uint32_t)B > 3u * (uint32_t)a.n_s;      // uniform
+  uint4 c;
+  int shift;
+  bool sorted, ends = false;
+  for (int round = 0;; ++round) {
+    shift = bin_shift(lo, hi, kSampleBinBits);
+    sample_count<true>(sh.s, v, a.n_s, lo, hi, shift);
+    c = sh.s.bin[tid];
+    block_scan<true>(sh.s.red, c.x + c.y + c.z + c.w, max(max(c.x, c.y), max(c.z, c.w)), first, total, most);
+    sorted = B > 1 && most * (uint32_t)B > 3u * (uint32_t)a.n_s;               // uniform
+    if (!sorted || shift == 0 || round == 2) break;
+    // Some outliers may have spread the bins over a range that hardly any score is in: again between the keys one and a half
+    // buckets from either end; what is outside is counted with the first and the last bin, which are buckets of their own.
+    ends = B >= 3;
+    const uint32_t q = max(3u * (uint32_t)a.n_s / (2u * (uint32_t)B), 1u), at[2] = {q, (uint32_t)a.n_s - 1u - q};
+    const uint32_t cs[4] = {c.x, c.y, c.z, c.w};
+    uint32_t f = first;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      for (int e = 0; e < 2; ++e)
+        if (f <= at[e] && at[e] < f + cs[i]) sh.s.out[e] = (uint32_t)(4 * tid + i);     // one bin of the workgroup
+      f += cs[i];
+    }
+    __syncthreads();
+    const uint32_t l = lo + (sh.s.out[0] << shift), h = lo + (sh.s.out[1] << shift), mask = (1u << shift) - 1u;
+    hi = hi - h < mask ? hi : h + mask;
+    lo = l;
+  }
   uint32_t* lut = &sh.s.bin[0].x;
   uint2* border = reinterpret_cast<uint2*>(sh.s.bin);   // [b]: first pair of bucket b, b > 0
   if (!sorted) {
-    const float per_key = (float)B / (float)a.n_s;      // monotone in `first` whatever the rounding
-    const uint32_t f1 = first + c.x, f2 = f1 + c.y, f3 = f2 + c.z, top = (uint32_t)(B - 1);
-    const uint32_t bucket[4] = {min((uint32_t)((float)first * per_key), top), min((uint32_t)((float)f1 * per_key), top),
-                                min((uint32_t)((float)f2 * per_key), top), min((uint32_t)((float)f3 * per_key), top)};
+    const uint32_t base = ends ? 1u : 0u, top = (uint32_t)B - 1u - base, past = (hi - lo) >> shift;
+    const float per_key = (float)(top - base + 1u) / (float)a.n_s;             // monotone in `first` whatever the rounding
+    const uint32_t cs[4] = {c.x, c.y, c.z, c.w};
+    uint32_t bucket[4], f = first;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t j = (uint32_t)(4 * tid + i);
+      bucket[i] = min(base + (uint32_t)((float)f * per_key), top);
+      if (ends && j == 0u) bucket[i] = 0u;
+      if (ends && j >= past) bucket[i] = (uint32_t)B - 1u;
+      f += cs[i];
+    }
     sh.s.bin[tid] = make_uint4(bucket[0], bucket[1], bucket[2], bucket[3]);   // own counts only were read
     __syncthreads();
     if (me == 0) {
       // first key of every bucket (empty ones: of the next that is not); bins behind the last key's: that key
       uint32_t prev = tid == 0 ? 0xffffffffu : lut[4 * tid - 1];             // + 1 = 0: bucket 0 begins with bin 0
-      const uint32_t past = (hi - lo) >> shift;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const uint32_t j = (uint32_t)(4 * tid + i);
@@ -344,7 +373,7 @@ __device__ __forceinline__ void partition_body(PartShared& sh, const RankArgs& a
     if (tid < B) border[tid] = mine;
     if (me == 0) {
       if (tid < B) a.edge[tid] = mine.x;                // bucket 0: the sample's first key
-      if (tid == 0) a.edge[B] = hi;
+      if (tid == 0) a.edge[B] = hi_all;
     }
   }
   {
@@ -609,6 +638,7 @@ __device__ __forceinline__ void bucket_body(BucketShared& sh, const RankArgs& a,
     cnt = w >> 16;
   }
   uint32_t lo = a.edge[b], hi = a.edge[b + 1];
+  const bool outer = lo == a.edge[0] || hi == a.edge[B];                       // uniform: keys beyond the bins are here
   if (b + 1 < B && hi > lo) hi -= 1u;
   sh.bin[2 * tid] = 0;
   sh.bin[2 * tid + 1] = 0;
@@ -634,8 +664,8 @@ __device__ __forceinline__ void bucket_body(BucketShared& sh, const RankArgs& a,
       sh.tok[i2] = p2.y;
     }
     __syncthreads();
-    if (b == 0 || b + 1 == B) {
-      // the outermost buckets reach beyond the sample's first and last key, by any distance
+    if (outer) {
+      // the outermost buckets reach beyond the bins' first and last key, by any distance
       for (uint32_t i = tid; i < n; i += kSortThreads) {
         lo = min(lo, sh.key[i]);
         hi = max(hi, sh.key[i]);

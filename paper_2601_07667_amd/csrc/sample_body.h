@@ -101,7 +101,9 @@ __device__ __forceinline__ uint32_t clamped_bin(uint32_t key, uint32_t lo, uint3
   return (min(max(key, lo), hi) - lo) >> shift;
 }
 
-// Counts the sample's keys in [lo, hi] in bins of width 2^shift from lo.
+// Counts the sample's keys in bins of width 2^shift from lo: those in [lo, hi], or (CLAMP) all, the others in the first
+// and the last bin.
+template <bool CLAMP = false>
 __device__ __forceinline__ void sample_count(SampleShared& sh, const uint32_t (&v)[kSamplePer], int n_s, uint32_t lo, uint32_t hi, int shift) {
   const int tid = threadIdx.x;
   uint32_t* bin = &sh.bin[0].x;
@@ -109,7 +111,7 @@ __device__ __forceinline__ void sample_count(SampleShared& sh, const uint32_t (&
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < kSamplePer; ++u)
-    if (tid + u * kRowThreads < n_s && v[u] >= lo && v[u] <= hi) atomicAdd(&bin[(v[u] - lo) >> shift], 1u);
+    if (tid + u * kRowThreads < n_s && (CLAMP || (v[u] >= lo && v[u] <= hi))) atomicAdd(&bin[clamped_bin(v[u], lo, hi, shift)], 1u);
   __syncthreads();
 }
 

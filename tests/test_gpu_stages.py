@@ -208,6 +208,26 @@ def test_short_vectors_by_bins(ctx, gpu_device, T, kind):
         _select_case(ctx, gpu_device, np.stack([s, -s]), budget, 8)
 
 
+@pytest.mark.parametrize("T", [12289, 40000, 131072, 300000])
+@pytest.mark.parametrize("share", [1e-3, 3e-3, 0.02, 0.3])
+@pytest.mark.parametrize("side", ["above", "below", "both"])
+def test_rank_of_a_cluster_and_outliers(gpu_device, T, share, side):
+    """Scores close to each other and a share of outliers far above, below or on both sides: fewer than the ranking's end
+    buckets are made for, about as many, and more.  Integers, exact."""
+    rng = np.random.default_rng(T)
+    s = (1 + 0.02 * rng.standard_normal(T)).astype(np.float32)
+    out = rng.random(T) < share
+    far = np.exp(4 + 2 * rng.random(T)).astype(np.float32)
+    if side == "below":
+        far = 1 / far
+    elif side == "both":
+        far = np.where(rng.random(T) < 0.5, far, 1 / far)
+    s[out] = far[out]
+    c = asl.Asl(T, 1, 32)
+    _rank_case(c, gpu_device, s)
+    c.close()
+
+
 @pytest.mark.parametrize("rows,T", [(63, 16385), (64, 16385), (64, 32768), (64, 32769)])
 def test_select_rows_one_workgroup_takes(gpu_device, rows, T):
     """The fewest rows and longest that one workgroup per row selects from, and one beyond each: integers, exact."""
