@@ -257,7 +257,7 @@ asl_status asl_device_fault(asl_ctx* ctx, int32_t* fault_out);
 
 /* Measurement aid (not a step of the paper's method; for callers that time the kernels of the
  * calls above).  Kernel ids: 0 score row statistics (pass 1), 1 its combine, 2 score column sums
- * (pass 2), 3 pool, 4 ranking sample, 5 ranking (partition, buckets, or counting), 6 rank-variance
+ * (pass 2), 3 pool, 4 ranking sample, 5 ranking (partition, buckets, or the one launch of short vectors), 6 rank-variance
  * finalisation (or the below-L_min skip), 7 rank-variance partial sums, 8 select histogram, 9 select write,
  * 10 gather, 11 plain-FMA score kernels, 12 the launches of asl_layer_step that carry stages of the ranking, the
  * top-k and the compaction together.  (8 covers the top-k's bound and filter kernels, 9 its finishing kernel
