@@ -26,9 +26,9 @@ pool_kernel(const float* __restrict__ u, int rows, int T, int S_any, float* __re
   const int span = kPoolBlock + 2 * h;
   const float fS = (float)S;
   float total = 0.f;
-  // token t is the top-k's sample number t / stride of every row if it sits on the sample grid
-  const bool sampled = sample != nullptr && t < T && t % sample_stride == 0 && t / sample_stride < n_sample;
-  const int sample_j = sampled ? t / sample_stride : 0;
+  // token t is sample number t / stride of every row if it is the one its stride is sampled at
+  const int sample_j = sample != nullptr ? t / sample_stride : 0;
+  const bool sampled = sample != nullptr && t < T && sample_j < n_sample && (uint32_t)t == sel_sample_position((uint32_t)sample_j, sample_stride);
   for (int row0 = 0; row0 < rows; row0 += kPoolRows) {
     const int nr = min(kPoolRows, rows - row0);
     __syncthreads();                                   // previous group's reads are done

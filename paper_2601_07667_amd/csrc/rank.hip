@@ -22,7 +22,7 @@ namespace asl {
 // Rows of n_s keys from `s`, one per stride (see load_sample), in compact form.
 __global__ void __launch_bounds__(256) rank_sample_kernel(const float* __restrict__ s, int n_s, int stride, uint32_t* __restrict__ out) {
   const uint32_t j = blockIdx.x * 256 + threadIdx.x;
-  if (j < (uint32_t)n_s) out[j] = order_key(s[sample_position(j, stride)]);
+  if (j < (uint32_t)n_s) out[j] = order_key(s[sel_sample_position(j, stride)]);
 }
 
 template <int R>
@@ -58,8 +58,7 @@ RankArgs rank_plan(int T) {
   if (a.n_buckets > 240) a.n_buckets = T <= 264000 ? 240 : T <= 512 * 2048 ? 512 : (T + 2047) / 2048;
   if (a.n_buckets > kRankMaxBuckets) a.n_buckets = kRankMaxBuckets;
   a.n_s = sel_sample_size(T);
-  if (a.n_s > T) a.n_s = T;
-  a.stride = T / a.n_s;
+  a.stride = sel_sample_stride(T);
   return a;
 }
 

@@ -367,7 +367,7 @@ __device__ __forceinline__ void partition_body(PartShared& sh, const RankArgs& a
     if (tid < B) {
       const int i = (int)((uint32_t)tid * (uint32_t)n_s / (uint32_t)B);
       const uint32_t j = num[i];
-      mine = make_uint2(sh.key[i], a.sample != nullptr ? j * (uint32_t)a.stride : sample_position(j, a.stride));
+      mine = make_uint2(sh.key[i], sel_sample_position(j, a.stride));
     }
     __syncthreads();                                    // num and key are read
     if (tid < B) border[tid] = mine;

@@ -20,11 +20,6 @@ struct SampleShared {
   uint32_t out[4];
 };
 
-// Position of sampled key j, one per stride: a scattered place of it, so that a periodic row does not meet a regular sample.
-__device__ __forceinline__ uint32_t sample_position(uint32_t j, int stride) {
-  return j * (uint32_t)stride + (((j * 2654435761u >> 16) * (uint32_t)stride) >> 16);   // < (j + 1) * stride
-}
-
 // Keys u * kRowThreads + tid of a sample of n_s keys (positions past its end repeat another of its keys): compact in
 // `sample`, or, where that is null, read from the row itself.  All loads are in flight together.
 __device__ __forceinline__ void load_sample(const float* __restrict__ row, const uint32_t* __restrict__ sample, int n_s, int stride,
@@ -38,7 +33,7 @@ __device__ __forceinline__ void load_sample(const float* __restrict__ row, const
     float f[kSamplePer];
 #pragma unroll
     for (int u = 0; u < kSamplePer; ++u)
-      if (u * kRowThreads < n_s) f[u] = row[sample_position((uint32_t)min(tid + u * kRowThreads, n_s - 1), stride)];
+      if (u * kRowThreads < n_s) f[u] = row[sel_sample_position((uint32_t)min(tid + u * kRowThreads, n_s - 1), stride)];
 #pragma unroll
     for (int u = 0; u < kSamplePer; ++u) v[u] = u * kRowThreads < n_s ? order_key(f[u]) : 0u;
   }

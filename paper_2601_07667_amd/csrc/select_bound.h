@@ -3,6 +3,13 @@
 // out by every workgroup of the bound kernel they cost it 0.5 us).
 #pragma once
 #include <math.h>
+#include <stdint.h>
+
+#ifdef __HIPCC__
+#define ASL_HOST_DEVICE __host__ __device__
+#else
+#define ASL_HOST_DEVICE
+#endif
 
 #ifndef ASL_SEL_TILE
 #define ASL_SEL_TILE 4096
@@ -20,15 +27,23 @@ constexpr int kShortT = 12288;           // longest score vector that is ranked 
 // kSelShortRows rows on (a call, us, with bound, filter and finish, and so: 8 rows of 16000 16.1, 11.9; 130 rows of 20000
 // 20.2, 15.5; 256 of 30000 27.8, 20.7; 64 of 30000 18.6, 17.0; with fewer rows of that length there is nothing left to gain).
 constexpr int kSelMidT = 16384, kSelShortT = 32768, kSelShortRows = 64;
-// n_s = sel_sample_size(T) keys of a row at positions j * sel_sample_stride(T), j < n_s, for T > kShortT.
+// The sample of a row of T scores: n_s = sel_sample_size(T) keys, one of every sel_sample_stride(T) tokens (all but the
+// row's last few: the stride is rounded up), for T > kShortT.
 constexpr int kSelMaxSample = 8192;    // sampled keys per row
-inline int sel_sample_size(int T) {
+inline int sel_sample_stride(int T) {
   int n = T / 32;
   n = n < 1024 ? 1024 : n;
   const int most = T <= 262144 ? kSelMaxSample / 2 : kSelMaxSample;   // the whole is for the ranking's 1024 buckets
-  return n > most ? most : n;
+  n = n > most ? most : n;
+  return (T + n - 1) / n;
 }
-inline int sel_sample_stride(int T) { return T / sel_sample_size(T); }
+inline int sel_sample_size(int T) { return T / sel_sample_stride(T); }
+// Position of sampled key j among the tokens j * stride .. (j + 1) * stride - 1 that it stands for: a scattered one, so
+// that scores with a period (rows of a grid, repeated text) do not meet a sample of the same period.  With positions
+// j * stride a layer step of 131072 tokens whose scores repeat every 32 had one bucket of 124 K tokens: 4.7 ms.
+ASL_HOST_DEVICE inline uint32_t sel_sample_position(uint32_t j, int stride) {
+  return j * (uint32_t)stride + (((j * 2654435761u >> 16) * (uint32_t)stride) >> 16);
+}
 // Rank m of the sample key taken as the bound: f = n_s / T of the row is sampled, the top-k members
 // among the sample are ~Binomial(n_s, k / T) with mean k f; m = k f + 5 sqrt(c k f) + 4 leaves the
 // bound too low with probability < 1e-6.  c = 1 for single sampled keys; c = `run` when the sample

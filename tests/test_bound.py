@@ -8,13 +8,18 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.fixture(scope="module")
-def bound(tmp_path_factory):
+def _client(tmp_path_factory, name):
     gxx = shutil.which("g++")
     assert gxx, "g++ is part of the toolchain this repository builds with"
-    exe = str(tmp_path_factory.mktemp("bound") / "bound_client")
+    exe = str(tmp_path_factory.mktemp("bound") / name)
     subprocess.run([gxx, "-std=c++17", "-Wall", "-Wextra", "-Werror", "-I", os.path.join(ROOT, "paper_2601_07667_amd", "csrc"),
-                    os.path.join(ROOT, "tests", "bound_client.cpp"), "-o", exe], check=True)
+                    os.path.join(ROOT, "tests", name + ".cpp"), "-o", exe], check=True)
+    return exe
+
+
+@pytest.fixture(scope="module")
+def bound(tmp_path_factory):
+    exe = _client(tmp_path_factory, "bound_client")
 
     def ask(queries):
         out = subprocess.run([exe], input="".join("%d %d %d\n" % q for q in queries), check=True, capture_output=True, text=True).stdout
@@ -48,3 +53,22 @@ def test_ordinary_budgets_keep_the_whole_slack(bound):
     queries = [(T, 2016, runs) for T in (32736, 131040, 262080) for runs in (0, 1)]
     for q, (n_s, run, m, slack, *_) in zip(queries, bound(queries)):
         assert slack == m // 8 > 0, q
+
+
+def test_sample_positions(tmp_path_factory):
+    """One position in every stride of the row up to its last few tokens, and for every period up to 64 (and some
+    longer ones) every phase of it about as often as any other: between half and twice, with six deviations to spare."""
+    sizes = (12289, 16352, 32736, 32769, 65504, 131040, 131072, 262080, 262145, 500001, 1048544, 2097152)
+    out = subprocess.run([_client(tmp_path_factory, "sample_client")], input="\n".join(map(str, sizes)), check=True,
+                         capture_output=True, text=True).stdout
+    for T, line in zip(sizes, out.splitlines()):
+        stride, *pos = (int(x) for x in line.split())
+        assert 900 <= len(pos) <= 8192 and T - stride < len(pos) * stride <= T
+        assert all(j * stride <= p < (j + 1) * stride for j, p in enumerate(pos)), T
+        for period in [*range(2, min(65, stride + 1)), 96, 128]:
+            count, mean = [0] * period, len(pos) / period
+            for p in pos:
+                count[p % period] += 1
+            if stride >= period:
+                assert min(count) >= mean / 2 - 6 * mean ** 0.5 and min(count) > 0, (T, period)
+                assert max(count) <= 2 * mean + 6 * mean ** 0.5, (T, period)

@@ -447,6 +447,41 @@ def test_layer_step_geometries(gpu_device, Hk, N, budget):
     _layer_step_case(gpu_device, synth.iid_layer(sh, N + Hk, name=f"geometry-{Hk}-{N}"))
 
 
+def _step_ms(dev, L):
+    """Median duration of a layer step, in ms, of seven after two that are not counted."""
+    import torch
+    sh = L.shape
+    ctx, p = asl.Asl(sh.N, sh.Hk + 1, sh.Hq * sh.W), gu.params_of(sh)
+    qd, kd, vd = (gu.to_dev(x, sh.dtype, dev) for x in (L.q_obs, L.k, L.v))
+    n_idx = sh.k + sh.W
+    scores = torch.empty((sh.Hk + 1, sh.T), dtype=torch.float32, device=dev)
+    ring, state, stat = torch.zeros((sh.L_obs, sh.T), dtype=torch.int32, device=dev), asl.new_state(dev), asl.new_stat(dev)
+    I = torch.empty((sh.Hk + 1, n_idx), dtype=torch.int32, device=dev)
+    Kc = torch.empty((sh.Hk, n_idx, sh.d), dtype=kd.dtype, device=dev)
+    Vc, times = torch.empty_like(Kc), []
+    for layer in range(9):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        ctx.asl_layer_step(p, qd, kd, vd, layer, 1 << 30, sh.L_obs, sh.tau, scores, ring, state, stat, I, Kc, Vc)
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b))
+    ctx.close()
+    return sorted(times[2:])[3]
+
+
+def test_layer_step_of_scores_with_a_period(gpu_device):
+    """Keys that repeat every 32 tokens, where every 32nd token is sampled: the step's results are those of the single
+    calls, and it takes no more than a few times as long as for keys without a period (a sample that meets one
+    phase only made it 190 times as long)."""
+    sh = synth.Shape(Hq=2, Hk=2, d=64, N=131040 + 16, W=16, S=1, budget=2048)
+    L = synth.iid_layer(sh, 77, name="period-32")
+    plain = _step_ms(gpu_device, L)
+    L.k[:] = np.tile(L.k[:, :32], (1, sh.N // 32 + 1, 1))[:, :sh.N]
+    _layer_step_case(gpu_device, L)
+    assert _step_ms(gpu_device, L) < 5 * plain + 0.1
+
+
 def test_layer_step_is_reproducible(gpu_device):
     """200 repetitions of asl_layer_step on the C3 layer, and of the single ranking and top-k calls on its
     scores: every output has the same bits every time (the workgroups of the ranking and statistic

@@ -95,9 +95,10 @@ def test_rank_beyond_the_small_tile_limit(gpu_device, T):
 
 
 def _rank_sample_positions(T):
-    """Where a ranking of T > 12288 scores takes its sample from a vector that nobody left one of."""
-    n = min(8192, max(1024, T // 32))
-    j, stride = np.arange(n, dtype=np.uint64), T // n
+    """Where a ranking of T > 12288 scores takes its sample from."""
+    most = min(4096 if T <= 262144 else 8192, max(1024, T // 32))
+    stride = -(-T // most)
+    j = np.arange(T // stride, dtype=np.uint64)
     return (j * stride + (((j * 2654435761 % 2 ** 32) >> 16) * stride >> 16)).astype(np.int64)
 
 
