@@ -45,7 +45,7 @@ size_t carve(char* base, int32_t max_seq_len, int32_t max_kv_heads, int32_t max_
   w.u_group = (float*)take(rows * N * sizeof(float));
   w.rank_pairs = (uint2*)take(N * sizeof(uint2));
   w.rank_count = (uint32_t*)take(N * sizeof(uint32_t));         // tiles x buckets <= T for every T (see rank_plan)
-  w.rank_edge = (uint32_t*)take((size_t)(asl::kRankMaxBuckets + 1) * sizeof(uint32_t));
+  w.rank_edge = (uint32_t*)take((size_t)(asl::kRankMaxBuckets + 2) * sizeof(uint32_t));
   w.rank_sample = (uint32_t*)take((size_t)asl::kSelMaxSample * sizeof(uint32_t));
   const size_t sel_tiles = (N + asl::kSelTile - 1) / asl::kSelTile;
   w.sel_rows = (int)(rows < (size_t)asl::kSelMaxRowsAtOnce ? rows : (size_t)asl::kSelMaxRowsAtOnce);

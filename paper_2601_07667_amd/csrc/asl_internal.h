@@ -57,7 +57,7 @@ struct Workspace {
   // ranking
   uint2* rank_pairs;       // [T] (key, token) pairs, grouped by bucket inside each tile
   uint32_t* rank_count;    // [n_tiles][n_buckets] where each tile's pairs of a bucket begin, and how many they are
-  uint32_t* rank_edge;     // [kRankMaxBuckets + 1] first key of each bucket
+  uint32_t* rank_edge;     // [kRankMaxBuckets + 2] first key of each bucket, and whether they are there
   uint32_t* rank_sample;   // [kSelMaxSample] sampled keys of a vector that nobody left a sample of
   // select
   uint32_t* sel_sample;    // [sel_rows][kSelMaxSample] sampled keys of freshly pooled score rows

@@ -242,33 +242,208 @@ struct RankArgs {
   int T, n_tiles, tile_log;      // tiles of 2^tile_log tokens
   int tile_step;                 // a power of two, at least half of n_tiles
   int n_buckets;
+  int heavy;                     // sampled keys of a bin beyond which it is not one bucket's or part of one
+  float per_key, per_key_deep;   // buckets per sampled key; where the sample has heavy bins (the last bucket is left to what
+                                 // comes after all sampled keys)
   uint2* pairs;                  // [T] (key, token), grouped by bucket inside each tile
   uint32_t* count;               // [n_tiles][n_buckets] a tile's first place of the bucket | its tokens of the bucket << 16
-  uint32_t* edge;                // [n_buckets + 1] first key of each bucket; the last one's last key
+  uint32_t* edge;                // [n_buckets + 1] first key of each bucket; the last one's last key; then 1: there are but the first and the last
   int32_t* rank_out;
 };
 
-constexpr int kSortedSample = 4096;                     // most keys of a sample that is sorted
+// Bucket of what has `place` sampled keys before it, where the sample has heavy bins.
+__device__ __forceinline__ uint32_t bucket_of_place(const RankArgs& a, uint32_t place) {
+  return min((uint32_t)((float)place * a.per_key_deep), (uint32_t)a.n_buckets - 1u);     // monotone whatever the rounding
+}
+
+constexpr uint32_t kHeavyBin = 0x80000000u;
+constexpr int kMaxHeavyBins = 2 * kRankMaxBuckets / 3 + 1;   // of one level: each holds more than 3/2 of a bucket's worth of the sample
 struct PartShared {
-  SampleShared s;                                       // bin: the sample's counts, then the bucket of each bin
+  SampleShared s;                                       // bin: the sample's counts, then the bucket of each bin, or kHeavyBin | its number
   union {
     uint16_t cnt[kSortWaves][kRankMaxBuckets];          // tokens per wavefront and bucket, then their first places
-    struct {                                            // a sample to be sorted (its numbers in s.bin)
-      uint32_t key[kSortedSample];
-      DigitShared digit;
+    struct {                                            // of heavy bins (heavy_bins), until every token has its bucket
+      union {
+        uint32_t words[4 * kMaxHeavyBins + kSampleBins];
+        struct {
+          uint32_t here[4 * kMaxHeavyBins];             // of a single key: sampled in earlier tiles, in this one
+          uint4 sub4[kSampleBins / 4];                  // sub-bins: their counts, then sampled keys before | number + 1 of a heavy one << 16
+        };
+      };
+      uint32_t lo[2 * kMaxHeavyBins], hi[2 * kMaxHeavyBins];   // smallest and largest sampled key
+      uint32_t place[2 * kMaxHeavyBins];                // sampled keys before (a sub-bin: before it, from all bins' first sub-bin on) | in it << 16
+      uint32_t cut[kMaxHeavyBins];                      // a bin's first sub-bin | log2 of their number << 16
     };
   };
 };
-static_assert(sizeof(uint16_t) * kSortedSample <= sizeof(SampleShared::bin) && kSortedSample >= 4 * kRankMaxBuckets &&
-                  sizeof(uint2) * kRankMaxBuckets <= sizeof(SampleShared::bin), "a sorted sample's numbers, then its borders, are held in bin");
+static_assert(sizeof(PartShared) <= 65536, "static LDS");
+
+// Sub-bin of a key of heavy bin h, or the bin's nearest one.
+__device__ __forceinline__ uint32_t sub_bin(const PartShared& sh, uint32_t h, uint32_t key) {
+  const uint32_t cut = sh.cut[h], lo = sh.lo[h], hi = sh.hi[h];
+  return (cut & 0xffffu) + clamped_bin(key, lo, hi, bin_shift(lo, hi, (int)(cut >> 16)));
+}
+
+// Bins with more than a.heavy sampled keys: scores that repeat, or that lie close together beside outliers that
+// spread the bins.  (c, first, h: the thread's four bins, the sampled keys and the heavy bins before them.)
+//  - A heavy bin of one sampled key gets the buckets strictly between those of its neighbours; the tokens with that key are
+//    shared out among them in token order, by how many of the sampled ones come before, so that such a bucket
+//    holds equal keys only.
+//  - Any other is cut into sub-bins between its smallest and largest sampled key: of 4096 in all as many as its share of the
+//    sample.  Sub-bins that are still heavy and hold one sampled key are treated as above; with several they make
+//    one bucket of more than it should have.
+// A wavefront's instruction takes 16 cycles of the unit here, so it is their number that counts: ~4.5 us for four sampled keys
+// a thread.  (Sorting the sample instead took 18 us in every tile.  Ranking alone, us, so and sorted: 131040 scores, a third zeros
+// 20.4, 42.5; rounded to whole numbers 26.2, 41.6; with a period of 32 19.6, 39.7; a million equal ones 30, 102.)
+__device__ __forceinline__ void heavy_bins(PartShared& sh, const RankArgs& a, const uint32_t (&v)[kSamplePer], uint32_t lo, int shift,
+                                           const uint4& c, uint32_t first, uint32_t h, uint32_t n_heavy, int me) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const uint32_t n_s = (uint32_t)a.n_s, most = (uint32_t)a.heavy;
+  uint32_t* lut = &sh.s.bin[0].x;
+  uint32_t* sub = &sh.sub4[0].x;
+  auto each = [&](auto f) {                             // the thread's sampled keys; uniform, `valid` is not
+#pragma unroll
+    for (int u = 0; u < kSamplePer; ++u)
+      if (u * kRowThreads < (int)n_s) f(u, (uint32_t)(tid + u * kRowThreads) < n_s);
+  };
+  int in[kSamplePer];                                   // heavy bin of each key, -1: none
+  auto ranges = [&] {                                   // lo and hi of these bins
+    each([&](int u, bool) {
+      if (in[u] >= 0) {                                 // any of the bin's keys
+        __hip_atomic_store(&sh.lo[in[u]], v[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_store(&sh.hi[in[u]], v[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    });
+    __syncthreads();
+    // equal keys take no part, and the wavefront's keys of one bin are put together first: atomics on one word come one
+    // after the other
+    auto widen = [&](int b, uint32_t k0, uint32_t k1) {
+      if (k0 < __hip_atomic_load(&sh.lo[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) atomicMin(&sh.lo[b], k0);
+      if (k1 > __hip_atomic_load(&sh.hi[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) atomicMax(&sh.hi[b], k1);
+    };
+    const uint64_t some = __ballot(in[0] >= 0);
+    const int one = some == 0ull ? -2 : __builtin_amdgcn_readlane(in[0], __ffsll((unsigned long long)some) - 1);
+    uint32_t k0 = 0xffffffffu, k1 = 0u;
+    each([&](int u, bool) {
+      if (in[u] == one) {
+        k0 = min(k0, v[u]);
+        k1 = max(k1, v[u]);
+      } else if (in[u] >= 0) {
+        widen(in[u], v[u], v[u]);
+      }
+    });
+    k0 = wave_min(k0);
+    k1 = wave_max(k1);
+    if (some != 0ull && lane == 0) widen(one, k0, k1);
+    __syncthreads();
+  };
+  // counts in[u]'s keys: those of a single key in sh.here (earlier tiles', this one's), others in their sub-bins
+  auto count = [&](bool sub_bins) {
+    const int last = (me + 1) << a.tile_log, first_here = me << a.tile_log;
+    Repeated rep = {};
+    each([&](int u, bool) {
+      uint32_t word = 0u;
+      bool valid = in[u] >= 0;
+      if (valid) {
+        const uint32_t b = (uint32_t)in[u];
+        if (sh.lo[b] == sh.hi[b]) {
+          const int t = (int)sel_sample_position((uint32_t)(tid + u * kRowThreads), a.stride);
+          word = 2u * b + (t >= first_here ? 1u : 0u);
+          valid = t < last;
+        } else {
+          valid = sub_bins;
+          if (sub_bins) word = 4u * kMaxHeavyBins + sub_bin(sh, b, v[u]);
+        }
+      }
+      if (u == 0) rep = find_repeated(word, valid);
+      const uint32_t n = add_for(rep, word, valid);
+      if (n != 0u) atomicAdd(&sh.words[word], n);
+    });
+    __syncthreads();
+  };
+
+  const uint32_t cs[4] = {c.x, c.y, c.z, c.w};
+  uint32_t entry[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    entry[i] = bucket_of_place(a, first);
+    if (cs[i] > most) {
+      entry[i] = kHeavyBin | h;
+      sh.place[h] = first | (cs[i] << 16);
+      // shares rounded down: [kSampleBins first / n_s, kSampleBins (first + cs) / n_s) are disjoint and hold 2^log
+      sh.cut[h++] = first * (uint32_t)kSampleBins / n_s | (uint32_t)(31 - __clz((int)(cs[i] * (uint32_t)kSampleBins / n_s))) << 16;
+    }
+    first += cs[i];
+  }
+  sh.s.bin[tid] = make_uint4(entry[0], entry[1], entry[2], entry[3]);         // own counts only were read
+  sh.sub4[tid] = make_uint4(0u, 0u, 0u, 0u);
+  for (int i = tid; i < 4 * kMaxHeavyBins; i += kRowThreads) sh.here[i] = 0u;
+  __syncthreads();
+  each([&](int u, bool valid) {
+    const uint32_t e = valid ? lut[(v[u] - lo) >> shift] : 0u;
+    in[u] = (e & kHeavyBin) != 0u ? (int)(e & 0xffffu) : -1;
+  });
+  ranges();
+  count(true);
+  const uint4 c2 = sh.sub4[tid];
+  const uint32_t cs2[4] = {c2.x, c2.y, c2.z, c2.w};
+  uint32_t x = c2.x + c2.y + c2.z + c2.w, total;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) x += cs2[i] > most ? 65536u : 0u;
+  block_prefix(sh.s.red, x, x, total);
+  if (total == 0u) return;                              // uniform: single keys only
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t before = x & 0xffffu, number = n_heavy + (x >> 16);         // < 2 kMaxHeavyBins
+    entry[i] = before;
+    if (cs2[i] > most) {
+      entry[i] |= (number + 1u) << 16;
+      sh.place[number] = before | (cs2[i] << 16);
+      x += 65536u;
+    }
+    x += cs2[i];
+  }
+  sh.sub4[tid] = make_uint4(entry[0], entry[1], entry[2], entry[3]);
+  __syncthreads();
+  if (total >> 16 == 0u) return;                        // uniform
+  each([&](int u, bool) {
+    const int b = in[u];
+    if (b >= 0) in[u] = sh.lo[b] == sh.hi[b] ? -1 : (int)(sub[sub_bin(sh, (uint32_t)b, v[u])] >> 16) - 1;
+  });
+  ranges();
+  count(false);
+}
+
+// Bucket of token t (in tile `me`) with this key, where the sample has heavy bins.  Monotone in (key, token).
+__device__ __forceinline__ uint32_t bucket_of_token(const PartShared& sh, const RankArgs& a, uint32_t lo, uint32_t hi, int shift, uint32_t key,
+                                                    int t, int me) {
+  const uint32_t* sub = &sh.sub4[0].x;
+  const uint32_t e = (&sh.s.bin[0].x)[clamped_bin(key, lo, hi, shift)];
+  if ((e & kHeavyBin) == 0u) return e;
+  uint32_t h = e & 0xffffu, place = sh.place[h] & 0xffffu, held = sh.place[h] >> 16;
+  uint32_t b0 = bucket_of_place(a, place), b1 = bucket_of_place(a, place + held);
+  if (sh.lo[h] != sh.hi[h]) {
+    // in buckets of their own, if there are any between the neighbours'
+    const uint32_t at = sh.cut[h] & 0xffffu, e2 = sub[sub_bin(sh, h, key)], least = b1 > b0 + 1u ? b0 + 1u : b0, last = b1 > b0 + 1u ? b1 - 1u : b1;
+    place += (e2 & 0xffffu) - (sub[at] & 0xffffu);
+    b0 = min(max(bucket_of_place(a, place), least), last);
+    h = (e2 >> 16) - 1u;
+    if (e2 >> 16 == 0u || sh.lo[h] != sh.hi[h]) return b0;
+    held = sh.place[h] >> 16;
+    b1 = min(max(bucket_of_place(a, place + held), least), last);
+  }
+  if (key < sh.lo[h]) return b0;
+  if (key > sh.lo[h] || b1 <= b0 + 1u) return b1;
+  const uint32_t before = sh.here[2u * h] + (sh.here[2u * h + 1u] * (uint32_t)(t - (me << a.tile_log)) >> a.tile_log);   // <= held
+  return b0 + 1u + min((uint32_t)((float)(before * (b1 - b0 - 1u)) * __builtin_amdgcn_rcpf((float)held)), b1 - b0 - 2u);
+}
 
 // Launch 1 for tile `me` (kSortThreads threads, R tokens each): the tile's (key, token) pairs, grouped by bucket and
 // in token order inside one, go to the tile's own stretch of `pairs`, and where each bucket's begin to `count`.
 // Every tile works out the same bucket borders from the same sample, so tiles agree on nothing else and wait for
 // nobody.  Bound by latency: the loads, three counts with a scan each, the stores.
-// Borders are those of the sample's histogram bins (narrowed to where the keys are, if outliers spread them): bucket b holds the bins whose first sampled key has a place in
-// [b, b + 1) n_s / B.  Where a bin still holds three buckets' worth or more (scores that repeat) the sample is sorted
-// instead, and every n_s / B-th pair (key, token) of it is a border: equal scores are then shared out by token.
+// Borders are those of the sample's histogram bins: bucket b holds the bins whose first sampled key has a place in
+// [b, b + 1) n_s / B.  Where a bin holds more than a.heavy sampled keys, see heavy_bins.
 template <int R>
 __device__ __forceinline__ void partition_body(PartShared& sh, const RankArgs& a, int me) {
   const int tid = threadIdx.x, wave = uniform_wave(), lane = tid & 63, T = a.T, B = a.n_buckets;
@@ -286,49 +461,37 @@ __device__ __forceinline__ void partition_body(PartShared& sh, const RankArgs& a
     hi = max(hi, v[u]);
   }
   block_min_max(sh.s.red, lo, hi);
-  const uint32_t hi_all = hi;
-  uint32_t first, total, most;
-  uint4 c;
-  int shift;
-  bool sorted, ends = false;
-  for (int round = 0;; ++round) {
-    shift = bin_shift(lo, hi, kSampleBinBits);
-    sample_count<true>(sh.s, v, a.n_s, lo, hi, shift);
-    c = sh.s.bin[tid];
-    block_scan<true>(sh.s.red, c.x + c.y + c.z + c.w, max(max(c.x, c.y), max(c.z, c.w)), first, total, most);
-    sorted = B > 1 && most * (uint32_t)B > 3u * (uint32_t)a.n_s;               // uniform
-    if (!sorted || shift == 0 || round == 2) break;
-    // Some outliers may have spread the bins over a range that hardly any score is in: again between the keys one and a half
-    // buckets from either end; what is outside is counted with the first and the last bin, which are buckets of their own.
-    ends = B >= 3;
-    const uint32_t q = max(3u * (uint32_t)a.n_s / (2u * (uint32_t)B), 1u), at[2] = {q, (uint32_t)a.n_s - 1u - q};
-    const uint32_t cs[4] = {c.x, c.y, c.z, c.w};
-    uint32_t f = first;
+  const int shift = bin_shift(lo, hi, kSampleBinBits);
+  sample_count<true>(sh.s, v, a.n_s, lo, hi, shift);
+  const uint4 c = sh.s.bin[tid];
+  const uint32_t cs[4] = {c.x, c.y, c.z, c.w};
+  uint32_t first = c.x + c.y + c.z + c.w, total;        // sampled keys before the thread's bins | heavy bins before << 16
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      for (int e = 0; e < 2; ++e)
-        if (f <= at[e] && at[e] < f + cs[i]) sh.s.out[e] = (uint32_t)(4 * tid + i);     // one bin of the workgroup
-      f += cs[i];
-    }
-    __syncthreads();
-    const uint32_t l = lo + (sh.s.out[0] << shift), h = lo + (sh.s.out[1] << shift), mask = (1u << shift) - 1u;
-    hi = hi - h < mask ? hi : h + mask;
-    lo = l;
-  }
+  for (int i = 0; i < 4; ++i) first += cs[i] > (uint32_t)a.heavy ? 65536u : 0u;
+  block_prefix(sh.s.red, first, first, total);
+  const uint32_t n_heavy = total >> 16;
+  const bool deep = n_heavy != 0u;                      // uniform
   uint32_t* lut = &sh.s.bin[0].x;
-  uint2* border = reinterpret_cast<uint2*>(sh.s.bin);   // [b]: first pair of bucket b, b > 0
-  if (!sorted) {
-    const uint32_t base = ends ? 1u : 0u, top = (uint32_t)B - 1u - base, past = (hi - lo) >> shift;
-    const float per_key = (float)(top - base + 1u) / (float)a.n_s;             // monotone in `first` whatever the rounding
-    const uint32_t cs[4] = {c.x, c.y, c.z, c.w};
-    uint32_t bucket[4], f = first;
+  uint32_t key[R], d[R], off[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) key[r] = order_key(f[r]);
+  if (me == 0 && tid == 0) a.edge[B + 1] = deep ? 1u : 0u;
+  if (__builtin_expect(deep, 0)) {
+    if (me == 0 && tid == 0) {
+      a.edge[0] = lo;
+      a.edge[B] = hi;
+    }
+    heavy_bins(sh, a, v, lo, shift, c, first & 0xffffu, first >> 16, n_heavy, me);
+#pragma unroll
+    for (int r = 0; r < R; ++r) d[r] = bucket_of_token(sh, a, lo, hi, shift, key[r], e0 + 64 * r, me);
+    __syncthreads();                                    // the tables are read, the counts go there
+  } else {
+    const uint32_t past = (hi - lo) >> shift;
+    uint32_t bucket[4], f1 = first;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const uint32_t j = (uint32_t)(4 * tid + i);
-      bucket[i] = min(base + (uint32_t)((float)f * per_key), top);
-      if (ends && j == 0u) bucket[i] = 0u;
-      if (ends && j >= past) bucket[i] = (uint32_t)B - 1u;
-      f += cs[i];
+      bucket[i] = min((uint32_t)((float)f1 * a.per_key), (uint32_t)B - 1u);     // monotone whatever the rounding
+      f1 += cs[i];
     }
     sh.s.bin[tid] = make_uint4(bucket[0], bucket[1], bucket[2], bucket[3]);   // own counts only were read
     __syncthreads();
@@ -344,37 +507,6 @@ __device__ __forceinline__ void partition_body(PartShared& sh, const RankArgs& a
       if (tid == kSortThreads - 1)
         for (uint32_t b = prev + 1u; b <= (uint32_t)B; ++b) a.edge[b] = hi;
     }
-  } else {
-    // one of every 2^thin keys of it: four a bucket are enough here, and sorting costs what it sorts (all 4096, 128 K
-    // scores, a third of them equal: 55 us the ranking, with 1024 of them 50)
-    const int need = max(4 * B, 1024);
-    const int thin = a.n_s >= 8 * need ? 3 : a.n_s >= 4 * need ? 2 : a.n_s >= 2 * need ? 1 : 0;
-    const int n_s = min(a.n_s >> thin, kSortedSample);
-    uint16_t* num = reinterpret_cast<uint16_t*>(sh.s.bin);
-    __syncthreads();                                    // the counts were read
-#pragma unroll
-    for (int u = 0; u < kSamplePer; ++u) {
-      const int j = tid + u * kSortThreads, i = j >> thin;
-      const uint32_t pick = (uint32_t)i * 2654435761u >> 24;                 // any of the group's, for periodic scores
-      if ((((uint32_t)j ^ pick) & ((1u << thin) - 1u)) == 0u && i < n_s) {
-        sh.key[i] = v[u];
-        num[i] = (uint16_t)j;
-      }
-    }
-    __syncthreads();
-    sort_by_digits<kSortedSample / kSortThreads>(sh.key, num, sh.digit, sh.s.red, n_s);
-    uint2 mine = make_uint2(0u, 0u);
-    if (tid < B) {
-      const int i = (int)((uint32_t)tid * (uint32_t)n_s / (uint32_t)B);
-      const uint32_t j = num[i];
-      mine = make_uint2(sh.key[i], sel_sample_position(j, a.stride));
-    }
-    __syncthreads();                                    // num and key are read
-    if (tid < B) border[tid] = mine;
-    if (me == 0) {
-      if (tid < B) a.edge[tid] = mine.x;                // bucket 0: the sample's first key
-      if (tid == 0) a.edge[B] = hi_all;
-    }
   }
   {
     // clear the wavefronts' counts
@@ -386,23 +518,9 @@ __device__ __forceinline__ void partition_body(PartShared& sh, const RankArgs& a
 
   // places inside the tile: equal buckets of a wavefront are ranked by ballots, stable by construction
   const int n_bits = B > 1 ? 32 - __clz(B - 1) : 0;
-  uint32_t key[R], d[R], off[R];
+  if (!deep) {                                          // uniform
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    key[r] = order_key(f[r]);
-    if (!sorted) {                                      // uniform
-      d[r] = lut[clamped_bin(key[r], lo, hi, shift)];
-    } else {
-      const uint32_t t = (uint32_t)(e0 + 64 * r);
-      int b = 0;                                        // last border that is not behind the pair
-      for (int step = kRankMaxBuckets / 2; step > 0; step >>= 1) {
-        if (b + step < B) {
-          const uint2 x = border[b + step];
-          if (x.x < key[r] || (x.x == key[r] && x.y <= t)) b += step;
-        }
-      }
-      d[r] = (uint32_t)b;
-    }
+    for (int r = 0; r < R; ++r) d[r] = lut[clamped_bin(key[r], lo, hi, shift)];
   }
 #pragma unroll
   for (int r = 0; r < R; ++r) {
@@ -426,7 +544,7 @@ __device__ __forceinline__ void partition_body(PartShared& sh, const RankArgs& a
     for (int w = 0; w < kSortWaves; ++w) tot += sh.cnt[w][tid];
   }
   uint32_t start;
-  block_scan<true>(sh.s.red, tot, 0u, start, total, most);
+  block_prefix(sh.s.red, tot, start, total);
   if (tid < B) {
     a.count[(int64_t)me * B + tid] = start | (tot << 16);
     uint32_t run = start;
@@ -459,20 +577,203 @@ struct BucketShared {
   uint32_t key[kBucketCap];
   uint32_t tok[kBucketCap];
   union {
-    uint32_t bin[kBucketBins + 1];
+    struct {
+      uint32_t bin[kBucketBins + 1];
+      uint32_t cut[kBucketBins];                        // bucket_by_sub_bins
+    };
     DigitShared digit;
   };
   uint32_t red[2 * kSortWaves];
   uint32_t seg_off[kRankMaxTiles + 1];                  // place of each tile's pairs in the bucket
   uint32_t seg_src[kRankMaxTiles];                      // ... and in `pairs`
-  RankArgs args;                                        // operands of bucket_by_ranges
+  struct Pairs {                                        // operands of bucket_by_ranges
+    const uint2* pairs;
+    int32_t* rank_out;
+    int T, n_tiles, tile_step;
+  } args;
   uint32_t n, base;
 };
+
+// Pairs of the bin at places i0 .. i1 - 1 that come before (key, tok): four at a time, a bin's length in memory round trips
+// otherwise.
+__device__ __forceinline__ uint32_t before_in_bin(const BucketShared& sh, uint32_t i0, uint32_t i1, uint32_t key, uint32_t tok) {
+  uint32_t c = 0;
+  if (i1 - i0 > 1u)
+#pragma unroll 1
+    for (uint32_t i = i0; i < i1; i += 4u) {
+#pragma unroll
+      for (uint32_t q = 0; q < 4u; ++q) {
+        const uint32_t j = min(i + q, i1 - 1u), k = sh.key[j], t = sh.tok[j];
+        c += (i + q < i1 && (k < key || (k == key && t < tok))) ? 1u : 0u;
+      }
+    }
+  return c;
+}
+
+// Ranks of the bucket's pairs (as bucket_by_bins has them: key, tok, slot of pair tid + r kSortThreads) where bins longer than
+// kBinMax hold one key each: a run of equal keys is ordered by token, which is the pairs' order.  Its pairs are counted
+// by groups of 64 (a wavefront's for one r), by ballots over the run's number; every later group begins where the ones before
+// end.  The other bins as in bucket_by_bins.  c0, c1, first: the thread's bins and the pairs before them.
+template <int R>
+__device__ __forceinline__ void bucket_with_runs(BucketShared& sh, int n, uint32_t lo, uint32_t hi, const uint32_t (&key)[R], const uint32_t (&tok)[R],
+                                                 uint32_t (&slot)[R], uint32_t c0, uint32_t c1, uint32_t first, uint32_t base, int T,
+                                                 int32_t* __restrict__ rank_out) {
+  constexpr int kRuns = 16 * R, kGroups = R * kSortWaves;                      // of more than kBinMax pairs each: fewer than 1024 R / 64
+  static_assert(kRuns * kGroups <= 2 * kBucketBins && kBinMax >= 64, "two counts a word of sh.cut");
+  const int tid = threadIdx.x, wave = uniform_wave(), shift = bin_shift(lo, hi, kBucketBinBits);
+  uint16_t* cnt = reinterpret_cast<uint16_t*>(sh.cut);  // [kGroups][kRuns]
+  uint32_t run = (c0 > kBinMax ? 1u : 0u) + (c1 > kBinMax ? 1u : 0u), n_runs;
+  const uint32_t mine = run;
+  block_prefix(sh.red, run, run, n_runs);
+  // first place | number of its run + 1 << 16
+  sh.bin[2 * tid] = first | (c0 > kBinMax ? (run + 1u) << 16 : 0u);
+  sh.bin[2 * tid + 1] = (first + c0) | (c1 > kBinMax ? (run + mine) << 16 : 0u);
+  if (tid == 0) sh.bin[kBucketBins] = (uint32_t)n;
+  sh.cut[tid] = 0;
+  sh.cut[tid + kSortThreads] = 0;
+  __syncthreads();
+  const int n_bits = 32 - __clz((int)n_runs);
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t w = tid + r * kSortThreads < n ? sh.bin[clamped_bin(key[r], lo, hi, shift)] >> 16 : 0u;
+    uint64_t peers = __ballot(w != 0u);
+    for (int b = 0; b < n_bits; ++b) {
+      const bool bit = (w >> b) & 1u;
+      const uint64_t bal = __ballot(bit);
+      peers &= bit ? bal : ~bal;
+    }
+    if (w != 0u) {
+      slot[r] = lanes_below(peers);
+      if (slot[r] == 0u) cnt[(r * kSortWaves + wave) * kRuns + (int)w - 1] = (uint16_t)__popcll(peers);
+    }
+    if (R > 2) __builtin_amdgcn_sched_barrier(0);
+  }
+  __syncthreads();
+  if (tid < (int)n_runs) {
+    uint32_t sum = 0;
+    for (int g = 0; g < kGroups; g += 16) {             // 16 reads in flight together
+      uint32_t c[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) c[q] = cnt[(g + q) * kRuns + tid];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        cnt[(g + q) * kRuns + tid] = (uint16_t)sum;
+        sum += c[q];
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (tid + r * kSortThreads < n) {
+      const uint32_t w = sh.bin[clamped_bin(key[r], lo, hi, shift)], i = (w & 0xffffu) + slot[r];
+      if (w >> 16 == 0u) {                              // then i < n
+        sh.key[i] = key[r];
+        sh.tok[i] = tok[r];
+      }
+    }
+    if (R > 2) __builtin_amdgcn_sched_barrier(0);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (tid + r * kSortThreads < n) {
+      const uint32_t b = clamped_bin(key[r], lo, hi, shift), w = sh.bin[b], i0 = w & 0xffffu, i1 = sh.bin[b + 1] & 0xffffu;
+      uint32_t c = base + i0;
+      if (w >> 16 != 0u)
+        c += cnt[(r * kSortWaves + wave) * kRuns + (int)(w >> 16) - 1] + slot[r];
+      else
+        c += before_in_bin(sh, i0, i1, key[r], tok[r]);
+      if (tok[r] < (uint32_t)T) rank_out[tok[r]] = (int32_t)c;               // always true
+    }
+    if (R > 2) __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// Ranks of the bucket's pairs where some bin is longer than kBinMax (keys close together beside outliers, or repeated): every
+// bin of c >= 8 keys is cut into about c / 6 sub-bins, two counts a word of sh.bin; where every long bin is one key,
+// bucket_with_runs.  key, tok, slot, c0, c1, first: as there.  Returns false, with sh.key and sh.tok as they were, where
+// repeated keys share bins or a sub-bin is still too long.
+// 131040 scores within 2 %, one far away: 24.2 us by digits, so 16.0; of a few values 28.4 by digits, so 26.2.
+template <int R>
+__device__ __forceinline__ bool bucket_by_sub_bins(BucketShared& sh, int n, uint32_t lo, uint32_t hi, uint32_t (&key)[R], uint32_t (&tok)[R],
+                                                   uint32_t (&slot)[R], uint32_t c0, uint32_t c1, uint32_t first, uint32_t base, int T,
+                                                   int32_t* __restrict__ rank_out) {
+  const int tid = threadIdx.x, shift = bin_shift(lo, hi, kBucketBinBits);
+  uint32_t alike = 0, total;                            // long bins' keys that are the one picked | those that are not << 16
+#pragma unroll
+  for (int r = 0; r < R; ++r)                           // any of the bin's keys
+    __hip_atomic_store(&sh.cut[clamped_bin(key[r], lo, hi, shift)], key[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t b = clamped_bin(key[r], lo, hi, shift);
+    if (tid + r * kSortThreads < n && sh.bin[b] > kBinMax) alike += sh.cut[b] == key[r] ? 1u : 65536u;
+  }
+  block_prefix(sh.red, alike, alike, total);
+  if (total >> 16 == 0u) {                              // uniform
+    bucket_with_runs<R>(sh, n, lo, hi, key, tok, slot, c0, c1, first, base, T, rank_out);
+    return true;
+  }
+  if (8u * (total & 0xffffu) > total >> 16) return false;   // uniform: repeated keys, several to a bin
+  auto log_of = [&](uint32_t c) { return c < 8u ? 0 : min(29 - __clz((int)c), shift); };
+  const int l0 = log_of(c0), l1 = log_of(c1);
+  uint32_t at, most;
+  block_prefix(sh.red, (1u << l0) + (1u << l1), at, total);                    // total <= kBucketBins + kBucketCap / 4
+  static_assert(kBucketCap / 4 <= kBucketBins, "two counts a word");
+  sh.cut[2 * tid] = at | (uint32_t)l0 << 16;
+  sh.cut[2 * tid + 1] = (at + (1u << l0)) | (uint32_t)l1 << 16;
+  sh.bin[2 * tid] = 0;
+  sh.bin[2 * tid + 1] = 0;
+  __syncthreads();
+  auto sub_of = [&](uint32_t k) {
+    const uint32_t off = min(max(k, lo), hi) - lo, cut = sh.cut[off >> shift];
+    return (cut & 0xffffu) + ((off & ((1u << shift) - 1u)) >> (shift - (int)(cut >> 16)));
+  };
+  auto first_of = [&](uint32_t b) { return (sh.bin[b >> 1] >> (16u * (b & 1u))) & 0xffffu; };
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    slot[r] = 0;
+    if (tid + r * kSortThreads < n) {
+      const uint32_t b = sub_of(key[r]), up = 16u * (b & 1u);
+      slot[r] = (atomicAdd(&sh.bin[b >> 1], 1u << up) >> up) & 0xffffu;
+    }
+    if (R > 2) __builtin_amdgcn_sched_barrier(0);
+  }
+  __syncthreads();
+  const uint32_t w0 = sh.bin[2 * tid], w1 = sh.bin[2 * tid + 1];
+  const uint32_t a0 = w0 & 0xffffu, a1 = w0 >> 16, a2 = w1 & 0xffffu, a3 = w1 >> 16;
+  block_scan<true>(sh.red, a0 + a1 + a2 + a3, max(max(a0, a1), max(a2, a3)), at, total, most);
+  if (most > kBinMax) return false;                     // uniform
+  sh.bin[2 * tid] = at | (at + a0) << 16;               // first places, at most n < 2^16
+  sh.bin[2 * tid + 1] = (at + a0 + a1) | (at + a0 + a1 + a2) << 16;
+  if (tid == 0) sh.bin[kBucketBins] = (uint32_t)n;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (tid + r * kSortThreads < n) {
+      const uint32_t i = first_of(sub_of(key[r])) + slot[r];     // < n
+      sh.key[i] = key[r];
+      sh.tok[i] = tok[r];
+    }
+    if (R > 2) __builtin_amdgcn_sched_barrier(0);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (tid + r * kSortThreads < n) {
+      const uint32_t b = sub_of(key[r]), i0 = first_of(b), i1 = first_of(b + 1u);
+      const uint32_t c = base + i0 + before_in_bin(sh, i0, i1, key[r], tok[r]);
+      if (tok[r] < (uint32_t)T) rank_out[tok[r]] = (int32_t)c;               // always true
+    }
+    if (R > 2) __builtin_amdgcn_sched_barrier(0);
+  }
+  return true;
+}
 
 // Ranks of the bucket's n <= R * kSortThreads pairs in sh.key / sh.tok, whose keys lie in or near [lo, hi]: that range is cut
 // into 2048 bins of equal width, a key's place is its bin's first plus the smaller keys of its bin.  sh.bin is clear.
 // A count, a scan and a short loop over the own bin; the order of the atomic additions decides only where inside its
-// bin a key waits to be compared.  Returns false, with sh.key and sh.tok as they were, where a bin is longer than kBinMax.
+// bin a key waits to be compared.  Where a bin is longer than kBinMax, see bucket_by_sub_bins.
 template <int R>
 __device__ __forceinline__ bool bucket_by_bins(BucketShared& sh, int n, uint32_t lo, uint32_t hi, uint32_t base, int T,
                                                int32_t* __restrict__ rank_out) {
@@ -491,7 +792,10 @@ __device__ __forceinline__ bool bucket_by_bins(BucketShared& sh, int n, uint32_t
   const uint32_t c0 = sh.bin[2 * tid], c1 = sh.bin[2 * tid + 1];
   uint32_t first, total, most;
   block_scan<true>(sh.red, c0 + c1, max(c0, c1), first, total, most);
-  if (most > kBinMax) return false;                     // uniform
+  if (__builtin_expect(most > kBinMax, 0)) {            // uniform
+    if constexpr (R > 4) return false;                  // rare: no more registers for these
+    else return bucket_by_sub_bins<R>(sh, n, lo, hi, key, tok, slot, c0, c1, first, base, T, rank_out);
+  }
   sh.bin[2 * tid] = first;
   sh.bin[2 * tid + 1] = first + c0;
   if (tid == 0) sh.bin[kBucketBins] = (uint32_t)n;
@@ -510,16 +814,7 @@ __device__ __forceinline__ bool bucket_by_bins(BucketShared& sh, int n, uint32_t
   for (int r = 0; r < R; ++r) {
     if (tid + r * kSortThreads < n) {
       const uint32_t b = clamped_bin(key[r], lo, hi, shift), i0 = sh.bin[b], i1 = sh.bin[b + 1];
-      uint32_t c = base + i0;
-      if (i1 - i0 > 1u)
-#pragma unroll 1
-        for (uint32_t i = i0; i < i1; i += 4u) {        // four at a time: a bin's length in memory round trips otherwise
-#pragma unroll
-          for (uint32_t q = 0; q < 4u; ++q) {
-            const uint32_t j = min(i + q, i1 - 1u), k = sh.key[j], t = sh.tok[j];
-            c += (i + q < i1 && (k < key[r] || (k == key[r] && t < tok[r]))) ? 1u : 0u;
-          }
-        }
+      const uint32_t c = base + i0 + before_in_bin(sh, i0, i1, key[r], tok[r]);
       if (tok[r] < (uint32_t)T) rank_out[tok[r]] = (int32_t)c;               // always true
     }
     if (R > 2) __builtin_amdgcn_sched_barrier(0);
@@ -528,7 +823,8 @@ __device__ __forceinline__ bool bucket_by_bins(BucketShared& sh, int n, uint32_t
 }
 
 // Pair number i of the bucket (i < seg_off[n_tiles]).
-__device__ __forceinline__ uint2 bucket_pair(const BucketShared& sh, const RankArgs& a, uint32_t i) {
+template <typename Args>
+__device__ __forceinline__ uint2 bucket_pair(const BucketShared& sh, const Args& a, uint32_t i) {
   int t = 0;                                            // last tile whose pairs begin at or before i
   for (int step = a.tile_step; step > 0; step >>= 1)
     if (t + step < a.n_tiles && sh.seg_off[t + step] <= i) t += step;
@@ -538,7 +834,7 @@ __device__ __forceinline__ uint2 bucket_pair(const BucketShared& sh, const RankA
 
 // Next range [from, to] of a large bucket's keys, `from` given: as many bins as LDS holds the pairs of, or (true) the
 // single key from = to, which has more.  At least one pair has a key >= from; returns with to < from if none has.
-__device__ __forceinline__ bool next_range(BucketShared& sh, const RankArgs& a, uint32_t n, uint32_t& from, uint32_t& to) {
+__device__ __forceinline__ bool next_range(BucketShared& sh, const BucketShared::Pairs& a, uint32_t n, uint32_t& from, uint32_t& to) {
   const int tid = threadIdx.x;
   to = 0xffffffffu;
   for (;;) {                                            // at most three trips: 11 bits of the range each
@@ -584,7 +880,7 @@ __device__ __forceinline__ bool next_range(BucketShared& sh, const RankArgs& a, 
 // bucket's pairs by this one workgroup (128 K equal scores: one sweep to find that out, one to write the ranks).
 // A function of its own, with its operands in LDS: inlined, it cost the ordinary path 60 registers or its spills.
 __device__ __forceinline__ void bucket_by_ranges(BucketShared& sh) {
-  const RankArgs& a = sh.args;
+  const BucketShared::Pairs& a = sh.args;
   const uint32_t n = sh.n, base = sh.base;
   const bool in_lds = n <= (uint32_t)kBucketCap;
   uint32_t from = 0, to = 0xffffffffu, done = 0;        // keys below `from` are ranked: `done` of them
@@ -638,8 +934,14 @@ __device__ __forceinline__ void bucket_body(BucketShared& sh, const RankArgs& a,
     cnt = w >> 16;
   }
   uint32_t lo = a.edge[b], hi = a.edge[b + 1];
-  const bool outer = lo == a.edge[0] || hi == a.edge[B];                       // uniform: keys beyond the bins are here
+  const bool no_edges = a.edge[B + 1] != 0u;
+  const uint32_t s0 = a.edge[0], s1 = a.edge[B];        // smallest and largest sampled key
+  const bool outer = no_edges || lo == s0 || hi == s1;  // uniform: the edges don't say where the keys are
   if (b + 1 < B && hi > lo) hi -= 1u;
+  if (no_edges) {
+    lo = 0xffffffffu;
+    hi = 0u;
+  }
   sh.bin[2 * tid] = 0;
   sh.bin[2 * tid + 1] = 0;
   uint32_t at, n, base;
@@ -665,12 +967,21 @@ __device__ __forceinline__ void bucket_body(BucketShared& sh, const RankArgs& a,
     }
     __syncthreads();
     if (outer) {
-      // the outermost buckets reach beyond the bins' first and last key, by any distance
       for (uint32_t i = tid; i < n; i += kSortThreads) {
         lo = min(lo, sh.key[i]);
         hi = max(hi, sh.key[i]);
       }
       block_min_max(sh.red, lo, hi);
+      if (lo == hi) {                                   // uniform: a share of a key's tokens, in token order
+        for (uint32_t i = tid; i < n; i += kSortThreads) a.rank_out[min(sh.tok[i], (uint32_t)a.T - 1u)] = (int32_t)(base + i);   // < T
+        return;
+      }
+      // keys far beyond all sampled ones (few) stay with the bins at the ends
+      const uint32_t far = (s1 - s0) / 4u + 1u, least = s0 > far ? s0 - far : 0u, last = s1 < 0xffffffffu - far ? s1 + far : 0xffffffffu;
+      if (max(lo, least) <= min(hi, last)) {
+        lo = max(lo, least);
+        hi = min(hi, last);
+      }
     }
     if (n <= 2u * kSortThreads   ? bucket_by_bins<2>(sh, (int)n, lo, hi, base, a.T, a.rank_out)
         : n <= 4u * kSortThreads ? bucket_by_bins<4>(sh, (int)n, lo, hi, base, a.T, a.rank_out)
@@ -678,7 +989,7 @@ __device__ __forceinline__ void bucket_body(BucketShared& sh, const RankArgs& a,
       return;
   }
   if (tid == 0) {
-    sh.args = a;
+    sh.args = {a.pairs, a.rank_out, a.T, n_tiles, a.tile_step};
     sh.n = n;
     sh.base = base;
   }

@@ -69,6 +69,18 @@ __device__ __forceinline__ void block_min_max(uint32_t* red, uint32_t& lo, uint3
   hi = wave_max(red[kRowWaves + (lane & (kRowWaves - 1))]);
 }
 
+// Exclusive prefix over the workgroup's threads of `x`, and its total.
+__device__ __forceinline__ void block_prefix(uint32_t* red, uint32_t x, uint32_t& excl, uint32_t& total) {
+  const int wave = uniform_wave(), lane = threadIdx.x & 63;
+  const uint32_t incl = wave_prefix_sum(x);
+  __syncthreads();                                     // red may still be in use
+  if (lane == 63) red[wave] = incl;
+  __syncthreads();
+  const uint32_t before = row_prefix_sum(red[lane & (kRowWaves - 1)]);
+  total = (uint32_t)__builtin_amdgcn_readlane((int)before, kRowWaves - 1);
+  excl = incl - x + (wave == 0 ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)before, wave - 1));
+}
+
 // Exclusive prefix over the workgroup's threads of `x`, its total, and the total of `y` (MAX: its largest).
 template <bool MAX>
 __device__ __forceinline__ void block_scan(uint32_t* red, uint32_t x, uint32_t y, uint32_t& excl, uint32_t& total, uint32_t& y_total) {
@@ -96,17 +108,48 @@ __device__ __forceinline__ uint32_t clamped_bin(uint32_t key, uint32_t lo, uint3
   return (min(max(key, lo), hi) - lo) >> shift;
 }
 
-// Counts the sample's keys in bins of width 2^shift from lo: those in [lo, hi], or (CLAMP) all, the others in the first
-// and the last bin.
-template <bool CLAMP = false>
+// LDS atomics of a wavefront on one word come one after the other, ~4 cycles a lane.  Words that two of the wavefront's
+// lanes want, if at least a sixth of it does (else 2^32 - 1): their lanes then add together.
+struct Repeated {
+  uint32_t w0, w1;
+};
+__device__ __forceinline__ Repeated find_repeated(uint32_t i, bool valid) {
+  Repeated r;
+  r.w0 = (uint32_t)__builtin_amdgcn_readlane((int)i, 0);
+  r.w1 = (uint32_t)__builtin_amdgcn_readlane((int)i, 37);
+  if (__popcll(__ballot(valid && i == r.w0)) < 11) r.w0 = 0xffffffffu;
+  if (r.w1 == r.w0 || __popcll(__ballot(valid && i == r.w1)) < 11) r.w1 = 0xffffffffu;
+  return r;
+}
+// What the lane adds to word i (0: another lane adds for it).  The whole wavefront calls it.
+__device__ __forceinline__ uint32_t add_for(const Repeated& r, uint32_t i, bool valid) {
+  const uint64_t m0 = __ballot(valid && i == r.w0), m1 = __ballot(valid && i == r.w1), mine = i == r.w0 ? m0 : m1;
+  if (!valid) return 0u;
+  if (i != r.w0 && i != r.w1) return 1u;
+  return lanes_below(mine) == 0u ? (uint32_t)__popcll(mine) : 0u;
+}
+
+// Counts the sample's keys in bins of width 2^shift from lo: all of them (ALL: they are in [lo, hi]), or those in [lo, hi].
+template <bool ALL>
 __device__ __forceinline__ void sample_count(SampleShared& sh, const uint32_t (&v)[kSamplePer], int n_s, uint32_t lo, uint32_t hi, int shift) {
   const int tid = threadIdx.x;
   uint32_t* bin = &sh.bin[0].x;
   sh.bin[tid] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
+  auto in = [&](int u) { return tid + u * kRowThreads < n_s && (ALL || (v[u] >= lo && v[u] <= hi)); };
+  const Repeated rep = find_repeated((v[0] - lo) >> shift, in(0));
+  if ((rep.w0 & rep.w1) != 0xffffffffu) {              // uniform
 #pragma unroll
-  for (int u = 0; u < kSamplePer; ++u)
-    if (tid + u * kRowThreads < n_s && (CLAMP || (v[u] >= lo && v[u] <= hi))) atomicAdd(&bin[clamped_bin(v[u], lo, hi, shift)], 1u);
+    for (int u = 0; u < kSamplePer; ++u)
+      if (u * kRowThreads < n_s) {
+        const uint32_t n = add_for(rep, (v[u] - lo) >> shift, in(u));
+        if (n != 0u) atomicAdd(&bin[(v[u] - lo) >> shift], n);
+      }
+  } else {
+#pragma unroll
+    for (int u = 0; u < kSamplePer; ++u)
+      if (in(u)) atomicAdd(&bin[(v[u] - lo) >> shift], 1u);
+  }
   __syncthreads();
 }
 
@@ -126,7 +169,7 @@ __device__ __forceinline__ void sample_bound(SampleShared& sh, const uint32_t (&
   below = lo;
   for (int round = 0;; ++round) {
     const int shift = bin_shift(lo, hi, kSampleBinBits);
-    sample_count(sh, v, n_s, lo, hi, shift);
+    sample_count<false>(sh, v, n_s, lo, hi, shift);
     const uint4 c = sh.bin[tid];
     uint32_t excl, total, most;
     block_scan<true>(sh.red, c.x + c.y + c.z + c.w, 0u, excl, total, most);

@@ -106,7 +106,7 @@ def _rank_sample_positions(T):
 @pytest.mark.parametrize("kind", ["lognormal", "two-signs", "equal", "third-zero", "few", "sorted", "outliers",
                                   "unsampled-equal", "unsampled-close"])
 def test_rank_buckets(gpu_device, T, kind):
-    """Scores that fill the ranking's buckets evenly, that its sample's bins do not tell apart (the sample is sorted), and
+    """Scores that fill the ranking's buckets evenly, that its sample's bins do not tell apart, and
     that the sample misses (a bucket of more pairs than LDS holds): integers, exact.  Sizes: the smallest that
     takes buckets, the 2048-token tiles' and the first of the 4096-token tiles, with one token in the last."""
     rng = np.random.default_rng(T)
@@ -130,6 +130,50 @@ def test_rank_buckets(gpu_device, T, kind):
         s[rest] = 0.5 if kind == "unsampled-equal" else 0.5 + 1e-6 * np.round(rng.random(int(rest.sum())) * 10)
     c = asl.Asl(T, 1, 32)
     _rank_case(c, gpu_device, s)
+    c.close()
+
+
+def _graph_us(f, n=20):
+    """Duration of one call of f in a replayed graph of n, in us: the median of five replays."""
+    import torch
+    f()
+    torch.cuda.synchronize()
+    g, times = torch.cuda.CUDAGraph(), []
+    with torch.cuda.graph(g):
+        for _ in range(n):
+            f()
+    for _ in range(6):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        g.replay()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) / n * 1e3)
+    return sorted(times[1:])[2]
+
+
+@pytest.mark.parametrize("T", [16000, 131040, 262080, 1048544])
+def test_rank_time_hardly_depends_on_the_scores(gpu_device, T):
+    """Scores that repeat, have a period or lie close together beside outliers: a ranking takes at most twice as long as that of
+    distinct, spread ones (a radix sort, whatever the scores, takes twice as long), and is exact."""
+    import torch
+    rng = np.random.default_rng(T)
+    spread = np.exp(2 * rng.standard_normal(T)).astype(np.float32)
+    near, far = (1 + 0.02 * rng.standard_normal(T)).astype(np.float32), (1 + 1e-5 * rng.random(T)).astype(np.float32)
+    near[rng.integers(0, T, T // 300)] += 300 * rng.random(T // 300).astype(np.float32) + 50
+    far[5] = -3e38
+    kinds = {"third-zero": np.where(rng.random(T) < 1 / 3, np.float32(0), spread), "equal": np.full(T, 0.25, np.float32),
+             "few": np.round(3 * rng.standard_normal(T)).astype(np.float32), "two": np.where(rng.random(T) < 0.5, 0.25, 0.5).astype(np.float32),
+             "period": np.tile(spread[:32], T // 32 + 1)[:T], "sorted": np.sort(spread), "cluster": near, "one far": far}
+    c = asl.Asl(T, 1, 32)
+    out = torch.empty((T,), dtype=torch.int32, device=gpu_device)
+    d = torch.from_numpy(spread).to(gpu_device)
+    limit = 2 * _graph_us(lambda: c.asl_rank(d, T, out))
+    for kind, s in kinds.items():
+        _rank_case(c, gpu_device, s)
+        d = torch.from_numpy(s).to(gpu_device)
+        us = _graph_us(lambda: c.asl_rank(d, T, out))
+        assert us <= limit, f"{kind}: {us:.1f} us, limit {limit:.1f}"
     c.close()
 
 
