@@ -59,8 +59,8 @@ RankArgs rank_plan(int T) {
   if (a.n_buckets > kRankMaxBuckets) a.n_buckets = kRankMaxBuckets;
   a.n_s = sel_sample_size(T);
   a.stride = sel_sample_stride(T);
-  // three buckets' worth, or one and a half where a bucket with the end of one before it would outgrow kBucketCap
-  a.heavy = (T / a.n_buckets > 1400 ? 3 * a.n_s / 2 : 3 * a.n_s) / a.n_buckets;
+  // three buckets' worth, or two where a bucket with the end of one before it would outgrow kBucketCap
+  a.heavy = (T / a.n_buckets > 1400 ? 2 * a.n_s : 3 * a.n_s) / a.n_buckets;
   a.per_key = (float)a.n_buckets / (float)a.n_s;
   a.per_key_deep = (float)(a.n_buckets - 1) / (float)a.n_s;
   return a;

@@ -93,26 +93,30 @@ constexpr uint32_t kBinMax = 64;                        // longest bin that is o
 //  - by counting: a token's 32 lanes compare its key with every other one, rank = keys before it in the order (key
 //    ascending, index ascending), 32 tokens a workgroup.  T^2 comparisons of two vector instructions.
 //  - by bins: the workgroup counts all keys in 4096 bins of equal width between the smallest and the largest; of those bins
-//    that begin at its 64 places of the order it groups the keys in LDS, and a thread per key compares it with the others of
-//    its bin.  Bound by latency (eight barriers).  Where some bin is longer than kBinMax (repeated or outlying scores) the
-//    workgroup ranks 64 tokens by counting instead.
-// Counting takes the sizes up to kCountT (one call, us, counting and bins: 2000 tokens 4.1, 5.9; 8000 8.4, 6.9;
-// 12000 17.0, 7.6; 12000 of which a third are equal 17.0, 23.1).
+//    that reach into its 64 places of the order it groups the keys in LDS, and a thread per key compares it with the others
+//    of its bin.  A bin longer than kBinMax that reaches into its places (at most two do) is cut into 4096 in turn, between the
+//    keys it holds, or is one key, whose tokens are counted in order.  Bound by latency (eight barriers, and as many per
+//    such bin).
+// Counting takes the sizes up to kCountT, where its time does not depend on the scores and the bins' would (one call, us, counting and
+// bins: 8000 tokens 8.4, 6.4 to 17; 9000 13.4, 6.5; 12000 17.0, 7.1; 12000 of which a third are equal 17, 16.8; of a few values 17,
+// 16.3; within 2 % beside outliers 17, 15.2; of 84 values and one far away 17, 21).
 constexpr int kCountTokens = kSortThreads / 32;
-constexpr int kCountT = 5120;
+constexpr int kCountT = 8192;
 constexpr int kShortPlaces = 2 * kCountTokens;
 constexpr int kShortPer = kShortT / kSortThreads;
 static_assert(kShortT % kSortThreads == 0 && kCountTokens == 32, "the keys of a workgroup's tokens are one group of 32");
 struct ShortRankShared {
-  uint32_t keys[kShortT];                               // by counting
+  uint32_t keys[kShortT];                               // by counting, and where long bins are cut
   union {
     uint4 bin4[kSampleBins / 4 + 1];                    // four bins a thread: their counts, then their first places and the last one's end
     uint32_t bin[kSampleBins + 4];
   };
-  uint32_t key[kShortPlaces + kBinMax];                 // by bins: this workgroup's keys ...
-  uint32_t tok[kShortPlaces + kBinMax];                 // ... and tokens
+  uint32_t key[kShortPlaces + 2 * kBinMax];             // by bins: keys of bins that reach into the workgroup's places ...
+  uint32_t tok[kShortPlaces + 2 * kBinMax];             // ... and tokens, from their bin's first place on; ~0: nothing there
+  uint32_t held[kShortPlaces + kBinMax];                // keys there from a bin's first place on
+  uint32_t todo[8][3];                                  // long bins yet to be cut: first and last key, first place
+  uint32_t n_todo;
   uint32_t red[2 * kSortWaves];
-  uint32_t from, to;                                    // the places whose bins begin at this workgroup's
 };
 inline int short_rank_blocks(int T) { return T <= kCountT ? (T + kCountTokens - 1) / kCountTokens : (T + kShortPlaces - 1) / kShortPlaces; }
 
@@ -136,10 +140,106 @@ __device__ __forceinline__ void count_ranks(const uint32_t* keys, int T, int gro
   if (lane == 0 && i < T) rank_out[i] = (int32_t)before;
 }
 
+// The rest of a way by bins, once the keys in [lo, hi] are counted: the bins' first places (`begin`: that of lo's) to sh.bin, and
+// those longer than kBinMax that reach into places [p0, p1) to sh.todo.
+__device__ __forceinline__ void short_bins(ShortRankShared& sh, uint32_t lo, uint32_t hi, int shift, uint32_t begin, uint32_t p0, uint32_t p1) {
+  const int tid = threadIdx.x;
+  const uint4 c = sh.bin4[tid];
+  uint32_t at, total;
+  block_prefix(sh.red, c.x + c.y + c.z + c.w, at, total);
+  const uint32_t cs[4] = {c.x, c.y, c.z, c.w};
+  uint32_t at4[4];
+  at += begin;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    at4[q] = at;
+    at += cs[q];
+    if (cs[q] > kBinMax && at4[q] < p1 && at > p0) {    // at most two of the workgroup's
+      const uint32_t i = min(atomicAdd(&sh.n_todo, 1u), 7u), from = lo + ((uint32_t)(4 * tid + q) << shift), width = (1u << shift) - 1u;
+      sh.todo[i][0] = from;
+      sh.todo[i][1] = hi - from < width ? hi : from + width;
+      sh.todo[i][2] = at4[q];
+    }
+  }
+  sh.bin4[tid] = make_uint4(at4[0], at4[1], at4[2], at4[3]);       // own counts only were read
+  if (tid == 0) sh.bin[kSampleBins] = begin + total;
+  __syncthreads();
+}
+// Ranks of the keys grouped in sh.key / sh.tok from place p0 - kBinMax on, of those with a place in [from, to).
+__device__ __forceinline__ void short_places(const ShortRankShared& sh, uint32_t lo, int shift, uint32_t p0, uint32_t from, uint32_t to,
+                                             int32_t* __restrict__ rank_out) {
+  // four threads per place: few keys are this workgroup's, and a wavefront that went through its own again would run the
+  // comparison once for each (12000 tokens: 28 us the ranking and its statistic, so 18)
+  const int tid = threadIdx.x, i = tid >> 2, part = tid & 3;
+  static_assert(4 * (kShortPlaces + 2 * kBinMax) <= kSortThreads, "four threads per place");
+  if (i >= kShortPlaces + 2 * (int)kBinMax) return;
+  const uint32_t k = sh.key[i], t = sh.tok[i];
+  uint32_t before = 0, i0 = 0;
+  if (t != 0xffffffffu) {
+    const uint32_t d = (k - lo) >> shift, i1 = sh.bin[d + 1u] + kBinMax - p0;
+    i0 = sh.bin[d] + kBinMax - p0;
+    if (i1 - i0 > 1u)
+      for (uint32_t j0 = i0 + part; j0 < i1; j0 += 16u) {
+#pragma unroll
+        for (uint32_t q = 0; q < 16u; q += 4u) {
+          const uint32_t j = min(j0 + q, i1 - 1u), kj = sh.key[j], tj = sh.tok[j];
+          before += (j0 + q < i1 && (kj < k || (kj == k && tj < t))) ? 1u : 0u;
+        }
+      }
+  }
+  before += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)before, 0xb1, 0xf, 0xf, false);   // quad_perm [1, 0, 3, 2]
+  before += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)before, 0x4e, 0xf, 0xf, false);   // quad_perm [2, 3, 0, 1]
+  const uint32_t place = p0 + i0 + before - kBinMax;
+  if (part == 0 && t != 0xffffffffu && place >= from && place < to) rank_out[t] = (int32_t)place;
+}
+
+// f(key, token, valid) for the thread's keys in sh.keys, read four at a time.
+template <typename F>
+__device__ __forceinline__ void four_at_a_time(const ShortRankShared& sh, int T, F f) {
+  for (int t0 = threadIdx.x; t0 < kShortT; t0 += 4 * kSortThreads) {
+    if (__builtin_amdgcn_readfirstlane(t0) >= T) break;
+    uint32_t k[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) k[q] = sh.keys[min(t0 + q * kSortThreads, T - 1)];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) f(k[q], t0 + q * kSortThreads, t0 + q * kSortThreads < T);
+  }
+}
+
+// A wavefront's stretch of tokens for the loops over all keys: token(g), g < groups.
+struct Stretch {
+  int t0, groups;
+};
+__device__ __forceinline__ Stretch short_stretch(int T) {
+  const int groups = (T + kSortThreads - 1) / kSortThreads;
+  return {uniform_wave() * 64 * groups + (int)(threadIdx.x & 63), groups};
+}
+// Ranks of the tokens with this key, which has the places from `first` on, that belong to places [p0, p1); n: those in the
+// wavefront's stretch.  The one or two wavefronts whose stretches hold such places go through theirs.
+__device__ __forceinline__ void rank_equal(ShortRankShared& sh, int T, uint32_t value, uint32_t n, uint32_t first, uint32_t p0, uint32_t p1,
+                                           int32_t* __restrict__ rank_out) {
+  const int wave = uniform_wave(), lane = threadIdx.x & 63;
+  const Stretch s = short_stretch(T);
+  __syncthreads();                                      // red may still be in use
+  if (lane == 0) sh.red[wave] = n;
+  __syncthreads();
+  const uint32_t before = row_prefix_sum(sh.red[lane & (kSortWaves - 1)]);
+  uint32_t place = first + (uint32_t)__builtin_amdgcn_readlane((int)before, wave) - n;
+  if (place >= p1 || place + n <= p0) return;           // uniform in the wavefront: no barrier follows
+  for (int g = 0; g < s.groups; ++g) {
+    const int t = s.t0 + 64 * g;
+    const bool in = t < T && sh.keys[min(t, T - 1)] == value;
+    const uint64_t m = __ballot(in);
+    const uint32_t at = place + lanes_below(m);
+    if (in && at >= p0 && at < p1) rank_out[t] = (int32_t)at;
+    place += (uint32_t)__popcll(m);
+  }
+}
+
 __device__ __forceinline__ void rank_short_body(ShortRankShared& sh, const float* __restrict__ s, int T, int32_t* __restrict__ rank_out,
                                                 int b) {
   const int tid = threadIdx.x;
-  uint32_t key[kShortPer], slot[kShortPer];
+  uint32_t key[kShortPer];
   {
     float f[kShortPer];
 #pragma unroll
@@ -160,10 +260,8 @@ __device__ __forceinline__ void rank_short_body(ShortRankShared& sh, const float
   }
   const uint32_t p0 = (uint32_t)(b * kShortPlaces), p1 = min(p0 + (uint32_t)kShortPlaces, (uint32_t)T);
   sh.bin4[tid] = make_uint4(0u, 0u, 0u, 0u);
-  if (tid == 0) {
-    sh.from = p0;
-    sh.to = p1;
-  }
+  if (tid < kShortPlaces + 2 * (int)kBinMax) sh.tok[tid] = 0xffffffffu;
+  if (tid == 0) sh.n_todo = 0;
   uint32_t lo = key[0], hi = key[0];                    // positions past the end repeat the last key
 #pragma unroll
   for (int u = 1; u < kShortPer; ++u)
@@ -176,61 +274,115 @@ __device__ __forceinline__ void rank_short_body(ShortRankShared& sh, const float
     if (tid < kShortPlaces && p0 + tid < p1) rank_out[p0 + tid] = (int32_t)(p0 + tid);
     return;
   }
-  const int shift = bin_shift(lo, hi, kSampleBinBits);
-  uint32_t* bin = sh.bin;
+  int shift = bin_shift(lo, hi, kSampleBinBits);
+  const Repeated rep = find_repeated((key[0] - lo) >> shift, tid < T);
+  uint32_t slot[kShortPer];
+  if (rep.none()) {                 // uniform
 #pragma unroll
-  for (int u = 0; u < kShortPer; ++u) {
-    slot[u] = 0;
-    if (tid + u * kSortThreads < T) slot[u] = atomicAdd(&bin[(key[u] - lo) >> shift], 1u);
+    for (int u = 0; u < kShortPer; ++u) {
+      slot[u] = 0;
+      if (tid + u * kSortThreads < T) slot[u] = atomicAdd(&sh.bin[(key[u] - lo) >> shift], 1u);
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < kShortPer; ++u) {
+      slot[u] = 0;
+      if (u * kSortThreads < T) slot[u] = slot_for(rep, sh.bin, (key[u] - lo) >> shift, tid + u * kSortThreads < T);    // uniform
+    }
   }
   __syncthreads();
-  const uint4 c = sh.bin4[tid];
-  uint32_t first, total, most;
-  block_scan<true>(sh.red, c.x + c.y + c.z + c.w, max(max(c.x, c.y), max(c.z, c.w)), first, total, most);
-  if (most > kBinMax) {                                 // uniform
-    all_keys();
-    count_ranks(sh.keys, T, 2 * b, rank_out);
-    if ((2 * b + 1) * kCountTokens < T) count_ranks(sh.keys, T, 2 * b + 1, rank_out);
-    return;
-  }
-  const uint32_t cs[4] = {c.x, c.y, c.z, c.w};
-  uint32_t at4[5] = {first, 0u, 0u, 0u, 0u};
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    at4[q + 1] = at4[q] + cs[q];
-    if (at4[q] < p0 && p0 < at4[q + 1]) sh.from = at4[q + 1];      // a bin of the workgroup before reaches into these places
-    if (at4[q] < p1 && p1 < at4[q + 1]) sh.to = at4[q + 1];
-  }
-  sh.bin4[tid] = make_uint4(at4[0], at4[1], at4[2], at4[3]);       // own counts only were read
-  if (tid == 0) bin[kSampleBins] = (uint32_t)T;
-  __syncthreads();
+  short_bins(sh, lo, hi, shift, 0u, p0, p1);
+  // bins that begin at the workgroup's places are all its own
 #pragma unroll
   for (int u = 0; u < kShortPer; ++u) {
     if (tid + u * kSortThreads < T) {
-      const uint32_t at = bin[(key[u] - lo) >> shift];
-      if (at >= p0 && at < p1) {
-        const uint32_t i = min(at - p0 + slot[u], (uint32_t)kShortPlaces + kBinMax - 1u);   // smaller by itself
+      const uint32_t d = (key[u] - lo) >> shift, first = sh.bin[d];
+      if (first >= p0 && first < p1 && sh.bin[d + 1u] - first <= kBinMax) {
+        const uint32_t i = min(first + kBinMax - p0 + slot[u], (uint32_t)kShortPlaces + 2u * kBinMax - 1u);   // smaller by itself
         sh.key[i] = key[u];
         sh.tok[i] = (uint32_t)(tid + u * kSortThreads);
       }
     }
   }
   __syncthreads();
-  // a thread per place: few keys are this workgroup's, and a wavefront that went through its own again would run the
-  // comparison once for each (12000 tokens: 28 us the ranking and its statistic, so 18)
-  const uint32_t i = sh.from - p0 + tid;
-  if (i < sh.to - p0) {                                 // at most kShortPlaces + kBinMax places, from <= to
-    const uint32_t k = sh.key[i], t = sh.tok[i], d = (k - lo) >> shift, i0 = bin[d] - p0, i1 = bin[d + 1u] - p0;
-    uint32_t before = 0;
-    if (i1 - i0 > 1u)
-      for (uint32_t j0 = i0; j0 < i1; j0 += 4u) {
+  short_places(sh, lo, shift, p0, p0, 0xffffffffu, rank_out);
+  if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)sh.n_todo) == 0, 1)) return;           // uniform
+  all_keys();
+  const Stretch s_t = short_stretch(T);
+  for (;;) {
+    const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.n_todo);
+    if (n == 0u) return;                                // uniform; every trip takes a bin off and adds parts of it
+    // the last two of the list: smallest and largest keys, and how many the wavefront's stretch holds
+    const bool two = n > 1u;
+    uint32_t from[2], to[2], at[2], held[2] = {0u, 0u}, lo2[2], hi2[2];
 #pragma unroll
-        for (uint32_t q = 0; q < 4u; ++q) {
-          const uint32_t j = min(j0 + q, i1 - 1u), kj = sh.key[j], tj = sh.tok[j];
-          before += (j0 + q < i1 && (kj < k || (kj == k && tj < t))) ? 1u : 0u;
+    for (int i = 0; i < 2; ++i) {
+      const uint32_t* r = sh.todo[min(n, 8u) - (two ? 1u + (uint32_t)i : 1u)];
+      from[i] = r[0];
+      to[i] = r[1];
+      at[i] = r[2];
+      lo2[i] = 0xffffffffu;
+      hi2[i] = 0u;
+    }
+#pragma unroll
+    for (int g = 0; g < kShortPer; ++g)
+      if (g < s_t.groups) {                             // uniform
+        const int t = s_t.t0 + 64 * g;
+        const uint32_t k = sh.keys[min(t, T - 1)];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const bool in = t < T && k - from[i] <= to[i] - from[i];
+          lo2[i] = min(lo2[i], in ? k : 0xffffffffu);
+          hi2[i] = max(hi2[i], in ? k : 0u);
+          held[i] += (uint32_t)__popcll(__ballot(in));
         }
       }
-    rank_out[t] = (int32_t)(p0 + i0 + before);
+    block_min_max(sh.red, lo2[0], hi2[0]);              // its barriers: everybody has read the list, the bins and the places
+    if (two) block_min_max(sh.red, lo2[1], hi2[1]);     // uniform
+    const bool one0 = lo2[0] == hi2[0], one1 = !two || lo2[1] == hi2[1];       // of a single key, or not there
+    if (one0) rank_equal(sh, T, lo2[0], held[0], at[0], p0, p1, rank_out);
+    if (two && one1) rank_equal(sh, T, lo2[1], held[1], at[1], p0, p1, rank_out);
+    // both at once if at most 16 bins apart
+    const bool both = !one0 && !one1 && max(to[0], to[1]) - min(from[0], from[1]) <= 16u * (to[0] - from[0]);
+    if (tid == 0) sh.n_todo = n - (two && (both || one0 || one1) ? 2u : 1u);
+    if (!one0 || !one1) {                               // uniform
+      const int i = one0 ? 1 : 0;
+      const uint32_t begin = both ? min(at[0], at[1]) : at[i];
+      lo = both ? min(lo2[0], lo2[1]) : lo2[i];
+      hi = both ? max(hi2[0], hi2[1]) : hi2[i];
+      // as above, but by the places themselves: the bins are the workgroup's own choice
+      shift = bin_shift(lo, hi, kSampleBinBits);
+      sh.bin4[tid] = make_uint4(0u, 0u, 0u, 0u);
+      if (tid < kShortPlaces + 2 * (int)kBinMax) sh.tok[tid] = 0xffffffffu;
+      if (tid < kShortPlaces + (int)kBinMax) sh.held[tid] = 0u;
+      __syncthreads();
+      auto in = [&](uint32_t k, bool valid) { return valid && k - lo <= hi - lo; };
+      const Repeated again = find_repeated((sh.keys[tid] - lo) >> shift, in(sh.keys[tid], true));
+      if (again.none())         // uniform
+        four_at_a_time(sh, T, [&](uint32_t k, int, bool valid) {
+          if (in(k, valid)) atomicAdd(&sh.bin[(k - lo) >> shift], 1u);
+        });
+      else
+        four_at_a_time(sh, T, [&](uint32_t k, int, bool valid) {
+          const uint32_t add = add_for(again, (k - lo) >> shift, in(k, valid));
+          if (add != 0u) atomicAdd(&sh.bin[(k - lo) >> shift], add);
+        });
+      __syncthreads();
+      short_bins(sh, lo, hi, shift, begin, p0, p1);
+      four_at_a_time(sh, T, [&](uint32_t k, int t, bool valid) {
+        if (in(k, valid)) {
+          const uint32_t d = (k - lo) >> shift, first = sh.bin[d], end = sh.bin[d + 1u], at = first + kBinMax - p0;
+          if (first < p1 && end > p0 && end - first <= kBinMax) {              // then at < kShortPlaces + kBinMax
+            const uint32_t i = min(at + atomicAdd(&sh.held[at], 1u), (uint32_t)kShortPlaces + 2u * kBinMax - 1u);   // smaller by itself
+            sh.key[i] = k;
+            sh.tok[i] = (uint32_t)t;
+          }
+        }
+      });
+      __syncthreads();
+      short_places(sh, lo, shift, p0, p0, p1, rank_out);
+    }
+    __syncthreads();
   }
 }
 
@@ -257,7 +409,7 @@ __device__ __forceinline__ uint32_t bucket_of_place(const RankArgs& a, uint32_t 
 }
 
 constexpr uint32_t kHeavyBin = 0x80000000u;
-constexpr int kMaxHeavyBins = 2 * kRankMaxBuckets / 3 + 1;   // of one level: each holds more than 3/2 of a bucket's worth of the sample
+constexpr int kMaxHeavyBins = kRankMaxBuckets / 2 + 1;  // of one level: each holds more than two buckets' worth of the sample
 struct PartShared {
   SampleShared s;                                       // bin: the sample's counts, then the bucket of each bin, or kHeavyBin | its number
   union {

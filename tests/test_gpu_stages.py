@@ -177,6 +177,30 @@ def test_rank_time_hardly_depends_on_the_scores(gpu_device, T):
     c.close()
 
 
+def _score_kinds(T):
+    """Spread scores, scores that repeat, and scores that lie close together beside an outlier."""
+    rng = np.random.default_rng(T)
+    spread = np.exp(2 * rng.standard_normal(T)).astype(np.float32)
+    near = (1 + 0.02 * rng.standard_normal(T)).astype(np.float32)
+    near[T // 2] = 1e3
+    return {"spread": spread, "third-zero": np.where(rng.random(T) < 1 / 3, np.float32(0), spread),
+            "two": np.where(rng.random(T) < 0.5, 0.25, 0.5).astype(np.float32), "near": near}
+
+
+@pytest.mark.parametrize("T,limit", [(8000, 1.5), (12000, 2.6)])
+def test_short_ranking_times(gpu_device, T, limit):
+    """Rankings in one launch: counting does not depend on the scores (8000 tokens), and long bins are cut in turn (before: 2.4 to
+    2.8 and 2.6 to 3.4 times the spread scores' time, everything once more by counting)."""
+    import torch
+    c = asl.Asl(T, 1, 32)
+    out, us = torch.empty((T,), dtype=torch.int32, device=gpu_device), {}
+    for kind, s in _score_kinds(T).items():
+        d = torch.from_numpy(s).to(gpu_device)
+        us[kind] = _graph_us(lambda: c.asl_rank(d, T, out))
+    c.close()
+    assert max(us.values()) <= limit * us["spread"], us
+
+
 def test_rank_special(ctx, gpu_device):
     T = 5000
     _rank_case(ctx, gpu_device, np.ones(T, dtype=np.float32))                               # all equal
@@ -210,8 +234,8 @@ def test_rank_and_select_at_tile_boundaries(ctx, gpu_device, T):
         _select_case(ctx, gpu_device, np.stack([s, -s]), budget, 8)
 
 
-# Up to 12288 scores are ranked in one launch (128 places per workgroup) and selected from by one workgroup per
-# row; above, the partition (tiles of 2048) and the bound / filter / finish launches (tiles of 4096) take over.
+# Up to 12288 scores are ranked in one launch (up to 8192 of them 32 tokens per workgroup, then 64 places) and selected
+# from by one workgroup per row; above, the partition (tiles of 2048) and the bound / filter / finish launches (tiles of 4096) take over.
 @pytest.mark.parametrize("T", [31, 32, 33, 95, 1023, 1025, 8192, 12256, 12257, 12287, 12288, 12289, 14335, 14336, 14337,
                                16383, 16384, 16385])
 def test_short_vectors_and_their_limit(ctx, gpu_device, T):
@@ -228,7 +252,7 @@ def test_short_vectors_and_their_limit(ctx, gpu_device, T):
         _select_case(ctx, gpu_device, np.stack([s, -s, wild]), budget, 8)
 
 
-@pytest.mark.parametrize("T", [1, 2, 127, 128, 129, 255, 257, 1024, 5120, 5121, 9994, 12287, 12288, 12289, 16385, 32736, 32767,
+@pytest.mark.parametrize("T", [1, 2, 127, 128, 129, 255, 257, 1024, 5120, 5121, 8192, 8193, 9994, 12287, 12288, 12289, 16385, 32736, 32767,
                                32768, 32769])
 @pytest.mark.parametrize("kind", ["lognormal", "pairs", "third-zero", "few", "two", "outlier"])
 def test_short_vectors_by_bins(ctx, gpu_device, T, kind):
