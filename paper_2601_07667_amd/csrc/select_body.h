@@ -20,13 +20,11 @@ static_assert(kSelMaxSample % kFinThreads == 0, "the bound kernel's threads shar
 // threads take part.  The keys' common leading bits are skipped: digits are taken from
 // key - min over the bits in which min and max differ, so the first digit already spreads the keys
 // over the bins (scores of one row share their sign and most of their exponent).
-// With `slack` > 0 the search may stop early: thr_out is then a key that at least k and at most k + slack
-// of the keys do not exceed (k_rem_out is meaningless).
 // h: kHistWords-word LDS histogram (bank-staggered copies), sm: >= 2 * kFinWaves + 2 words.
 constexpr int kSelBatch = 4;                           // keys a thread reads together in the selection loops
 template <typename KeyAt>
 __device__ __forceinline__ void radix_select_block(int n, uint32_t k, KeyAt key_at, uint32_t* h, uint32_t* sm,
-                                                   uint32_t& thr_out, uint32_t& k_rem_out, uint32_t slack = 0) {
+                                                   uint32_t& thr_out, uint32_t& k_rem_out) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   // The loops over the keys take kSelBatch of a thread's keys at a time (positions past the end
   // re-read the thread's first key of the batch), so that their reads are in flight together.
@@ -83,7 +81,6 @@ __device__ __forceinline__ void radix_select_block(int n, uint32_t k, KeyAt key_
     if (tid == 0) {
       sm[4] = 0;                                       // defined even if no digit qualifies
       sm[5] = 1;                                       // (cannot happen while 1 <= k <= n)
-      sm[6] = 0xffffffffu;
     }
     __syncthreads();
     if (tid < 256) {
@@ -92,17 +89,11 @@ __device__ __forceinline__ void radix_select_block(int n, uint32_t k, KeyAt key_
       if (excl < k_rem && excl + cnt >= k_rem) {       // exactly one digit satisfies this
         sm[4] = (uint32_t)tid;
         sm[5] = k_rem - excl;
-        sm[6] = cnt;
       }
     }
     __syncthreads();
     prefix = (prefix << 8) | sm[4];
     k_rem = sm[5];
-    if (slack > 0 && sm[6] - k_rem <= slack) {          // uniform: the whole bin may pass
-      const uint32_t top = (prefix << shift) | ((1u << shift) - 1u);
-      prefix = top < span ? top : span;
-      break;
-    }
   }
   thr_out = lo + prefix;
   k_rem_out = k_rem;
@@ -140,9 +131,9 @@ __device__ __forceinline__ void select_guess_body(GuessShared& sh, const SelectA
   const float* sr = a.scores + (int64_t)row * a.T;
   uint32_t v[kSamplePer];
 #pragma unroll
-  for (int u = 0; u < kSamplePer; ++u) {               // key j = member j % run of run j / run
-    const int j = min(tid + u * kFinThreads, n_s - 1);
-    v[u] = order_key(sr[(j / kSelSampleRun) * (kSelSampleRun * stride) + (j % kSelSampleRun)]);
+  for (int u = 0; u < kSamplePer; ++u) {               // key j = member j % run of run j / run, whose place is scattered
+    const uint32_t j = (uint32_t)min(tid + u * kFinThreads, n_s - 1);
+    v[u] = order_key(sr[kSelSampleRun * sel_sample_position(j / kSelSampleRun, stride) + j % kSelSampleRun]);
   }
   uint32_t bound, below;
   select_bound(sh.s, a, v, bound, below);
@@ -335,11 +326,15 @@ constexpr int kFinBins = 2 * kFinThreads;               // two per thread
 constexpr int kFinBinBits = 11;
 constexpr uint32_t kFinListMax = 64;
 static_assert(kFinBins == 1 << kFinBinBits && kFinBins <= kHistWords, "the bins share the histogram's memory");
+// Shared words of a search by bins.
+struct BinPick {
+  uint32_t list[kFinListMax];
+  uint32_t pick[4];                                    // the bin that holds the key looked for, its place there, keys in the bin; keys listed
+};
 struct FinishShared {
   uint32_t h[kHistWords];
   uint32_t sm[2 * kFinWaves + 2];
-  uint32_t list[kFinListMax];
-  uint32_t pick[4];
+  BinPick bins;
   uint32_t seg_off[kSelMaxRowTiles + 1];
   int whole_row;
 };
@@ -357,7 +352,7 @@ __device__ __forceinline__ int finish_load(FinishShared& sh, uint32_t* lds_cand,
   if (tid < n_tiles && n_tiles <= kSelMaxRowTiles) c = a.seg_count[(int64_t)row * n_tiles + tid];
   sh.h[2 * tid] = 0;                                    // finish_threshold's bins
   sh.h[2 * tid + 1] = 0;
-  if (tid == 0) sh.pick[3] = 0;
+  if (tid == 0) sh.bins.pick[3] = 0;
   {
     const uint32_t over = (c == kSegOverflow) ? 1u : 0u;
     c = over ? 0u : c;
@@ -432,10 +427,99 @@ __device__ __forceinline__ void pick_listed(const uint32_t* list, uint32_t c, ui
   k_rem -= (uint32_t)__builtin_amdgcn_readlane((int)less, who);
 }
 
+// PER bins per thread (their counts: c) with `excl` keys before the thread's: which holds the kk-th key?
+template <int PER>
+__device__ __forceinline__ void pick_bin(BinPick& sh, const uint32_t (&c)[PER], uint32_t excl, uint32_t kk) {
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    if (excl < kk && kk <= excl + c[q]) {               // one bin of the workgroup, if any
+      sh.pick[0] = (uint32_t)(PER * (int)threadIdx.x + q);
+      sh.pick[1] = kk - excl;
+      sh.pick[2] = c[q];
+    }
+    excl += c[q];
+  }
+  __syncthreads();
+}
+
+// f(key, valid) for the thread's of n keys in LDS, four reads at a time, as often for every thread of a wavefront.
+template <typename F>
+__device__ __forceinline__ void each_key(const uint32_t* keys, int n, F f) {
+  for (int i0 = (int)threadIdx.x; __builtin_amdgcn_readfirstlane(i0) < n; i0 += 4 * kFinThreads) {
+    uint32_t k[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) k[q] = keys[min(i0 + q * kFinThreads, n - 1)];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) f(k[q], i0 + q * kFinThreads < n);
+  }
+}
+// Counts the keys in [lo, hi] in bins of width 2^shift from lo, where many want the same.
+__device__ __forceinline__ void count_repeated(const uint32_t* keys, int n, uint32_t lo, uint32_t hi, int shift, const Repeated& rep, uint32_t* bin) {
+  each_key(keys, n, [&](uint32_t k, bool valid) {
+    const uint32_t add = add_for(rep, (k - lo) >> shift, valid && k - lo <= hi - lo);
+    if (add != 0u) atomicAdd(&bin[(k - lo) >> shift], add);
+  });
+}
+
+// The k_rem-th smallest of the keys in [from, to], of which there are more than kFinListMax, and (k_rem) how many of those equal
+// to it are kept.  keys: all n in LDS; bin: PER * kFinThreads words.  The range is cut into bins between the smallest and
+// the largest key in it, then the bin that holds the key looked for, until that is one key or has few enough
+// to compare: at most three times, ~2 us each.
+template <int PER>
+__device__ __forceinline__ void zoom_threshold(BinPick& sh, uint32_t* red, uint32_t* bin, const uint32_t* keys, int n, uint32_t from, uint32_t to,
+                                               uint32_t& thr, uint32_t& k_rem) {
+  constexpr int kBits = PER == 4 ? 12 : 11;
+  static_assert(PER * kFinThreads == 1 << kBits, "bins");
+  const int tid = threadIdx.x;
+  auto each = [&](auto f) { each_key(keys, n, f); };
+  for (;;) {
+    uint32_t lo = 0xffffffffu, hi = 0u;
+    each([&](uint32_t k, bool) {
+      const bool in = k - from <= to - from;
+      lo = min(lo, in ? k : 0xffffffffu);
+      hi = max(hi, in ? k : 0u);
+    });
+#pragma unroll
+    for (int q = 0; q < PER; ++q) bin[q * kFinThreads + tid] = 0u;
+    block_min_max(red, lo, hi);
+    thr = lo;
+    if (lo >= hi) return;                               // uniform: one key
+    const int shift = bin_shift(lo, hi, kBits);
+    const uint32_t one = keys[min(tid, n - 1)];
+    const Repeated rep = find_repeated((one - lo) >> shift, tid < n && one - lo <= hi - lo);
+    if (rep.none())                                     // uniform
+      each([&](uint32_t k, bool valid) {
+        if (valid && k - lo <= hi - lo) atomicAdd(&bin[(k - lo) >> shift], 1u);
+      });
+    else
+      count_repeated(keys, n, lo, hi, shift, rep, bin);
+    __syncthreads();
+    uint32_t c[PER], sum = 0, excl, total;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) sum += c[q] = bin[PER * tid + q];
+    block_prefix(red, sum, excl, total);
+    pick_bin<PER>(sh, c, excl, k_rem);
+    const uint32_t d = sh.pick[0], held = sh.pick[2], width = (1u << shift) - 1u;
+    k_rem = sh.pick[1];
+    from = lo + (d << shift);
+    to = hi - from < width ? hi : from + width;
+    if (held <= kFinListMax) {                          // uniform
+      if (tid == 0) sh.pick[3] = 0;
+      __syncthreads();
+      each([&](uint32_t k, bool valid) {
+        if (valid && k - from <= to - from) sh.list[atomicAdd(&sh.pick[3], 1u)] = k;      // `held` of them
+      });
+      __syncthreads();
+      pick_listed(sh.list, held, thr, k_rem);
+      return;
+    }
+  }
+}
+
 // The k-th smallest of the row's keys and how many keys equal to it are kept.  n: finish_load's result.
 // The k-th key is hardly outside [below, bound] (both from the sample): 2048 bins of equal width there, and the few keys
-// of the bin that holds the k-th compared with each other.  Where the k-th is before them or its bin holds more than
-// kFinListMax, and for whole rows, the radix select.
+// of the bin that holds the k-th compared with each other.  Where its bin holds more than kFinListMax, that is cut in turn; where
+// it is before them, all keys before them are.  Whole rows take the radix select.
 __device__ __forceinline__ void finish_threshold(FinishShared& sh, const uint32_t* lds_cand, const SelectArgs& a, int row,
                                                  int n, uint32_t bound, uint32_t below, uint32_t& thr, uint32_t& k_rem) {
   const int tid = threadIdx.x;
@@ -454,36 +538,28 @@ __device__ __forceinline__ void finish_threshold(FinishShared& sh, const uint32_
       atomicAdd(&sh.h[clamped_bin(key, below, bound, shift)], 1u);
   }
   __syncthreads();
-  const uint32_t c0 = sh.h[2 * tid], c1 = sh.h[2 * tid + 1], kk = (uint32_t)a.k;
+  const uint32_t c[2] = {sh.h[2 * tid], sh.h[2 * tid + 1]}, kk = (uint32_t)a.k;
   uint32_t excl, total;
-  block_scan<false>(sh.sm, c0 + c1, lower, excl, total, lower);
-  excl += lower;
-  if (tid == 0 && lower >= kk) {                        // the k-th is before `below`
-    sh.pick[1] = kk;
-    sh.pick[2] = kFinListMax + 1u;
+  block_scan<false>(sh.sm, c[0] + c[1], lower, excl, total, lower);
+  if (__builtin_expect(lower >= kk, 0)) {               // uniform: the k-th is before `below`
+    k_rem = kk;
+    zoom_threshold<2>(sh.bins, sh.sm, sh.h, lds_cand, n, 0u, below - 1u, thr, k_rem);
+    return;
   }
-  if (excl < kk && kk <= excl + c0) {                   // one bin of the workgroup (n >= k)
-    sh.pick[0] = 2u * tid;
-    sh.pick[1] = kk - excl;
-    sh.pick[2] = c0;
-  } else if (excl + c0 < kk && kk <= excl + c0 + c1) {
-    sh.pick[0] = 2u * tid + 1u;
-    sh.pick[1] = kk - excl - c0;
-    sh.pick[2] = c1;
-  }
-  __syncthreads();
-  const uint32_t d = sh.pick[0], c = sh.pick[2];
-  k_rem = sh.pick[1];
-  if (c > kFinListMax) {                                // uniform
-    radix_select_block(n, kk, [&](int i) { return lds_cand[i]; }, sh.h, sh.sm, thr, k_rem);
+  pick_bin<2>(sh.bins, c, lower + excl, kk);            // n >= k
+  const uint32_t d = sh.bins.pick[0], held = sh.bins.pick[2];
+  k_rem = sh.bins.pick[1];
+  if (__builtin_expect(held > kFinListMax, 0)) {        // uniform
+    const uint32_t from = below + (d << shift), width = (1u << shift) - 1u;
+    zoom_threshold<2>(sh.bins, sh.sm, sh.h, lds_cand, n, from, bound - from < width ? bound : from + width, thr, k_rem);
     return;
   }
   for (int i = tid; i < n; i += kFinThreads) {
     const uint32_t key = lds_cand[i];
-    if (key >= below && clamped_bin(key, below, bound, shift) == d) sh.list[atomicAdd(&sh.pick[3], 1u)] = key;   // c of them
+    if (key >= below && clamped_bin(key, below, bound, shift) == d) sh.bins.list[atomicAdd(&sh.bins.pick[3], 1u)] = key;   // `held` of them
   }
   __syncthreads();
-  pick_listed(sh.list, c, thr, k_rem);
+  pick_listed(sh.bins.list, held, thr, k_rem);
 }
 
 // The kept tokens in ascending order, then the window tokens.
@@ -532,28 +608,23 @@ __device__ __forceinline__ void select_finish_body(void* lds, const SelectArgs& 
 }
 
 // All three steps for a row of at most PER * kFinThreads scores, one workgroup per row: every token is a candidate.  The
-// threshold as in the finish step, in 4096 bins between the row's smallest and largest key; the radix select where the k-th's
-// bin holds more than kFinListMax.  Bound by latency.  8 rows, us, with the radix select for all and so: 2000 scores 7.4,
-// 5.7; 8000 10.4, 7.1; 12000 12.9, 7.9; 12000 of a few
-// values 12.9, 16.6 (equal keys are counted one after the other; kept apart by ballots they cost ordinary rows 1 to 2.5 us).
+// threshold as in the finish step, in 4096 bins between the row's smallest and largest key.  Bound by latency.  8 rows, us, with
+// the radix select and so: 2000 scores 7.4, 5.7; 8000 10.4, 7.1; 12000 12.9, 7.9; 12000
+// of a few values 15.0, 11.2; within 2 % beside outliers 15.5, 12.2; 16000 so (then in three launches) 21.5, 16.9.
 // PER keys a thread.
 template <int PER>
 struct ShortSelectShared {
   uint4 keys[PER * kFinThreads / 4];
-  union {
-    uint4 bin[kFinThreads];
-    uint32_t h[kHistWords];
-  };
+  uint4 bin[kFinThreads];
   uint32_t sm[2 * kFinWaves + 2];
-  uint32_t list[kFinListMax];
-  uint32_t pick[4];
+  BinPick bins;
 };
 template <int PER>
 __device__ __forceinline__ void select_short_body(ShortSelectShared<PER>& sh, const SelectArgs& a, int row) {
   const int tid = threadIdx.x, T = a.T;
   constexpr int kPer = PER, kMost = PER * kFinThreads, kWrite = PER <= 16 ? PER : 16;      // keys a thread writes together
   static_assert(PER % 4 == 0 && PER % kWrite == 0, "four keys per read");
-  const float* sr = a.scores + (int64_t)row * T;
+  const float* sr = a.scores + (int64_t)row * a.T;
   uint32_t* keys = &sh.keys[0].x;
   uint32_t key[kPer], lo = 0xffffffffu, hi = 0u, thr, k_rem;
   {
@@ -564,7 +635,7 @@ __device__ __forceinline__ void select_short_body(ShortSelectShared<PER>& sh, co
     for (int u = 0; u < kPer; ++u) key[u] = order_key(f[u]);
   }
   sh.bin[tid] = make_uint4(0u, 0u, 0u, 0u);
-  if (tid == 0) sh.pick[3] = 0;
+  if (tid == 0) sh.bins.pick[3] = 0;
 #pragma unroll
   for (int u = 0; u < kPer; ++u)
     if (u * kFinThreads < T) {                          // uniform; positions past the end repeat the last key
@@ -573,39 +644,39 @@ __device__ __forceinline__ void select_short_body(ShortSelectShared<PER>& sh, co
       hi = max(hi, key[u]);
     }
   block_min_max(sh.sm, lo, hi);
-  const int shift = bin_shift(lo, hi, kSampleBinBits);
-  uint32_t* bin = &sh.bin[0].x;
+  thr = lo;
+  k_rem = (uint32_t)a.k;
+  if (lo != hi) {                                       // uniform; else all scores are equal
+    const int shift = bin_shift(lo, hi, kSampleBinBits);
+    uint32_t* bin = &sh.bin[0].x;
+    const Repeated rep = find_repeated((key[0] - lo) >> shift, tid < T);
+    if (rep.none()) {             // uniform
 #pragma unroll
-  for (int u = 0; u < kPer; ++u)
-    if (lo != hi && tid + u * kFinThreads < T) atomicAdd(&bin[(key[u] - lo) >> shift], 1u);
-  __syncthreads();
-  const uint4 c4 = sh.bin[tid];
-  const uint32_t cs[4] = {c4.x, c4.y, c4.z, c4.w}, kk = (uint32_t)a.k;
-  uint32_t excl, total, most;
-  block_scan<true>(sh.sm, c4.x + c4.y + c4.z + c4.w, 0u, excl, total, most);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    if (excl < kk && kk <= excl + cs[q]) {              // one bin of the workgroup (1 <= k <= T)
-      sh.pick[0] = (uint32_t)(4 * tid + q);
-      sh.pick[1] = kk - excl;
-      sh.pick[2] = cs[q];
+      for (int u = 0; u < kPer; ++u)
+        if (tid + u * kFinThreads < T) atomicAdd(&bin[(key[u] - lo) >> shift], 1u);
+    } else {
+      count_repeated(keys, T, lo, hi, shift, rep, bin);  // (in registers, like the others, it cost rows without any 0.2 to 0.8 us)
     }
-    excl += cs[q];
-  }
-  __syncthreads();
-  const uint32_t d = sh.pick[0], c = sh.pick[2];
-  k_rem = sh.pick[1];
-  if (lo == hi) {                                       // uniform: all scores are equal, nothing was counted
-    thr = lo;
-    k_rem = kk;
-  } else if (c > kFinListMax) {                         // uniform
-    radix_select_block(T, kk, [&](int i) { return keys[i]; }, sh.h, sh.sm, thr, k_rem);
-  } else {
-#pragma unroll
-    for (int u = 0; u < kPer; ++u)
-      if (tid + u * kFinThreads < T && (key[u] - lo) >> shift == d) sh.list[atomicAdd(&sh.pick[3], 1u)] = key[u];   // c of them
     __syncthreads();
-    pick_listed(sh.list, c, thr, k_rem);
+    const uint4 c4 = sh.bin[tid];
+    const uint32_t cs[4] = {c4.x, c4.y, c4.z, c4.w};
+    uint32_t excl, total;
+    block_prefix(sh.sm, c4.x + c4.y + c4.z + c4.w, excl, total);
+    pick_bin<4>(sh.bins, cs, excl, k_rem);              // 1 <= k <= T
+    const uint32_t d = sh.bins.pick[0], held = sh.bins.pick[2];
+    k_rem = sh.bins.pick[1];
+    if (__builtin_expect(held > kFinListMax, 0)) {      // uniform
+      const uint32_t from = lo + (d << shift), width = (1u << shift) - 1u;
+      zoom_threshold<4>(sh.bins, sh.sm, bin, keys, T, from, hi - from < width ? hi : from + width, thr, k_rem);
+    } else {
+#pragma unroll
+      for (int u = 0; u < kPer; ++u)
+        if (tid + u * kFinThreads < T && (key[u] - lo) >> shift == d) sh.bins.list[atomicAdd(&sh.bins.pick[3], 1u)] = key[u];   // `held` of them
+      __syncthreads();
+      pick_listed(sh.bins.list, held, thr, k_rem);
+    }
+  } else {
+    __syncthreads();                                    // the keys are there
   }
   int32_t* out = a.idx_out + (int64_t)row * (a.k + a.W);
   auto four = [&](int i0, uint32_t* x) {

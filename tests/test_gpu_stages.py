@@ -201,6 +201,38 @@ def test_short_ranking_times(gpu_device, T, limit):
     assert max(us.values()) <= limit * us["spread"], us
 
 
+@pytest.mark.parametrize("rows,T", [(8, 8000), (8, 12000), (8, 16000), (64, 30000)])
+def test_short_top_k_times(gpu_device, rows, T):
+    """Top-k by one workgroup per row: the bin that holds the threshold is cut in turn (before: up to 2.6 times the spread scores'
+    time, the whole row again by digits)."""
+    import torch
+    c, k, us = asl.Asl(T + 32, rows, 32), 2048, {}
+    idx = torch.empty((rows, k + 32), dtype=torch.int32, device=gpu_device)
+    p = asl.make_params(1, 1, 64, T + 32, 32, 7, k + 32)
+    for kind, s in _score_kinds(T).items():
+        d = torch.from_numpy(s).to(gpu_device)[None].repeat(rows, 1).contiguous()
+        us[kind] = _graph_us(lambda: c.asl_select_topk(p, d, rows, idx))
+    c.close()
+    assert max(us.values()) <= 2 * us["spread"], us
+
+
+def test_top_k_time_of_scores_with_a_period(gpu_device):
+    """Rows that repeat every 32 scores, where one run of four is sampled per 128: no more than a few times as long as rows without a
+    period (with the runs at one phase, eight times: the bound let too many or too few pass)."""
+    import torch
+    T, rows, us = 131040, 8, []
+    rng = np.random.default_rng(1)
+    spread = np.exp(2 * rng.standard_normal(T)).astype(np.float32)
+    c = asl.Asl(T + 32, rows, 32)
+    idx = torch.empty((rows, 2048 + 32), dtype=torch.int32, device=gpu_device)
+    p = asl.make_params(1, 1, 64, T + 32, 32, 7, 2048 + 32)
+    for s in (spread, np.tile(spread[:32], T // 32)):
+        d = torch.from_numpy(s).to(gpu_device)[None].repeat(rows, 1).contiguous()
+        us.append(_graph_us(lambda: c.asl_select_topk(p, d, rows, idx)))
+    c.close()
+    assert us[1] <= 4 * us[0], us
+
+
 def test_rank_special(ctx, gpu_device):
     T = 5000
     _rank_case(ctx, gpu_device, np.ones(T, dtype=np.float32))                               # all equal
