@@ -598,7 +598,7 @@ asl_status asl_layer_step(asl_ctx* ctx, const asl_params* p, const void* q_obs, 
     asl::RankvarArgs ra = asl::rankvar_args(ctx->ws, rank_ring, l_obs, T, layer_idx, k_sel, tau, 1, state, out);
     ra.skip = layer_idx < l_min ? 1 : 0;
     hipError_t et = asl::launch_tail(ctx->ws, scores, Hk + 1, T, k_sel, p->window, row, idx_out,
-                                     k_out != nullptr ? &ga : nullptr, Hk, want_sample, ra, hs, &taken);
+                                     k_out != nullptr ? &ga : nullptr, Hk, want_sample, p->pool_kernel, ra, hs, &taken);
     if (et != hipSuccess) return hip_fail(ctx, et, "tail launch");
     if (taken) return ASL_OK;
     // sizes these launches do not take: the two-stream sequence of single calls below

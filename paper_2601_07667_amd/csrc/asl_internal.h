@@ -252,8 +252,8 @@ bool gather_prepare(GatherArgs& a);   // sets cpr_shift; returns whether cpr is 
 // compaction in three launches (two for short contexts) on one stream (tail.hip); *taken = false when the sizes do not fit and nothing was launched.
 struct RankvarArgs;
 hipError_t launch_tail(const Workspace& ws, const float* scores, int rows, int T, int k, int W, int32_t* rank_row,
-                       int32_t* idx_out, const GatherArgs* gather, int Hk, bool have_sample, const RankvarArgs& stat,
-                       hipStream_t st, bool* taken);
+                       int32_t* idx_out, const GatherArgs* gather, int Hk, bool have_sample, int S,
+                       const RankvarArgs& stat, hipStream_t st, bool* taken);
 // Whether launch_tail would take these sizes (so that the pooling kernel can prepare the sample).
 bool tail_takes(const Workspace& ws, int rows, int T);
 

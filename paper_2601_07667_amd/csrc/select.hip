@@ -63,7 +63,7 @@ static hipError_t launch_select_short(Prof* prof, const SelectArgs& a, int rows,
 }
 
 SelectArgs select_args(const Workspace& ws, const float* scores, int T, int k, int W, int32_t* idx_out,
-                       bool have_sample) {
+                       bool have_sample, int S) {
   SelectArgs a = {};
   a.scores = scores;
   a.sample = have_sample ? ws.sel_sample : nullptr;
@@ -77,7 +77,7 @@ SelectArgs select_args(const Workspace& ws, const float* scores, int T, int k, i
   a.m = sel_sample_rank(T, k, a.n_s, run);
   a.slack = sel_bound_slack(T, a.m, a.n_s, run);
   a.m_low = sel_sample_rank_low(T, k, a.n_s, run);
-  a.cand_cap = sel_cand_cap(T, a.m, a.slack, a.n_s, run);
+  a.cand_cap = sel_cand_cap(T, a.m, a.slack, a.n_s, have_sample ? sel_sample_alike(T, S) : run);
   a.bound = ws.sel_bound;
   a.cand = ws.sel_cand;
   a.seg_count = ws.sel_seg_count;
@@ -94,7 +94,7 @@ hipError_t launch_select(const Workspace& ws, const float* scores, int rows, int
   const int rows_per_round = ws.sel_rows;
   for (int row0 = 0; row0 < rows; row0 += rows_per_round) {
     const int nr = rows - row0 < rows_per_round ? rows - row0 : rows_per_round;
-    const SelectArgs a = select_args(ws, scores + (int64_t)row0 * T, T, k, W, idx_out + (int64_t)row0 * (k + W), false);
+    const SelectArgs a = select_args(ws, scores + (int64_t)row0 * T, T, k, W, idx_out + (int64_t)row0 * (k + W), false, 1);
     if (T <= kSelMidT || (T <= kSelShortT && rows >= kSelShortRows)) {
       const hipError_t e = T <= kShortT ? launch_select_short<kShortT / kFinThreads>(ws.prof, a, nr, st)
                                         : launch_select_short<kSelShortT / kFinThreads>(ws.prof, a, nr, st);

@@ -697,8 +697,9 @@ __device__ __forceinline__ void select_short_body(ShortSelectShared<PER>& sh, co
   for (int i = tid; i < a.W; i += kFinThreads) out[a.k + i] = T + i;   // window tokens (Alg. 1 step 10)
 }
 
-// Arguments of a select over `rows` rows of scores (buffers from the workspace; rows <= ws.sel_rows).
+// Arguments of a select over `rows` rows of scores (buffers from the workspace; rows <= ws.sel_rows).  have_sample: the pooling
+// kernel left one behind, of scores it pooled over S tokens.
 SelectArgs select_args(const Workspace& ws, const float* scores, int T, int k, int W, int32_t* idx_out,
-                       bool have_sample);
+                       bool have_sample, int S);
 
 }  // namespace asl

@@ -38,6 +38,8 @@ inline int sel_sample_stride(int T) {
   return (T + n - 1) / n;
 }
 inline int sel_sample_size(int T) { return T / sel_sample_stride(T); }
+// Sampled keys, one per stride, that a pooling of width S makes alike.
+inline int sel_sample_alike(int T, int S) { return (S + sel_sample_stride(T) - 1) / sel_sample_stride(T); }
 // Position of sampled key j among the tokens j * stride .. (j + 1) * stride - 1 that it stands for: a scattered one, so
 // that scores with a period (rows of a grid, repeated text) do not meet a sample of the same period.  With positions
 // j * stride a layer step of 131072 tokens whose scores repeat every 32 had one bucket of 124 K tokens: 4.7 ms.
@@ -79,10 +81,11 @@ inline int sel_bound_slack(int T, int m, int n_s, int run) {
 }
 // Candidates of a row that the finishing workgroup makes room for: half of kSelCandCap where the bound admits more than
 // that once in 10^6 rows at most, since two workgroups then share a compute unit (a row with more is selected from
-// global memory).
-inline int sel_cand_cap(int T, int m, int slack, int n_s, int run) {
+// global memory).  alike: sampled keys that may be as correlated as identical, `run` as above or, for scores pooled over
+// more tokens than the sample's stride, as many strides as the pooling covers.
+inline int sel_cand_cap(int T, int m, int slack, int n_s, int alike) {
   const float per_key = (float)T / (float)n_s;
-  return (float)(m + slack) * per_key + 5.0f * per_key * sqrtf((float)run * (float)m) <= (float)(kSelCandCap / 2) ? kSelCandCap / 2 : kSelCandCap;
+  return (float)(m + slack) * per_key + 5.0f * per_key * sqrtf((float)alike * (float)m) <= (float)(kSelCandCap / 2) ? kSelCandCap / 2 : kSelCandCap;
 }
 // Without a prepared sample the bound kernel reads runs of kSelSampleRun neighbouring keys, one run
 // per kSelSampleRun sample strides: the same number of keys from a quarter of the cache lines.

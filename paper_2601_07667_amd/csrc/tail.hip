@@ -140,14 +140,14 @@ static hipError_t launch_stat_gather(const Workspace& ws, const GatherArgs* gath
 bool tail_takes(const Workspace& ws, int rows, int T) { return rows <= ws.sel_rows && T <= kRankMaxT; }
 
 hipError_t launch_tail(const Workspace& ws, const float* scores, int rows, int T, int k, int W, int32_t* rank_row,
-                       int32_t* idx_out, const GatherArgs* gather, int Hk, bool have_sample, const RankvarArgs& stat,
-                       hipStream_t st, bool* taken) {
+                       int32_t* idx_out, const GatherArgs* gather, int Hk, bool have_sample, int S,
+                       const RankvarArgs& stat, hipStream_t st, bool* taken) {
   *taken = false;
   if (!tail_takes(ws, rows, T)) return hipSuccess;
   if (gather != nullptr && ((int64_t)gather->n_idx * gather->cpr >= (int64_t(1) << 31))) return hipSuccess;
   *taken = true;
   const float* s_all = scores + (int64_t)(rows - 1) * T;       // the all-head row is the last one
-  const SelectArgs se = select_args(ws, scores, T, k, W, idx_out, have_sample);
+  const SelectArgs se = select_args(ws, scores, T, k, W, idx_out, have_sample, S);
   hipError_t e;
   if (T <= kShortT) {
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(tail_short_kernel),

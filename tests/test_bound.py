@@ -55,6 +55,24 @@ def test_ordinary_budgets_keep_the_whole_slack(bound):
         assert slack == m // 8 > 0, q
 
 
+def test_candidates_of_pooled_scores(tmp_path_factory):
+    """Half the candidate buffer is made room for only where the bound admits more once in 10^6 rows, also where pooling makes
+    neighbouring sampled keys alike (the variance of what it admits is then as many times the independent keys')."""
+    queries = [(T, k, S) for T in (12289, 20001, 32736, 65504, 131040, 262080, 1048544) for k in (64, 1000, 2016, 2500, 3000, 3500, 4064)
+               for S in (1, 7, 31, 63, 129)]
+    out = subprocess.run([_client(tmp_path_factory, "cap_client")], input="".join("%d %d %d\n" % q for q in queries), check=True,
+                         capture_output=True, text=True).stdout
+    halves = narrowed = 0
+    for (T, k, S), line in zip(queries, out.splitlines()):
+        n_s, m, slack, alike, cap = (int(x) for x in line.split())
+        assert alike == -(-S // (T // n_s))
+        admits, dev = (m + slack) * T / n_s, T / n_s * m ** 0.5
+        assert cap == 16384 or (cap == 8192 and admits + 5 * alike ** 0.5 * dev <= 8192 * (1 + 1e-6)), (T, k, S)
+        halves += cap == 8192
+        narrowed += cap == 16384 and admits + 5 * dev <= 8192
+    assert halves > 80 and narrowed > 0                # the ordinary budgets; the widest poolings
+
+
 def test_sample_positions(tmp_path_factory):
     """One position in every stride of the row up to its last few tokens, and for every period up to 64 (and some
     longer ones) every phase of it about as often as any other: between half and twice, with six deviations to spare."""
