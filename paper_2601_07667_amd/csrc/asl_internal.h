@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <stddef.h>
 #include "asl.h"
+#include "per_device.h"
 #include "select_bound.h"
 
 namespace asl {
@@ -47,6 +48,14 @@ inline int prof_slot(Prof* p, int kid) {
     else                                                                                                      \
       hipLaunchKernelGGL(kernel, grid, block, lds, stream, __VA_ARGS__);                                      \
   } while (0)
+
+// Lets `kernel` have up to `bytes` of dynamic LDS on the current device.
+inline hipError_t allow_lds(OncePerDevice& once, const void* kernel, size_t bytes) {
+  int device = 0;
+  const hipError_t e = hipGetDevice(&device);
+  if (e != hipSuccess) return e;
+  return once(device, hipSuccess, [&] { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes); });
+}
 
 // Workspace carve-up (device memory owned by the ctx).
 struct Workspace {

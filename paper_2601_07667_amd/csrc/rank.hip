@@ -87,16 +87,16 @@ hipError_t launch_rank(const Workspace& ws, const float* s, int T, int32_t* rank
   const uintptr_t s0 = reinterpret_cast<uintptr_t>(s), r0 = reinterpret_cast<uintptr_t>(rank_out), bytes = (uintptr_t)T * 4;
   const bool in_place = s0 < r0 + bytes && r0 < s0 + bytes;
   if (T <= kShortT && !in_place) {
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(rank_short_kernel),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(ShortRankShared));
+    static OncePerDevice once;
+    const hipError_t attr = allow_lds(once, reinterpret_cast<const void*>(rank_short_kernel), sizeof(ShortRankShared));
     if (attr != hipSuccess) return attr;
     ASL_LAUNCH(ws.prof, kKernSortScatter, st, rank_short_kernel, dim3(short_rank_blocks(T)), dim3(kSortThreads), sizeof(ShortRankShared), st,
                s, T, rank_out);
     return hipGetLastError();
   }
   if (T > kRankMaxT) return hipErrorInvalidConfiguration;
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(rank_bucket_kernel),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(BucketShared));
+  static OncePerDevice once;
+  const hipError_t attr = allow_lds(once, reinterpret_cast<const void*>(rank_bucket_kernel), sizeof(BucketShared));
   if (attr != hipSuccess) return attr;
   RankArgs a = rank_args(ws, s, T, nullptr, rank_out);
   if ((int64_t)a.n_tiles * a.n_s > kSampleDirect) {

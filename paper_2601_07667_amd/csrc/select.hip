@@ -55,8 +55,8 @@ __global__ void __launch_bounds__(kFinThreads) select_short_kernel(SelectArgs a)
 template <int PER>
 static hipError_t launch_select_short(Prof* prof, const SelectArgs& a, int rows, hipStream_t st) {
   constexpr size_t lds = sizeof(ShortSelectShared<PER>);
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(select_short_kernel<PER>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  static OncePerDevice once;
+  const hipError_t attr = allow_lds(once, reinterpret_cast<const void*>(select_short_kernel<PER>), lds);
   if (attr != hipSuccess) return attr;
   ASL_LAUNCH(prof, kKernSelWrite, st, select_short_kernel<PER>, dim3(rows), dim3(kFinThreads), lds, st, a);
   return hipGetLastError();
@@ -87,8 +87,8 @@ SelectArgs select_args(const Workspace& ws, const float* scores, int T, int k, i
 
 hipError_t launch_select(const Workspace& ws, const float* scores, int rows, int T, int k, int W,
                          int32_t* idx_out, hipStream_t st) {
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(select_finish_kernel),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)finish_lds_bytes(kSelCandCap));
+  static OncePerDevice once;
+  const hipError_t attr = allow_lds(once, reinterpret_cast<const void*>(select_finish_kernel), finish_lds_bytes(kSelCandCap));
   if (attr != hipSuccess) return attr;
   // rows beyond what the candidate buffers hold at once take further rounds of the three launches
   const int rows_per_round = ws.sel_rows;

@@ -85,8 +85,8 @@ __global__ void __launch_bounds__(kVarThreads) tail2_kernel(RankvarArgs ra, int 
 template <bool VEC>
 static hipError_t launch_rank_select(const Workspace& ws, const SelectArgs& se, const RankArgs& ra, int rows, hipStream_t st) {
   constexpr size_t kMost = finish_lds_bytes(kSelCandCap) > sizeof(BucketShared) ? finish_lds_bytes(kSelCandCap) : sizeof(BucketShared);
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(tail1_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     (int)kMost);
+  static OncePerDevice once;
+  const hipError_t attr = allow_lds(once, reinterpret_cast<const void*>(tail1_kernel), kMost);
   if (attr != hipSuccess) return attr;
   const dim3 block(kTailThreads), grid1(rows + ra.n_buckets);
   // Tiles per filtering workgroup: as few as leave launch 0 one workgroup per compute unit; two on a unit slow down each
@@ -150,8 +150,8 @@ hipError_t launch_tail(const Workspace& ws, const float* scores, int rows, int T
   const SelectArgs se = select_args(ws, scores, T, k, W, idx_out, have_sample, S);
   hipError_t e;
   if (T <= kShortT) {
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(tail_short_kernel),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTailShortLds);
+    static OncePerDevice once;
+    const hipError_t attr = allow_lds(once, reinterpret_cast<const void*>(tail_short_kernel), kTailShortLds);
     if (attr != hipSuccess) return attr;
     ASL_LAUNCH(ws.prof, kKernTail, st, tail_short_kernel, dim3(rows + short_rank_blocks(T)), dim3(kTailThreads), kTailShortLds, st,
                s_all, rank_row, se, rows);

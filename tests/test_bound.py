@@ -1,4 +1,5 @@
-"""The top-k's bound leaves the candidate buffers room (host arithmetic of the library's header; no GPU needed)."""
+"""Host arithmetic of the library's headers, no GPU needed: the top-k's bound leaves the candidate buffers room, the sample
+is scattered, attributes are set once per device."""
 import os
 import shutil
 import subprocess
@@ -90,3 +91,9 @@ def test_sample_positions(tmp_path_factory):
             if stride >= period:
                 assert min(count) >= mean / 2 - 6 * mean ** 0.5 and min(count) > 0, (T, period)
                 assert max(count) <= 2 * mean + 6 * mean ** 0.5, (T, period)
+
+
+def test_once_per_device(tmp_path_factory):
+    """Kernel attributes are set on every device that launches the kernel, not once in the process; failures are tried again."""
+    out = subprocess.run([_client(tmp_path_factory, "once_client")], capture_output=True, text=True)
+    assert out.returncode == 0 and out.stdout == "ok\n"
