@@ -9,8 +9,8 @@ constexpr int kSortThreads = kRowThreads;
 constexpr int kSortWaves = kSortThreads / 64;
 
 struct DigitShared {
-  uint16_t cnt[kSortWaves][256];                        // pairs per wavefront and digit
-  uint16_t start[kSortWaves][256];                      // their first places
+  alignas(8) uint16_t cnt[kSortWaves][256];             // pairs per wavefront and digit
+  alignas(8) uint16_t start[kSortWaves][256];           // their first places
 };
 
 // Sorts n <= PER * kSortThreads pairs in LDS by key, equal keys in the order they are in: LSD radix passes of 8 bits over the
@@ -28,13 +28,15 @@ __device__ __forceinline__ void sort_by_digits(uint32_t* key, Tok* tok, DigitSha
   }
   block_min_max(red, lo, hi);
   const int bits = hi == lo ? 0 : 32 - __clz((int)(hi - lo)), n_pass = (bits + 7) / 8;
-  uint2* my_cnt = reinterpret_cast<uint2*>(&sh.cnt[wave][4 * lane]);         // digits 4 lane .. 4 lane + 3
   for (int pass = 0; pass < n_pass; ++pass) {           // uniform
     const int shift = 8 * pass;
     int e = wave * 64 * rounds + lane;                  // this thread's pair r: e + 64 r
     asm volatile("" : "+v"(e));                         // addresses are worked out per pass, not held through it
     uint32_t k[PER], t[PER], off[PER];
-    *my_cnt = make_uint2(0u, 0u);
+    // digits 4 lane .. 4 lane + 3.  Lanes read what others of their wavefront wrote without a workgroup barrier between (LDS
+    // operations of a wavefront are in order): by bytes, since words of another type might be taken not to be the same
+    __builtin_memset(&sh.cnt[wave][4 * lane], 0, 8);
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int r = 0; r < PER; ++r) {
       k[r] = lo;
@@ -66,13 +68,16 @@ __device__ __forceinline__ void sort_by_digits(uint32_t* key, Tok* tok, DigitSha
 #pragma unroll 8
     for (int w = 0; w < kSortWaves; ++w) {
       if (w == wave) prev = tot;
-      const uint2 c = *reinterpret_cast<const uint2*>(&sh.cnt[w][4 * lane]);
+      uint2 c;
+      __builtin_memcpy(&c, &sh.cnt[w][4 * lane], 8);
       tot.x += c.x;
       tot.y += c.y;
     }
     const uint32_t t0 = tot.x & 0xffffu, t1 = tot.x >> 16, t2 = tot.y & 0xffffu, t3 = tot.y >> 16, sum = t0 + t1 + t2 + t3;
     const uint32_t s0 = wave_prefix_sum(sum) - sum, s1 = s0 + t0, s2 = s1 + t1;
-    *reinterpret_cast<uint2*>(&sh.start[wave][4 * lane]) = make_uint2(prev.x + (s0 | (s1 << 16)), prev.y + (s2 | ((s2 + t2) << 16)));
+    const uint2 starts = make_uint2(prev.x + (s0 | (s1 << 16)), prev.y + (s2 | ((s2 + t2) << 16)));
+    __builtin_memcpy(&sh.start[wave][4 * lane], &starts, 8);
+    __builtin_amdgcn_wave_barrier();                    // a lane reads what others of its wavefront wrote
 #pragma unroll
     for (int r = 0; r < PER; ++r) {
       if (r < rounds && e + 64 * r < n) {
