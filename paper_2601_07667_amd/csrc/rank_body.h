@@ -415,10 +415,16 @@ __device__ __forceinline__ uint32_t bucket_of_place(const RankArgs& a, uint32_t 
 
 constexpr uint32_t kHeavyBin = 0x80000000u;
 constexpr int kMaxHeavyBins = kRankMaxBuckets / 2 + 1;  // of one level: each holds more than two buckets' worth of the sample
+constexpr int kSortedSample = 4096;                     // most keys of a sample that is sorted
 struct PartShared {
-  SampleShared s;                                       // bin: the sample's counts, then the bucket of each bin, or kHeavyBin | its number
+  SampleShared s;                                       // bin: the sample's counts, then the bucket of each bin, or kHeavyBin | its number;
+                                                        // of a sorted sample its numbers, then the buckets' first pairs
   union {
     uint16_t cnt[kSortWaves][kRankMaxBuckets];          // tokens per wavefront and bucket, then their first places
+    struct {                                            // a sample to be sorted (sort_sample)
+      uint32_t key[kSortedSample];
+      DigitShared digit;
+    };
     struct {                                            // of heavy bins (heavy_bins), until every token has its bucket
       union {
         uint32_t words[4 * kMaxHeavyBins + kSampleBins];
@@ -434,6 +440,8 @@ struct PartShared {
   };
 };
 static_assert(sizeof(PartShared) <= 65536, "static LDS");
+static_assert(sizeof(uint16_t) * kSortedSample <= sizeof(SampleShared::bin) && kSortedSample >= 4 * kRankMaxBuckets &&
+                  sizeof(uint2) * kRankMaxBuckets <= sizeof(SampleShared::bin), "a sorted sample's numbers, then its borders, are held in bin");
 
 // Sub-bin of a key of heavy bin h, or the bin's nearest one.
 __device__ __forceinline__ uint32_t sub_bin(const PartShared& sh, uint32_t h, uint32_t key) {
@@ -447,12 +455,13 @@ __device__ __forceinline__ uint32_t sub_bin(const PartShared& sh, uint32_t h, ui
 //    shared out among them in token order, by how many of the sampled ones come before, so that such a bucket
 //    holds equal keys only.
 //  - Any other is cut into sub-bins between its smallest and largest sampled key: of 4096 in all as many as its share of the
-//    sample.  Sub-bins that are still heavy and hold one sampled key are treated as above; with several they make
-//    one bucket of more than it should have.
+//    sample.  Sub-bins that are still heavy and hold one sampled key are treated as above.
+// Returns whether there are any that hold several: the bins' buckets are then of no use (half of 131040 scores within 100 of
+// the next representable ones, all others spread: one bucket of 65 K, 490 us; with three such scores 1550).
 // A wavefront's instruction takes 16 cycles of the unit here, so it is their number that counts: ~4.5 us for four sampled keys
 // a thread.  (Sorting the sample instead took 18 us in every tile.  Ranking alone, us, so and sorted: 131040 scores, a third zeros
 // 20.4, 42.5; rounded to whole numbers 26.2, 41.6; with a period of 32 19.6, 39.7; a million equal ones 30, 102.)
-__device__ __forceinline__ void heavy_bins(PartShared& sh, const RankArgs& a, const uint32_t (&v)[kSamplePer], uint32_t lo, int shift,
+__device__ __forceinline__ bool heavy_bins(PartShared& sh, const RankArgs& a, const uint32_t (&v)[kSamplePer], uint32_t lo, int shift,
                                            const uint4& c, uint32_t first, uint32_t h, uint32_t n_heavy, int me) {
   const int tid = threadIdx.x, lane = tid & 63;
   const uint32_t n_s = (uint32_t)a.n_s, most = (uint32_t)a.heavy;
@@ -548,7 +557,7 @@ __device__ __forceinline__ void heavy_bins(PartShared& sh, const RankArgs& a, co
 #pragma unroll
   for (int i = 0; i < 4; ++i) x += cs2[i] > most ? 65536u : 0u;
   block_prefix(sh.s.red, x, x, total);
-  if (total == 0u) return;                              // uniform: single keys only
+  if (total == 0u) return false;                        // uniform: single keys only
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const uint32_t before = x & 0xffffu, number = n_heavy + (x >> 16);         // < 2 kMaxHeavyBins
@@ -562,13 +571,57 @@ __device__ __forceinline__ void heavy_bins(PartShared& sh, const RankArgs& a, co
   }
   sh.sub4[tid] = make_uint4(entry[0], entry[1], entry[2], entry[3]);
   __syncthreads();
-  if (total >> 16 == 0u) return;                        // uniform
+  if (total >> 16 == 0u) return false;                  // uniform
   each([&](int u, bool) {
     const int b = in[u];
     if (b >= 0) in[u] = sh.lo[b] == sh.hi[b] ? -1 : (int)(sub[sub_bin(sh, (uint32_t)b, v[u])] >> 16) - 1;
   });
   ranges();
+  const uint32_t number = n_heavy + min((uint32_t)tid, (total >> 16) - 1u);
+  if (__syncthreads_or(sh.lo[number] != sh.hi[number]) != 0) return true;      // uniform
   count(false);
+  return false;
+}
+
+// For a sample that bins and sub-bins do not tell apart: sorted, every n_s / B-th pair (key, token) of it is the first of a
+// bucket, so that equal scores are shared out by token whatever the scores are.  Leaves border[b], b > 0, in sh.s.bin.
+// One of every 2^thin keys: four a bucket are enough here, and sorting costs what it sorts (1024 keys ~18 us in every tile).
+__device__ __forceinline__ void sort_sample(PartShared& sh, const RankArgs& a, const uint32_t (&v)[kSamplePer]) {
+  const int tid = threadIdx.x, B = a.n_buckets, need = max(4 * B, 1024);
+  const int thin = a.n_s >= 8 * need ? 3 : a.n_s >= 4 * need ? 2 : a.n_s >= 2 * need ? 1 : 0;
+  const int n_s = min(a.n_s >> thin, kSortedSample);
+  uint16_t* num = reinterpret_cast<uint16_t*>(sh.s.bin);
+#pragma unroll
+  for (int u = 0; u < kSamplePer; ++u) {
+    const int j = tid + u * kSortThreads, i = j >> thin;
+    const uint32_t pick = (uint32_t)i * 2654435761u >> 24;                   // any of the group's, for periodic scores
+    if ((((uint32_t)j ^ pick) & ((1u << thin) - 1u)) == 0u && i < n_s) {
+      sh.key[i] = v[u];
+      num[i] = (uint16_t)j;
+    }
+  }
+  __syncthreads();
+  sort_by_digits<kSortedSample / kSortThreads>(sh.key, num, sh.digit, sh.s.red, n_s);
+  uint2 first = make_uint2(0u, 0u);
+  if (tid < B) {
+    const int i = (int)((uint32_t)tid * (uint32_t)n_s / (uint32_t)B);
+    first = make_uint2(sh.key[i], sel_sample_position(num[i], a.stride));
+  }
+  __syncthreads();                                      // num is read
+  if (tid < B) reinterpret_cast<uint2*>(sh.s.bin)[tid] = first;
+  __syncthreads();
+}
+// Bucket of token t with this key, by such borders: the last that is not behind the pair.
+__device__ __forceinline__ uint32_t bucket_by_borders(const PartShared& sh, int B, uint32_t key, uint32_t t) {
+  const uint2* border = reinterpret_cast<const uint2*>(sh.s.bin);
+  int b = 0;
+  for (int step = kRankMaxBuckets / 2; step > 0; step >>= 1) {
+    if (b + step < B) {
+      const uint2 x = border[b + step];
+      if (x.x < key || (x.x == key && x.y <= t)) b += step;
+    }
+  }
+  return (uint32_t)b;
 }
 
 // Bucket of token t (in tile `me`) with this key, where the sample has heavy bins.  Monotone in (key, token).
@@ -600,7 +653,7 @@ __device__ __forceinline__ uint32_t bucket_of_token(const PartShared& sh, const 
 // Every tile works out the same bucket borders from the same sample, so tiles agree on nothing else and wait for
 // nobody.  Bound by latency: the loads, three counts with a scan each, the stores.
 // Borders are those of the sample's histogram bins: bucket b holds the bins whose first sampled key has a place in
-// [b, b + 1) n_s / B.  Where a bin holds more than a.heavy sampled keys, see heavy_bins.
+// [b, b + 1) n_s / B.  Where a bin holds more than a.heavy sampled keys, see heavy_bins, and sort_sample.
 template <int R>
 __device__ __forceinline__ void partition_body(PartShared& sh, const RankArgs& a, int me) {
   const int tid = threadIdx.x, wave = uniform_wave(), lane = tid & 63, T = a.T, B = a.n_buckets;
@@ -638,9 +691,14 @@ __device__ __forceinline__ void partition_body(PartShared& sh, const RankArgs& a
       a.edge[0] = lo;
       a.edge[B] = hi;
     }
-    heavy_bins(sh, a, v, lo, shift, c, first & 0xffffu, first >> 16, n_heavy, me);
+    if (heavy_bins(sh, a, v, lo, shift, c, first & 0xffffu, first >> 16, n_heavy, me)) {       // uniform
+      sort_sample(sh, a, v);
 #pragma unroll
-    for (int r = 0; r < R; ++r) d[r] = bucket_of_token(sh, a, lo, hi, shift, key[r], e0 + 64 * r, me);
+      for (int r = 0; r < R; ++r) d[r] = bucket_by_borders(sh, B, key[r], (uint32_t)(e0 + 64 * r));
+    } else {
+#pragma unroll
+      for (int r = 0; r < R; ++r) d[r] = bucket_of_token(sh, a, lo, hi, shift, key[r], e0 + 64 * r, me);
+    }
     __syncthreads();                                    // the tables are read, the counts go there
   } else {
     const uint32_t past = (hi - lo) >> shift;

@@ -177,6 +177,32 @@ def test_rank_time_hardly_depends_on_the_scores(gpu_device, T):
     c.close()
 
 
+@pytest.mark.parametrize("T", [40000, 131040, 262080, 1048544])
+def test_rank_time_of_scores_few_ulps_apart(gpu_device, T):
+    """Half of the scores, or a third, so close together that neither the sample's bins nor the sub-bins of the full ones tell them
+    apart, beside spread ones: the sample is sorted, and a ranking takes at most five times as long as that of spread ones (before:
+    in one bucket of a single workgroup, up to 140 times), and is exact."""
+    import torch
+    rng = np.random.default_rng(T)
+    spread = np.exp(2 * rng.standard_normal(T)).astype(np.float32)
+    part, one = rng.random(T), np.float32(1).view(np.int32)
+    wide = np.exp(4 * rng.standard_normal(T))
+    kinds = {f"within {n} ulps": np.where(part < 0.5, (one + rng.integers(0, n, T)).astype(np.int32).view(np.float32), spread) for n in (3, 100)}
+    kinds["two clusters"] = np.select([part < 1 / 3, part < 2 / 3], [1 + 1e-6 * rng.standard_normal(T), 1 + 1e-3 * rng.standard_normal(T)],
+                                      wide).astype(np.float32)
+    kinds["mostly"] = np.where(part < 0.97, (one + rng.integers(0, 20, T)).astype(np.int32).view(np.float32), wide).astype(np.float32)
+    c = asl.Asl(T, 1, 32)
+    out = torch.empty((T,), dtype=torch.int32, device=gpu_device)
+    d = torch.from_numpy(spread).to(gpu_device)
+    limit = 5 * _graph_us(lambda: c.asl_rank(d, T, out))
+    for kind, s in kinds.items():
+        _rank_case(c, gpu_device, s)
+        d = torch.from_numpy(s).to(gpu_device)
+        us = _graph_us(lambda: c.asl_rank(d, T, out))
+        assert us <= limit, f"{kind}: {us:.1f} us, limit {limit:.1f}"
+    c.close()
+
+
 def _score_kinds(T):
     """Spread scores, scores that repeat, and scores that lie close together beside an outlier."""
     rng = np.random.default_rng(T)
