@@ -583,7 +583,7 @@ asl_status asl_layer_step(asl_ctx* ctx, const asl_params* p, const void* q_obs, 
   st = score_layer_impl(ctx, p, q_obs, k, lse, p_head, s_all, stream, true, want_sample);
   if (st != ASL_OK) return st;
   if (fused) {
-    // one stream: launch i carries pass i of the ranking sort and stage i of top-k + compaction
+    // one stream: its launches carry the stages of the ranking and the statistic beside those of the top-k and the compaction
     if (!rank_ring || !state || !out) return fail(ctx, ASL_EINVAL, "null pointer");
     st = rankvar_checks(ctx, l_obs, T, layer_idx, k_sel);
     if (st != ASL_OK) return st;

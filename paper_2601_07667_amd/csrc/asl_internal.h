@@ -257,7 +257,7 @@ struct GatherArgs {
 };
 hipError_t launch_gather(Prof* prof, const GatherArgs& args, int Hk, int n_layers, hipStream_t st);
 bool gather_prepare(GatherArgs& a);   // sets cpr_shift; returns whether cpr is a power of two
-// Ranking sort of the last of `rows` score rows + top-k of all rows + optional statistic and KV
+// Ranking of the last of `rows` score rows + top-k of all rows + optional statistic and KV
 // compaction in three launches (two for short contexts) on one stream (tail.hip); *taken = false when the sizes do not fit and nothing was launched.
 struct RankvarArgs;
 hipError_t launch_tail(const Workspace& ws, const float* scores, int rows, int T, int k, int W, int32_t* rank_row,
