@@ -37,7 +37,8 @@ __global__ void __launch_bounds__(kTailThreads) tail_short_kernel(const float* s
 }
 
 // launch 0: the ranking's partition | top-k bound and filter (TILES tiles of a score row per workgroup; VEC: 16-byte
-// loads, for rows that start on 16-byte boundaries)
+// loads, for rows that start on 16-byte boundaries).  64 registers, for two workgroups a unit where the grid has more than one for
+// each: rows off 16 bytes in four tiles a workgroup spill 9 of them (36 bytes of scratch).
 template <int R, bool VEC, int TILES>
 __global__ void __launch_bounds__(kTailThreads, 8) tail0_kernel(RankArgs ra, SelectArgs se) {
   __shared__ PartFilterShared sh;
@@ -96,12 +97,17 @@ static hipError_t launch_rank_select(const Workspace& ws, const SelectArgs& se, 
   const int tiles = grid0(1) <= kTailUnits ? 1 : grid0(2) <= kTailUnits ? 2 : kFilterMostTiles;
   auto launch0 = [&](auto r) {
     constexpr int R = decltype(r)::value;
-    if (tiles == 1)
-      ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<R, VEC, 1>), dim3(grid0(1)), block, 0, st, ra, se);
-    else if (tiles == 2)
-      ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<R, VEC, 2>), dim3(grid0(2)), block, 0, st, ra, se);
-    else
-      ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<R, VEC, 4>), dim3(grid0(4)), block, 0, st, ra, se);
+    if constexpr (R < 8) {                              // the 8192-token tiles come with more than a unit's share of the filter's
+      if (tiles == 1) {
+        ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<R, VEC, 1>), dim3(grid0(1)), block, 0, st, ra, se);
+        return;
+      }
+      if (tiles == 2) {
+        ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<R, VEC, 2>), dim3(grid0(2)), block, 0, st, ra, se);
+        return;
+      }
+    }
+    ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<R, VEC, 4>), dim3(grid0(4)), block, 0, st, ra, se);
   };
   if (ra.tile_log == 11)
     launch0(std::integral_constant<int, 2>());
