@@ -420,15 +420,14 @@ def test_layer_step_evaluates_around_the_short_limit(gpu_device, N):
 
 
 def test_layer_step_at_bench_size_and_beyond(gpu_device):
-    """asl_layer_step at the size the benchmark times (C3: 64 sort tiles beside the top-k stages) and at
-    2^20 tokens (the ranking sort switches to its large tiles): bit-identical to the single calls, and
-    both match the oracle."""
+    """asl_layer_step at the size the benchmark times (C3: 64 ranking tiles beside the top-k stages) and at
+    2^20 tokens (256 tiles of 4096): bit-identical to the single calls, and both match the oracle."""
     L = synth.config_layer(3)
     _check_layer(L, _layer_step_case(gpu_device, L))
     sh = synth.Shape(Hq=4, Hk=2, d=128, N=1 << 20, W=32, S=7, budget=8192)
     L = synth.iid_layer(sh, 78, name="1M-step")
     _check_layer(L, _layer_step_case(gpu_device, L))
-    # the other shapes the benchmark times: 256K / W = 64 (128 sort tiles) and the second model shape with
+    # the other shapes the benchmark times: 256K / W = 64 (64 ranking tiles) and the second model shape with
     # budget 8192 (5 score rows); here against the single calls only (their oracle parity is tested above)
     _layer_step_case(gpu_device, synth.config_layer(5), layer_idx=12)
     sh = synth.Shape(Hq=28, Hk=4, d=128, N=131072, W=32, S=7, budget=8192, L_min=9)
@@ -440,10 +439,11 @@ def test_layer_step_at_bench_size_and_beyond(gpu_device):
                                          (32, 60017, 777),      # four, the last workgroup of a row with three
                                          (16, 75020, 8192),     # rows on 16-byte boundaries, large budget
                                          (2, 131072 + 17, 64),  # the first size with ranking tiles of 4096
+                                         (1, 1048576 + 17, 2048), (1, 1048576 + 20, 500),   # ... of 8192, rows off 16 bytes and on
                                          (1, 12289 + 16, 8192)])
 def test_layer_step_geometries(gpu_device, Hk, N, budget):
     """Sizes at which the shared launches change how they are cut: against the single calls, bit for bit."""
-    sh = synth.Shape(Hq=Hk, Hk=Hk, d=64, N=N, W=16, S=7, budget=budget)
+    sh = synth.Shape(Hq=Hk, Hk=Hk, d=64, N=N, W=16, S=7, budget=budget, L_obs=8 if N <= 1 << 20 else 4)   # longer rows' sums fit 64 bits so
     _layer_step_case(gpu_device, synth.iid_layer(sh, N + Hk, name=f"geometry-{Hk}-{N}"))
 
 

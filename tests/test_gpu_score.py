@@ -147,8 +147,6 @@ def test_chunk_counts(gpu_device, Hq, Hk, W, N):
     _close_to_64_bits(P, s, L)
 
 
-# (tiles, chunks per head) on 256 compute units: partials folded in one round of loads of each batch size and in two,
-# three and four, tile counts that leave ragged shares, and the last tile ragged too
 @pytest.mark.parametrize("Hq,Hk,d,W,N,dtype", [(8, 1, 128, 16, 20001, "bf16"), (4, 2, 64, 16, 65600, "bf16"), (7, 1, 128, 64, 20000, "bf16"),
                                                 (3, 3, 128, 32, 65537, "bf16"), (14, 2, 128, 32, 65536, "bf16"),
                                                 (16, 1, 96, 48, 20000, "bf16"), (4, 2, 64, 32, 20000, "f32")])
@@ -160,11 +158,13 @@ def test_partials_combined_by_a_launch_of_their_own(gpu_device, Hq, Hk, d, W, N,
     _close_to_64_bits(P, s, L)
 
 
+# (tiles, chunks per head) on 256 compute units: partials folded in batches of each size and combined by a launch of their
+# own, tile counts that leave ragged shares, and the last tile ragged too
 @pytest.mark.parametrize("Hq,Hk,d,W,N", [
     (1, 1, 64, 16, 64 * 14), (1, 1, 64, 16, 64 * 48), (6, 2, 64, 32, 64 * 95 + 1),       # 14, 48; 96 tiles in 64
     (8, 8, 64, 32, 64 * 2000 + 1),                                                        # 2001 in 96
-    (1, 1, 64, 32, 64 * 600 + 5), (4, 4, 64, 64, 64 * 1100 + 3), (1, 1, 64, 32, 64 * 4096),   # 601 and 1101 in 192; 4096 in 256
-    (6, 1, 64, 32, 64 * 300), (6, 1, 64, 32, 64 * 2048 + 1), (48, 8, 64, 32, 64 * 65 + 9)])   # 192 rows: 300 in 128; 2049 in 256; 66 in 32
+    (1, 1, 64, 32, 64 * 600 + 5), (4, 4, 64, 64, 64 * 1100 + 3), (1, 1, 64, 32, 64 * 4096),   # 601 in 256; 1101 in 192; 4096 in 256
+    (6, 1, 64, 32, 64 * 300), (6, 1, 64, 32, 64 * 2048 + 1), (48, 8, 64, 32, 64 * 65 + 9)])   # 192 rows: 300 in 64; 2049 in 256; 66 in 32
 def test_chunk_counts_of_two_passes(gpu_device, Hq, Hk, d, W, N):
     L = _small(Hq, Hk, d, N, W, S=1, seed=N)
     P, s = _run_score(gpu_device, L)

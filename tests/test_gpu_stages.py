@@ -80,8 +80,8 @@ def test_rank_over_its_own_scores(ctx, gpu_device, T):
 
 @pytest.mark.parametrize("T", [524288, 524289, 700001])
 def test_rank_beyond_the_small_tile_limit(gpu_device, T):
-    """Above 256 tiles of 2048 the sort switches to tiles of 8192 elements: the last size that still uses
-    the small tiles, the first that does not, and a ragged larger one."""
+    """Sizes with half as many tiles of 4096 tokens as one ranking takes, one more with a single token in it, and a ragged one, with
+    heavy ties.  (The tiles change at 131072 and 1048576 tokens: test_rank_buckets, test_rank_where_the_bucket_count_changes.)"""
     torch = _torch()
     c = asl.Asl(T, 1, 32)
     rng = np.random.default_rng(T)
@@ -372,6 +372,23 @@ def test_rank_where_the_bucket_count_changes(gpu_device, T):
     """The last size of 240 buckets, the first and last of 512 and the first beyond, scores mostly distinct: exact."""
     c = asl.Asl(T, 1, 32)
     _rank_case(c, gpu_device, np.exp(2 * np.random.default_rng(T).standard_normal(T)).astype(np.float32))
+    c.close()
+
+
+@pytest.mark.parametrize("kind", ["distinct", "third-zero"])
+def test_longest_ranking(gpu_device, kind):
+    """The longest vector one call takes (2^21 tokens: 256 tiles of 8192, 1024 buckets): exact.  One more token is refused."""
+    import torch
+    T = 1 << 21
+    c = asl.Asl(T + 1, 1, 32)
+    rng = np.random.default_rng(T)
+    s = np.exp(2 * rng.standard_normal(T)).astype(np.float32)
+    if kind == "third-zero":
+        s[rng.random(T) < 1 / 3] = 0.0
+    _rank_case(c, gpu_device, s)
+    with pytest.raises(asl.AslError) as e:
+        c.asl_rank(torch.zeros(T + 1, device=gpu_device), T + 1, torch.zeros(T + 1, dtype=torch.int32, device=gpu_device))
+    assert e.value.status == asl.ASL_EUNSUPPORTED
     c.close()
 
 
