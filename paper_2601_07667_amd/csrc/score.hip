@@ -417,13 +417,14 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
   }
 }
 
-// Fold the per-chunk partials (m_c, z_c), at most 2 kB, of one query row into the row's log2-domain softmax offset
+// Fold the per-chunk partials (m_c, z_c) of one query row into the row's log2-domain softmax offset
 // m + log2(Z).  Two lanes share a row (`half` = 0 or 1, partner = lane ^ 32): each takes every
-// second chunk, in chunk order; the two halves are added in a fixed order, so all workgroups of a launch get
-// the same bits for the same partials.  (score_combine_kernel adds in another order.)
+// second chunk, in chunk order with a running maximum; the two halves are added in a fixed order,
+// so every caller gets the same bits for the same partials.
 // p points at the row's partial of chunk 0; consecutive chunks are M float2 apart.
-// NR rows at once (pointers p[0..NR-1]): the loads go out for all of them before the first
-// is used, so NR rows cost one memory round trip, like one.
+// Batches of kB chunks per lane: all loads of a batch are issued before the first is used.
+// NR rows at once (pointers p[0..NR-1]): the loads of a batch go out for all of them before the first
+// is used, so NR rows cost as many memory round trips as one.
 // kFoldChunks: most partials that pass 2's workgroups fold themselves, two lanes a row in one round of loads.  Beyond, every
 // workgroup reading all of them costs more than a launch in front of pass 2 that does so once (28 heads, 128K, 128 chunks:
 // 92.7 us the scoring with the fold in two rounds, 88.8 with that launch; 7 heads on one, W = 64, 200K, 256 chunks: 78.3,
@@ -433,23 +434,32 @@ template <int NR, int kB>
 __device__ __forceinline__ void combine_rows(const float2* const (&p)[NR], int M, int n_chunks, int half,
                                              float (&out)[NR]) {
   float m[NR], z[NR];
-  float2 v[NR][kB];
-#pragma unroll
-  for (int q = 0; q < NR; ++q)
-#pragma unroll
-    for (int j = 0; j < kB; ++j) {
-      const int c = half + 2 * j;
-      v[q][j] = p[q][(int64_t)min(c, n_chunks - 1) * M];
-      if (c >= n_chunks) v[q][j] = make_float2(kNegBig, 0.f);
-    }
 #pragma unroll
   for (int q = 0; q < NR; ++q) {
     m[q] = kNegBig;
-#pragma unroll
-    for (int j = 0; j < kB; ++j) m[q] = fmaxf(m[q], v[q][j].x);
     z[q] = 0.f;
+  }
+  for (int c0 = half; c0 < n_chunks; c0 += 2 * kB) {
+    float2 v[NR][kB];
 #pragma unroll
-    for (int j = 0; j < kB; ++j) z[q] += v[q][j].y * fast_exp2(v[q][j].x - m[q]);
+    for (int q = 0; q < NR; ++q)
+#pragma unroll
+      for (int j = 0; j < kB; ++j) {
+        const int c = c0 + 2 * j;
+        v[q][j] = p[q][(int64_t)min(c, n_chunks - 1) * M];
+        if (c >= n_chunks) v[q][j] = make_float2(kNegBig, 0.f);
+      }
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      float mb = m[q];
+#pragma unroll
+      for (int j = 0; j < kB; ++j) mb = fmaxf(mb, v[q][j].x);
+      float zb = 0.f;
+#pragma unroll
+      for (int j = 0; j < kB; ++j) zb += v[q][j].y * fast_exp2(v[q][j].x - mb);
+      z[q] = z[q] * fast_exp2(m[q] - mb) + zb;
+      m[q] = mb;
+    }
   }
 #pragma unroll
   for (int q = 0; q < NR; ++q) {
