@@ -7,7 +7,7 @@
 // the row statistics, pass 2 streams K again for the normalised column sums.  When the caller
 // hands over the rows' log-sum-exp, pass 1 is skipped.
 //
-// Work split: a workgroup owns one KV head and a contiguous chunk of keys; wave w owns RB blocks of
+// Work split: a workgroup owns one KV head and every so many-th of its key tiles; wave w owns RB blocks of
 // 32 query rows (RB = 1 up to M = 128 rows, 2 above for the main bf16 shapes) and keeps their
 // fragments in registers for the whole kernel; K tiles of 64 or 32 keys stream global -> LDS directly
 // (ring of 3 buffers, XOR-swizzled) and every wave reads all of them as the other MFMA operand
@@ -81,8 +81,10 @@ struct TilePieces {
   }
 };
 
-// kg, rsb: first key of the KV head and the key stride in bytes.
-template <int P, int NT, bool FULL>
+// kg, rsb: first key of the KV head and the key stride in bytes.  AUX: cache policy of the loads (kAuxStream: see
+// stream_keys).
+constexpr int kAuxPlain = 0, kAuxStream = 2;          // the non-temporal bit
+template <int P, int NT, bool FULL, int AUX>
 __device__ __forceinline__ void issue_tile_loads_impl(const TilePieces<P, NT>& tp, const char* __restrict__ kg,
                                                       int64_t rsb, int key0, int N, int last_piece,
                                                       Piece* __restrict__ lds_buf, int tid) {
@@ -96,7 +98,7 @@ __device__ __forceinline__ void issue_tile_loads_impl(const TilePieces<P, NT>& t
       const char* src = tile_base + tp.src_off[i];
       Piece* dst = lds_buf + (i * NT + wave_slot0);     // wave-uniform base
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                       (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+                                       (__attribute__((address_space(3))) void*)dst, 16, 0, AUX);
     }
   } else {
     // last, partial tile of a head: rows past N - 1 read key N - 1 instead.  Kept as a loop (it runs
@@ -108,7 +110,7 @@ __device__ __forceinline__ void issue_tile_loads_impl(const TilePieces<P, NT>& t
       const char* src = tile_base + (int64_t)r * rsb + TilePieces<P, NT>::piece(i, tid, last_piece) * 16;
       Piece* dst = lds_buf + (i * NT + wave_slot0);
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                       (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+                                       (__attribute__((address_space(3))) void*)dst, 16, 0, AUX);
     }
   }
 }
@@ -116,11 +118,14 @@ __device__ __forceinline__ void issue_tile_loads_impl(const TilePieces<P, NT>& t
 // Full tiles take the precomputed offsets; only a tile that reaches past N pays for clamping.
 template <int P, int NT>
 __device__ __forceinline__ void issue_tile_loads(const TilePieces<P, NT>& tp, const char* __restrict__ kg, int64_t rsb,
-                                                 int key0, int N, int last_piece, Piece* __restrict__ lds_buf, int tid) {
-  if (key0 + key_tile<P>() <= N)
-    issue_tile_loads_impl<P, NT, true>(tp, kg, rsb, key0, N, last_piece, lds_buf, tid);
+                                                 int key0, int N, int last_piece, Piece* __restrict__ lds_buf, int tid,
+                                                 bool stream) {
+  if (key0 + key_tile<P>() > N)
+    issue_tile_loads_impl<P, NT, false, kAuxPlain>(tp, kg, rsb, key0, N, last_piece, lds_buf, tid);
+  else if (stream)                                      // uniform
+    issue_tile_loads_impl<P, NT, true, kAuxStream>(tp, kg, rsb, key0, N, last_piece, lds_buf, tid);
   else
-    issue_tile_loads_impl<P, NT, false>(tp, kg, rsb, key0, N, last_piece, lds_buf, tid);
+    issue_tile_loads_impl<P, NT, true, kAuxPlain>(tp, kg, rsb, key0, N, last_piece, lds_buf, tid);
 }
 
 // Wait until at most CNT of this wave's vector-memory operations (incl. its LDS-direct loads) are
@@ -237,43 +242,45 @@ __device__ __forceinline__ void mma_subtile(const Piece* __restrict__ buf, int s
     _Pragma("unroll") for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[rb][ks]));
 
 
-// Share of the key tiles a workgroup takes.  All workgroups of a pass are resident at once (one
-// round), block b being the (b / n_cu)-th workgroup placed on its compute unit.  A unit's older wavefronts
-// go first, so with two workgroups per unit the second ends up alone on it for the last part of the
-// kernel: the first gets a larger share, the more so the more the arithmetic bounds the kernel (pass 1 +
-// pass 2 at 256K, W = 64, RB = 2: equal shares 152 + 158 us, 1250 : 798 147 + 153, 1350 : 698 145 + 150;
-// 128K, RB = 1: 58 + 51, 55 + 50, 54 + 52).  Up to four tiles per chunk that come out even to 1/16 stay equal:
-// weighted, rounding makes some chunks a tile longer (8 KV heads, whole call, weighted and equal: one tile, W = 64
-// 27.3 and 25.1 us; two tiles, W = 32 20.4 and 19.9; 2.9 22.8 and 22.2; but 2.45, W = 64 31.1 and 31.7, 2.7 of
-// d = 256 21.8 and 22.8, 5.9 28.5 and 28.9).  Weights in 1/1024.
-struct ChunkRange {
-  int tile0, tile_end;
+// The key tiles of a workgroup.  The n_chunks workgroups of a KV head take the tiles in turn: the k-th of them tiles k,
+// k + n_chunks, ..., so that a head's workgroups, which advance together, read one stretch of memory at a time.  (Each with a
+// contiguous share they read at as many places, a power of two apart: a bare ring of this shape streams 268 MB in 44.9 us so,
+// in turn in 41.6; 8B shape, 128K, `lse` supplied, pass 2 61.2 and 58.8 us; 32K, both passes, 33.4 and 31.5.)
+// All workgroups of a pass are resident at once (one round), block b being the (b / n_cu)-th placed on its compute unit.  A
+// unit's older wavefronts go first, so with two workgroups per unit the second ends up alone on it for the last part of the
+// kernel: after `all` rounds of everybody only the first placed take turns (1250 : 798 of a unit's tiles, with two row blocks a
+// wavefront 1350 : 698, the more unequal the more the arithmetic bounds the kernel; pass 1 + pass 2 at 256K, W = 64, equal shares
+// 152 + 158 us, 1250 : 798 147 + 153, 1350 : 698 145 + 150).  Up to four tiles per chunk that come out even to 1/16 stay
+// equal: weighted, rounding makes some chunks a tile longer (8 KV heads, whole call, weighted and equal: one tile, W = 64
+// 27.3 and 25.1 us; two tiles, W = 32 20.4 and 19.9; but 2.45, W = 64 31.1 and 31.7, 5.9 28.5 and 28.9).
+struct TileSplit {
+  int n_chunks;
+  int all;                       // rounds that every chunk takes part in
+  int first;                     // chunks that go on after them
+  int more, longer;              // their further tiles: `more` each, and one for the first `longer` of them
+  __host__ __device__ int count(int chunk) const { return all + (chunk < first ? more + (chunk < longer ? 1 : 0) : 0); }
+  __host__ __device__ int tile(int chunk, int i) const {              // i-th tile of a chunk, i < count(chunk)
+    return chunk + (i < all ? i * n_chunks : all * n_chunks + (i - all) * first);
+  }
+  // from the i-th to the next; backwards from the i-th to the one before: step(i - 1)
+  __device__ __forceinline__ int step(int i) const { return i < all ? n_chunks : first; }
 };
-// Tiles [tile0, tile_end) of chunk `chunk` (0 .. n_chunks-1) of KV head g; the chunks of a head tile
-// [0, n_tiles) exactly, in order.
 template <int RB>
-__device__ __forceinline__ ChunkRange chunk_range(int chunk, int g, int Hk, int n_chunks, int n_tiles, int n_cu) {
+static TileSplit split_tiles(int Hk, int n_chunks, int n_tiles, int n_cu) {
   constexpr int kFirst = RB > 1 ? 1350 : 1250, kSecond = 2048 - kFirst;
   const int grid = n_chunks * Hk;
   const int slots = n_chunks * (1 + (n_tiles > n_chunks) + (n_tiles > 2 * n_chunks) + (n_tiles > 3 * n_chunks));
   const bool even = n_tiles <= slots && 16 * (slots - n_tiles) <= slots;
-  const bool two = grid > n_cu && grid <= 2 * n_cu && !even;
-  // cumulative weight of this head's chunks 0 .. c-1: chunk c' is block c'*Hk + g, placed as number
-  // (c'*Hk + g) / n_cu on its compute unit; the first on it iff c' < ceil((n_cu - g) / Hk)
-  const int n_first = max((n_cu - g + Hk - 1) / Hk, 0);
-  auto cum = [&](int c) -> int {
-    if (!two) return 1024 * c;
-    const int u0 = min(n_first, c);
-    return kFirst * u0 + kSecond * (c - u0);              // < 2^21 for n_chunks <= 256
-  };
-  // Boundaries in fp32 (a 64-bit integer division would cost microseconds at the start of every
-  // workgroup): neighbours evaluate the same expression on the same inputs, so their shared
-  // boundary is the same number, and any monotone rounding gives a valid partition.
-  const float per_weight = (float)n_tiles / (float)cum(n_chunks);
-  ChunkRange r;
-  r.tile0 = min((int)((float)cum(chunk) * per_weight), n_tiles);
-  r.tile_end = (chunk + 1 == n_chunks) ? n_tiles : min((int)((float)cum(chunk + 1) * per_weight), n_tiles);
-  return r;
+  TileSplit s = {n_chunks, 0, n_chunks, 0, 0};
+  if (grid > n_cu && grid <= 2 * n_cu && !even) {
+    s.first = n_cu / Hk < 1 ? 1 : n_cu / Hk;           // block c * Hk + g is the first of its unit iff it is below n_cu
+    s.all = (int)((int64_t)n_tiles * kSecond / (kFirst * s.first + kSecond * (n_chunks - s.first)));
+    if (s.all < 1) s.all = 1;                          // n_chunks <= n_tiles
+  }
+  const int left = n_tiles - s.all * n_chunks;
+  s.more = left / s.first;
+  s.longer = left % s.first;
+  return s;
 }
 
 // This file is compiled with NaNs assumed absent, so this is a bare v_max_f32 / v_max3_f32
@@ -317,18 +324,18 @@ __device__ __forceinline__ void rowstats_fold(const f32x16 (&acc)[RB], int key_l
 // time its MFMAs take.  MASK: tiles that touch the window block or the tail past N (they come last).
 template <typename TE, int P, int NT, int RB, bool PAD, bool MASK>
 __device__ __forceinline__ void rowstats_tile(const Piece* __restrict__ cur, Piece* __restrict__ nxt,
-                                              bool prefetch, const TilePieces<P, NT>& tp, const char* __restrict__ kg, int64_t rsb,
-                                              int prefetch_key0, int np, int last_piece, int tile, int N, int T, const int (&wi)[RB],
+                                              bool prefetch, bool stream, const TilePieces<P, NT>& tp, const char* __restrict__ kg, int64_t rsb,
+                                              int prefetch_key0, int np, int last_piece, int tile, int prev, int N, int T, const int (&wi)[RB],
                                               int tid, int ln, int half, const Piece (&qf)[RB][P / 2], float c1,
                                               f32x16 (&acc)[RB], float (&m_run)[RB], float (&z_run)[RB]) {
   constexpr int KT = key_tile<P>();
-  if (prefetch) issue_tile_loads<P, NT>(tp, kg, rsb, prefetch_key0, N, last_piece, nxt, tid);
+  if (prefetch) issue_tile_loads<P, NT>(tp, kg, rsb, prefetch_key0, N, last_piece, nxt, tid, stream);
 #pragma unroll
   for (int sub = 0; sub < KT / 32; ++sub) {
     f32x16 nxt_acc[RB];
     mma_subtile<TE, P, true, RB, PAD>(cur, sub, ln, half, np, qf, nxt_acc);
-    // the sub-tile before this one: keys (tile * KT + (sub - 1) * 32) + 4 * half ..
-    rowstats_fold<RB, MASK>(acc, tile * KT + (sub - 1) * 32 + 4 * half, N, T, wi, c1, m_run, z_run);
+    // the sub-tile before this one: the last of tile `prev`, or of this tile
+    rowstats_fold<RB, MASK>(acc, (sub == 0 ? prev * KT + KT - 32 : tile * KT + (sub - 1) * 32) + 4 * half, N, T, wi, c1, m_run, z_run);
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) acc[rb] = nxt_acc[rb];
   }
@@ -341,7 +348,7 @@ __device__ __forceinline__ void rowstats_tile(const Piece* __restrict__ cur, Pie
 template <typename TE, int P, int NW, int RB, bool PAD>
 __global__ void __launch_bounds__(NW * 64)
 score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, int64_t ksh,
-                      int64_t kst, int np, int Hk, int M, int m0, int m1, int W, int N, int n_cu, int n_chunks,
+                      int64_t kst, int np, int Hk, int M, int m0, int m1, int W, int N, TileSplit split, bool stream,
                       float c1, float* __restrict__ row_part) {
   constexpr int NT = loader_threads<P, NW>();      // threads that load the K tiles
   constexpr int KS = P / 2, KT = key_tile<P>();
@@ -358,17 +365,18 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) wi[rb] = (row0 + rb * 32 + ln) % W;
   const char* kg = k + (int64_t)g * ksh;
-  const ChunkRange cr = chunk_range<RB>(chunk, g, Hk, n_chunks, (N + KT - 1) / KT, n_cu);
-  const int tile0 = cr.tile0, tile_end = cr.tile_end;
+  const int n_my = split.count(chunk);
+  int ahead = chunk;                            // next tile to load
 
   ASL_LOAD_Q_FRAGS();
   TilePieces<P, NT> tp;
   tp.init(kst, tid, last_piece);
   // prologue: STAGES-1 tiles in flight (after the Q loads, so the in-order wait counts line up)
 #pragma unroll
-  for (int j = 0; j < STAGES - 1; ++j)
-    if (tile0 + j < tile_end)
-      issue_tile_loads<P, NT>(tp, kg, kst, (tile0 + j) * KT, N, last_piece, lds_k + j * TILE_ELEMS, tid);
+  for (int j = 0; j < STAGES - 1; ++j) {
+    if (j < n_my) issue_tile_loads<P, NT>(tp, kg, kst, ahead * KT, N, last_piece, lds_k + j * TILE_ELEMS, tid, stream);
+    ahead += split.step(j);
+  }
 
   ASL_WAIT_Q_FRAGS();
 
@@ -384,23 +392,26 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[rb][r] = -INFINITY;
   int stage = 0;                                  // buffer that holds tile `tile`
-  auto step = [&](int tile, auto mask) {
-    wait_tile<P, NT, STAGES>(min(STAGES - 2, tile_end - 1 - tile));
-    __syncthreads();      // tile `tile` has landed for every wave; the buffer of tile-1 is free again
+  int it = 0, tile = chunk, prev = chunk;
+  auto step = [&](auto mask) {
+    wait_tile<P, NT, STAGES>(min(STAGES - 2, n_my - 1 - it));
+    __syncthreads();      // tile `tile` has landed for every wave; the buffer of the tile before is free again
     const int free_stage = (stage == 0) ? STAGES - 1 : stage - 1;
     rowstats_tile<TE, P, NT, RB, PAD, decltype(mask)::value>(
-        lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS, tile + STAGES - 1 < tile_end, tp, kg, kst,
-        (tile + STAGES - 1) * KT, np, last_piece, tile, N, T, wi, tid, ln, half, qf, c1, acc, m_run, z_run);
+        lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS, it + STAGES - 1 < n_my, stream, tp, kg, kst,
+        ahead * KT, np, last_piece, tile, prev, N, T, wi, tid, ln, half, qf, c1, acc, m_run, z_run);
     stage = (stage + 1 == STAGES) ? 0 : stage + 1;
+    ahead += split.step(it + STAGES - 1);
+    prev = tile;
+    tile += split.step(it);
+    ++it;
   };
-  // tiles of visible keys only, then those that touch the window block or the end (at most
-  // (W + KT - 1) / KT + 1 of a head's last tiles)
-  const int tile_mid = min(max(T / KT, tile0), tile_end);
-  int tile = tile0;
-  for (; tile < tile_mid; ++tile) step(tile, std::false_type());
-  for (; tile < tile_end; ++tile) step(tile, std::true_type());
-  if (tile_end > tile0)                           // the last sub-tile is still to be folded
-    rowstats_fold<RB, true>(acc, tile_end * KT - 32 + 4 * half, N, T, wi, c1, m_run, z_run);
+  // tiles of visible keys only, then those that touch the window block or the end
+  const int plain = T / KT;
+  while (it < n_my && tile < plain) step(std::false_type());
+  while (it < n_my) step(std::true_type());
+  if (n_my > 0)                                   // the last sub-tile is still to be folded
+    rowstats_fold<RB, true>(acc, prev * KT + KT - 32 + 4 * half, N, T, wi, c1, m_run, z_run);
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     // the two lane halves hold disjoint keys of the same query row
@@ -410,7 +421,7 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
     const float z = (half == 0) ? (za + zb) : (zb + za);
     const int qrow = row0 + rb * 32 + ln;
     if (half == 0 && qrow < m1) {
-      float* dst = row_part + ((int64_t)(g * n_chunks + chunk) * M + qrow) * 2;
+      float* dst = row_part + ((int64_t)(g * split.n_chunks + chunk) * M + qrow) * 2;
       dst[0] = m;
       dst[1] = z;
     }
@@ -552,12 +563,12 @@ __device__ __forceinline__ float colsum_subtile(const f32x16 (&acc)[RB], const f
 // KT keys of the tile before and of this one.  ONLY: a workgroup's only tile; nothing is before it.
 template <typename TE, int P, int NT, int RB, bool PAD, bool DENORM, bool ONLY>
 __device__ __forceinline__ void colsum_tile(const Piece* __restrict__ cur, Piece* __restrict__ nxt,
-                                            bool prefetch, const TilePieces<P, NT>& tp, const char* __restrict__ kg, int64_t rsb,
+                                            bool prefetch, bool stream, const TilePieces<P, NT>& tp, const char* __restrict__ kg, int64_t rsb,
                                             int prefetch_key0, int np, int last_piece, int N, int tid, int ln, int half,
                                             const Piece (&qf)[RB][P / 2], const float (&rc)[RB][16], float c1,
                                             f32x16 (&acc)[RB], float* __restrict__ red_prev, float* __restrict__ red_cur) {
   constexpr int KT = key_tile<P>();
-  if (prefetch) issue_tile_loads<P, NT>(tp, kg, rsb, prefetch_key0, N, last_piece, nxt, tid);
+  if (prefetch) issue_tile_loads<P, NT>(tp, kg, rsb, prefetch_key0, N, last_piece, nxt, tid, stream);
 #pragma unroll
   for (int sub = 0; sub < KT / 32; ++sub) {
     f32x16 nxt_acc[RB];
@@ -579,7 +590,7 @@ __device__ __forceinline__ void colsum_tile(const Piece* __restrict__ cur, Piece
 template <typename TE, int P, int NW, int RB, bool PAD, bool DENORM>
 __global__ void __launch_bounds__(NW * 64)
 score_colsum_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, int64_t ksh,
-                    int64_t kst, int np, int Hk, int M, int m0, int m1, int N, int T, int n_cu, float c1,
+                    int64_t kst, int np, int Hk, int M, int m0, int m1, int N, int T, TileSplit split, bool stream, float c1,
                     const float* __restrict__ row_const, float rc_mul, const float* __restrict__ row_part,
                     int n_parts, float* __restrict__ u_group) {
   constexpr int NT = loader_threads<P, NW>();      // threads that load the K tiles
@@ -595,21 +606,21 @@ score_colsum_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, 
   const int row0 = m0 + wave * 32 * RB;         // first query row of this wave
   const int last_piece = PAD ? np - 1 : P - 1;
   const char* kg = k + (int64_t)g * ksh;
-  const ChunkRange cr = chunk_range<RB>(chunk, g, Hk, (int)(gridDim.x / Hk), (T + KT - 1) / KT, n_cu);
-  const int tile0 = cr.tile0, tile_end = cr.tile_end;
 
   ASL_LOAD_Q_FRAGS();
   TilePieces<P, NT> tp;
   tp.init(kst, tid, last_piece);
-  // The chunk is walked from its last tile to its first: pass 1 walked it first to last, so the
-  // tiles read most recently (still in the last-level cache) are the ones this pass reads first.
-  const int n_my = max(tile_end - tile0, 0);
+  // The tiles are taken from the last to the first: pass 1 took them first to last, so those read most
+  // recently (still in the last-level cache) are the ones this pass reads first.
+  const int n_my = split.count(chunk);
+  int ahead = split.tile(chunk, n_my - 1), tile = ahead, prev = ahead, prev2 = ahead;   // next tile to load; this one, the two before
   // prologue: STAGES-1 tiles in flight before the row offsets are worked out, so that their latency
   // hides behind the first tiles' (later loads complete later: the counted waits below stay valid)
 #pragma unroll
-  for (int j = 0; j < STAGES - 1; ++j)
-    if (j < n_my)
-      issue_tile_loads<P, NT>(tp, kg, kst, (tile_end - 1 - j) * KT, N, last_piece, lds_k + j * TILE_ELEMS, tid);
+  for (int j = 0; j < STAGES - 1; ++j) {
+    if (j < n_my) issue_tile_loads<P, NT>(tp, kg, kst, ahead * KT, N, last_piece, lds_k + j * TILE_ELEMS, tid, stream);
+    ahead -= split.step(n_my - 2 - j);
+  }
 
   // Log2-domain softmax offsets of this lane's accumulator rows: from the caller's log-sum-exp
   // (row_const, scaled by rc_mul), or folded here from pass 1's per-chunk partials (row_part).
@@ -667,17 +678,20 @@ score_colsum_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, 
   int stage = 0;                                  // buffer that holds the current tile
   int cur_red = 0, prev_red = 2;                  // red buffers of this tile and of the one before
   auto step = [&](int it, auto only) {
-    const int tile = tile_end - 1 - it;
     wait_tile<P, NT, STAGES>(min(STAGES - 2, n_my - 1 - it));
     __syncthreads();      // the tile has landed; tile it-1's fragment reads and tile it-2's partials are done
-    if (it > 1) reduce_store(3 - cur_red - prev_red, (tile + 2) * KT);
+    if (it > 1) reduce_store(3 - cur_red - prev_red, prev2 * KT);
     const int free_stage = (stage == 0) ? STAGES - 1 : stage - 1;
     colsum_tile<TE, P, NT, RB, PAD, DENORM, decltype(only)::value>(
-        lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS, it + STAGES - 1 < n_my, tp, kg, kst,
-        (tile - (STAGES - 1)) * KT, np, last_piece, N, tid, ln, half, qf, rc, c1, acc, &red[prev_red][wave][0], &red[cur_red][wave][0]);
+        lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS, it + STAGES - 1 < n_my, stream, tp, kg, kst,
+        ahead * KT, np, last_piece, N, tid, ln, half, qf, rc, c1, acc, &red[prev_red][wave][0], &red[cur_red][wave][0]);
     stage = (stage + 1 == STAGES) ? 0 : stage + 1;
     prev_red = cur_red;
     cur_red = (cur_red == 2) ? 0 : cur_red + 1;
+    ahead -= split.step(n_my - 1 - STAGES - it);
+    prev2 = prev;
+    prev = tile;
+    tile -= split.step(n_my - 2 - it);
   };
   // Calls of one tile per workgroup are start-up from end to end; without the turn of the pipeline that has nothing
   // before it they take 7.0 instead of 7.3 us (2 heads, d = 64, 4K, `lse` supplied).  The first of several tiles
@@ -690,8 +704,8 @@ score_colsum_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, 
     const float cs = colsum_subtile<RB, DENORM>(acc, rc, c1);
     if (half == 0) red[prev_red][wave][KT - 32 + ln] = cs;
     __syncthreads();
-    if (n_my > 1) reduce_store(3 - cur_red - prev_red, (tile0 + 1) * KT);
-    reduce_store(prev_red, tile0 * KT);
+    if (n_my > 1) reduce_store(3 - cur_red - prev_red, prev2 * KT);
+    reduce_store(prev_red, prev * KT);
   }
 }
 
@@ -846,6 +860,17 @@ static int score_chunks(int Hk, int n_tiles, int n_cu, int resident, bool fold) 
   return best;
 }
 
+// Whether the keys, so many bytes of them, are loaded with the non-temporal bit, past the last-level cache (256 MB).  Keys that are read
+// once gain from 64 MB on (8B shape, `lse` supplied, layer step, us without and with: 32K 46.0, 42.1; 64K 59.5, 53.4; 128K 87.7, 79.3;
+// 256K 147.6, 127.8).  Read by both passes, smaller ones are there for the second: 16K 45.7, 47.4; 24K 51.4, 51.2; 48K 75.2, 73.0;
+// 96K 114.1, 108.7; 128K 145.7, 137.4; 256K 253.3, 236.1; calls of asl_score_layer alone on a few sets of keys in turn gain
+// less and up to 3 % at 128K are lost.  With two row blocks a wavefront both passes are bound by arithmetic: 28 heads, 256K 186.5, 185.9,
+// asl_score_layer alone 158.4, 163.9.
+template <int RB>
+static bool stream_keys(int64_t bytes, bool both_passes) {
+  return both_passes ? RB == 1 && bytes >= int64_t(96) << 20 : bytes >= int64_t(64) << 20;
+}
+
 // Workgroups of `kernel` that fit on one compute unit at once (registers, LDS, wave slots).
 template <typename K>
 static int resident_per_cu(K kernel, int threads, size_t dynamic_lds = 0) {
@@ -874,11 +899,11 @@ static hipError_t launch_score_mfma(const asl_params& p, const Workspace& ws, co
   }();
   const int n_cu = device_cu_count();
   const int n_chunks = score_chunks<TE, P, NW, RB>(Hk, (N + KT - 1) / KT, n_cu, resident, lse == nullptr);
-  const bool combine = n_chunks > kFoldChunks;
+  const bool combine = n_chunks > kFoldChunks, stream = stream_keys<RB>((int64_t)Hk * N * p.head_dim * (int64_t)sizeof(TE), lse == nullptr);
   if (!lse) {
     for (int m0 = 0; m0 < M; m0 += kRows)
       ASL_LAUNCH(ws.prof, kKernRowstats, st, (score_rowstats_kernel<TE, P, NW, RB, PAD>), dim3(Hk * n_chunks), dim3(NW * 64), 0,
-                 st, q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, p.window, N, n_cu, n_chunks, c1,
+                 st, q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, p.window, N, split_tiles<RB>(Hk, n_chunks, (N + KT - 1) / KT, n_cu), stream, c1,
                  ws.row_part);
     if (lse_out || combine) {
       ASL_LAUNCH(ws.prof, kKernCombine, st, score_combine_kernel, dim3((Hk * M + kCombineRows - 1) / kCombineRows), dim3(256), 0, st,
@@ -892,8 +917,8 @@ static hipError_t launch_score_mfma(const asl_params& p, const Workspace& ws, co
   // its own rows
   for (int m0 = 0; m0 < M; m0 += kRows)
     ASL_LAUNCH(ws.prof, kKernColsum, st, (score_colsum_kernel<TE, P, NW, RB, PAD, DENORM>), dim3(Hk * n_chunks2), dim3(NW * 64), 0, st,
-               q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, N, T, n_cu, c1, lse ? lse : ws.row_const, lse ? kLog2e : 1.0f,
-               lse || combine ? nullptr : ws.row_part, n_chunks, ws.u_group);
+               q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, N, T, split_tiles<RB>(Hk, n_chunks2, n_tiles2, n_cu), stream, c1, lse ? lse : ws.row_const,
+               lse ? kLog2e : 1.0f, lse || combine ? nullptr : ws.row_part, n_chunks, ws.u_group);
   return hipGetLastError();
 }
 

@@ -185,6 +185,16 @@ def test_chunk_counts_of_one_pass(gpu_device, Hq, Hk, d, W, N):
     _close_to_64_bits(P, s, L)
 
 
+# keys of 64 MB and, read by both passes, 96 MB are where the loads change their cache policy: a key or two to either side
+@pytest.mark.parametrize("N,use_lse", [(49151, False), (49154, False), (32767, True), (32770, True)])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
+def test_keys_loaded_past_the_last_level_cache(gpu_device, N, use_lse, dtype, d):
+    L = _small(8, 8, d, N, 16, dtype=dtype, seed=N)
+    lse = orc.row_lse(L.q_obs, L.k, 16) if use_lse else None
+    P, s = _run_score(gpu_device, L, lse=lse)
+    _close_to_64_bits(P, s, L)
+
+
 def test_misaligned_rows_stay_with_the_plain_kernels(gpu_device):
     """fp32 K one element off a 16-byte boundary, and with a token stride of d + 1."""
     import torch
