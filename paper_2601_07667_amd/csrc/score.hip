@@ -288,31 +288,56 @@ static TileSplit split_tiles(int Hk, int n_chunks, int n_tiles, int n_cu) {
 __device__ __forceinline__ float max2(float a, float b) { return __builtin_fmaxf(a, b); }
 
 // Fold the logits of one 32-key sub-tile (keys on the accumulator's register axis; `key_lo` = key of
-// this lane's register 0) into the running (max, sum) of the lane's query row, per row block.
-template <int RB, bool MASK>
+// this lane's register 0) into the running (reference, sum) of the lane's query row, per row block:  sum of the
+// exponentials = z_run * 2^m_run.
+// LAZY: the reference is the largest logit up to some sub-tile, and stays until a sub-tile's sum of 16 is above kRescale: no term
+// is then more than 2^8 times the reference's, which the fp32 sum holds as exactly as the terms below it, and the maximum of the 16 and
+// the rescaling, a fifth of the vector work, are left out (256K, W = 64, pass 1 147.7 -> 138.5 us; 128K 131.7 -> 130.8, 64K 84.2
+// -> 81.1 the layer step).  One branch for all row blocks, behind all of their arithmetic: with one per block half of it stood in
+// a basic block without MFMAs (144.6).  Not for the shapes whose calls are start-up mostly: their one or two sub-tiles take the
+// branch every time (d = 256, 8K, 17.2 -> 17.7).
+constexpr float kRescale = 256.f;
+template <int RB, bool MASK, bool LAZY>
 __device__ __forceinline__ void rowstats_fold(const f32x16 (&acc)[RB], int key_lo, int N, int T,
                                               const int (&wi)[RB], float c1, float (&m_run)[RB], float (&z_run)[RB]) {
+  float x[RB][16], sum[RB];
+  bool far = false;
+  auto raise = [&](int rb) {                              // the reference up to the sub-tile's largest logit, the sum with it
+    float mx = x[rb][0];
+#pragma unroll
+    for (int r = 1; r < 16; r += 2) mx = max2(mx, max2(x[rb][r], x[rb][(r + 1) & 15]));
+    const float m_new = max2(m_run[rb], mx * c1);
+    sum[rb] = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sum[rb] += fast_exp2(fmaf(x[rb][r], c1, -m_new));
+    z_run[rb] *= fast_exp2(m_run[rb] - m_new);
+    m_run[rb] = m_new;
+  };
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
-    float x[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) x[r] = acc[rb][r];
+    for (int r = 0; r < 16; ++r) x[rb][r] = acc[rb][r];
     if (MASK) {
       // visible iff key < N and (key < T or key - T <= wi)  <=>  key < min(N, T + wi + 1)
       const int lim = min(N, T + wi[rb] + 1) - key_lo;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) x[r] = (8 * (r >> 2) + (r & 3) < lim) ? x[r] : -INFINITY;
+      for (int r = 0; r < 16; ++r) x[rb][r] = (8 * (r >> 2) + (r & 3) < lim) ? x[rb][r] : -INFINITY;
     }
-    float mx = x[0];
+    if (LAZY) {
+      sum[rb] = 0.f;
 #pragma unroll
-    for (int r = 1; r < 16; r += 2) mx = max2(mx, max2(x[r], x[(r + 1) & 15]));
-    const float m_new = max2(m_run[rb], mx * c1);
-    float sum = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sum += fast_exp2(fmaf(x[r], c1, -m_new));
-    z_run[rb] = z_run[rb] * fast_exp2(m_run[rb] - m_new) + sum;
-    m_run[rb] = m_new;
+      for (int r = 0; r < 16; ++r) sum[rb] += fast_exp2(fmaf(x[rb][r], c1, -m_run[rb]));
+      far |= sum[rb] > kRescale;
+    } else {
+      raise(rb);
+    }
   }
+  if (LAZY && __builtin_expect(__ballot(far) != 0ull, 0)) {   // uniform; so for the first visible keys, whose m_run is kNegBig
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) raise(rb);
+  }
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) z_run[rb] += sum[rb];
 }
 
 // One tile of pass 1: start the next tile's LDS-direct loads into `nxt`, then work on the tile in
@@ -335,7 +360,7 @@ __device__ __forceinline__ void rowstats_tile(const Piece* __restrict__ cur, Pie
     f32x16 nxt_acc[RB];
     mma_subtile<TE, P, true, RB, PAD>(cur, sub, ln, half, np, qf, nxt_acc);
     // the sub-tile before this one: the last of tile `prev`, or of this tile
-    rowstats_fold<RB, MASK>(acc, (sub == 0 ? prev * KT + KT - 32 : tile * KT + (sub - 1) * 32) + 4 * half, N, T, wi, c1, m_run, z_run);
+    rowstats_fold<RB, MASK, sizeof(TE) == 2 && P <= 16 && !PAD>(acc, (sub == 0 ? prev * KT + KT - 32 : tile * KT + (sub - 1) * 32) + 4 * half, N, T, wi, c1, m_run, z_run);
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) acc[rb] = nxt_acc[rb];
   }
@@ -411,7 +436,7 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
   while (it < n_my && tile < plain) step(std::false_type());
   while (it < n_my) step(std::true_type());
   if (n_my > 0)                                   // the last sub-tile is still to be folded
-    rowstats_fold<RB, true>(acc, prev * KT + KT - 32 + 4 * half, N, T, wi, c1, m_run, z_run);
+    rowstats_fold<RB, true, sizeof(TE) == 2 && P <= 16 && !PAD>(acc, prev * KT + KT - 32 + 4 * half, N, T, wi, c1, m_run, z_run);
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     // the two lane halves hold disjoint keys of the same query row
@@ -443,6 +468,14 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
 // 92.7 us the scoring with the fold in two rounds, 88.8 with that launch; 7 heads on one, W = 64, 200K, 256 chunks: 78.3,
 // 67.6; but 64 chunks, 8B shape: 32K 37.2, 37.9).
 constexpr int kFoldChunks = 64;
+// m + log2(z), z about 1 to 2^30, as if rounded once: the logarithm's own rounding is taken back by one exponential and the sum's
+// is carried along.  An error here is one of all probabilities of a row (128K, offsets around 21: with m + log2f(z) the scores are
+// 2.3 to 2.7e-7 off their values in 64 bits, so 0.9 to 1.6e-7).
+__device__ __forceinline__ float row_offset(float m, float z) {
+  const float l = __builtin_amdgcn_logf(z), s = m + l, b = s - m;
+  const float lost = (m - (s - b)) + (l - b);
+  return s + fmaf(fmaf(z, fast_exp2(-l), -1.0f), kLog2e, lost);
+}
 template <int NR, int kB>
 __device__ __forceinline__ void combine_rows(const float2* const (&p)[NR], int M, int n_chunks, int half,
                                              float (&out)[NR]) {
@@ -480,7 +513,7 @@ __device__ __forceinline__ void combine_rows(const float2* const (&p)[NR], int M
     const float mm = fmaxf(m[q], mo);
     const float za = z[q] * fast_exp2(m[q] - mm), zb2 = zo * fast_exp2(mo - mm);
     const float zs = (half == 0) ? (za + zb2) : (zb2 + za);
-    out[q] = mm + log2f(zs);
+    out[q] = row_offset(mm, zs);
   }
 }
 
@@ -524,7 +557,7 @@ score_combine_kernel(const float* __restrict__ row_part, int Hk, int M, int n_ch
     z = part[0][tid].y;
 #pragma unroll
     for (int w = 1; w < 4; ++w) add(part[w][tid].x, part[w][tid].y, true);
-    const float c = m + log2f(z);
+    const float c = row_offset(m, z);
     if (r < Hk * M) {
       row_const[r] = c;
       if (lse_out != nullptr) lse_out[r] = c * kLn2;

@@ -276,6 +276,24 @@ def test_heavy_tailed_keys(gpu_device):
     _compare(gpu_device, L)
 
 
+# what each sub-tile of 32 keys adds to its logits, times a constant: small steps up and down, one above the bound that makes the
+# reference of the row sums move, one that overflows without it, a first sub-tile far above all others, two waves of them
+@pytest.mark.parametrize("Hq,Hk,d,W,dtype", [(8, 2, 128, 16, "bf16"), (6, 1, 128, 32, "bf16"), (4, 2, 64, 16, "f32"), (4, 2, 256, 8, "bf16")])
+@pytest.mark.parametrize("levels", [(0, 1, 2, 1), (0, 4, 8, 12, 16), (0, 100, 30), (60, 0), (0, 200, 0, 201, 90), (-90, -60, -90)])
+def test_logits_on_several_levels(gpu_device, Hq, Hk, d, W, dtype, levels):
+    """The reference of pass 1's sums of exponentials follows the logits only when they leave it behind.  The logits are up to 200
+    here, where their own rounding to fp32 (and of the product with log2 e) moves a probability by up to 200 * 2^-23 * 2: 5e-5."""
+    L = _small(Hq, Hk, d, 64 * 40 + 7, W, S=1, dtype=dtype, seed=d + len(levels))
+    L.q_obs[:, :, 0] = 1.0
+    for i, lo in enumerate(range(0, L.shape.N, 32)):
+        L.k[:, lo:lo + 32, 0] = levels[i * len(levels) // ((L.shape.N + 31) // 32)] * np.sqrt(d)
+    L.k = synth.round_bf16(L.k) if dtype == "bf16" else L.k.astype(np.float32)
+    P_ref, s_ref = orc.score_layer(L.q_obs, L.k, W, 1)
+    P, s = _run_score(gpu_device, L)
+    np.testing.assert_allclose(P, P_ref, rtol=5e-5, atol=1e-30)
+    np.testing.assert_allclose(s, s_ref, rtol=5e-5, atol=1e-30)
+
+
 def test_config2_full(gpu_device):
     L = synth.config_layer(2)
     P, s = _compare(gpu_device, L)
