@@ -53,6 +53,9 @@ size_t carve(char* base, int32_t max_seq_len, int32_t max_kv_heads, int32_t max_
   w.sel_bound = (uint32_t*)take((size_t)w.sel_rows * 2 * sizeof(uint32_t));
   w.sel_cand = (uint2*)take((size_t)w.sel_rows * sel_tiles * asl::kSelSegment * sizeof(uint2));
   w.sel_seg_count = (uint32_t*)take((size_t)w.sel_rows * sel_tiles * sizeof(uint32_t));
+  w.pick_rows = (int)(rows < (size_t)asl::kPickMaxRows ? rows : (size_t)asl::kPickMaxRows);
+  w.sel_picks = (unsigned long long*)take((size_t)w.pick_rows * (N < (size_t)asl::kPickWords ? N : (size_t)asl::kPickWords) * sizeof(unsigned long long));
+  w.pick_tag = (uint32_t*)take(sizeof(uint32_t));
   w.var_table = (unsigned long long*)take((size_t)asl::kVarMaxBlocks * 4 * sizeof(unsigned long long));
   w.var_epoch = (unsigned long long*)take(sizeof(unsigned long long));
   w.fault = (uint32_t*)take(sizeof(uint32_t));
@@ -296,7 +299,7 @@ static asl_status check_score_operands(asl_ctx* ctx, const asl_params* p, const 
 // score rows) is ordered behind the side-stream work a deferred asl_layer_step left behind.
 static asl_status score_layer_impl(asl_ctx* ctx, const asl_params* p, const void* q_obs, const void* k,
                                    const float* lse, float* p_head, float* s_all, void* stream, bool wait_side,
-                                   bool want_sample) {
+                                   bool want_sample, bool want_tag) {
   asl_status st = check_params(ctx, p);
   if (st != ASL_OK) return st;
   if (!q_obs || !k || !p_head || !s_all) return fail(ctx, ASL_EINVAL, "null tensor pointer");
@@ -314,14 +317,14 @@ static asl_status score_layer_impl(asl_ctx* ctx, const asl_params* p, const void
   }
   const int T = p->seq_len - p->window;
   e = asl::launch_pool(ctx->ws.prof, ctx->ws.u_group, p->n_kv_heads, T, p->pool_kernel, p_head, s_all,
-                       want_sample ? ctx->ws.sel_sample : nullptr, hs);
+                       want_sample ? ctx->ws.sel_sample : nullptr, want_tag ? ctx->ws.pick_tag : nullptr, hs);
   if (e != hipSuccess) return hip_fail(ctx, e, "pool launch");
   return ASL_OK;
 }
 
 asl_status asl_score_layer(asl_ctx* ctx, const asl_params* p, const void* q_obs, const void* k,
                            const float* lse, float* p_head, float* s_all, void* stream) {
-  return score_layer_impl(ctx, p, q_obs, k, lse, p_head, s_all, stream, false, false);
+  return score_layer_impl(ctx, p, q_obs, k, lse, p_head, s_all, stream, false, false, false);
 }
 
 asl_status asl_window_lse(asl_ctx* ctx, const asl_params* p, const void* q_obs, const void* k,
@@ -347,7 +350,7 @@ asl_status asl_pool(asl_ctx* ctx, const float* u, int32_t rows, int32_t T, int32
   if (S > kMaxPoolKernel) return fail(ctx, ASL_EUNSUPPORTED, "pool kernel S > %d not supported", kMaxPoolKernel);
   DeviceGuard guard(ctx->device);
   if (guard.err != hipSuccess) return hip_fail(ctx, guard.err, "set device");
-  hipError_t e = asl::launch_pool(ctx->ws.prof, u, rows, T, S, p_out, s_out, nullptr, static_cast<hipStream_t>(stream));
+  hipError_t e = asl::launch_pool(ctx->ws.prof, u, rows, T, S, p_out, s_out, nullptr, nullptr, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(ctx, e, "pool launch");
   return ASL_OK;
 }
@@ -415,12 +418,10 @@ asl_status asl_rank_stat(asl_ctx* ctx, const asl_params* p, const float* s_all, 
   st = check_rank_size(ctx, T);
   if (st != ASL_OK) return st;
   int32_t* row = rank_ring + (int64_t)(layer_idx % l_obs) * T;
-  hipError_t e = asl::launch_rank(ctx->ws, s_all, T, row, hs);
-  if (e != hipSuccess) return hip_fail(ctx, e, "rank launch");
-  e = (layer_idx < l_min)
-          ? asl::launch_stat_skip(ctx->ws.prof, out, state, layer_idx, l_obs, 1, hs)
-          : asl::launch_rankvar(ctx->ws, rank_ring, l_obs, T, layer_idx, k, tau, 1, state, out, hs);
-  if (e != hipSuccess) return hip_fail(ctx, e, "rankvar launch");
+  asl::RankvarArgs ra = asl::rankvar_args(ctx->ws, rank_ring, l_obs, T, layer_idx, k, tau, 1, state, out);
+  ra.skip = layer_idx < l_min ? 1 : 0;
+  hipError_t e = asl::launch_rank_stat(ctx->ws, s_all, row, ra, hs);
+  if (e != hipSuccess) return hip_fail(ctx, e, "rank and statistic launch");
   return ASL_OK;
 }
 
@@ -580,7 +581,7 @@ asl_status asl_layer_step(asl_ctx* ctx, const asl_params* p, const void* q_obs, 
   // when the shared launches of the tail will follow, the pooling kernel leaves the top-k's sample behind
   const bool fused = !(p->flags & ASL_FLAG_DEFER_JOIN) && asl::tail_takes(ctx->ws, Hk + 1, T);
   const bool want_sample = fused && T > asl::kShortT;   // short rows need no bound
-  st = score_layer_impl(ctx, p, q_obs, k, lse, p_head, s_all, stream, true, want_sample);
+  st = score_layer_impl(ctx, p, q_obs, k, lse, p_head, s_all, stream, true, want_sample, fused && !want_sample);
   if (st != ASL_OK) return st;
   if (fused) {
     // one stream: its launches carry the stages of the ranking and the statistic beside those of the top-k and the compaction

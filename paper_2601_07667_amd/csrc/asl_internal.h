@@ -74,6 +74,9 @@ struct Workspace {
   uint2* sel_cand;         // [sel_rows][n_tiles][kSelSegment] (key, token) of the keys that passed the bound, in token order
   uint32_t* sel_seg_count; // [sel_rows][n_tiles] entries used in each segment
   int sel_rows;            // rows the candidate buffers hold at once
+  unsigned long long* sel_picks;    // [pick_rows][up to kPickWords] (tag, token): what a launch selects and compacts (short contexts)
+  uint32_t* pick_tag;      // [1] counted up by the pooling kernel in front of such a launch
+  int pick_rows;
   // rank variance
   unsigned long long* var_table;    // [kVarMaxBlocks][4] tagged per-workgroup partial sums
   unsigned long long* var_epoch;    // [1]
@@ -87,6 +90,8 @@ constexpr int kRankMaxT = kRankMaxTiles * 8192;   // longest vector one ranking 
 constexpr int kMaxChunks = 256;        // key chunks per KV head in scoring pass 1
 constexpr int kVarMaxBlocks = 256;     // workgroups of the rank-variance kernel
 constexpr int kSelMaxRowTiles = 1024;  // tiles per row the candidate path handles
+constexpr int kPickMaxRows = 64;       // KV heads that a launch selects for and compacts ...
+constexpr int kPickWords = 4096;       // ... and tokens of each
 constexpr int kSelMaxRowsAtOnce = 256; // rows per round of select launches (bounds the candidate buffers)
 
 // ---- counts handed between workgroups of one launch -------------------------------------------
@@ -223,10 +228,13 @@ __device__ __forceinline__ bool flag_poll_batch(const unsigned long long* col, i
 hipError_t launch_score(const asl_params& p, const Workspace& ws, const void* q_obs, const void* k,
                         const float* lse, float* lse_out, hipStream_t st);
 // sample (optional): [rows + 1][kSelMaxSample], receives the top-k's strided sample of the pooled
-// rows and, as the last row, of their sum.
+// rows and, as the last row, of their sum.  tag (optional): a word that is counted up by one.
 hipError_t launch_pool(Prof* prof, const float* u, int rows, int T, int S, float* p_out, float* s_out,
-                       uint32_t* sample, hipStream_t st);
+                       uint32_t* sample, uint32_t* tag, hipStream_t st);
 hipError_t launch_rank(const Workspace& ws, const float* s, int T, int32_t* rank_out, hipStream_t st);
+struct RankvarArgs;
+// The ranking of s into the ring row of stat.layer_idx and the statistic (stat.skip: the note that there is none).
+hipError_t launch_rank_stat(const Workspace& ws, const float* s, int32_t* rank_row, const RankvarArgs& stat, hipStream_t st);
 // push != 0: first account for this layer's freshly written ring row in the state (a layer index
 // that does not follow state->last_layer restarts the ring)
 hipError_t launch_rankvar(const Workspace& ws, const int32_t* ring, int l_obs, int T, int layer_idx,
@@ -258,8 +266,7 @@ struct GatherArgs {
 hipError_t launch_gather(Prof* prof, const GatherArgs& args, int Hk, int n_layers, hipStream_t st);
 bool gather_prepare(GatherArgs& a);   // sets cpr_shift; returns whether cpr is a power of two
 // Ranking of the last of `rows` score rows + top-k of all rows + optional statistic and KV
-// compaction in three launches (two for short contexts) on one stream (tail.hip); *taken = false when the sizes do not fit and nothing was launched.
-struct RankvarArgs;
+// compaction in three launches (one or two for short contexts) on one stream (tail.hip); *taken = false when the sizes do not fit and nothing was launched.
 hipError_t launch_tail(const Workspace& ws, const float* scores, int rows, int T, int k, int W, int32_t* rank_row,
                        int32_t* idx_out, const GatherArgs* gather, int Hk, bool have_sample, int S,
                        const RankvarArgs& stat, hipStream_t st, bool* taken);

@@ -17,9 +17,10 @@ constexpr int kPoolRows = 8;       // rows staged together
 template <int S_CT>
 __global__ void __launch_bounds__(kPoolBlock)
 pool_kernel(const float* __restrict__ u, int rows, int T, int S_any, float* __restrict__ p_out,
-            float* __restrict__ s_out, uint32_t* __restrict__ sample, int n_sample, int sample_stride) {
+            float* __restrict__ s_out, uint32_t* __restrict__ sample, int n_sample, int sample_stride, uint32_t* __restrict__ tag) {
   __shared__ float tile[kPoolRows][kPoolBlock + 2 * kPoolMaxHalf];
   const int S = S_CT > 0 ? S_CT : S_any;
+  if (tag != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *tag += 1u;
   const int h = S / 2;
   const int base = blockIdx.x * kPoolBlock;
   const int t = base + threadIdx.x;
@@ -84,14 +85,14 @@ pool_kernel(const float* __restrict__ u, int rows, int T, int S_any, float* __re
 }
 
 hipError_t launch_pool(Prof* prof, const float* u, int rows, int T, int S, float* p_out, float* s_out,
-                       uint32_t* sample, hipStream_t st) {
+                       uint32_t* sample, uint32_t* tag, hipStream_t st) {
   const dim3 grid((T + kPoolBlock - 1) / kPoolBlock), block(kPoolBlock);
   if (S == 7)                                          // the paper's pooling window (App. C.2)
     ASL_LAUNCH(prof, kKernPool, st, pool_kernel<7>, grid, block, 0, st, u, rows, T, S, p_out, s_out, sample,
-               sel_sample_size(T), sel_sample_stride(T));
+               sel_sample_size(T), sel_sample_stride(T), tag);
   else
     ASL_LAUNCH(prof, kKernPool, st, pool_kernel<0>, grid, block, 0, st, u, rows, T, S, p_out, s_out, sample,
-               sel_sample_size(T), sel_sample_stride(T));
+               sel_sample_size(T), sel_sample_stride(T), tag);
   return hipGetLastError();
 }
 

@@ -15,7 +15,7 @@
 #include <cstdio>
 #include <mutex>
 
-#include "rank_body.h"
+#include "rank_stat_body.h"
 
 namespace asl {
 
@@ -40,7 +40,13 @@ __global__ void __launch_bounds__(kSortThreads, 8) rank_bucket_kernel(RankArgs a
 // dynamic LDS: sizeof(ShortRankShared)
 __global__ void __launch_bounds__(kSortThreads) rank_short_kernel(const float* __restrict__ s, int T, int32_t* __restrict__ rank_out) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_dyn[];
-  rank_short_body(*reinterpret_cast<ShortRankShared*>(lds_dyn), s, T, rank_out, (int)blockIdx.x);
+  rank_short_body(*reinterpret_cast<ShortRankShared*>(lds_dyn), s, T, PutRank{rank_out}, (int)blockIdx.x);
+}
+
+// dynamic LDS: sizeof(RankStatShared)
+__global__ void __launch_bounds__(kSortThreads) rank_stat_short_kernel(const float* __restrict__ s, int32_t* __restrict__ rank_row, RankvarArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_dyn[];
+  rank_stat_short_body(*reinterpret_cast<RankStatShared*>(lds_dyn), s, rank_row, a, (int)blockIdx.x, (int)gridDim.x);
 }
 
 RankArgs rank_plan(int T) {
@@ -81,12 +87,31 @@ RankArgs rank_args(const Workspace& ws, const float* s, int T, const uint32_t* s
 // of it collects them.
 constexpr int64_t kSampleDirect = 64 * 4096;
 
-hipError_t launch_rank(const Workspace& ws, const float* s, int T, int32_t* rank_out, hipStream_t st) {
-  // The workgroups of the one launch read all scores while others already write ranks; the partition reads them in its first launch
-  // and writes ranks in its last, so it takes the calls that rank a vector in place.
+// Whether a ranking is one launch.  Its workgroups read all scores while others already write ranks; the partition reads them in its
+// first launch and writes ranks in its last, so it takes the calls that rank a vector in place.
+static bool one_launch(const float* s, int T, const int32_t* rank_out) {
   const uintptr_t s0 = reinterpret_cast<uintptr_t>(s), r0 = reinterpret_cast<uintptr_t>(rank_out), bytes = (uintptr_t)T * 4;
   const bool in_place = s0 < r0 + bytes && r0 < s0 + bytes;
-  if (T <= kShortT && !in_place) {
+  return T <= kShortT && !in_place;
+}
+
+hipError_t launch_rank_stat(const Workspace& ws, const float* s, int32_t* rank_row, const RankvarArgs& stat, hipStream_t st) {
+  if (one_launch(s, stat.T, rank_row)) {
+    static OncePerDevice once;
+    const hipError_t attr = allow_lds(once, reinterpret_cast<const void*>(rank_stat_short_kernel), sizeof(RankStatShared));
+    if (attr != hipSuccess) return attr;
+    ASL_LAUNCH(ws.prof, kKernSortScatter, st, rank_stat_short_kernel, dim3(short_rank_blocks(stat.T)), dim3(kSortThreads),
+               sizeof(RankStatShared), st, s, rank_row, stat);
+    return hipGetLastError();
+  }
+  const hipError_t e = launch_rank(ws, s, stat.T, rank_row, st);
+  if (e != hipSuccess) return e;
+  if (stat.skip != 0) return launch_stat_skip(ws.prof, stat.out, stat.state, stat.layer_idx, stat.l_obs, stat.push, st);
+  return launch_rankvar(ws, stat.ring, stat.l_obs, stat.T, stat.layer_idx, stat.k, stat.tau, stat.push, stat.state, stat.out, st);
+}
+
+hipError_t launch_rank(const Workspace& ws, const float* s, int T, int32_t* rank_out, hipStream_t st) {
+  if (one_launch(s, T, rank_out)) {
     static OncePerDevice once;
     const hipError_t attr = allow_lds(once, reinterpret_cast<const void*>(rank_short_kernel), sizeof(ShortRankShared));
     if (attr != hipSuccess) return attr;

@@ -110,6 +110,29 @@ constexpr int kCountT = 8192;
 constexpr int kShortPlaces = 2 * kCountTokens;
 constexpr int kShortPer = kShortT / kSortThreads;
 static_assert(kShortT % kSortThreads == 0 && kCountTokens == 32, "the keys of a workgroup's tokens are one group of 32");
+// Where a short vector's ranks go: put(token, rank).
+struct PutRank {
+  int32_t* out;
+  __device__ __forceinline__ void operator()(uint32_t t, uint32_t rank) const { out[t] = (int32_t)rank; }
+};
+// ... and are kept for the statistic: a workgroup ranks tokens from `first` on by counting, or the tokens of places from `first`
+// on by bins, each once.
+constexpr int kShortKept = kShortPlaces + (int)kBinMax;
+struct KeptRanks {
+  uint32_t tok[kShortKept], rank[kShortKept];           // tok ~0: none
+};
+struct PutAndKeepRank {
+  int32_t* out;
+  KeptRanks* kept;
+  uint32_t first;
+  bool by_token;
+  __device__ __forceinline__ void operator()(uint32_t t, uint32_t rank) const {
+    out[t] = (int32_t)rank;
+    const uint32_t i = min((by_token ? t : rank) - first, (uint32_t)kShortKept - 1u);   // smaller by itself
+    kept->tok[i] = t;
+    kept->rank[i] = rank;
+  }
+};
 struct ShortRankShared {
   uint32_t keys[kShortT];                               // by counting, and where long bins are cut
   union {
@@ -127,7 +150,8 @@ inline int short_rank_blocks(int T) { return T <= kCountT ? (T + kCountTokens - 
 
 // Ranks of tokens 32 group .. 32 group + 31 by counting.  keys: all T of them; up to the next multiple of 32 the largest
 // key, which precedes nothing.
-__device__ __forceinline__ void count_ranks(const uint32_t* keys, int T, int group, int32_t* __restrict__ rank_out) {
+template <typename Put>
+__device__ __forceinline__ void count_ranks(const uint32_t* keys, int T, int group, const Put& put) {
   const int tid = threadIdx.x, lane = tid & 31, n_groups = (T + 31) / 32;
   const int i0 = group * kCountTokens, i = i0 + (tid >> 5);
   const uint32_t ki = keys[i];                          // i < kShortT
@@ -142,7 +166,7 @@ __device__ __forceinline__ void count_ranks(const uint32_t* keys, int T, int gro
   }
 #pragma unroll
   for (int d = 16; d > 0; d >>= 1) before += (uint32_t)__shfl_xor((int)before, d);
-  if (lane == 0 && i < T) rank_out[i] = (int32_t)before;
+  if (lane == 0 && i < T) put((uint32_t)i, before);
 }
 
 // The rest of a way by bins, once the keys in [lo, hi] are counted: the bins' first places (`begin`: that of lo's) to sh.bin, and
@@ -171,8 +195,9 @@ __device__ __forceinline__ void short_bins(ShortRankShared& sh, uint32_t lo, uin
   __syncthreads();
 }
 // Ranks of the keys grouped in sh.key / sh.tok from place p0 - kBinMax on, of those with a place in [from, to).
+template <typename Put>
 __device__ __forceinline__ void short_places(const ShortRankShared& sh, uint32_t lo, int shift, uint32_t p0, uint32_t from, uint32_t to,
-                                             int32_t* __restrict__ rank_out) {
+                                             const Put& put) {
   // four threads per place: few keys are this workgroup's, and a wavefront that went through its own again would run the
   // comparison once for each (12000 tokens: 28 us the ranking and its statistic, so 18)
   const int tid = threadIdx.x, i = tid >> 2, part = tid & 3;
@@ -195,7 +220,7 @@ __device__ __forceinline__ void short_places(const ShortRankShared& sh, uint32_t
   before += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)before, 0xb1, 0xf, 0xf, false);   // quad_perm [1, 0, 3, 2]
   before += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)before, 0x4e, 0xf, 0xf, false);   // quad_perm [2, 3, 0, 1]
   const uint32_t place = p0 + i0 + before - kBinMax;
-  if (part == 0 && t != 0xffffffffu && place >= from && place < to) rank_out[t] = (int32_t)place;
+  if (part == 0 && t != 0xffffffffu && place >= from && place < to) put(t, place);
 }
 
 // f(key, token, valid) for the thread's keys in sh.keys, read four at a time.
@@ -221,8 +246,9 @@ __device__ __forceinline__ Stretch short_stretch(int T) {
 }
 // Ranks of the tokens with this key, which has the places from `first` on, that belong to places [p0, p1); n: those in the
 // wavefront's stretch.  The one or two wavefronts whose stretches hold such places go through theirs.
+template <typename Put>
 __device__ __forceinline__ void rank_equal(ShortRankShared& sh, int T, uint32_t value, uint32_t n, uint32_t first, uint32_t p0, uint32_t p1,
-                                           int32_t* __restrict__ rank_out) {
+                                           const Put& put) {
   const int wave = uniform_wave(), lane = threadIdx.x & 63;
   const Stretch s = short_stretch(T);
   __syncthreads();                                      // red may still be in use
@@ -236,13 +262,13 @@ __device__ __forceinline__ void rank_equal(ShortRankShared& sh, int T, uint32_t 
     const bool in = t < T && sh.keys[min(t, T - 1)] == value;
     const uint64_t m = __ballot(in);
     const uint32_t at = place + lanes_below(m);
-    if (in && at >= p0 && at < p1) rank_out[t] = (int32_t)at;
+    if (in && at >= p0 && at < p1) put((uint32_t)t, at);
     place += (uint32_t)__popcll(m);
   }
 }
 
-__device__ __forceinline__ void rank_short_body(ShortRankShared& sh, const float* __restrict__ s, int T, int32_t* __restrict__ rank_out,
-                                                int b) {
+template <typename Put>
+__device__ __forceinline__ void rank_short_body(ShortRankShared& sh, const float* __restrict__ s, int T, const Put& put, int b) {
   const int tid = threadIdx.x;
   uint32_t key[kShortPer];
   {
@@ -260,7 +286,7 @@ __device__ __forceinline__ void rank_short_body(ShortRankShared& sh, const float
   };
   if (T <= kCountT) {                                   // uniform
     all_keys();
-    count_ranks(sh.keys, T, b, rank_out);
+    count_ranks(sh.keys, T, b, put);
     return;
   }
   const uint32_t p0 = (uint32_t)(b * kShortPlaces), p1 = min(p0 + (uint32_t)kShortPlaces, (uint32_t)T);
@@ -276,7 +302,7 @@ __device__ __forceinline__ void rank_short_body(ShortRankShared& sh, const float
     }
   block_min_max(sh.red, lo, hi);
   if (lo == hi) {                                       // uniform: all scores are equal
-    if (tid < kShortPlaces && p0 + tid < p1) rank_out[p0 + tid] = (int32_t)(p0 + tid);
+    if (tid < kShortPlaces && p0 + tid < p1) put(p0 + (uint32_t)tid, p0 + (uint32_t)tid);
     return;
   }
   int shift = bin_shift(lo, hi, kSampleBinBits);
@@ -310,7 +336,7 @@ __device__ __forceinline__ void rank_short_body(ShortRankShared& sh, const float
     }
   }
   __syncthreads();
-  short_places(sh, lo, shift, p0, p0, 0xffffffffu, rank_out);
+  short_places(sh, lo, shift, p0, p0, 0xffffffffu, put);
   if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)sh.n_todo) == 0, 1)) return;           // uniform
   all_keys();
   const Stretch s_t = short_stretch(T);
@@ -345,8 +371,8 @@ __device__ __forceinline__ void rank_short_body(ShortRankShared& sh, const float
     block_min_max(sh.red, lo2[0], hi2[0]);              // its barriers: everybody has read the list, the bins and the places
     if (two) block_min_max(sh.red, lo2[1], hi2[1]);     // uniform
     const bool one0 = lo2[0] == hi2[0], one1 = !two || lo2[1] == hi2[1];       // of a single key, or not there
-    if (one0) rank_equal(sh, T, lo2[0], held[0], at[0], p0, p1, rank_out);
-    if (two && one1) rank_equal(sh, T, lo2[1], held[1], at[1], p0, p1, rank_out);
+    if (one0) rank_equal(sh, T, lo2[0], held[0], at[0], p0, p1, put);
+    if (two && one1) rank_equal(sh, T, lo2[1], held[1], at[1], p0, p1, put);
     // both at once if at most 16 bins apart
     const bool both = !one0 && !one1 && max(to[0], to[1]) - min(from[0], from[1]) <= 16u * (to[0] - from[0]);
     if (tid == 0) sh.n_todo = n - (two && (both || one0 || one1) ? 2u : 1u);
@@ -385,7 +411,7 @@ __device__ __forceinline__ void rank_short_body(ShortRankShared& sh, const float
         }
       });
       __syncthreads();
-      short_places(sh, lo, shift, p0, p0, p1, rank_out);
+      short_places(sh, lo, shift, p0, p0, p1, put);
     }
     __syncthreads();
   }

@@ -17,7 +17,7 @@ __global__ void stat_skip_kernel(asl_stat* out, asl_state* state, int layer_idx,
 }
 
 __global__ void __launch_bounds__(kVarThreads) rankvar_kernel(RankvarArgs a) {
-  __shared__ RankvarShared sh;
+  __shared__ RankvarShared<> sh;
   rankvar_body(sh, a, (int)blockIdx.x, (int)gridDim.x);
 }
 

@@ -28,9 +28,10 @@ __device__ __forceinline__ int rows_in_use(const asl_state* state, int layer_idx
   return n;
 }
 
+template <int NT = kVarThreads>
 struct RankvarShared {
-  unsigned long long red_num[kVarThreads / 64];
-  uint32_t red_cnt[kVarThreads / 64];
+  unsigned long long red_num[NT / 64];
+  uint32_t red_cnt[NT / 64];
   int gave_up;
 };
 
@@ -71,7 +72,19 @@ __device__ __forceinline__ void stat_skip_body(asl_stat* out, asl_state* state, 
 // with tau and the state update; the other workgroups wait for nobody, so the launch needs no
 // particular residency.  Every workgroup reads the old state before it publishes, and workgroup 0
 // writes the state only after it has seen every publication.
-__device__ __forceinline__ void rankvar_body(RankvarShared& sh, const RankvarArgs& a, int block, int n_blocks) {
+// A workgroup's sums to its words of the table (one thread).
+__device__ __forceinline__ void rankvar_publish(const RankvarArgs& a, int block, unsigned long long tag, unsigned long long bn, uint32_t bc) {
+  unsigned long long* mine = a.table + (int64_t)block * 4;
+  const uint32_t m14 = (1u << kFlagCountBits) - 1u;
+  flag_publish(mine + 0, tag, (uint32_t)bn & m14, (uint32_t)(bn >> 14) & m14);
+  flag_publish(mine + 1, tag, (uint32_t)(bn >> 28) & m14, (uint32_t)(bn >> 42) & m14);
+  flag_publish(mine + 2, tag, (uint32_t)(bn >> 56) & m14, 0u);
+  flag_publish(mine + 3, tag, bc & m14, (bc >> 14) & m14);
+}
+template <int NT>
+__device__ __forceinline__ void rankvar_collect(RankvarShared<NT>& sh, const RankvarArgs& a, int n_blocks, unsigned long long tag, int n);
+
+__device__ __forceinline__ void rankvar_body(RankvarShared<>& sh, const RankvarArgs& a, int block, int n_blocks) {
   const int tid = threadIdx.x;
   const unsigned long long tag = *a.epoch + 1ull;
   const int n = rows_in_use(a.state, a.layer_idx, a.l_obs, a.push);
@@ -142,20 +155,21 @@ __device__ __forceinline__ void rankvar_body(RankvarShared& sh, const RankvarArg
       bn += sh.red_num[w];
       bc += sh.red_cnt[w];
     }
-    unsigned long long* mine = a.table + (int64_t)block * 4;
-    const uint32_t m14 = (1u << kFlagCountBits) - 1u;
-    flag_publish(mine + 0, tag, (uint32_t)bn & m14, (uint32_t)(bn >> 14) & m14);
-    flag_publish(mine + 1, tag, (uint32_t)(bn >> 28) & m14, (uint32_t)(bn >> 42) & m14);
-    flag_publish(mine + 2, tag, (uint32_t)(bn >> 56) & m14, 0u);
-    flag_publish(mine + 3, tag, bc & m14, (bc >> 14) & m14);
+    rankvar_publish(a, block, tag, bn, bc);
   }
   if (block != 0) return;
+  __syncthreads();                                   // red_* are reused
+  rankvar_collect<kVarThreads>(sh, a, n_blocks, tag, n);
+}
 
-  // workgroup 0: gather every workgroup's partials (thread b takes workgroups b, b + 256, ...)
-  __syncthreads();                                   // red_* are reused below
+// The one workgroup that waits, all NT threads of it: every workgroup's partials (thread b takes workgroups b, b + NT, ...), the
+// result, the state.  n: rows in use; sh.gave_up is 0 and seen by all.
+template <int NT>
+__device__ __forceinline__ void rankvar_collect(RankvarShared<NT>& sh, const RankvarArgs& a, int n_blocks, unsigned long long tag, int n) {
+  const int tid = threadIdx.x;
   unsigned long long total = 0;
   uint32_t m = 0;
-  for (int b = tid; b < n_blocks; b += kVarThreads) {
+  for (int b = tid; b < n_blocks; b += NT) {
     unsigned long long v[4];
     if (!flag_poll_batch<1, 4>(a.table + (int64_t)b * 4, 1, 0, 4, tag, v)) sh.gave_up = 1;
     const unsigned long long piece0 = (unsigned long long)flag_count0(v[0]) | ((unsigned long long)flag_count1(v[0]) << 14);
@@ -185,7 +199,7 @@ __device__ __forceinline__ void rankvar_body(RankvarShared& sh, const RankvarArg
   *a.epoch = tag;
   total = 0;
   m = 0;
-  for (int w = 0; w < kVarThreads / 64; ++w) {
+  for (int w = 0; w < NT / 64; ++w) {
     total += sh.red_num[w];
     m += sh.red_cnt[w];
   }

@@ -111,6 +111,11 @@ struct SelectArgs {
   uint2* cand;                   // [rows][n_tiles][kSelSegment] (key, token)
   uint32_t* seg_count;           // [rows][n_tiles]
   int32_t* idx_out;              // [rows][k + W]
+  // where a launch compacts the rows' keys and values too (gather_picked_body): the first pick_rows rows' tokens for its
+  // other workgroups, each in a word with the launch's tag
+  unsigned long long* picks;     // [pick_rows][k]
+  const uint32_t* pick_tag;
+  int pick_rows;                 // 0: none
 };
 
 struct GuessShared {
@@ -283,10 +288,10 @@ __device__ __forceinline__ void select_filter_body(FilterShared<INSIDE>& sh, con
 // Ordered write of the kept elements of a sequence of n (key, token) pairs given in token order:
 // kept = key < thr, or key == thr and fewer than k_rem equal keys precede it.
 // PER consecutive elements per thread and round.
-// load(i0, key): the keys of elements i0 .. i0 + PER - 1; those from n on may be anything.
-template <int PER, typename Load, typename TokAt>
+// load(i0, key): the keys of elements i0 .. i0 + PER - 1; those from n on may be anything.  put(pos, token).
+template <int PER, typename Load, typename TokAt, typename Put>
 __device__ __forceinline__ void ordered_write(int n, uint32_t thr, uint32_t k_rem, int k, Load load, TokAt tok_at,
-                                              uint32_t* red, int32_t* __restrict__ out) {
+                                              uint32_t* red, Put put) {
   const int tid = threadIdx.x;
   static_assert(kFinThreads * PER < 65536, "a round's two counts share a word");
   uint32_t lt_base = 0, eq_base = 0;
@@ -309,7 +314,7 @@ __device__ __forceinline__ void ordered_write(int n, uint32_t thr, uint32_t k_re
         const bool is_lt = key[j] < thr, is_eq = key[j] == thr;
         if (is_lt || (is_eq && eq_run < k_rem)) {
           const uint32_t pos = lt_run + (eq_run < k_rem ? eq_run : k_rem);
-          if (pos < (uint32_t)k) out[pos] = (int32_t)tok_at(i0 + j);      // always true for consistent counts
+          if (pos < (uint32_t)k) put(pos, (uint32_t)tok_at(i0 + j));      // always true for consistent counts
         }
         lt_run += is_lt ? 1u : 0u;
         eq_run += is_eq ? 1u : 0u;
@@ -567,12 +572,13 @@ __device__ __forceinline__ void finish_write(FinishShared& sh, const uint32_t* l
                                              int n, uint32_t thr, uint32_t k_rem) {
   const int tid = threadIdx.x, T = a.T, k = a.k, W = a.W;
   int32_t* out = a.idx_out + (int64_t)row * (k + W);
+  auto put = [&](uint32_t pos, uint32_t tok) { out[pos] = (int32_t)tok; };
   const uint32_t* li = lds_cand + a.cand_cap;
   if (sh.whole_row) {                                  // uniform
     const float* sr = a.scores + (int64_t)row * T;
     ordered_write<8>(T, thr, k_rem, k, [&](int i0, uint32_t* key) {
       for (int j = 0; j < 8; ++j) key[j] = order_key(sr[min(i0 + j, T - 1)]);
-    }, [&](int i) { return (uint32_t)i; }, sh.sm, out);
+    }, [&](int i) { return (uint32_t)i; }, sh.sm, put);
   } else {
     // four keys per LDS read: cand_cap is a multiple of eight
     const uint4* lk = reinterpret_cast<const uint4*>(lds_cand);
@@ -585,12 +591,12 @@ __device__ __forceinline__ void finish_write(FinishShared& sh, const uint32_t* l
     };
     auto tok = [&](int i) { return li[i]; };
     if (n <= 4 * kFinThreads)
-      ordered_write<4>(n, thr, k_rem, k, four, tok, sh.sm, out);
+      ordered_write<4>(n, thr, k_rem, k, four, tok, sh.sm, put);
     else
       ordered_write<8>(n, thr, k_rem, k, [&](int i0, uint32_t* key) {
         four(i0, key);
         four(i0 + 4, key + 4);
-      }, tok, sh.sm, out);
+      }, tok, sh.sm, put);
   }
   // window tokens T .. T+W-1 (Alg. 1 step 10: Concat with I_w)
   for (int i = tid; i < W; i += kFinThreads) out[k + i] = T + i;
@@ -612,6 +618,8 @@ __device__ __forceinline__ void select_finish_body(void* lds, const SelectArgs& 
 // the radix select and so: 2000 scores 7.4, 5.7; 8000 10.4, 7.1; 12000 12.9, 7.9; 12000
 // of a few values 15.0, 11.2; within 2 % beside outliers 15.5, 12.2; 16000 so (then in three launches) 21.5, 16.9.
 // PER keys a thread.
+constexpr int kPickMost = kPickWords;                   // most tokens of a row that go to SelectArgs.picks
+static_assert(kPickMost == 4 * kFinThreads, "they are staged in the bins");
 template <int PER>
 struct ShortSelectShared {
   uint4 keys[PER * kFinThreads / 4];
@@ -619,7 +627,8 @@ struct ShortSelectShared {
   uint32_t sm[2 * kFinWaves + 2];
   BinPick bins;
 };
-template <int PER>
+// PICKS: the launch has a place for the tokens (SelectArgs).
+template <int PER, bool PICKS = false>
 __device__ __forceinline__ void select_short_body(ShortSelectShared<PER>& sh, const SelectArgs& a, int row) {
   const int tid = threadIdx.x, T = a.T;
   constexpr int kPer = PER, kMost = PER * kFinThreads, kWrite = PER <= 16 ? PER : 16;      // keys a thread writes together
@@ -687,13 +696,26 @@ __device__ __forceinline__ void select_short_body(ShortSelectShared<PER>& sh, co
     x[3] = v.w;
   };
   auto tok = [&](int i) { return (uint32_t)i; };
+  const bool picks = PICKS && row < a.pick_rows;
+  uint32_t* staged = &sh.bin[0].x;                      // kPickMost words
+  auto put = [&](uint32_t pos, uint32_t token) {
+    out[pos] = (int32_t)token;
+    if (picks) staged[pos] = token;                     // pos < k <= kPickMost
+  };
+  if (picks) __syncthreads();                           // the bins are done with
   if (T <= 4 * kFinThreads)
-    ordered_write<4>(T, thr, k_rem, a.k, four, tok, sh.sm, out);
+    ordered_write<4>(T, thr, k_rem, a.k, four, tok, sh.sm, put);
   else
     ordered_write<kWrite>(T, thr, k_rem, a.k, [&](int i0, uint32_t* x) {
 #pragma unroll
       for (int j = 0; j < kWrite; j += 4) four(min(i0 + j, kMost - 4), x + j);
-    }, tok, sh.sm, out);
+    }, tok, sh.sm, put);
+  if (picks) {                                          // 64 words a store: written where they are found, a few at a time, 6 us more
+    const unsigned long long tag = (unsigned long long)*a.pick_tag << 32;
+    unsigned long long* pick = a.picks + (int64_t)row * a.k;
+    __syncthreads();
+    for (int i = tid; i < a.k; i += kFinThreads) __hip_atomic_store(pick + i, tag | staged[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   for (int i = tid; i < a.W; i += kFinThreads) out[a.k + i] = T + i;   // window tokens (Alg. 1 step 10)
 }
 

@@ -1,4 +1,4 @@
-// The part of a layer step that follows the scoring, in three launches on one stream (two for short contexts).
+// The part of a layer step that follows the scoring, in three launches on one stream (one for short contexts).
 //
 // After the scores are pooled two independent chains remain: the ranking (partition, buckets: Alg. 1 step 11) with the
 // statistic (Alg. 2 steps 4-10), and the top-k + KV compaction (bound, filter, finish, gather: Alg. 1
@@ -9,8 +9,7 @@
 #include <type_traits>
 
 #include "gather_body.h"
-#include "rank_body.h"
-#include "rankvar_body.h"
+#include "rank_stat_body.h"
 #include "select_body.h"
 
 namespace asl {
@@ -24,16 +23,36 @@ union PartFilterShared {
   FilterShared<true> filter;
 };
 
-// Short contexts (T <= kShortT): the ranking and the top-k of every row in one launch instead of the two below.  The
-// selecting workgroups, the longer ones, come first.  Dynamic LDS: kTailShortLds.
-constexpr size_t kTailShortLds = sizeof(ShortSelectShared<kShortPer>) > sizeof(ShortRankShared) ? sizeof(ShortSelectShared<kShortPer>) : sizeof(ShortRankShared);
-__global__ void __launch_bounds__(kTailThreads) tail_short_kernel(const float* s_all, int32_t* rank_row, SelectArgs se, int rows) {
+// Short contexts (T <= kShortT) take one launch for all of it: the top-k of every row, the ranking with the statistic, and the compaction
+// (up to kPickMost tokens of kPickMaxRows heads; else that follows in a launch of its own).  The selecting workgroups, the longer
+// ones, come first; workgroup r < Hk leaves row r's tokens in words that carry the launch's tag, and the compacting
+// workgroups of head r wait for theirs.  Those come last, 8 * i + x for heads r with r % 8 == x: on the die of the workgroup they
+// wait for, behind it in the order in which a die starts them, so that waiting workgroups cannot keep the waited-for ones from
+// starting, whatever else runs on the device.  gx: blocks per (head, tensor) slab, 0 for no compaction here.  A layer step, us, with
+// statistic and compaction in a launch of their own and so: 8 KV heads 1K 23.5, 21.1; 8K 37.4, 34.3; 12K 35.4, 33.9; two heads of
+// d = 64, 4K 23.5, 21.1; 10K 26.2, 24.9; 10K below L_min 24.8, 24.9.  WAVES: wavefronts of a SIMD that the scalar registers
+// allow: 8 for two workgroups a unit where ranking and top-k have more than one for each (8K 37.3, 34.4); else 4, whose code is 0.6
+// to 1 us faster.  Dynamic LDS: kTailShortLds.
+constexpr size_t kTailShortLds = sizeof(ShortSelectShared<kShortPer>) > sizeof(RankStatShared) ? sizeof(ShortSelectShared<kShortPer>) : sizeof(RankStatShared);
+constexpr int kDies = 8;
+__host__ __device__ constexpr int short_gather_from(int rows, int n_rank) { return (rows + n_rank + kDies - 1) / kDies * kDies; }
+template <bool POW2, int WAVES>
+__global__ void __launch_bounds__(kTailThreads, WAVES) tail_whole_kernel(const float* s_all, int32_t* rank_row, SelectArgs se, int rows, int n_rank,
+                                                                     RankvarArgs ra, GatherArgs ga, int gx, int Hk) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_dyn[];
   const int b = (int)blockIdx.x;
-  if (b < rows)
-    select_short_body<kShortPer>(*reinterpret_cast<ShortSelectShared<kShortPer>*>(lds_dyn), se, b);
-  else
-    rank_short_body(*reinterpret_cast<ShortRankShared*>(lds_dyn), s_all, se.T, rank_row, b - rows);
+  if (b < rows) {
+    select_short_body<kShortPer, true>(*reinterpret_cast<ShortSelectShared<kShortPer>*>(lds_dyn), se, b);
+  } else if (b < rows + n_rank) {
+    rank_stat_short_body(*reinterpret_cast<RankStatShared*>(lds_dyn), s_all, rank_row, ra, b - rows, n_rank);
+  } else {
+    const int j = b - short_gather_from(rows, n_rank);
+    if (j < 0) return;
+    const int i = j / kDies, slabs = gx * ga.n_tensors, h = j % kDies + kDies * (i / slabs), slab = i % slabs;
+    if (h >= Hk) return;
+    if (!gather_picked_body<POW2, kTailThreads>(ga, slab % gx, h, slab / gx, se.T, se.k, se.picks + (int64_t)h * se.k, *se.pick_tag))
+      *ra.fault = 1u;
+  }
 }
 
 // launch 0: the ranking's partition | top-k bound and filter (TILES tiles of a score row per workgroup; VEC: 16-byte
@@ -67,7 +86,7 @@ __global__ void __launch_bounds__(kTailThreads, 8) tail1_kernel(RankArgs ra, Sel
 // launch 1 (gx blocks per (head, tensor) slab)
 template <bool POW2>
 __global__ void __launch_bounds__(kVarThreads) tail2_kernel(RankvarArgs ra, int n_stat, GatherArgs ga, int gx, int Hk) {
-  __shared__ RankvarShared sh;
+  __shared__ RankvarShared<> sh;
   const int b = (int)blockIdx.x;
   if (b < n_stat) {
     if (ra.skip != 0) {
@@ -156,12 +175,29 @@ hipError_t launch_tail(const Workspace& ws, const float* scores, int rows, int T
   const SelectArgs se = select_args(ws, scores, T, k, W, idx_out, have_sample, S);
   hipError_t e;
   if (T <= kShortT) {
-    static OncePerDevice once;
-    const hipError_t attr = allow_lds(once, reinterpret_cast<const void*>(tail_short_kernel), kTailShortLds);
+    const int n_rank = short_rank_blocks(T);
+    GatherArgs ga = {};
+    SelectArgs sp = se;
+    int gx = 0, grid = rows + n_rank;
+    bool pow2 = true;
+    if (gather != nullptr && Hk <= ws.pick_rows && k <= kPickMost) {
+      ga = *gather;
+      pow2 = gather_prepare(ga);
+      gx = (int)(((int64_t)ga.n_idx * ga.cpr + kTailThreads * kGatherUnroll - 1) / (kTailThreads * kGatherUnroll));
+      grid = short_gather_from(rows, n_rank) + kDies * ((Hk + kDies - 1) / kDies) * gx * ga.n_tensors;
+      sp.picks = ws.sel_picks;
+      sp.pick_tag = ws.pick_tag;
+      sp.pick_rows = Hk;
+    }
+    const bool two = rows + n_rank > kTailUnits;        // two workgroups a unit
+    auto* const kernel = two ? (pow2 ? tail_whole_kernel<true, 8> : tail_whole_kernel<false, 8>)
+                             : (pow2 ? tail_whole_kernel<true, 4> : tail_whole_kernel<false, 4>);
+    static OncePerDevice once[4];
+    const hipError_t attr = allow_lds(once[2 * two + pow2], reinterpret_cast<const void*>(kernel), kTailShortLds);
     if (attr != hipSuccess) return attr;
-    ASL_LAUNCH(ws.prof, kKernTail, st, tail_short_kernel, dim3(rows + short_rank_blocks(T)), dim3(kTailThreads), kTailShortLds, st,
-               s_all, rank_row, se, rows);
+    ASL_LAUNCH(ws.prof, kKernTail, st, kernel, dim3(grid), dim3(kTailThreads), kTailShortLds, st, s_all, rank_row, sp, rows, n_rank, stat, ga, gx, Hk);
     e = hipGetLastError();
+    return e != hipSuccess || gather == nullptr || gx != 0 ? e : launch_gather(ws.prof, *gather, Hk, 1, st);
   } else {
     const uint32_t* sample = have_sample ? ws.sel_sample + (int64_t)(rows - 1) * kSelMaxSample : nullptr;
     const RankArgs ra = rank_args(ws, s_all, T, sample, rank_row);

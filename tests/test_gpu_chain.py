@@ -419,6 +419,74 @@ def test_layer_step_evaluates_around_the_short_limit(gpu_device, N):
     np.testing.assert_array_equal(got["I_all"][:sh.k], np.nonzero(got["rank"] < sh.k)[0])
 
 
+def _exact_statistic(held, rank, k):
+    rows = np.concatenate([held, rank[None]]).astype(object)                       # exact integers
+    n, kept = len(rows), rows[:, (rows < k).any(axis=0)]
+    return n, kept.shape[1], int((n * (kept * kept).sum(axis=0) - kept.sum(axis=0) ** 2).sum())
+
+
+# ranked by counting and by bins, one and two workgroups a compute unit; heads beyond the eight dies and beyond 64, rows that are no
+# power of two of pieces, as many tokens as one launch hands on and one more (then compacted by a launch of its own)
+@pytest.mark.parametrize("Hq,Hk,d,dtype,N,W,budget,n_held", [
+    (9, 9, 64, "bf16", 8192 + 16, 16, 300, 3), (2, 1, 128, "bf16", 8193 + 16, 16, 2048, 10), (70, 70, 64, "bf16", 600, 8, 64, 1),
+    (2, 2, 96, "f32", 3000, 8, 700, 7), (4, 2, 64, "bf16", 12000, 16, 4112, 2), (4, 2, 64, "bf16", 12000, 16, 4113, 2),
+    (1, 1, 64, "bf16", 2, 1, 2, 1)])
+def test_short_layer_step_in_one_launch(gpu_device, Hq, Hk, d, dtype, N, W, budget, n_held):
+    sh = synth.Shape(Hq=Hq, Hk=Hk, d=d, N=N, W=W, S=7, budget=budget, L_min=0, L_obs=n_held + 1, dtype=dtype)
+    L = synth.iid_layer(sh, 2200 + N + budget, name=f"one-launch-{N}-{Hk}")
+    rng = np.random.default_rng(N)
+    held = np.stack([rng.permutation(sh.T) for _ in range(n_held)])
+    got = _layer_step_case(gpu_device, L, layer_idx=2 * n_held + 1, held=held)
+    np.testing.assert_array_equal(got["rank"], orc.rank_desc(got["s"].astype(np.float64)))
+    st = got["stat"]
+    n, union, numerator = _exact_statistic(held, got["rank"], sh.k)
+    assert (st.evaluated, st.n_rows, st.union_size, st.numerator) == (1, n, union, numerator)
+    for g in range(Hk):
+        np.testing.assert_array_equal(got["Kc"][g], L.k[g][got["I_head"][g]])
+        np.testing.assert_array_equal(got["Vc"][g], L.v[g][got["I_head"][g]])
+
+
+def test_short_layer_steps_on_two_streams(gpu_device):
+    """Steps of two contexts on two streams at once, more workgroups than the device holds, some of which wait for others of
+    their launch: the results are those of the same steps one after the other."""
+    import torch
+    dev, reps = gpu_device, 40
+    sh = synth.Shape(Hq=16, Hk=8, d=128, N=8000, W=16, S=7, budget=2048, L_min=0, L_obs=4)
+    layers = [synth.iid_layer(sh, 2300 + j) for j in range(2)]
+    p, T, n_idx = gu.params_of(sh), sh.T, sh.k + sh.W
+    ops = [[gu.to_dev(x, "bf16", dev) for x in (L.q_obs, L.k, L.v)] for L in layers]
+
+    def buffers():
+        return dict(ctx=asl.Asl(sh.N, sh.Hk + 1, sh.Hq * sh.W), scores=torch.zeros((sh.Hk + 1, T), device=dev),
+                    ring=torch.zeros((sh.L_obs, T), dtype=torch.int32, device=dev), state=asl.new_state(dev), stat=asl.new_stat(dev),
+                    I=torch.zeros((sh.Hk + 1, n_idx), dtype=torch.int32, device=dev),
+                    K=torch.zeros((sh.Hk, n_idx, sh.d), dtype=torch.bfloat16, device=dev),
+                    V=torch.zeros((sh.Hk, n_idx, sh.d), dtype=torch.bfloat16, device=dev))
+
+    def step(b, i, j, compact=True):
+        q, k, v = ops[(i + j) % 2]
+        b["ctx"].asl_layer_step(p, q, k, v, j, 0, sh.L_obs, 0.0, b["scores"], b["ring"], b["state"], b["stat"], b["I"],
+                                b["K"] if compact else None, b["V"] if compact else None)
+
+    ref, got = [buffers() for _ in range(2)], [buffers() for _ in range(2)]
+    for i in range(2):
+        for j in range(reps):
+            step(ref[i], i, j)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    for j in range(reps):
+        for i in range(2):
+            with torch.cuda.stream(streams[i]):
+                step(got[i], i, j, compact=j % 5 != 3)
+    torch.cuda.synchronize()
+    for i in range(2):
+        assert got[i]["ctx"].asl_device_fault() == 0
+        for name in ("scores", "ring", "state", "stat", "I", "K", "V"):
+            assert torch.equal(got[i][name], ref[i][name]), f"stream {i}: {name}"
+        ref[i]["ctx"].close()
+        got[i]["ctx"].close()
+
+
 def test_layer_step_at_bench_size_and_beyond(gpu_device):
     """asl_layer_step at the size the benchmark times (C3: 64 ranking tiles beside the top-k stages) and at
     2^20 tokens (256 tiles of 4096): bit-identical to the single calls, and both match the oracle."""
