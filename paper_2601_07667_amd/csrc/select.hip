@@ -34,10 +34,10 @@ __global__ void __launch_bounds__(kFinThreads) select_guess_kernel(SelectArgs a)
 // grid: x = tile, y = row.  Small workgroups when there are enough tiles to fill the device several
 // times over (a workgroup lives ~5 us whatever its size: more of them in flight stream faster), large
 // ones for a few rows (one round of workgroups: the shorter each one's share, the sooner it ends).
-template <int NT, bool VEC>
+template <int NT>
 __global__ void __launch_bounds__(NT) select_filter_kernel(SelectArgs a) {
   __shared__ FilterShared<false> sh;
-  select_filter_body<NT, VEC, false>(sh, a, (int)blockIdx.y, (int)blockIdx.x);
+  select_filter_body<NT, false>(sh, a, (int)blockIdx.y, (int)blockIdx.x);
 }
 
 // dynamic LDS: finish_lds_bytes(a.cand_cap)
@@ -102,18 +102,11 @@ hipError_t launch_select(const Workspace& ws, const float* scores, int rows, int
       continue;
     }
     ASL_LAUNCH(ws.prof, kKernSelHist, st, select_guess_kernel, dim3(nr), dim3(kFinThreads), 0, st, a);
-    // rows that start on 16-byte boundaries are read four scores at a time
-    const bool vec = (T % 4 == 0) && (reinterpret_cast<uintptr_t>(a.scores) % 16 == 0);
-    const bool small = (long)a.n_tiles * nr >= kFilterSmallFrom;
     const dim3 fgrid(a.n_tiles, nr);
-    if (small && vec)
-      ASL_LAUNCH(ws.prof, kKernSelHist, st, (select_filter_kernel<kFilterThreads, true>), fgrid, dim3(kFilterThreads), 0, st, a);
-    else if (small)
-      ASL_LAUNCH(ws.prof, kKernSelHist, st, (select_filter_kernel<kFilterThreads, false>), fgrid, dim3(kFilterThreads), 0, st, a);
-    else if (vec)
-      ASL_LAUNCH(ws.prof, kKernSelHist, st, (select_filter_kernel<kFinThreads, true>), fgrid, dim3(kFinThreads), 0, st, a);
+    if ((long)a.n_tiles * nr >= kFilterSmallFrom)
+      ASL_LAUNCH(ws.prof, kKernSelHist, st, select_filter_kernel<kFilterThreads>, fgrid, dim3(kFilterThreads), 0, st, a);
     else
-      ASL_LAUNCH(ws.prof, kKernSelHist, st, (select_filter_kernel<kFinThreads, false>), fgrid, dim3(kFinThreads), 0, st, a);
+      ASL_LAUNCH(ws.prof, kKernSelHist, st, select_filter_kernel<kFinThreads>, fgrid, dim3(kFinThreads), 0, st, a);
     ASL_LAUNCH(ws.prof, kKernSelWrite, st, select_finish_kernel, dim3(nr), dim3(kFinThreads), finish_lds_bytes(a.cand_cap), st, a);
   }
   return hipGetLastError();

@@ -179,15 +179,19 @@ template <> struct FilterShared<true> {
 
 // Step 2: the tile's keys <= bound, in token order, to the tile's segment of the candidate buffer.
 // NT threads per workgroup: each wavefront takes kSelTile / (NT / 64) consecutive tokens.
-// VEC: a lane reads four neighbouring scores with one 16-byte load (the row must start on a 16-byte
-// boundary: T % 4 == 0 and an aligned base); otherwise one score per load.
+// On its own a lane reads one score per load: what a ballot says of 64 neighbours is their order, and a kept token is what its
+// lane holds.  Four at a time took a loop over each lane's kept ones, as often as the busiest lane has any, with a choice among four
+// registers in it: 256 rows of 131040 scores 49.9 us, so 44.4; 64 rows 25.2, 21.8; 256 of 40000 29.6, 26.3 (counts of four
+// rounds packed into two prefix sums, the kept scores read again: 53.9).  Inside a layer step, one round a tile, four with one 16-byte load, on
+// whatever 4-byte boundary the row starts (8 heads, 32K 59.9, one per load 60.3).
 // INSIDE (NT = kFinThreads): the sample is there in compact form and the workgroup takes the bound from it
 // (step 1) beside its own loads; the row's first one stores it for step 3.  TILES: consecutive tiles of a workgroup,
 // from `tile` on: a bound costs as much as two of them.
-template <int NT, bool VEC, bool INSIDE, int TILES = 1>
+template <int NT, bool INSIDE, int TILES = 1>
 __device__ __forceinline__ void select_filter_body(FilterShared<INSIDE>& sh, const SelectArgs& a, int row, int tile) {
   constexpr int kWaves = NT / 64, kSelPerWave = kSelTile / kWaves;
-  constexpr int kPer = VEC ? 4 : 1;                     // neighbouring tokens per lane and round
+  constexpr int kPer = INSIDE ? 4 : 1;                  // neighbouring tokens per lane and round
+  typedef float Four __attribute__((ext_vector_type(4), aligned(4)));
   constexpr int kSelRounds = kSelPerWave / (64 * kPer);
   static_assert(kSelRounds >= 1 && (TILES == 1 || INSIDE) && TILES <= kFilterMostTiles, "filter tile geometry");
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, T = a.T;
@@ -199,19 +203,17 @@ __device__ __forceinline__ void select_filter_body(FilterShared<INSIDE>& sh, con
 #pragma unroll
     for (int r = 0; r < kSelRounds; ++r) {             // all loads in flight before the first use
       const int e = base + i * kSelTile + (r * 64 + lane) * kPer;
-      if (VEC) {
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      if constexpr (kPer == 4) {
+        Four v = {0.f, 0.f, 0.f, 0.f};
         if (e + 3 < T) {
-          v = *reinterpret_cast<const float4*>(sr + e);
+          v = *reinterpret_cast<const Four*>(sr + e);
         } else {                                        // the row's last, partial piece
           if (e < T) v.x = sr[e];
           if (e + 1 < T) v.y = sr[e + 1];
           if (e + 2 < T) v.z = sr[e + 2];
         }
-        sc[i][r][0] = v.x;
-        sc[i][r][1 % kPer] = v.y;
-        sc[i][r][2 % kPer] = v.z;
-        sc[i][r][3 % kPer] = v.w;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sc[i][r][j] = v[j];
       } else {
         sc[i][r][0] = (e < T) ? sr[e] : 0.f;
       }

@@ -55,10 +55,9 @@ __global__ void __launch_bounds__(kTailThreads, WAVES) tail_whole_kernel(const f
   }
 }
 
-// launch 0: the ranking's partition | top-k bound and filter (TILES tiles of a score row per workgroup; VEC: 16-byte
-// loads, for rows that start on 16-byte boundaries).  64 registers, for two workgroups a unit where the grid has more than one for
-// each: rows off 16 bytes in four tiles a workgroup spill 9 of them (36 bytes of scratch).
-template <int R, bool VEC, int TILES>
+// launch 0: the ranking's partition | top-k bound and filter (TILES tiles of a score row per workgroup).  64 registers, for two
+// workgroups a unit where the grid has more than one for each.
+template <int R, int TILES>
 __global__ void __launch_bounds__(kTailThreads, 8) tail0_kernel(RankArgs ra, SelectArgs se) {
   __shared__ PartFilterShared sh;
   const int b = (int)blockIdx.x;
@@ -66,7 +65,7 @@ __global__ void __launch_bounds__(kTailThreads, 8) tail0_kernel(RankArgs ra, Sel
     partition_body<R>(sh.part, ra, b);
   } else {
     const int j = b - ra.n_tiles, per_row = (se.n_tiles + TILES - 1) / TILES;
-    select_filter_body<kTailThreads, VEC, true, TILES>(sh.filter, se, j / per_row, (j % per_row) * TILES);
+    select_filter_body<kTailThreads, true, TILES>(sh.filter, se, j / per_row, (j % per_row) * TILES);
   }
 }
 
@@ -102,7 +101,6 @@ __global__ void __launch_bounds__(kVarThreads) tail2_kernel(RankvarArgs ra, int 
 }
 
 // Launches 0 and 1.
-template <bool VEC>
 static hipError_t launch_rank_select(const Workspace& ws, const SelectArgs& se, const RankArgs& ra, int rows, hipStream_t st) {
   constexpr size_t kMost = finish_lds_bytes(kSelCandCap) > sizeof(BucketShared) ? finish_lds_bytes(kSelCandCap) : sizeof(BucketShared);
   static OncePerDevice once;
@@ -118,15 +116,15 @@ static hipError_t launch_rank_select(const Workspace& ws, const SelectArgs& se, 
     constexpr int R = decltype(r)::value;
     if constexpr (R < 8) {                              // the 8192-token tiles come with more than a unit's share of the filter's
       if (tiles == 1) {
-        ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<R, VEC, 1>), dim3(grid0(1)), block, 0, st, ra, se);
+        ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<R, 1>), dim3(grid0(1)), block, 0, st, ra, se);
         return;
       }
       if (tiles == 2) {
-        ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<R, VEC, 2>), dim3(grid0(2)), block, 0, st, ra, se);
+        ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<R, 2>), dim3(grid0(2)), block, 0, st, ra, se);
         return;
       }
     }
-    ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<R, VEC, 4>), dim3(grid0(4)), block, 0, st, ra, se);
+    ASL_LAUNCH(ws.prof, kKernTail, st, (tail0_kernel<R, 4>), dim3(grid0(4)), block, 0, st, ra, se);
   };
   if (ra.tile_log == 11)
     launch0(std::integral_constant<int, 2>());
@@ -201,8 +199,7 @@ hipError_t launch_tail(const Workspace& ws, const float* scores, int rows, int T
   } else {
     const uint32_t* sample = have_sample ? ws.sel_sample + (int64_t)(rows - 1) * kSelMaxSample : nullptr;
     const RankArgs ra = rank_args(ws, s_all, T, sample, rank_row);
-    e = T % 4 == 0 && reinterpret_cast<uintptr_t>(scores) % 16 == 0 ? launch_rank_select<true>(ws, se, ra, rows, st)
-                                                                    : launch_rank_select<false>(ws, se, ra, rows, st);
+    e = launch_rank_select(ws, se, ra, rows, st);
   }
   return e != hipSuccess ? e : launch_stat_gather(ws, gather, Hk, stat, st);
 }
