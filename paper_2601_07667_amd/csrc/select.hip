@@ -17,9 +17,9 @@
 // (With four radix passes for the bound and for the threshold instead of one histogram each, 256 rows of 131040 scores
 // took 57.2 us, now 48.7; a layer step's tail with the bound in a launch of its own and the finish in another 37 us,
 // now 26.)
-// The bound is only a guess: if fewer than k keys passed it, or a tile's or the row's candidates
-// do not fit their buffers, step 3 runs the same selection over the whole row straight from the
-// scores instead (slower, same result).  The result therefore never depends on the sample.
+// The bound is only a guess: if more candidates passed it than step 3 has room for, it tightens the bound by a histogram of them; if
+// fewer than k keys passed it, or a tile's candidates do not fit their segment, it runs the same selection over the whole row
+// straight from the scores instead (slower, same result).  The result therefore never depends on the sample.
 // Rows of at most kSelMidT scores (many rows: kSelShortT; in a layer step: kShortT) need no bound: one launch, one workgroup per row, all tokens in LDS.
 // Integer work throughout: nothing depends on scheduling.
 #include "select_body.h"

@@ -343,8 +343,9 @@ struct FinishShared {
   uint32_t sm[2 * kFinWaves + 2];
   BinPick bins;
   uint32_t seg_off[kSelMaxRowTiles + 1];
-  int whole_row;
+  int whole_row;                                       // 1: select from the scores; kTooMany: the candidates do not fit
 };
+constexpr int kTooMany = 2;
 constexpr size_t finish_lds_bytes(int cand_cap) { return (sizeof(FinishShared) + 15) / 16 * 16 + 2 * (size_t)cand_cap * sizeof(uint32_t); }
 __device__ __forceinline__ uint32_t* finish_cand(void* lds) {
   return reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(lds) + (sizeof(FinishShared) + 15) / 16 * 16);
@@ -368,7 +369,7 @@ __device__ __forceinline__ int finish_load(FinishShared& sh, uint32_t* lds_cand,
     if (tid < n_tiles && n_tiles <= kSelMaxRowTiles) sh.seg_off[tid] = c_excl;
     if (tid == 0) {
       if (n_tiles <= kSelMaxRowTiles) sh.seg_off[n_tiles] = c_tot;
-      sh.whole_row = (n_tiles > kSelMaxRowTiles || any_over != 0 || c_tot < (uint32_t)k || c_tot > (uint32_t)a.cand_cap) ? 1 : 0;
+      sh.whole_row = (n_tiles > kSelMaxRowTiles || any_over != 0 || c_tot < (uint32_t)k) ? 1 : c_tot > (uint32_t)a.cand_cap ? kTooMany : 0;
     }
   }
   __syncthreads();
@@ -447,6 +448,104 @@ __device__ __forceinline__ void pick_bin(BinPick& sh, const uint32_t (&c)[PER], 
     excl += c[q];
   }
   __syncthreads();
+}
+
+// More candidates than fit: they are counted in the bins between `below` and the bound, where they lie, and those up to the end of the
+// bin that holds the k-th, which is the bound from here on, are collected.  Returns how many; sh.whole_row 1 where that does not help.
+// (By the radix select over all scores such a row took 220 us; k = 8160, where the bound has to be wide, 9 rows of 200001 243.5 us,
+// so 32.3; 32 of 262080 320, 39; 256 of 131040, a few of which have too many, 167, 64.)
+__device__ __forceinline__ int finish_tighten(FinishShared& sh, uint32_t* lds_cand, const SelectArgs& a, int row, uint32_t& bound, uint32_t below) {
+  const int tid = threadIdx.x, n_tiles = a.n_tiles, wave = uniform_wave(), lane = tid & 63;
+  const uint32_t kk = (uint32_t)a.k;
+  const uint2* row_cand = a.cand + (int64_t)row * n_tiles * kSelSegment;
+  const uint32_t* counts = a.seg_count + (int64_t)row * n_tiles;
+  const int shift = bin_shift(below, bound, kFinBinBits);
+  uint32_t lower = 0;
+  for (int t = wave; t < n_tiles; t += kFinWaves) {
+    const uint32_t n = counts[t];
+    const uint2* seg = row_cand + (int64_t)t * kSelSegment;
+    for (uint32_t j0 = 0; j0 < n; j0 += 256) {
+      uint32_t key[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) key[u] = seg[min(j0 + 64 * u + lane, n - 1)].x;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (j0 + 64 * u + lane < n) {
+          if (key[u] < below)
+            ++lower;
+          else
+            atomicAdd(&sh.h[clamped_bin(key[u], below, bound, shift)], 1u);
+        }
+    }
+  }
+  __syncthreads();
+  const uint32_t c[2] = {sh.h[2 * tid], sh.h[2 * tid + 1]};
+  uint32_t excl, total;
+  block_scan<false>(sh.sm, c[0] + c[1], lower, excl, total, lower);
+  if (tid == 0) sh.bins.pick[2] = 0;
+  __syncthreads();
+  pick_bin<2>(sh.bins, c, lower + excl, kk);
+  const uint32_t d = sh.bins.pick[0], n_new = kk - sh.bins.pick[1] + sh.bins.pick[2];
+  const bool fits = lower < kk && sh.bins.pick[2] != 0 && n_new <= (uint32_t)a.cand_cap;
+  if (!fits) {                                          // uniform
+    __syncthreads();
+    if (tid == 0) sh.whole_row = 1;
+    __syncthreads();
+    return 0;
+  }
+  const uint32_t from = below + (d << shift), width = (1u << shift) - 1u;
+  bound = bound - from < width ? bound : from + width;
+  // the tiles' candidates up to the new bound: how many, then where
+  for (int t = wave; t < n_tiles; t += kFinWaves) {
+    const uint32_t n = counts[t];
+    const uint2* seg = row_cand + (int64_t)t * kSelSegment;
+    uint32_t held = 0;
+    for (uint32_t j0 = 0; j0 < n; j0 += 256) {
+      uint32_t key[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) key[u] = seg[min(j0 + 64 * u + lane, n - 1)].x;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) held += (uint32_t)__popcll(__ballot(j0 + 64 * u + lane < n && key[u] <= bound));
+    }
+    if (lane == 0) sh.seg_off[t] = held;
+  }
+  __syncthreads();
+  uint32_t c_excl, c_tot, none;
+  block_scan<false>(sh.sm, tid < n_tiles ? sh.seg_off[tid] : 0u, 0u, c_excl, c_tot, none);
+  if (tid < n_tiles) sh.seg_off[tid] = c_excl;
+  if (tid == 0) {
+    sh.seg_off[n_tiles] = c_tot;
+    sh.whole_row = 0;
+    sh.bins.pick[3] = 0;
+  }
+  sh.h[2 * tid] = 0;                                    // the bins again
+  sh.h[2 * tid + 1] = 0;
+  __syncthreads();
+  uint32_t* lk = lds_cand;
+  uint32_t* li = lds_cand + a.cand_cap;
+  for (int t = wave; t < n_tiles; t += kFinWaves) {
+    const uint32_t n = counts[t];
+    const uint2* seg = row_cand + (int64_t)t * kSelSegment;
+    uint32_t at = sh.seg_off[t];
+    for (uint32_t j0 = 0; j0 < n; j0 += 256) {
+      uint2 x[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) x[u] = seg[min(j0 + 64 * u + lane, n - 1)];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const bool keep = j0 + 64 * u + lane < n && x[u].x <= bound;
+        const uint64_t bal = __ballot(keep);
+        const uint32_t i = min(at + lanes_below(bal), (uint32_t)a.cand_cap - 1u);   // smaller by itself
+        if (keep) {
+          lk[i] = x[u].x;
+          li[i] = x[u].y;
+        }
+        at += (uint32_t)__popcll(bal);
+      }
+    }
+  }
+  __syncthreads();
+  return (int)min(sh.seg_off[n_tiles], (uint32_t)a.cand_cap);
 }
 
 // f(key, valid) for the thread's of n keys in LDS, four reads at a time, as often for every thread of a wavefront.
@@ -608,8 +707,10 @@ __device__ __forceinline__ void finish_write(FinishShared& sh, const uint32_t* l
 __device__ __forceinline__ void select_finish_body(void* lds, const SelectArgs& a, int row) {
   FinishShared& sh = *static_cast<FinishShared*>(lds);
   uint32_t* lds_cand = finish_cand(lds);
-  const uint32_t bound = a.bound[2 * row], below = a.bound[2 * row + 1];
-  const int n = finish_load(sh, lds_cand, a, row);
+  const uint32_t below = a.bound[2 * row + 1];
+  uint32_t bound = a.bound[2 * row];
+  int n = finish_load(sh, lds_cand, a, row);
+  if (__builtin_expect(sh.whole_row == kTooMany, 0)) n = finish_tighten(sh, lds_cand, a, row, bound, below);   // uniform
   uint32_t thr, k_rem;
   finish_threshold(sh, lds_cand, a, row, n, bound, below, thr, k_rem);
   finish_write(sh, lds_cand, a, row, n, thr, k_rem);

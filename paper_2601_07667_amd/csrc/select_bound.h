@@ -66,9 +66,9 @@ inline int sel_sample_rank_low(int T, int k, int n_s, int run) {
 // hold.  The m-th sample key admits m T / n_s tokens with standard deviation T / n_s sqrt(c m), c as above; a row's
 // buffer must keep 3 of those free.  A tile's segment holds kSelTile / n_s keys per sample key, with the bound's
 // deviation and that of the tile itself (kSelTile / 4 tokens in independent groups of 8, wider than pooling
-// couples them); it must keep 4 free, since any of a row's tiles may overflow.  A row whose buffers overflow is
-// selected from global memory (128K, one layer step: 190 us at k = 11 800 so, 235 with m / 8 throughout); where the
-// m-th key alone overflows them by a deviation, nothing is left to lose.
+// couples them); it must keep 4 free, since any of a row's tiles may overflow.  A row with more than its buffer
+// holds costs ~10 us, one with a full tile is selected from global memory (~200 us); where the m-th key alone overflows them by
+// a deviation, nothing is left to lose.
 inline int sel_bound_slack(int T, int m, int n_s, int run) {
   const float per_key = (float)T / (float)n_s, per_key_tile = (float)kSelTile / (float)n_s, var = (float)run * (float)m;
   const float row_room = (float)kSelCandCap - (float)m * per_key, row_dev = per_key * sqrtf(var);
@@ -80,8 +80,7 @@ inline int sel_bound_slack(int T, int m, int n_s, int run) {
   return cap <= 0.f ? 0 : ((float)s < cap ? s : (int)cap);
 }
 // Candidates of a row that the finishing workgroup makes room for: half of kSelCandCap where the bound admits more than
-// that once in 10^6 rows at most, since two workgroups then share a compute unit (a row with more is selected from
-// global memory).  alike: sampled keys that may be as correlated as identical, `run` as above or, for scores pooled over
+// that once in 10^6 rows at most, since two workgroups then share a compute unit (a row with more takes ~10 us more).  alike: sampled keys that may be as correlated as identical, `run` as above or, for scores pooled over
 // more tokens than the sample's stride, as many strides as the pooling covers.
 inline int sel_cand_cap(int T, int m, int slack, int n_s, int alike) {
   const float per_key = (float)T / (float)n_s;

@@ -580,6 +580,24 @@ def test_select_around_zero(gpu_device, rows):
         c.close()
 
 
+# candidates beyond what the finishing workgroup holds: a bound tightened by bins, by bins that hold a run of equal scores (too long
+# for any bound, then the whole row), rows beside which others fit, a tile's last candidates off a round of 256
+@pytest.mark.parametrize("rows,T,k", [(16, 131040, 8160), (9, 200001, 8160), (5, 262080, 8128), (3, 300007, 12000), (2, 90001, 16384)])
+def test_select_more_candidates_than_fit(gpu_device, rows, T, k):
+    W = 16
+    rng = np.random.default_rng(T + k)
+    s = np.exp(2 * rng.standard_normal((rows, T + 6)))
+    s = np.stack([np.convolve(r, np.full(7, 1 / 7), "valid") for r in s]).astype(np.float32)
+    s[1] = np.round(s[1], 1)                              # ties around the threshold
+    s[-1, ::3] = s[-1].max()                              # a third of the row
+    if rows > 3:
+        s[2, T // 2:] = np.sort(s[2, T // 2:])
+        s[3, ::40] = np.quantile(s[3], 1 - k / T).astype(np.float32)   # a run of the threshold's own value
+    c = asl.Asl(T + W, rows, rows * W)
+    _select_case(c, gpu_device, s, k + W, W)
+    c.close()
+
+
 def test_select_special(ctx, gpu_device):
     T, W = 6000, 16
     _select_case(ctx, gpu_device, np.ones((2, T), dtype=np.float32), 100, W)               # all equal: first k
