@@ -10,8 +10,8 @@
 //              of the row and not many more; the key as far on the other side says where the row's k-th is likely;
 //  2. filter   one workgroup per tile of 4096 tokens keeps the tile's keys <= the bound, in token
 //              order, in the tile's own segment of a candidate buffer (no offsets to agree on).  Where the pooling
-//              kernel left the sample behind in compact form (layer steps) the filter's workgroups take the bound from
-//              it themselves and there is no launch 1;
+//              kernel left the sample behind in compact form (layer steps), and for a few rows, the filter's workgroups
+//              take the bound themselves and there is no launch 1;
 //  3. finish   one workgroup per row loads the row's candidates (a few thousand) into LDS, finds
 //              the k-th smallest key among them (finish_threshold), and writes the kept tokens in order.
 // (With four radix passes for the bound and for the threshold instead of one histogram each, 256 rows of 131040 scores
@@ -38,6 +38,16 @@ template <int NT>
 __global__ void __launch_bounds__(NT) select_filter_kernel(SelectArgs a) {
   __shared__ FilterShared<false> sh;
   select_filter_body<NT, false>(sh, a, (int)blockIdx.y, (int)blockIdx.x);
+}
+
+// Steps 1 and 2 of a few rows, with one workgroup or less for each compute unit: every workgroup takes its row's bound itself, beside
+// the loads of its TILES tiles, which saves a launch (us, so and with it: one row of 131040 scores 12.5, 13.9; 8 rows of 20000 14.3,
+// 16.0; 8 of 262080 17.3, 18.2; but four tiles a workgroup, 32 rows of 131040, 22.6, 19.6, and two workgroups a unit, 9 rows, 16.8, 16.1).
+constexpr long kOwnBoundMost = 256;
+template <int TILES>
+__global__ void __launch_bounds__(kFinThreads) select_bound_filter_kernel(SelectArgs a) {
+  __shared__ FilterShared<true> sh;
+  select_filter_body<kFinThreads, true, TILES, false>(sh, a, (int)blockIdx.y, (int)blockIdx.x * TILES);
 }
 
 // dynamic LDS: finish_lds_bytes(a.cand_cap)
@@ -101,12 +111,18 @@ hipError_t launch_select(const Workspace& ws, const float* scores, int rows, int
       if (e != hipSuccess) return e;
       continue;
     }
-    ASL_LAUNCH(ws.prof, kKernSelHist, st, select_guess_kernel, dim3(nr), dim3(kFinThreads), 0, st, a);
-    const dim3 fgrid(a.n_tiles, nr);
-    if ((long)a.n_tiles * nr >= kFilterSmallFrom)
-      ASL_LAUNCH(ws.prof, kKernSelHist, st, select_filter_kernel<kFilterThreads>, fgrid, dim3(kFilterThreads), 0, st, a);
-    else
-      ASL_LAUNCH(ws.prof, kKernSelHist, st, select_filter_kernel<kFinThreads>, fgrid, dim3(kFinThreads), 0, st, a);
+    const dim3 fgrid(a.n_tiles, nr), two((a.n_tiles + 1) / 2, nr);
+    if ((long)a.n_tiles * nr <= kOwnBoundMost) {
+      ASL_LAUNCH(ws.prof, kKernSelHist, st, select_bound_filter_kernel<1>, fgrid, dim3(kFinThreads), 0, st, a);
+    } else if ((long)two.x * nr <= kOwnBoundMost) {
+      ASL_LAUNCH(ws.prof, kKernSelHist, st, select_bound_filter_kernel<2>, two, dim3(kFinThreads), 0, st, a);
+    } else {
+      ASL_LAUNCH(ws.prof, kKernSelHist, st, select_guess_kernel, dim3(nr), dim3(kFinThreads), 0, st, a);
+      if ((long)a.n_tiles * nr >= kFilterSmallFrom)
+        ASL_LAUNCH(ws.prof, kKernSelHist, st, select_filter_kernel<kFilterThreads>, fgrid, dim3(kFilterThreads), 0, st, a);
+      else
+        ASL_LAUNCH(ws.prof, kKernSelHist, st, select_filter_kernel<kFinThreads>, fgrid, dim3(kFinThreads), 0, st, a);
+    }
     ASL_LAUNCH(ws.prof, kKernSelWrite, st, select_finish_kernel, dim3(nr), dim3(kFinThreads), finish_lds_bytes(a.cand_cap), st, a);
   }
   return hipGetLastError();

@@ -9,7 +9,7 @@ constexpr int kFinThreads = kRowThreads;               // workgroup of all three
 constexpr int kFinWaves = kFinThreads / 64;
 constexpr int kFilterThreads = 256;                    // filter workgroup of its own launch over many tiles ...
 constexpr int kFilterSmallFrom = 2048;                 // ... (rows x tiles per row) from this many on; kFinThreads below
-constexpr int kFilterMostTiles = 4;                    // tiles of one workgroup that takes the bound itself
+constexpr int kFilterMostTiles = 4;                    // most tiles of one workgroup that takes the bound itself
 constexpr uint32_t kSegOverflow = 0xffffffffu;         // a tile's count when its segment was too small
 static_assert(kSelTile % kFinThreads == 0 && kSelTile % kFilterThreads == 0, "filter tile geometry");
 
@@ -130,16 +130,21 @@ __device__ __forceinline__ void select_bound(SampleShared& sh, const SelectArgs&
   if (a.m < a.n_s) sample_bound(sh, v, a.n_s, (uint32_t)a.m, (uint32_t)a.m_low, (uint32_t)a.slack, bound, below);   // uniform
 }
 
-// Step 1 on its own, from the scores: runs of kSelSampleRun neighbouring keys.
-__device__ __forceinline__ void select_guess_body(GuessShared& sh, const SelectArgs& a, int row) {
-  const int tid = threadIdx.x, n_s = a.n_s, stride = a.stride;
-  const float* sr = a.scores + (int64_t)row * a.T;
-  uint32_t v[kSamplePer];
+// The sample of a row that nobody left one of: runs of kSelSampleRun neighbouring keys.
+__device__ __forceinline__ void load_runs(const float* sr, int n_s, int stride, uint32_t (&v)[kSamplePer]) {
+  const int tid = threadIdx.x;
 #pragma unroll
   for (int u = 0; u < kSamplePer; ++u) {               // key j = member j % run of run j / run, whose place is scattered
     const uint32_t j = (uint32_t)min(tid + u * kFinThreads, n_s - 1);
     v[u] = order_key(sr[kSelSampleRun * sel_sample_position(j / kSelSampleRun, stride) + j % kSelSampleRun]);
   }
+}
+
+// Step 1 on its own.
+__device__ __forceinline__ void select_guess_body(GuessShared& sh, const SelectArgs& a, int row) {
+  const int tid = threadIdx.x;
+  uint32_t v[kSamplePer];
+  load_runs(a.scores + (int64_t)row * a.T, a.n_s, a.stride, v);
   uint32_t bound, below;
   select_bound(sh.s, a, v, bound, below);
   if (tid == 0) {
@@ -184,13 +189,13 @@ template <> struct FilterShared<true> {
 // registers in it: 256 rows of 131040 scores 49.9 us, so 44.4; 64 rows 25.2, 21.8; 256 of 40000 29.6, 26.3 (counts of four
 // rounds packed into two prefix sums, the kept scores read again: 53.9).  Inside a layer step, one round a tile, four with one 16-byte load, on
 // whatever 4-byte boundary the row starts (8 heads, 32K 59.9, one per load 60.3).
-// INSIDE (NT = kFinThreads): the sample is there in compact form and the workgroup takes the bound from it
-// (step 1) beside its own loads; the row's first one stores it for step 3.  TILES: consecutive tiles of a workgroup,
+// INSIDE (NT = kFinThreads): the workgroup takes the bound (step 1) beside its own loads, from a sample that is there in compact
+// form (SAMPLED) or from the row; the row's first one stores it for step 3.  TILES: consecutive tiles of a workgroup,
 // from `tile` on: a bound costs as much as two of them.
-template <int NT, bool INSIDE, int TILES = 1>
+template <int NT, bool INSIDE, int TILES = 1, bool SAMPLED = true>
 __device__ __forceinline__ void select_filter_body(FilterShared<INSIDE>& sh, const SelectArgs& a, int row, int tile) {
   constexpr int kWaves = NT / 64, kSelPerWave = kSelTile / kWaves;
-  constexpr int kPer = INSIDE ? 4 : 1;                  // neighbouring tokens per lane and round
+  constexpr int kPer = INSIDE && SAMPLED ? 4 : 1;                  // neighbouring tokens per lane and round
   typedef float Four __attribute__((ext_vector_type(4), aligned(4)));
   constexpr int kSelRounds = kSelPerWave / (64 * kPer);
   static_assert(kSelRounds >= 1 && (TILES == 1 || INSIDE) && TILES <= kFilterMostTiles, "filter tile geometry");
@@ -223,7 +228,10 @@ __device__ __forceinline__ void select_filter_body(FilterShared<INSIDE>& sh, con
   if constexpr (INSIDE) {
     static_assert(NT == kFinThreads, "the sample is shared out among kFinThreads threads");
     uint32_t v[kSamplePer];
-    load_sample(nullptr, a.sample + (int64_t)row * kSelMaxSample, a.n_s, a.stride, v);
+    if constexpr (SAMPLED)
+      load_sample(nullptr, a.sample + (int64_t)row * kSelMaxSample, a.n_s, a.stride, v);
+    else
+      load_runs(sr, a.n_s, a.stride, v);
     select_bound(sh.s, a, v, bound, below);
     if (tile == 0 && tid == 0) {
       a.bound[2 * row] = bound;

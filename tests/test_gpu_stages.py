@@ -580,6 +580,20 @@ def test_select_around_zero(gpu_device, rows):
         c.close()
 
 
+# as many tiles as take one and two a workgroup, and one more of each; the last workgroup's second tile missing, one token long, full
+@pytest.mark.parametrize("rows,T", [(8, 32 * 4096), (8, 32 * 4096 + 1), (8, 64 * 4096), (8, 64 * 4096 + 1), (1, 16385), (64, 4 * 4096 + 1),
+                                    (64, 8 * 4096 + 1), (256, 32769), (51, 9 * 4096 + 1)])
+def test_select_rows_whose_filter_takes_the_bound(gpu_device, rows, T):
+    rng = np.random.default_rng(rows + T)
+    s = np.exp(2 * rng.standard_normal((rows, T), dtype=np.float32))
+    s[::4, ::3] = s[0, 5]                                 # a third of the row ties
+    s[1::4] = np.sort(s[1::4])
+    c = asl.Asl(T + 8, rows, rows * 8)
+    for budget in (9, 2048, T // 3):
+        _select_case(c, gpu_device, s, budget, 8)
+    c.close()
+
+
 # candidates beyond what the finishing workgroup holds: a bound tightened by bins, by bins that hold a run of equal scores (too long
 # for any bound, then the whole row), rows beside which others fit, a tile's last candidates off a round of 256
 @pytest.mark.parametrize("rows,T,k", [(16, 131040, 8160), (9, 200001, 8160), (5, 262080, 8128), (3, 300007, 12000), (2, 90001, 16384)])
