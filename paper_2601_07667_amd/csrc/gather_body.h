@@ -66,6 +66,9 @@ __device__ __forceinline__ void gather_body(const GatherArgs& a, int bx, int h, 
   if (qd < total) store(vd, (GDst16)(dst + (int64_t)qd * 16));
 }
 
+// Pieces per thread of a compaction beside its selection: fewer than above, since its latency follows the selection's (layer step, us,
+// with four, two, one: two heads of d = 64, 10K 25.2, 24.4, 24.1; 8 heads, 4K 25.2, 25.5, 26.5; 12K 33.8, 33.4, 34.9).
+constexpr int kPickedUnroll = 2;
 // The same for rows that another workgroup of this launch is still selecting: the block's source tokens are read from the words
 // (tag, token) in which it leaves them, T + i for the row's last, window tokens.  A word that carries the launch's tag is whole
 // and this launch's, whatever it held before, so nothing else is ordered between the two.  k: the row's selected tokens; picks:
@@ -80,10 +83,10 @@ __device__ __forceinline__ bool gather_picked_body(const GatherArgs& a, int bx, 
   char* dst = (which == 0 ? a.k_out : a.v_out) + (int64_t)h * a.n_idx * ((int64_t)a.cpr * 16);
   const int64_t stt = which == 0 ? a.kst : a.vst;
   const uint32_t total = (uint32_t)a.n_idx * (uint32_t)a.cpr, last = total - 1u, cpr = (uint32_t)a.cpr;
-  uint32_t q[kGatherUnroll], c[kGatherUnroll], r[kGatherUnroll], tok[kGatherUnroll];
+  uint32_t q[kPickedUnroll], c[kPickedUnroll], r[kPickedUnroll], tok[kPickedUnroll];
 #pragma unroll
-  for (int u = 0; u < kGatherUnroll; ++u) {
-    q[u] = (uint32_t)bx * (NT * kGatherUnroll) + threadIdx.x + u * NT;
+  for (int u = 0; u < kPickedUnroll; ++u) {
+    q[u] = (uint32_t)bx * (NT * kPickedUnroll) + threadIdx.x + u * NT;
     const uint32_t cq = min(q[u], last);
     r[u] = POW2 ? (cq >> a.cpr_shift) : (cq / cpr);
     c[u] = cq - r[u] * cpr;
@@ -92,27 +95,27 @@ __device__ __forceinline__ bool gather_picked_body(const GatherArgs& a, int bx, 
     for (int spins = 0; spins < kFlagSpinLimit; ++spins) {
       const unsigned long long w = __hip_atomic_load(picks + k - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if ((uint32_t)__builtin_amdgcn_readfirstlane((int)(w >> 32)) == tag) break;
-      __builtin_amdgcn_s_sleep(4);
+      __builtin_amdgcn_s_sleep(1);
     }
   }
   __syncthreads();
   for (int spins = 0;; ++spins) {
     bool ok = true;
 #pragma unroll
-    for (int u = 0; u < kGatherUnroll; ++u) {
+    for (int u = 0; u < kPickedUnroll; ++u) {
       const unsigned long long w = __hip_atomic_load(picks + min(r[u], (uint32_t)k - 1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       ok = ok && (uint32_t)(w >> 32) == tag;
       tok[u] = r[u] < (uint32_t)k ? (uint32_t)w : (uint32_t)T + (r[u] - (uint32_t)k);
     }
     if (__ballot(!ok) == 0ull) break;                   // uniform
     if (spins >= kFlagSpinLimit) return false;
-    __builtin_amdgcn_s_sleep(8);
+    __builtin_amdgcn_s_sleep(2);
   }
-  Piece v[kGatherUnroll];
+  Piece v[kPickedUnroll];
 #pragma unroll
-  for (int u = 0; u < kGatherUnroll; ++u) v[u] = *(GSrc16)(src + (int64_t)tok[u] * stt + (int64_t)c[u] * 16);
+  for (int u = 0; u < kPickedUnroll; ++u) v[u] = *(GSrc16)(src + (int64_t)tok[u] * stt + (int64_t)c[u] * 16);
 #pragma unroll
-  for (int u = 0; u < kGatherUnroll; ++u)
+  for (int u = 0; u < kPickedUnroll; ++u)
     if (q[u] < total) *(GDst16)(dst + (int64_t)q[u] * 16) = v[u];
   return true;
 }

@@ -29,8 +29,8 @@ union PartFilterShared {
 // workgroups of head r wait for theirs.  Those come last, 8 * i + x for heads r with r % 8 == x: on the die of the workgroup they
 // wait for, behind it in the order in which a die starts them, so that waiting workgroups cannot keep the waited-for ones from
 // starting, whatever else runs on the device.  gx: blocks per (head, tensor) slab, 0 for no compaction here.  A layer step, us, with
-// statistic and compaction in a launch of their own and so: 8 KV heads 1K 23.5, 21.1; 8K 37.4, 34.3; 12K 35.4, 33.9; two heads of
-// d = 64, 4K 23.5, 21.1; 10K 26.2, 24.9; 10K below L_min 24.8, 24.9.  WAVES: wavefronts of a SIMD that the scalar registers
+// statistic and compaction in a launch of their own and so: 8 KV heads 1K 23.6, 20.3; 8K 37.4, 33.7; 12K 35.2, 33.4; two heads of
+// d = 64, 4K 21.7, 19.7; 11K 26.4, 24.5; 10K below L_min 25.2, 24.4.  WAVES: wavefronts of a SIMD that the scalar registers
 // allow: 8 for two workgroups a unit where ranking and top-k have more than one for each (8K 37.3, 34.4); else 4, whose code is 0.6
 // to 1 us faster.  Dynamic LDS: kTailShortLds.
 constexpr size_t kTailShortLds = sizeof(ShortSelectShared<kShortPer>) > sizeof(RankStatShared) ? sizeof(ShortSelectShared<kShortPer>) : sizeof(RankStatShared);
@@ -181,7 +181,7 @@ hipError_t launch_tail(const Workspace& ws, const float* scores, int rows, int T
     if (gather != nullptr && Hk <= ws.pick_rows && k <= kPickMost) {
       ga = *gather;
       pow2 = gather_prepare(ga);
-      gx = (int)(((int64_t)ga.n_idx * ga.cpr + kTailThreads * kGatherUnroll - 1) / (kTailThreads * kGatherUnroll));
+      gx = (int)(((int64_t)ga.n_idx * ga.cpr + kTailThreads * kPickedUnroll - 1) / (kTailThreads * kPickedUnroll));
       grid = short_gather_from(rows, n_rank) + kDies * ((Hk + kDies - 1) / kDies) * gx * ga.n_tensors;
       sp.picks = ws.sel_picks;
       sp.pick_tag = ws.pick_tag;
