@@ -295,11 +295,14 @@ __device__ __forceinline__ float max2(float a, float b) { return __builtin_fmaxf
 // the rescaling, a fifth of the vector work, are left out (256K, W = 64, pass 1 147.7 -> 138.5 us; 128K 131.7 -> 130.8, 64K 84.2
 // -> 81.1 the layer step).  One branch for all row blocks, behind all of their arithmetic: with one per block half of it stood in
 // a basic block without MFMAs (144.6).  Not for the shapes whose calls are start-up mostly: their one or two sub-tiles take the
-// branch every time (d = 256, 8K, 17.2 -> 17.7).
+// branch every time (d = 256, 8K, 17.2 -> 17.7).  And a wavefront whose references move in more than an eighth of the sub-tiles goes on
+// with the running maximum: logits of hundreds that grow (lognormal key lengths, 256K, W = 64) took
+// 166 us without that, 149 with it, 147 with the running maximum throughout.
 constexpr float kRescale = 256.f;
+template <typename TE, int P, bool PAD> constexpr bool kLazy = sizeof(TE) == 2 && P <= 16 && !PAD;
 template <int RB, bool MASK, bool LAZY>
 __device__ __forceinline__ void rowstats_fold(const f32x16 (&acc)[RB], int key_lo, int N, int T,
-                                              const int (&wi)[RB], float c1, float (&m_run)[RB], float (&z_run)[RB]) {
+                                              const int (&wi)[RB], float c1, float (&m_run)[RB], float (&z_run)[RB], int& raised) {
   float x[RB][16], sum[RB];
   bool far = false;
   auto raise = [&](int rb) {                              // the reference up to the sub-tile's largest logit, the sum with it
@@ -333,6 +336,7 @@ __device__ __forceinline__ void rowstats_fold(const f32x16 (&acc)[RB], int key_l
     }
   }
   if (LAZY && __builtin_expect(__ballot(far) != 0ull, 0)) {   // uniform; so for the first visible keys, whose m_run is kNegBig
+    ++raised;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) raise(rb);
   }
@@ -347,12 +351,12 @@ __device__ __forceinline__ void rowstats_fold(const f32x16 (&acc)[RB], int key_l
 // in one block of straight-line code with the softmax arithmetic of the sub-tile before it (`acc`, the
 // last sub-tile of the tile before on entry), so that a wavefront's own vector instructions fill the
 // time its MFMAs take.  MASK: tiles that touch the window block or the tail past N (they come last).
-template <typename TE, int P, int NT, int RB, bool PAD, bool MASK>
+template <typename TE, int P, int NT, int RB, bool PAD, bool MASK, bool LAZY>
 __device__ __forceinline__ void rowstats_tile(const Piece* __restrict__ cur, Piece* __restrict__ nxt,
                                               bool prefetch, bool stream, const TilePieces<P, NT>& tp, const char* __restrict__ kg, int64_t rsb,
                                               int prefetch_key0, int np, int last_piece, int tile, int prev, int N, int T, const int (&wi)[RB],
                                               int tid, int ln, int half, const Piece (&qf)[RB][P / 2], float c1,
-                                              f32x16 (&acc)[RB], float (&m_run)[RB], float (&z_run)[RB]) {
+                                              f32x16 (&acc)[RB], float (&m_run)[RB], float (&z_run)[RB], int& raised) {
   constexpr int KT = key_tile<P>();
   if (prefetch) issue_tile_loads<P, NT>(tp, kg, rsb, prefetch_key0, N, last_piece, nxt, tid, stream);
 #pragma unroll
@@ -360,7 +364,7 @@ __device__ __forceinline__ void rowstats_tile(const Piece* __restrict__ cur, Pie
     f32x16 nxt_acc[RB];
     mma_subtile<TE, P, true, RB, PAD>(cur, sub, ln, half, np, qf, nxt_acc);
     // the sub-tile before this one: the last of tile `prev`, or of this tile
-    rowstats_fold<RB, MASK, sizeof(TE) == 2 && P <= 16 && !PAD>(acc, (sub == 0 ? prev * KT + KT - 32 : tile * KT + (sub - 1) * 32) + 4 * half, N, T, wi, c1, m_run, z_run);
+    rowstats_fold<RB, MASK, LAZY>(acc, (sub == 0 ? prev * KT + KT - 32 : tile * KT + (sub - 1) * 32) + 4 * half, N, T, wi, c1, m_run, z_run, raised);
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) acc[rb] = nxt_acc[rb];
   }
@@ -418,13 +422,14 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
     for (int r = 0; r < 16; ++r) acc[rb][r] = -INFINITY;
   int stage = 0;                                  // buffer that holds tile `tile`
   int it = 0, tile = chunk, prev = chunk;
-  auto step = [&](auto mask) {
+  int raised = 0;                                 // sub-tiles that moved the references (uniform in the wavefront)
+  auto step = [&](auto mask, auto lazy) {
     wait_tile<P, NT, STAGES>(min(STAGES - 2, n_my - 1 - it));
     __syncthreads();      // tile `tile` has landed for every wave; the buffer of the tile before is free again
     const int free_stage = (stage == 0) ? STAGES - 1 : stage - 1;
-    rowstats_tile<TE, P, NT, RB, PAD, decltype(mask)::value>(
+    rowstats_tile<TE, P, NT, RB, PAD, decltype(mask)::value, decltype(lazy)::value>(
         lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS, it + STAGES - 1 < n_my, stream, tp, kg, kst,
-        ahead * KT, np, last_piece, tile, prev, N, T, wi, tid, ln, half, qf, c1, acc, m_run, z_run);
+        ahead * KT, np, last_piece, tile, prev, N, T, wi, tid, ln, half, qf, c1, acc, m_run, z_run, raised);
     stage = (stage + 1 == STAGES) ? 0 : stage + 1;
     ahead += split.step(it + STAGES - 1);
     prev = tile;
@@ -433,10 +438,13 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
   };
   // tiles of visible keys only, then those that touch the window block or the end
   const int plain = T / KT;
-  while (it < n_my && tile < plain) step(std::false_type());
-  while (it < n_my) step(std::true_type());
+  if constexpr (kLazy<TE, P, PAD>) {
+    while (it < n_my && tile < plain && raised <= 3 + it / 4) step(std::false_type(), std::true_type());
+  }
+  while (it < n_my && tile < plain) step(std::false_type(), std::false_type());
+  while (it < n_my) step(std::true_type(), std::false_type());
   if (n_my > 0)                                   // the last sub-tile is still to be folded
-    rowstats_fold<RB, true, sizeof(TE) == 2 && P <= 16 && !PAD>(acc, prev * KT + KT - 32 + 4 * half, N, T, wi, c1, m_run, z_run);
+    rowstats_fold<RB, true, false>(acc, prev * KT + KT - 32 + 4 * half, N, T, wi, c1, m_run, z_run, raised);
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     // the two lane halves hold disjoint keys of the same query row
