@@ -221,7 +221,7 @@ asl_status asl_gather_rows(asl_ctx* ctx, const void* src, int64_t src_row_stride
  * the single calls.  After the scoring, ranking and top-k + compaction are independent; the call
  * runs them side by side in three launches on `stream`: two that each carry a stage of the ranking and one of the
  * top-k, and one with the statistic (below l_min the note that it was not evaluated) beside the
- * compaction.  Contexts of up to 12288 past tokens take one launch for the ranking and the top-k.
+ * compaction.  Contexts of up to 12288 past tokens take one launch for all of it.
  *   scores  [Hk+1, T] f32 out: rows 0..Hk-1 = P (per KV head), row Hk = s (all heads).
  *   idx_out [Hk+1, k+W] int32 out: rows 0..Hk-1 = Alg. 1's per-head I, row Hk = Alg. 2's select_idx
  *           (to be used only when out->selected is set).
@@ -261,8 +261,8 @@ asl_status asl_device_fault(asl_ctx* ctx, int32_t* fault_out);
  * finalisation (or the below-L_min skip), 7 rank-variance partial sums, 8 select histogram, 9 select write,
  * 10 gather, 11 plain-FMA score kernels, 12 the launches of asl_layer_step that carry stages of the ranking, the
  * top-k and the compaction together.  (8 covers the top-k's bound and filter kernels, 9 its finishing kernel
- * (and the one of short rows); the statistic is one kernel, 7; 6 is the below-L_min skip of asl_rank_stat,
- * asl_rankvar and steps without compaction: with it, it is part of 12.)
+ * (and the one of short rows); the statistic is one kernel, 7, or up to 12288 tokens part of 5; 6 is the below-L_min skip of
+ * asl_rank_stat beyond them, asl_rankvar and longer steps without compaction: else it is part of 5 or 12.)
  * asl_profile_enable: launches whose id bit is set in kernel_mask carry a HIP event pair that the
  *   runtime stamps with the kernel's start and end on the device (the call's stream; not under
  *   stream capture), up to max_records launches (further ones run unrecorded); mask 0 turns

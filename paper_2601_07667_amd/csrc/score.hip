@@ -292,7 +292,7 @@ __device__ __forceinline__ float max2(float a, float b) { return __builtin_fmaxf
 // exponentials = z_run * 2^m_run.
 // LAZY: the reference is the largest logit up to some sub-tile, and stays until a sub-tile's sum of 16 is above kRescale: no term
 // is then more than 2^8 times the reference's, which the fp32 sum holds as exactly as the terms below it, and the maximum of the 16 and
-// the rescaling, a fifth of the vector work, are left out (256K, W = 64, pass 1 147.7 -> 138.5 us; 128K 131.7 -> 130.8, 64K 84.2
+// the rescaling, a fifth of the vector work, are left out (256K, W = 64, pass 1 147.7 -> 138.5 us; 128K 132.9 -> 130.8, 64K 84.2
 // -> 81.1 the layer step).  One branch for all row blocks, behind all of their arithmetic: with one per block half of it stood in
 // a basic block without MFMAs (144.6).  Not for the shapes whose calls are start-up mostly: their one or two sub-tiles take the
 // branch every time (d = 256, 8K, 17.2 -> 17.7).  And a wavefront whose references move in more than an eighth of the sub-tiles goes on

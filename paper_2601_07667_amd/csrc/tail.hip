@@ -5,7 +5,7 @@
 // steps 9-10 and 12; Alg. 2 steps 11-12).  Run as separate launches they either serialise (one
 // stream) or pay two cross-queue synchronisations per layer (two streams).  Here the stages share launches:
 // the two jobs of a launch are independent, and every stage depends only on earlier launches, which the launch
-// boundary orders.  The bodies are the same device functions the single-call kernels use.
+// boundary orders (short contexts' compaction and statistic apart, which wait for words of other workgroups).  The bodies are the same device functions the single-call kernels use.
 #include <type_traits>
 
 #include "gather_body.h"

@@ -391,7 +391,7 @@ def test_layer_step_ragged_shapes(gpu_device, Hq, Hk, d, N, W, S, budget):
 @pytest.mark.parametrize("N,layer_idx,L_min", [(12288 + 16, 0, 0), (12288 + 17, 0, 0), (12288 + 16, 0, 5), (12288 + 17, 3, 5),
                                                (49, 0, 2)])
 def test_layer_step_around_the_short_limit(gpu_device, N, layer_idx, L_min):
-    """12288 past tokens (ranked and selected from in one launch) and 12289 (five launches): a first layer, which has
+    """12288 past tokens (ranked and selected from in one launch) and 12289 (three launches): a first layer, which has
     nothing to be compared with yet, and layers below L_min (the state only advances)."""
     sh = synth.Shape(Hq=4, Hk=2, d=64, N=N, W=16, S=7, budget=300, L_min=L_min)
     L = synth.iid_layer(sh, 2000 + N, name=f"short-limit-{N}-{layer_idx}")
