@@ -31,13 +31,11 @@ __global__ void __launch_bounds__(kFinThreads) select_guess_kernel(SelectArgs a)
   select_guess_body(sh, a, (int)blockIdx.x);
 }
 
-// grid: x = tile, y = row.  Small workgroups when there are enough tiles to fill the device several
-// times over (a workgroup lives ~5 us whatever its size: more of them in flight stream faster), large
-// ones for a few rows (one round of workgroups: the shorter each one's share, the sooner it ends).
-template <int NT>
-__global__ void __launch_bounds__(NT) select_filter_kernel(SelectArgs a) {
+// grid: x = tile, y = row.  Small workgroups: one lives ~5 us whatever its size, and more of them in flight stream faster (us, with
+// 1024 threads and so: 32 rows of 200001 scores 22.9, 21.5; 64 of 100001 20.7, 19.3; 130 of 40000 22.2, 20.8).
+__global__ void __launch_bounds__(kFilterThreads) select_filter_kernel(SelectArgs a) {
   __shared__ FilterShared<false> sh;
-  select_filter_body<NT, false>(sh, a, (int)blockIdx.y, (int)blockIdx.x);
+  select_filter_body<kFilterThreads, false>(sh, a, (int)blockIdx.y, (int)blockIdx.x);
 }
 
 // Steps 1 and 2 of a few rows, with one workgroup or less for each compute unit: every workgroup takes its row's bound itself, beside
@@ -118,10 +116,7 @@ hipError_t launch_select(const Workspace& ws, const float* scores, int rows, int
       ASL_LAUNCH(ws.prof, kKernSelHist, st, select_bound_filter_kernel<2>, two, dim3(kFinThreads), 0, st, a);
     } else {
       ASL_LAUNCH(ws.prof, kKernSelHist, st, select_guess_kernel, dim3(nr), dim3(kFinThreads), 0, st, a);
-      if ((long)a.n_tiles * nr >= kFilterSmallFrom)
-        ASL_LAUNCH(ws.prof, kKernSelHist, st, select_filter_kernel<kFilterThreads>, fgrid, dim3(kFilterThreads), 0, st, a);
-      else
-        ASL_LAUNCH(ws.prof, kKernSelHist, st, select_filter_kernel<kFinThreads>, fgrid, dim3(kFinThreads), 0, st, a);
+      ASL_LAUNCH(ws.prof, kKernSelHist, st, select_filter_kernel, fgrid, dim3(kFilterThreads), 0, st, a);
     }
     ASL_LAUNCH(ws.prof, kKernSelWrite, st, select_finish_kernel, dim3(nr), dim3(kFinThreads), finish_lds_bytes(a.cand_cap), st, a);
   }

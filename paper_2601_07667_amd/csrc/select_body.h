@@ -5,10 +5,9 @@
 
 namespace asl {
 
-constexpr int kFinThreads = kRowThreads;               // workgroup of all three kernels
+constexpr int kFinThreads = kRowThreads;               // workgroup of the other kernels
 constexpr int kFinWaves = kFinThreads / 64;
-constexpr int kFilterThreads = 256;                    // filter workgroup of its own launch over many tiles ...
-constexpr int kFilterSmallFrom = 2048;                 // ... (rows x tiles per row) from this many on; kFinThreads below
+constexpr int kFilterThreads = 256;                    // filter workgroup of its own launch
 constexpr int kFilterMostTiles = 4;                    // most tiles of one workgroup that takes the bound itself
 constexpr uint32_t kSegOverflow = 0xffffffffu;         // a tile's count when its segment was too small
 static_assert(kSelTile % kFinThreads == 0 && kSelTile % kFilterThreads == 0, "filter tile geometry");

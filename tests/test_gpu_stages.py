@@ -508,9 +508,7 @@ def test_rank_select_pool_random_shapes(ctx, gpu_device):
                                            (128, 131040, 2080), (130, 100001, 1056), (256, 20000, 8192),
                                            (129, 70000, 35000), (128, 5, 4), (140, 4096, 33)])
 def test_select_many_rows(gpu_device, rows, T, budget):
-    """96 rows x 25 tiles: the tile count from which the filter stage runs as many small workgroups
-    (a few rows take one round of large ones), with rows on 16-byte boundaries and, T = 100001, off
-    them.  300 rows: more than the candidate buffers hold at once,
+    """96 rows x 25 tiles, with rows on 16-byte boundaries and, T = 100001, off them.  300 rows: more than the candidate buffers hold at once,
     so the three launches run twice.  Further: 128 full-size rows, a budget of 8192 on many rows, a
     budget of half the row (the candidates overflow: selection from the whole row), rows of five
     tokens, rows of exactly one tile."""
