@@ -18,6 +18,7 @@
 #include <type_traits>
 
 #include "asl_internal.h"
+#include "score_split.h"
 
 namespace asl {
 
@@ -241,47 +242,6 @@ __device__ __forceinline__ void mma_subtile(const Piece* __restrict__ buf, int s
   _Pragma("unroll") for (int rb = 0; rb < RB; ++rb)                                               \
     _Pragma("unroll") for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[rb][ks]));
 
-
-// The key tiles of a workgroup.  The n_chunks workgroups of a KV head take the tiles in turn: the k-th of them tiles k,
-// k + n_chunks, ..., so that a head's workgroups, which advance together, read one stretch of memory at a time.  (Each with a
-// contiguous share they read at as many places, a power of two apart: a bare ring of this shape streams 268 MB in 44.9 us so,
-// in turn in 41.6; 8B shape, 128K, `lse` supplied, pass 2 61.2 and 58.8 us; 32K, both passes, 33.4 and 31.5.)
-// All workgroups of a pass are resident at once (one round), block b being the (b / n_cu)-th placed on its compute unit.  A
-// unit's older wavefronts go first, so with two workgroups per unit the second ends up alone on it for the last part of the
-// kernel: after `all` rounds of everybody only the first placed take turns (1250 : 798 of a unit's tiles, with two row blocks a
-// wavefront 1350 : 698, the more unequal the more the arithmetic bounds the kernel; pass 1 + pass 2 at 256K, W = 64, equal shares
-// 152 + 158 us, 1250 : 798 147 + 153, 1350 : 698 145 + 150).  Up to four tiles per chunk that come out even to 1/16 stay
-// equal: weighted, rounding makes some chunks a tile longer (8 KV heads, whole call, weighted and equal: one tile, W = 64
-// 27.3 and 25.1 us; two tiles, W = 32 20.4 and 19.9; but 2.45, W = 64 31.1 and 31.7, 5.9 28.5 and 28.9).
-struct TileSplit {
-  int n_chunks;
-  int all;                       // rounds that every chunk takes part in
-  int first;                     // chunks that go on after them
-  int more, longer;              // their further tiles: `more` each, and one for the first `longer` of them
-  __host__ __device__ int count(int chunk) const { return all + (chunk < first ? more + (chunk < longer ? 1 : 0) : 0); }
-  __host__ __device__ int tile(int chunk, int i) const {              // i-th tile of a chunk, i < count(chunk)
-    return chunk + (i < all ? i * n_chunks : all * n_chunks + (i - all) * first);
-  }
-  // from the i-th to the next; backwards from the i-th to the one before: step(i - 1)
-  __device__ __forceinline__ int step(int i) const { return i < all ? n_chunks : first; }
-};
-template <int RB>
-static TileSplit split_tiles(int Hk, int n_chunks, int n_tiles, int n_cu) {
-  constexpr int kFirst = RB > 1 ? 1350 : 1250, kSecond = 2048 - kFirst;
-  const int grid = n_chunks * Hk;
-  const int slots = n_chunks * (1 + (n_tiles > n_chunks) + (n_tiles > 2 * n_chunks) + (n_tiles > 3 * n_chunks));
-  const bool even = n_tiles <= slots && 16 * (slots - n_tiles) <= slots;
-  TileSplit s = {n_chunks, 0, n_chunks, 0, 0};
-  if (grid > n_cu && grid <= 2 * n_cu && !even) {
-    s.first = n_cu / Hk < 1 ? 1 : n_cu / Hk;           // block c * Hk + g is the first of its unit iff it is below n_cu
-    s.all = (int)((int64_t)n_tiles * kSecond / (kFirst * s.first + kSecond * (n_chunks - s.first)));
-    if (s.all < 1) s.all = 1;                          // n_chunks <= n_tiles
-  }
-  const int left = n_tiles - s.all * n_chunks;
-  s.more = left / s.first;
-  s.longer = left % s.first;
-  return s;
-}
 
 // This file is compiled with NaNs assumed absent, so this is a bare v_max_f32 / v_max3_f32
 // (inputs are finite or -inf here).
@@ -944,7 +904,7 @@ static hipError_t launch_score_mfma(const asl_params& p, const Workspace& ws, co
   if (!lse) {
     for (int m0 = 0; m0 < M; m0 += kRows)
       ASL_LAUNCH(ws.prof, kKernRowstats, st, (score_rowstats_kernel<TE, P, NW, RB, PAD>), dim3(Hk * n_chunks), dim3(NW * 64), 0,
-                 st, q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, p.window, N, split_tiles<RB>(Hk, n_chunks, (N + KT - 1) / KT, n_cu), stream, c1,
+                 st, q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, p.window, N, split_tiles(Hk, n_chunks, (N + KT - 1) / KT, n_cu, RB > 1), stream, c1,
                  ws.row_part);
     if (lse_out || combine) {
       ASL_LAUNCH(ws.prof, kKernCombine, st, score_combine_kernel, dim3((Hk * M + kCombineRows - 1) / kCombineRows), dim3(256), 0, st,
@@ -958,7 +918,7 @@ static hipError_t launch_score_mfma(const asl_params& p, const Workspace& ws, co
   // its own rows
   for (int m0 = 0; m0 < M; m0 += kRows)
     ASL_LAUNCH(ws.prof, kKernColsum, st, (score_colsum_kernel<TE, P, NW, RB, PAD, DENORM>), dim3(Hk * n_chunks2), dim3(NW * 64), 0, st,
-               q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, N, T, split_tiles<RB>(Hk, n_chunks2, n_tiles2, n_cu), stream, c1, lse ? lse : ws.row_const,
+               q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, N, T, split_tiles(Hk, n_chunks2, n_tiles2, n_cu, RB > 1), stream, c1, lse ? lse : ws.row_const,
                lse ? kLog2e : 1.0f, lse || combine ? nullptr : ws.row_part, n_chunks, ws.u_group);
   return hipGetLastError();
 }

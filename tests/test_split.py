@@ -1,0 +1,35 @@
+"""Host arithmetic of a scoring launch, no GPU needed: how key tiles are shared out among workgroups."""
+import random
+import subprocess
+
+from test_bound import _client
+
+
+def _shares(tmp_path_factory, queries):
+    out = subprocess.run([_client(tmp_path_factory, "split_client")], input="".join("%d %d %d %d %d\n" % q for q in queries),
+                         check=True, capture_output=True, text=True).stdout
+    return [tuple(int(x) for x in line.split()) for line in out.splitlines()]
+
+
+def test_key_tiles_of_a_launch(tmp_path_factory):
+    """Every tile is taken once, pass 2 walks a share backwards over the same tiles, and no share is longer than the first-placed
+    workgroups' weighted part of the tiles, rounded up (equal parts where a unit holds one workgroup, or more than two)."""
+    rng, n_cu = random.Random(1), 256
+    queries = [(8, 64, 194, n_cu, 0), (8, 64, 258, n_cu, 0), (8, 64, 386, n_cu, 0), (4, 128, 770, n_cu, 0), (2, 192, 328, n_cu, 0)]
+    while len(queries) < 4000:
+        Hk = rng.choice([1, 2, 3, 4, 7, 8, 8, 16, 40, 64, 300])
+        n_chunks = rng.randint(1, min(256, max(1, 4 * n_cu // Hk)))
+        queries.append((Hk, n_chunks, n_chunks + rng.choice([0, 1, rng.randint(0, 2 * n_chunks), rng.randint(0, 40 * n_chunks)]),
+                        n_cu, rng.randint(0, 1)))
+    weighted = 0
+    for (Hk, n_chunks, n_tiles, _, two), (ok, longest, w) in zip(queries, _shares(tmp_path_factory, queries)):
+        assert ok, (Hk, n_chunks, n_tiles, two)
+        equal = -(-n_tiles // n_chunks)
+        if n_cu < n_chunks * Hk <= 2 * n_cu:
+            first = max(1, n_cu // Hk)
+            most = -(-n_tiles * w // (w * first + (2048 - w) * (n_chunks - first)))
+            weighted += longest > equal
+            assert longest <= max(most, equal), (Hk, n_chunks, n_tiles, two, longest, most)
+        else:
+            assert longest == equal, (Hk, n_chunks, n_tiles, two)
+    assert weighted > 100                              # the unequal shares are there
