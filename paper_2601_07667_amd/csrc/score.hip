@@ -861,17 +861,6 @@ static int score_chunks(int Hk, int n_tiles, int n_cu, int resident, bool fold) 
   return best;
 }
 
-// Whether the keys, so many bytes of them, are loaded with the non-temporal bit, past the last-level cache (256 MB).  Keys that are read
-// once gain from 64 MB on (8B shape, `lse` supplied, layer step, us without and with: 32K 46.0, 42.1; 64K 59.5, 53.4; 128K 87.7, 79.3;
-// 256K 147.6, 127.8).  Read by both passes, smaller ones are there for the second: 16K 45.7, 47.4; 24K 51.4, 51.2; 48K 75.2, 73.0;
-// 96K 114.1, 108.7; 128K 145.7, 137.4; 256K 253.3, 236.1; calls of asl_score_layer alone on a few sets of keys in turn gain
-// less and up to 3 % at 128K are lost.  With two row blocks a wavefront both passes are bound by arithmetic: 28 heads, 256K 186.5, 185.9,
-// asl_score_layer alone 158.4, 163.9.
-template <int RB>
-static bool stream_keys(int64_t bytes, bool both_passes) {
-  return both_passes ? RB == 1 && bytes >= int64_t(96) << 20 : bytes >= int64_t(64) << 20;
-}
-
 // Workgroups of `kernel` that fit on one compute unit at once (registers, LDS, wave slots).
 template <typename K>
 static int resident_per_cu(K kernel, int threads, size_t dynamic_lds = 0) {
@@ -900,7 +889,14 @@ static hipError_t launch_score_mfma(const asl_params& p, const Workspace& ws, co
   }();
   const int n_cu = device_cu_count();
   const int n_chunks = score_chunks<TE, P, NW, RB>(Hk, (N + KT - 1) / KT, n_cu, resident, lse == nullptr);
-  const bool combine = n_chunks > kFoldChunks, stream = stream_keys<RB>((int64_t)Hk * N * p.head_dim * (int64_t)sizeof(TE), lse == nullptr);
+  const bool combine = n_chunks > kFoldChunks;
+  // Keys that are read once (kOnce) or more often are loaded past the last-level cache (stream_keys) where that gains:
+  // not in fp32, bound by its arithmetic (both passes, us, without and with: 8 heads of d = 64, 96 MB 60.6, 63.3; of d = 128 59.3, 61.9;
+  // `lse` supplied at most 1 % either way), nor, read more than once, with two row blocks a wavefront (28 heads, 256K 186.5, 185.9, alone
+  // 158.4, 163.9; 1024 rows a head, `lse` supplied, 200 MB 294.6, 300.3) or padded rows (d = 80, 252 MB 158, 161).
+  constexpr bool kOnce = sizeof(TE) == 2, kTwice = kOnce && RB == 1 && !PAD;
+  const int reads = (M + kRows - 1) / kRows * (lse ? 1 : 2);
+  const bool stream = (reads == 1 ? kOnce : kTwice) && stream_keys((int64_t)Hk * N * p.head_dim * (int64_t)sizeof(TE), reads, Hk > 1 && ksh == 0);
   if (!lse) {
     for (int m0 = 0; m0 < M; m0 += kRows)
       ASL_LAUNCH(ws.prof, kKernRowstats, st, (score_rowstats_kernel<TE, P, NW, RB, PAD>), dim3(Hk * n_chunks), dim3(NW * 64), 0,

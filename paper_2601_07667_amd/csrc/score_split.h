@@ -1,5 +1,5 @@
-// How a scoring launch shares a KV head's key tiles out among its workgroups.  Host code but for TileSplit, which the
-// kernels get as an argument.
+// How a scoring launch shares a KV head's key tiles out among its workgroups, and which loads it takes them with.  Host code
+// but for TileSplit, which the kernels get as an argument.
 #pragma once
 #include <stdint.h>
 
@@ -68,6 +68,20 @@ inline TileSplit split_tiles(int Hk, int n_chunks, int n_tiles, int n_cu, bool t
   s.more = left / s.first;
   s.longer = left % s.first;
   return s;
+}
+
+// Whether the keys, so many bytes of them, are loaded with the non-temporal bit, past the last-level cache (256 MB).  `reads`: how
+// often the call goes through them, once a pass and row group.  shared: several heads read the same keys (a head stride of 0).
+// Lines where it gains in a layer step, whose other tensors leave little of the keys in the cache, and loses next to nothing in
+// calls of asl_score_layer alone on a few sets of keys in turn, which find them there; us, without and with, of the 8B shape:
+//  read once: 64 MB, step 42.3, 42.4, alone 21.5, 22.2; 80 MB 46.6, 45.3 and 24.1, 25.3; 96 MB 51.5, 48.0 and 27.7, 28.3; 200 MB
+//    76.7, 68.2 and 50.4, 45.7; four heads of d = 256, step, 80 MB 45.4, 44.1; 96 MB 50.3, 46.9;
+//  read by both passes: 96 MB, step 71.3, 70.7, alone 46.2, 51.3; 112 MB 79.2, 75.6 and 52.9, 56.6; 128 MB 85.3, 81.0 and 60.4, 60.7;
+//    200 MB 114, 107 and 87.7, 85.2; d = 256, step, 128 MB 86.1, 80.5;
+//  two row groups, `lse` supplied, four heads of d = 256 alone: 96 MB 56.0, 56.5; 200 MB 98.1, 97.6; 400 MB 191, 179.
+// Shared keys are in the cache for the other heads: 8 of 4 query heads on one set, `lse` supplied, 32K 20.8, 22.5; 128K 54.3, 57.2.
+inline bool stream_keys(int64_t bytes, int reads, bool shared) {
+  return !shared && bytes >= int64_t(reads == 1 ? 80 : 112) << 20;
 }
 
 }  // namespace asl

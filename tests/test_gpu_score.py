@@ -103,6 +103,24 @@ def test_row_lengths(gpu_device, dtype, d):
         _compare(gpu_device, L, use_lse=True)
 
 
+def test_heads_that_share_their_keys(gpu_device):
+    """A head stride of 0: 8 KV heads read one set of keys (84 MB if it were eight)."""
+    import torch
+    L = _small(8, 8, 128, 43000, 16, seed=43)
+    L.k[:] = L.k[:1]
+    sh = L.shape
+    lse = orc.row_lse(L.q_obs, L.k, sh.W)
+    p = asl.make_params(sh.Hq, sh.Hk, sh.d, sh.N, sh.W, sh.S, sh.budget, k_strides=(0, sh.d))
+    q, k = gu.to_dev(L.q_obs, "bf16", gpu_device), gu.to_dev(L.k[:1], "bf16", gpu_device)
+    for given in (None, torch.from_numpy(lse.astype(np.float32)).to(gpu_device)):
+        ctx = gu.ctx_for(sh)
+        P = torch.full((sh.Hk, sh.T), float("nan"), device=gpu_device)
+        s = torch.full((sh.T,), float("nan"), device=gpu_device)
+        ctx.asl_score_layer(p, q, k, P, s, lse=given)
+        _close_to_64_bits(P.cpu().numpy(), s.cpu().numpy(), L)
+        ctx.close()
+
+
 @pytest.mark.parametrize("Hq,Hk,d,W,dtype", [(16, 1, 128, 48, "bf16"), (33, 1, 64, 16, "bf16"), (9, 1, 256, 64, "bf16"),
                                              (10, 2, 128, 64, "f32")])
 def test_row_groups(gpu_device, Hq, Hk, d, W, dtype):
@@ -185,9 +203,13 @@ def test_chunk_counts_of_one_pass(gpu_device, Hq, Hk, d, W, N):
     _close_to_64_bits(P, s, L)
 
 
-# keys of 64 MB and, read by both passes, 96 MB are where the loads change their cache policy: a key or two to either side
-@pytest.mark.parametrize("N,use_lse", [(49151, False), (49154, False), (32767, True), (32770, True)])
-@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
+# keys of 80 MB and, read by both passes, 112 MB are where the loads change their cache policy: a key or two to either side; every
+# kind of kernel that has both, and sizes below
+@pytest.mark.parametrize("N,use_lse,dtype,d", [(N, l, dtype, d) for N, l in ((49151, False), (49154, False), (32767, True), (32770, True))
+                                               for dtype, d in (("bf16", 128), ("f32", 64))] +
+                         [(57343, False, "bf16", 128), (57346, False, "bf16", 128), (40959, True, "bf16", 128),
+                          (40962, True, "bf16", 128), (57346, False, "f32", 64), (28674, False, "bf16", 256),
+                          (54615, True, "bf16", 96), (81922, True, "bf16", 64)])
 def test_keys_loaded_past_the_last_level_cache(gpu_device, N, use_lse, dtype, d):
     L = _small(8, 8, d, N, 16, dtype=dtype, seed=N)
     lse = orc.row_lse(L.q_obs, L.k, 16) if use_lse else None

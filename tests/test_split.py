@@ -1,4 +1,5 @@
-"""Host arithmetic of a scoring launch, no GPU needed: how key tiles are shared out among workgroups."""
+"""Host arithmetic of a scoring launch, no GPU needed: how key tiles are shared out among workgroups, which keys are loaded past
+the last-level cache."""
 import random
 import subprocess
 
@@ -33,3 +34,14 @@ def test_key_tiles_of_a_launch(tmp_path_factory):
         else:
             assert longest == equal, (Hk, n_chunks, n_tiles, two)
     assert weighted > 100                              # the unequal shares are there
+
+
+def test_keys_that_are_read_again_stay_in_the_cache(tmp_path_factory):
+    """Past the last-level cache go keys of 80 MB that a call reads once and of 112 MB that it reads again, by the other pass or the
+    next group of rows; never those that several heads share."""
+    mb = 1 << 20
+    ask = [(80 * mb, 1, 0), (80 * mb - 1, 1, 0), (112 * mb - 1, 2, 0), (112 * mb, 2, 0), (100 * mb, 4, 0), (400 * mb, 3, 0),
+           (80 * mb, 1, 1), (4000 * mb, 1, 1), (4000 * mb, 2, 1)]
+    out = subprocess.run([_client(tmp_path_factory, "stream_client")], input="".join("%d %d %d\n" % q for q in ask),
+                         check=True, capture_output=True, text=True).stdout
+    assert [int(x) for x in out.split()] == [1, 0, 0, 1, 0, 1, 0, 0, 0]
