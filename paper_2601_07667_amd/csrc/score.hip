@@ -82,7 +82,7 @@ struct TilePieces {
   }
 };
 
-// kg, rsb: first key of the KV head and the key stride in bytes.  AUX: cache policy of the loads (kAuxStream: see
+// kg, rsb: first key of the KV head and the key stride in bytes.  AUX: cache policy of the loads (STREAM, kAuxStream: see
 // stream_keys).
 constexpr int kAuxPlain = 0, kAuxStream = 2;          // the non-temporal bit
 template <int P, int NT, bool FULL, int AUX>
@@ -117,16 +117,13 @@ __device__ __forceinline__ void issue_tile_loads_impl(const TilePieces<P, NT>& t
 }
 
 // Full tiles take the precomputed offsets; only a tile that reaches past N pays for clamping.
-template <int P, int NT>
+template <int P, int NT, bool STREAM>
 __device__ __forceinline__ void issue_tile_loads(const TilePieces<P, NT>& tp, const char* __restrict__ kg, int64_t rsb,
-                                                 int key0, int N, int last_piece, Piece* __restrict__ lds_buf, int tid,
-                                                 bool stream) {
-  if (key0 + key_tile<P>() > N)
-    issue_tile_loads_impl<P, NT, false, kAuxPlain>(tp, kg, rsb, key0, N, last_piece, lds_buf, tid);
-  else if (stream)                                      // uniform
-    issue_tile_loads_impl<P, NT, true, kAuxStream>(tp, kg, rsb, key0, N, last_piece, lds_buf, tid);
+                                                 int key0, int N, int last_piece, Piece* __restrict__ lds_buf, int tid) {
+  if (key0 + key_tile<P>() <= N)
+    issue_tile_loads_impl<P, NT, true, STREAM ? kAuxStream : kAuxPlain>(tp, kg, rsb, key0, N, last_piece, lds_buf, tid);
   else
-    issue_tile_loads_impl<P, NT, true, kAuxPlain>(tp, kg, rsb, key0, N, last_piece, lds_buf, tid);
+    issue_tile_loads_impl<P, NT, false, kAuxPlain>(tp, kg, rsb, key0, N, last_piece, lds_buf, tid);
 }
 
 // Wait until at most CNT of this wave's vector-memory operations (incl. its LDS-direct loads) are
@@ -311,14 +308,14 @@ __device__ __forceinline__ void rowstats_fold(const f32x16 (&acc)[RB], int key_l
 // in one block of straight-line code with the softmax arithmetic of the sub-tile before it (`acc`, the
 // last sub-tile of the tile before on entry), so that a wavefront's own vector instructions fill the
 // time its MFMAs take.  MASK: tiles that touch the window block or the tail past N (they come last).
-template <typename TE, int P, int NT, int RB, bool PAD, bool MASK, bool LAZY>
+template <typename TE, int P, int NT, int RB, bool PAD, bool STREAM, bool MASK, bool LAZY>
 __device__ __forceinline__ void rowstats_tile(const Piece* __restrict__ cur, Piece* __restrict__ nxt,
-                                              bool prefetch, bool stream, const TilePieces<P, NT>& tp, const char* __restrict__ kg, int64_t rsb,
+                                              bool prefetch, const TilePieces<P, NT>& tp, const char* __restrict__ kg, int64_t rsb,
                                               int prefetch_key0, int np, int last_piece, int tile, int prev, int N, int T, const int (&wi)[RB],
                                               int tid, int ln, int half, const Piece (&qf)[RB][P / 2], float c1,
                                               f32x16 (&acc)[RB], float (&m_run)[RB], float (&z_run)[RB], int& raised) {
   constexpr int KT = key_tile<P>();
-  if (prefetch) issue_tile_loads<P, NT>(tp, kg, rsb, prefetch_key0, N, last_piece, nxt, tid, stream);
+  if (prefetch) issue_tile_loads<P, NT, STREAM>(tp, kg, rsb, prefetch_key0, N, last_piece, nxt, tid);
 #pragma unroll
   for (int sub = 0; sub < KT / 32; ++sub) {
     f32x16 nxt_acc[RB];
@@ -334,10 +331,10 @@ __device__ __forceinline__ void rowstats_tile(const Piece* __restrict__ cur, Pie
 // Pass 1: per-row running (max, sum) over this workgroup's key chunk, in the log2 domain, for query
 // rows [m0, m1) of every KV head (m1 - m0 <= NW * 32 * RB).  ksh, kst: head and key strides in bytes.
 // row_part[((g*n_chunks + chunk)*M + row)*2 + {0,1}] = (m, z) with  sum_j 2^(c1*l_j) = z * 2^m.
-template <typename TE, int P, int NW, int RB, bool PAD>
+template <typename TE, int P, int NW, int RB, bool PAD, bool STREAM>
 __global__ void __launch_bounds__(NW * 64)
 score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, int64_t ksh,
-                      int64_t kst, int np, int Hk, int M, int m0, int m1, int W, int N, TileSplit split, bool stream,
+                      int64_t kst, int np, int Hk, int M, int m0, int m1, int W, int N, TileSplit split,
                       float c1, float* __restrict__ row_part) {
   constexpr int NT = loader_threads<P, NW>();      // threads that load the K tiles
   constexpr int KS = P / 2, KT = key_tile<P>();
@@ -363,7 +360,7 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
   // prologue: STAGES-1 tiles in flight (after the Q loads, so the in-order wait counts line up)
 #pragma unroll
   for (int j = 0; j < STAGES - 1; ++j) {
-    if (j < n_my) issue_tile_loads<P, NT>(tp, kg, kst, ahead * KT, N, last_piece, lds_k + j * TILE_ELEMS, tid, stream);
+    if (j < n_my) issue_tile_loads<P, NT, STREAM>(tp, kg, kst, ahead * KT, N, last_piece, lds_k + j * TILE_ELEMS, tid);
     ahead += split.step(j);
   }
 
@@ -387,8 +384,8 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
     wait_tile<P, NT, STAGES>(min(STAGES - 2, n_my - 1 - it));
     __syncthreads();      // tile `tile` has landed for every wave; the buffer of the tile before is free again
     const int free_stage = (stage == 0) ? STAGES - 1 : stage - 1;
-    rowstats_tile<TE, P, NT, RB, PAD, decltype(mask)::value, decltype(lazy)::value>(
-        lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS, it + STAGES - 1 < n_my, stream, tp, kg, kst,
+    rowstats_tile<TE, P, NT, RB, PAD, STREAM, decltype(mask)::value, decltype(lazy)::value>(
+        lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS, it + STAGES - 1 < n_my, tp, kg, kst,
         ahead * KT, np, last_piece, tile, prev, N, T, wi, tid, ln, half, qf, c1, acc, m_run, z_run, raised);
     stage = (stage + 1 == STAGES) ? 0 : stage + 1;
     ahead += split.step(it + STAGES - 1);
@@ -562,14 +559,14 @@ __device__ __forceinline__ float colsum_subtile(const f32x16 (&acc)[RB], const f
 // beside the column partial sums of the sub-tile before each (`acc`; the last sub-tile of the tile
 // before on entry): the same pipeline as pass 1's.  red_prev, red_cur: this wave's partial sums of the
 // KT keys of the tile before and of this one.  ONLY: a workgroup's only tile; nothing is before it.
-template <typename TE, int P, int NT, int RB, bool PAD, bool DENORM, bool ONLY>
+template <typename TE, int P, int NT, int RB, bool PAD, bool DENORM, bool STREAM, bool ONLY>
 __device__ __forceinline__ void colsum_tile(const Piece* __restrict__ cur, Piece* __restrict__ nxt,
-                                            bool prefetch, bool stream, const TilePieces<P, NT>& tp, const char* __restrict__ kg, int64_t rsb,
+                                            bool prefetch, const TilePieces<P, NT>& tp, const char* __restrict__ kg, int64_t rsb,
                                             int prefetch_key0, int np, int last_piece, int N, int tid, int ln, int half,
                                             const Piece (&qf)[RB][P / 2], const float (&rc)[RB][16], float c1,
                                             f32x16 (&acc)[RB], float* __restrict__ red_prev, float* __restrict__ red_cur) {
   constexpr int KT = key_tile<P>();
-  if (prefetch) issue_tile_loads<P, NT>(tp, kg, rsb, prefetch_key0, N, last_piece, nxt, tid, stream);
+  if (prefetch) issue_tile_loads<P, NT, STREAM>(tp, kg, rsb, prefetch_key0, N, last_piece, nxt, tid);
 #pragma unroll
   for (int sub = 0; sub < KT / 32; ++sub) {
     f32x16 nxt_acc[RB];
@@ -588,10 +585,10 @@ __device__ __forceinline__ void colsum_tile(const Piece* __restrict__ cur, Piece
 // Pass 2: u_group[g][j] = sum over query rows [m0, m1) of 2^(c1*l_rj - rc_r),  j < T,
 // rc_r = rc_mul * row_const[g*M + r]  (log2-domain offset that already contains log2 Z_r).
 // From the second row group on (m0 > 0) the sum is added to what the launch before left there.
-template <typename TE, int P, int NW, int RB, bool PAD, bool DENORM>
+template <typename TE, int P, int NW, int RB, bool PAD, bool DENORM, bool STREAM>
 __global__ void __launch_bounds__(NW * 64)
 score_colsum_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, int64_t ksh,
-                    int64_t kst, int np, int Hk, int M, int m0, int m1, int N, int T, TileSplit split, bool stream, float c1,
+                    int64_t kst, int np, int Hk, int M, int m0, int m1, int N, int T, TileSplit split, float c1,
                     const float* __restrict__ row_const, float rc_mul, const float* __restrict__ row_part,
                     int n_parts, float* __restrict__ u_group) {
   constexpr int NT = loader_threads<P, NW>();      // threads that load the K tiles
@@ -619,7 +616,7 @@ score_colsum_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, 
   // hides behind the first tiles' (later loads complete later: the counted waits below stay valid)
 #pragma unroll
   for (int j = 0; j < STAGES - 1; ++j) {
-    if (j < n_my) issue_tile_loads<P, NT>(tp, kg, kst, ahead * KT, N, last_piece, lds_k + j * TILE_ELEMS, tid, stream);
+    if (j < n_my) issue_tile_loads<P, NT, STREAM>(tp, kg, kst, ahead * KT, N, last_piece, lds_k + j * TILE_ELEMS, tid);
     ahead -= split.step(n_my - 2 - j);
   }
 
@@ -683,8 +680,8 @@ score_colsum_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, 
     __syncthreads();      // the tile has landed; tile it-1's fragment reads and tile it-2's partials are done
     if (it > 1) reduce_store(3 - cur_red - prev_red, prev2 * KT);
     const int free_stage = (stage == 0) ? STAGES - 1 : stage - 1;
-    colsum_tile<TE, P, NT, RB, PAD, DENORM, decltype(only)::value>(
-        lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS, it + STAGES - 1 < n_my, stream, tp, kg, kst,
+    colsum_tile<TE, P, NT, RB, PAD, DENORM, STREAM, decltype(only)::value>(
+        lds_k + stage * TILE_ELEMS, lds_k + free_stage * TILE_ELEMS, it + STAGES - 1 < n_my, tp, kg, kst,
         ahead * KT, np, last_piece, N, tid, ln, half, qf, rc, c1, acc, &red[prev_red][wave][0], &red[cur_red][wave][0]);
     stage = (stage + 1 == STAGES) ? 0 : stage + 1;
     prev_red = cur_red;
@@ -883,24 +880,32 @@ static hipError_t launch_score_mfma(const asl_params& p, const Workspace& ws, co
   const int np = p.head_dim * (int)sizeof(TE) / 16;
   // both passes use the same LDS ring and nearly the same registers; take the smaller residency
   static const int resident = [] {
-    const int a = resident_per_cu(score_rowstats_kernel<TE, P, NW, RB, PAD>, NW * 64);
-    const int b = resident_per_cu(score_colsum_kernel<TE, P, NW, RB, PAD, DENORM>, NW * 64);
+    const int a = resident_per_cu(score_rowstats_kernel<TE, P, NW, RB, PAD, false>, NW * 64);
+    const int b = resident_per_cu(score_colsum_kernel<TE, P, NW, RB, PAD, DENORM, false>, NW * 64);
     return a < b ? a : b;
   }();
   const int n_cu = device_cu_count();
   const int n_chunks = score_chunks<TE, P, NW, RB>(Hk, (N + KT - 1) / KT, n_cu, resident, lse == nullptr);
   const bool combine = n_chunks > kFoldChunks;
-  // Keys that are read once (kOnce) or more often are loaded past the last-level cache (stream_keys) where that gains:
+  // Kernels that load past the last-level cache (stream_keys), for keys read once (kOnce) or more often, are built where they gain:
   // not in fp32, bound by its arithmetic (both passes, us, without and with: 8 heads of d = 64, 96 MB 60.6, 63.3; of d = 128 59.3, 61.9;
   // `lse` supplied at most 1 % either way), nor, read more than once, with two row blocks a wavefront (28 heads, 256K 186.5, 185.9, alone
-  // 158.4, 163.9; 1024 rows a head, `lse` supplied, 200 MB 294.6, 300.3) or padded rows (d = 80, 252 MB 158, 161).
+  // 158.4, 163.9; 1024 rows a head, `lse` supplied, 200 MB 294.6, 300.3) or padded rows (d = 80, 252 MB 158, 161).  A branch
+  // in front of every tile's loads instead costs calls that do not stream up to 3 % (28 heads, W = 5, 67K 36.8, 38.0).
   constexpr bool kOnce = sizeof(TE) == 2, kTwice = kOnce && RB == 1 && !PAD;
-  const int reads = (M + kRows - 1) / kRows * (lse ? 1 : 2);
-  const bool stream = (reads == 1 ? kOnce : kTwice) && stream_keys((int64_t)Hk * N * p.head_dim * (int64_t)sizeof(TE), reads, Hk > 1 && ksh == 0);
+  auto* rowstats = score_rowstats_kernel<TE, P, NW, RB, PAD, false>;
+  auto* colsum = score_colsum_kernel<TE, P, NW, RB, PAD, DENORM, false>;
+  if constexpr (kOnce) {
+    const int reads = (M + kRows - 1) / kRows * (lse ? 1 : 2);
+    if ((reads == 1 || kTwice) && stream_keys((int64_t)Hk * N * p.head_dim * (int64_t)sizeof(TE), reads, Hk > 1 && ksh == 0)) {
+      colsum = score_colsum_kernel<TE, P, NW, RB, PAD, DENORM, true>;
+      if constexpr (kTwice) rowstats = score_rowstats_kernel<TE, P, NW, RB, PAD, true>;
+    }
+  }
   if (!lse) {
     for (int m0 = 0; m0 < M; m0 += kRows)
-      ASL_LAUNCH(ws.prof, kKernRowstats, st, (score_rowstats_kernel<TE, P, NW, RB, PAD>), dim3(Hk * n_chunks), dim3(NW * 64), 0,
-                 st, q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, p.window, N, split_tiles(Hk, n_chunks, (N + KT - 1) / KT, n_cu, RB > 1), stream, c1,
+      ASL_LAUNCH(ws.prof, kKernRowstats, st, rowstats, dim3(Hk * n_chunks), dim3(NW * 64), 0,
+                 st, q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, p.window, N, split_tiles(Hk, n_chunks, (N + KT - 1) / KT, n_cu, RB > 1), c1,
                  ws.row_part);
     if (lse_out || combine) {
       ASL_LAUNCH(ws.prof, kKernCombine, st, score_combine_kernel, dim3((Hk * M + kCombineRows - 1) / kCombineRows), dim3(256), 0, st,
@@ -913,8 +918,8 @@ static hipError_t launch_score_mfma(const asl_params& p, const Workspace& ws, co
   // without the caller's log-sum-exp or a launch that combined them every pass-2 workgroup folds pass 1's partials of
   // its own rows
   for (int m0 = 0; m0 < M; m0 += kRows)
-    ASL_LAUNCH(ws.prof, kKernColsum, st, (score_colsum_kernel<TE, P, NW, RB, PAD, DENORM>), dim3(Hk * n_chunks2), dim3(NW * 64), 0, st,
-               q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, N, T, split_tiles(Hk, n_chunks2, n_tiles2, n_cu, RB > 1), stream, c1, lse ? lse : ws.row_const,
+    ASL_LAUNCH(ws.prof, kKernColsum, st, colsum, dim3(Hk * n_chunks2), dim3(NW * 64), 0, st,
+               q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, N, T, split_tiles(Hk, n_chunks2, n_tiles2, n_cu, RB > 1), c1, lse ? lse : ws.row_const,
                lse ? kLog2e : 1.0f, lse || combine ? nullptr : ws.row_part, n_chunks, ws.u_group);
   return hipGetLastError();
 }
