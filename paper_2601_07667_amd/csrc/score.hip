@@ -252,11 +252,12 @@ __device__ __forceinline__ float max2(float a, float b) { return __builtin_fmaxf
 // the rescaling, a fifth of the vector work, are left out (256K, W = 64, pass 1 147.7 -> 138.5 us; 128K 132.9 -> 130.8, 64K 84.2
 // -> 81.1 the layer step).  One branch for all row blocks, behind all of their arithmetic: with one per block half of it stood in
 // a basic block without MFMAs (144.6).  Not for the shapes whose calls are start-up mostly: their one or two sub-tiles take the
-// branch every time (d = 256, 8K, 17.2 -> 17.7).  And a wavefront whose references move in more than an eighth of the sub-tiles goes on
+// branch every time (d = 256, 8K, 17.2 -> 17.7); nor for up to 64 query rows, where the key stream bounds the pass and another loop
+// is only more code (28 heads, W = 5, the scoring, 64K 36.9, without 36.1; 128K 60.5, 59.2).  And a wavefront whose references move in more than an eighth of the sub-tiles goes on
 // with the running maximum: logits of hundreds that grow (lognormal key lengths, 256K, W = 64) took
 // 166 us without that, 149 with it, 147 with the running maximum throughout.
 constexpr float kRescale = 256.f;
-template <typename TE, int P, bool PAD> constexpr bool kLazy = sizeof(TE) == 2 && P <= 16 && !PAD;
+template <typename TE, int P, int NW, bool PAD> constexpr bool kLazy = sizeof(TE) == 2 && P <= 16 && !PAD && NW > 2;
 template <int RB, bool MASK, bool LAZY>
 __device__ __forceinline__ void rowstats_fold(const f32x16 (&acc)[RB], int key_lo, int N, int T,
                                               const int (&wi)[RB], float c1, float (&m_run)[RB], float (&z_run)[RB], int& raised) {
@@ -395,7 +396,7 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
   };
   // tiles of visible keys only, then those that touch the window block or the end
   const int plain = T / KT;
-  if constexpr (kLazy<TE, P, PAD>) {
+  if constexpr (kLazy<TE, P, NW, PAD>) {
     while (it < n_my && tile < plain && raised <= 3 + it / 4) step(std::false_type(), std::true_type());
   }
   while (it < n_my && tile < plain) step(std::false_type(), std::false_type());
