@@ -335,7 +335,7 @@ __device__ __forceinline__ void rowstats_tile(const Piece* __restrict__ cur, Pie
 template <typename TE, int P, int NW, int RB, bool PAD, bool STREAM>
 __global__ void __launch_bounds__(NW * 64)
 score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, int64_t ksh,
-                      int64_t kst, int np, int Hk, int M, int m0, int m1, int W, int N, TileSplit split,
+                      int64_t kst, int np, int Hk, int M, int m0, int m1, int W, int N, TileSplit<kInTurn<NW>> split,
                       float c1, float* __restrict__ row_part) {
   constexpr int NT = loader_threads<P, NW>();      // threads that load the K tiles
   constexpr int KS = P / 2, KT = key_tile<P>();
@@ -353,7 +353,7 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
   for (int rb = 0; rb < RB; ++rb) wi[rb] = (row0 + rb * 32 + ln) % W;
   const char* kg = k + (int64_t)g * ksh;
   const int n_my = split.count(chunk);
-  int ahead = chunk;                            // next tile to load
+  int ahead = split.tile(chunk, 0);             // next tile to load
 
   ASL_LOAD_Q_FRAGS();
   TilePieces<P, NT> tp;
@@ -379,7 +379,7 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[rb][r] = -INFINITY;
   int stage = 0;                                  // buffer that holds tile `tile`
-  int it = 0, tile = chunk, prev = chunk;
+  int it = 0, tile = split.tile(chunk, 0), prev = tile;
   int raised = 0;                                 // sub-tiles that moved the references (uniform in the wavefront)
   auto step = [&](auto mask, auto lazy) {
     wait_tile<P, NT, STAGES>(min(STAGES - 2, n_my - 1 - it));
@@ -589,7 +589,7 @@ __device__ __forceinline__ void colsum_tile(const Piece* __restrict__ cur, Piece
 template <typename TE, int P, int NW, int RB, bool PAD, bool DENORM, bool STREAM>
 __global__ void __launch_bounds__(NW * 64)
 score_colsum_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, int64_t ksh,
-                    int64_t kst, int np, int Hk, int M, int m0, int m1, int N, int T, TileSplit split, float c1,
+                    int64_t kst, int np, int Hk, int M, int m0, int m1, int N, int T, TileSplit<kInTurn<NW>> split, float c1,
                     const float* __restrict__ row_const, float rc_mul, const float* __restrict__ row_part,
                     int n_parts, float* __restrict__ u_group) {
   constexpr int NT = loader_threads<P, NW>();      // threads that load the K tiles
@@ -906,7 +906,7 @@ static hipError_t launch_score_mfma(const asl_params& p, const Workspace& ws, co
   if (!lse) {
     for (int m0 = 0; m0 < M; m0 += kRows)
       ASL_LAUNCH(ws.prof, kKernRowstats, st, rowstats, dim3(Hk * n_chunks), dim3(NW * 64), 0,
-                 st, q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, p.window, N, split_tiles(Hk, n_chunks, (N + KT - 1) / KT, n_cu, RB > 1), c1,
+                 st, q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, p.window, N, split_tiles<kInTurn<NW>>(Hk, n_chunks, (N + KT - 1) / KT, n_cu, RB > 1), c1,
                  ws.row_part);
     if (lse_out || combine) {
       ASL_LAUNCH(ws.prof, kKernCombine, st, score_combine_kernel, dim3((Hk * M + kCombineRows - 1) / kCombineRows), dim3(256), 0, st,
@@ -920,7 +920,7 @@ static hipError_t launch_score_mfma(const asl_params& p, const Workspace& ws, co
   // its own rows
   for (int m0 = 0; m0 < M; m0 += kRows)
     ASL_LAUNCH(ws.prof, kKernColsum, st, colsum, dim3(Hk * n_chunks2), dim3(NW * 64), 0, st,
-               q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, N, T, split_tiles(Hk, n_chunks2, n_tiles2, n_cu, RB > 1), c1, lse ? lse : ws.row_const,
+               q, k, ksh, kst, np, Hk, M, m0, M < m0 + kRows ? M : m0 + kRows, N, T, split_tiles<kInTurn<NW>>(Hk, n_chunks2, n_tiles2, n_cu, RB > 1), c1, lse ? lse : ws.row_const,
                lse ? kLog2e : 1.0f, lse || combine ? nullptr : ws.row_part, n_chunks, ws.u_group);
   return hipGetLastError();
 }

@@ -13,10 +13,12 @@
 
 namespace asl {
 
-// The key tiles of a workgroup.  The n_chunks workgroups of a KV head take the tiles in turn: the k-th of them tiles k,
+// The key tiles of a workgroup.  IN_TURN: the n_chunks workgroups of a KV head take the tiles in turn: the k-th of them tiles k,
 // k + n_chunks, ..., so that a head's workgroups, which advance together, read one stretch of memory at a time.  (Each with a
 // contiguous share they read at as many places, a power of two apart: a bare ring of this shape streams 268 MB in 44.9 us so,
-// in turn in 41.6; 8B shape, 128K, `lse` supplied, pass 2 61.2 and 58.8 us; 32K, both passes, 33.4 and 31.5.)
+// in turn in 41.6; 8B shape, 128K, `lse` supplied, pass 2 61.2 and 58.8 us; 32K, both passes, 33.4 and 31.5.)  Not IN_TURN:
+// contiguous shares; for workgroups of one wavefront (kInTurn), which wait for every tile: theirs are then neighbours in memory
+// (8B shape, W = 8, both passes, in turn and so: 16K 19.8, 18.9; 32K 31.6, 30.0; 64K 54.7, 52.8; two heads of d = 64, 8K 13.5, 13.0).
 // All workgroups of a pass are resident at once (one round), block b being the (b / n_cu)-th placed on its compute unit.  A
 // unit's older wavefronts go first, so with two workgroups per unit the second ends up alone on it for the last part of the
 // kernel: after `all` rounds of everybody only the first placed take turns (1250 : 798 of a unit's tiles, with two row blocks a
@@ -24,6 +26,7 @@ namespace asl {
 // 152 + 158 us, 1250 : 798 147 + 153, 1350 : 698 145 + 150).  Up to four tiles per chunk that come out even to 1/16 stay
 // equal: weighted, rounding makes some chunks a tile longer (8 KV heads, whole call, weighted and equal: one tile, W = 64
 // 27.3 and 25.1 us; two tiles, W = 32 20.4 and 19.9; but 2.45, W = 64 31.1 and 31.7, 5.9 28.5 and 28.9).
+template <bool IN_TURN>
 struct TileSplit {
   int n_chunks;
   int all;                       // rounds that every chunk takes part in
@@ -31,22 +34,25 @@ struct TileSplit {
   int more, longer;              // their further tiles: `more` each, and one for the first `longer` of them
   ASL_HOST_DEVICE int count(int chunk) const { return all + (chunk < first ? more + (chunk < longer ? 1 : 0) : 0); }
   ASL_HOST_DEVICE int tile(int chunk, int i) const {                  // i-th tile of a chunk, i < count(chunk)
+    if (!IN_TURN) return chunk * all + (chunk < first ? chunk : first) * more + (chunk < longer ? chunk : longer) + i;
     return chunk + (i < all ? i * n_chunks : all * n_chunks + (i - all) * first);
   }
   // from the i-th to the next; backwards from the i-th to the one before: step(i - 1)
-  ASL_HOST_DEVICE int step(int i) const { return i < all ? n_chunks : first; }
+  ASL_HOST_DEVICE int step(int i) const { return !IN_TURN ? 1 : i < all ? n_chunks : first; }
 };
+template <int NW> constexpr bool kInTurn = NW > 1;     // NW wavefronts a workgroup
 
 // Tiles of a unit's first-placed workgroup of every 2048 of the unit's.
 inline int first_placed_weight(bool two_blocks) { return two_blocks ? 1350 : 1250; }
 
 // two_blocks: two row blocks a wavefront.  n_chunks <= n_tiles.
-inline TileSplit split_tiles(int Hk, int n_chunks, int n_tiles, int n_cu, bool two_blocks) {
+template <bool IN_TURN>
+TileSplit<IN_TURN> split_tiles(int Hk, int n_chunks, int n_tiles, int n_cu, bool two_blocks) {
   const int first_w = first_placed_weight(two_blocks), second_w = 2048 - first_w;
   const int grid = n_chunks * Hk;
   const int slots = n_chunks * (1 + (n_tiles > n_chunks) + (n_tiles > 2 * n_chunks) + (n_tiles > 3 * n_chunks));
   const bool even = n_tiles <= slots && 16 * (slots - n_tiles) <= slots;
-  TileSplit s = {n_chunks, 0, n_chunks, 0, 0};
+  TileSplit<IN_TURN> s = {n_chunks, 0, n_chunks, 0, 0};
   if (grid > n_cu && grid <= 2 * n_cu && !even) {
     const int first = n_cu / Hk < 1 ? 1 : n_cu / Hk;   // block c * Hk + g is the first of its unit iff it is below n_cu
     const int64_t weight = (int64_t)first_w * first + (int64_t)second_w * (n_chunks - first);
