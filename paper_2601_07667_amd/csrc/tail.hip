@@ -1,4 +1,4 @@
-// The part of a layer step that follows the scoring, in three launches on one stream (one for short contexts).
+// The part of a layer step that follows the scoring, in three launches on one stream (one or two for short contexts).
 //
 // After the scores are pooled two independent chains remain: the ranking (partition, buckets: Alg. 1 step 11) with the
 // statistic (Alg. 2 steps 4-10), and the top-k + KV compaction (bound, filter, finish, gather: Alg. 1
@@ -11,12 +11,12 @@
 #include "gather_body.h"
 #include "rank_stat_body.h"
 #include "select_body.h"
+#include "short_plan.h"
 
 namespace asl {
 
 static_assert(kSortThreads == kFinThreads, "both jobs of a launch use the same workgroup size");
 constexpr int kTailThreads = kSortThreads;
-constexpr int kTailUnits = 256;                       // compute units of an MI355X
 
 union PartFilterShared {
   PartShared part;
@@ -24,7 +24,7 @@ union PartFilterShared {
 };
 
 // Short contexts (T <= kShortT) take one launch for all of it: the top-k of every row, the ranking with the statistic, and the compaction
-// (up to kPickMost tokens of kPickMaxRows heads; else that follows in a launch of its own).  The selecting workgroups, the longer
+// (up to kPickMost tokens of kPickMaxRows heads, where short_whole says so; else tail_short_kernel).  The selecting workgroups, the longer
 // ones, come first; workgroup r < Hk leaves row r's tokens in words that carry the launch's tag, and the compacting
 // workgroups of head r wait for theirs.  Those come last, 8 * i + x for heads r with r % 8 == x: on the die of the workgroup they
 // wait for, behind it in the order in which a die starts them, so that waiting workgroups cannot keep the waited-for ones from
@@ -34,7 +34,6 @@ union PartFilterShared {
 // allow: 8 for two workgroups a unit where ranking and top-k have more than one for each (8K 37.3, 34.4); else 4, whose code is 0.6
 // to 1 us faster.  Dynamic LDS: kTailShortLds.
 constexpr size_t kTailShortLds = sizeof(ShortSelectShared<kShortPer>) > sizeof(RankStatShared) ? sizeof(ShortSelectShared<kShortPer>) : sizeof(RankStatShared);
-constexpr int kDies = 8;
 __host__ __device__ constexpr int short_gather_from(int rows, int n_rank) { return (rows + n_rank + kDies - 1) / kDies * kDies; }
 template <bool POW2, int WAVES>
 __global__ void __launch_bounds__(kTailThreads, WAVES) tail_whole_kernel(const float* s_all, int32_t* rank_row, SelectArgs se, int rows, int n_rank,
@@ -53,6 +52,17 @@ __global__ void __launch_bounds__(kTailThreads, WAVES) tail_whole_kernel(const f
     if (!gather_picked_body<POW2, kTailThreads>(ga, slab % gx, h, slab / gx, se.T, se.k, se.picks + (int64_t)h * se.k, *se.pick_tag))
       *ra.fault = 1u;
   }
+}
+
+// The top-k and the ranking alone, where statistic and compaction follow in a launch of their own, side by side (28 heads, 6592 tokens, of
+// which 6366 are kept: 36.1 us the layer step, with the statistic in this launch 36.9).  Dynamic LDS: kTailShortLds.
+__global__ void __launch_bounds__(kTailThreads) tail_short_kernel(const float* s_all, int32_t* rank_row, SelectArgs se, int rows) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_dyn[];
+  const int b = (int)blockIdx.x;
+  if (b < rows)
+    select_short_body<kShortPer>(*reinterpret_cast<ShortSelectShared<kShortPer>*>(lds_dyn), se, b);
+  else
+    rank_short_body(*reinterpret_cast<ShortRankShared*>(lds_dyn), s_all, se.T, PutRank{rank_row}, b - rows);
 }
 
 // launch 0: the ranking's partition | top-k bound and filter (TILES tiles of a score row per workgroup).  64 registers, for two
@@ -177,25 +187,32 @@ hipError_t launch_tail(const Workspace& ws, const float* scores, int rows, int T
     GatherArgs ga = {};
     SelectArgs sp = se;
     int gx = 0, grid = rows + n_rank;
-    bool pow2 = true;
-    if (gather != nullptr && Hk <= ws.pick_rows && k <= kPickMost) {
+    bool pow2 = true, whole = true;
+    if (gather != nullptr) {
       ga = *gather;
       pow2 = gather_prepare(ga);
       gx = (int)(((int64_t)ga.n_idx * ga.cpr + kTailThreads * kPickedUnroll - 1) / (kTailThreads * kPickedUnroll));
+      whole = Hk <= ws.pick_rows && k <= kPickMost && short_whole(Hk, gx * ga.n_tensors);
       grid = short_gather_from(rows, n_rank) + kDies * ((Hk + kDies - 1) / kDies) * gx * ga.n_tensors;
       sp.picks = ws.sel_picks;
       sp.pick_tag = ws.pick_tag;
       sp.pick_rows = Hk;
     }
-    const bool two = rows + n_rank > kTailUnits;        // two workgroups a unit
-    auto* const kernel = two ? (pow2 ? tail_whole_kernel<true, 8> : tail_whole_kernel<false, 8>)
-                             : (pow2 ? tail_whole_kernel<true, 4> : tail_whole_kernel<false, 4>);
-    static OncePerDevice once[4];
-    const hipError_t attr = allow_lds(once[2 * two + pow2], reinterpret_cast<const void*>(kernel), kTailShortLds);
+    if (whole) {
+      const bool two = rows + n_rank > kTailUnits;      // two workgroups a unit
+      auto* const kernel = two ? (pow2 ? tail_whole_kernel<true, 8> : tail_whole_kernel<false, 8>)
+                               : (pow2 ? tail_whole_kernel<true, 4> : tail_whole_kernel<false, 4>);
+      static OncePerDevice once[4];
+      const hipError_t attr = allow_lds(once[2 * two + pow2], reinterpret_cast<const void*>(kernel), kTailShortLds);
+      if (attr != hipSuccess) return attr;
+      ASL_LAUNCH(ws.prof, kKernTail, st, kernel, dim3(grid), dim3(kTailThreads), kTailShortLds, st, s_all, rank_row, sp, rows, n_rank, stat, ga, gx, Hk);
+      return hipGetLastError();
+    }
+    static OncePerDevice once;
+    const hipError_t attr = allow_lds(once, reinterpret_cast<const void*>(tail_short_kernel), kTailShortLds);
     if (attr != hipSuccess) return attr;
-    ASL_LAUNCH(ws.prof, kKernTail, st, kernel, dim3(grid), dim3(kTailThreads), kTailShortLds, st, s_all, rank_row, sp, rows, n_rank, stat, ga, gx, Hk);
+    ASL_LAUNCH(ws.prof, kKernTail, st, tail_short_kernel, dim3(rows + n_rank), dim3(kTailThreads), kTailShortLds, st, s_all, rank_row, se, rows);
     e = hipGetLastError();
-    return e != hipSuccess || gather == nullptr || gx != 0 ? e : launch_gather(ws.prof, *gather, Hk, 1, st);
   } else {
     const uint32_t* sample = have_sample ? ws.sel_sample + (int64_t)(rows - 1) * kSelMaxSample : nullptr;
     const RankArgs ra = rank_args(ws, s_all, T, sample, rank_row);

@@ -426,10 +426,13 @@ def _exact_statistic(held, rank, k):
 
 
 # ranked by counting and by bins, one and two workgroups a compute unit; heads beyond the eight dies and beyond 64, rows that are no
-# power of two of pieces, as many tokens as one launch hands on and one more (then compacted by a launch of its own)
+# power of two of pieces, as many tokens as one launch hands on and one more (then compacted by a launch of its own, as is one head of
+# more workgroups than a die has units)
 @pytest.mark.parametrize("Hq,Hk,d,dtype,N,W,budget,n_held", [
     (9, 9, 64, "bf16", 8192 + 16, 16, 300, 3), (2, 1, 128, "bf16", 8193 + 16, 16, 2048, 10), (70, 70, 64, "bf16", 600, 8, 64, 1),
     (2, 2, 96, "f32", 3000, 8, 700, 7), (4, 2, 64, "bf16", 12000, 16, 4112, 2), (4, 2, 64, "bf16", 12000, 16, 4113, 2),
+    (8, 8, 64, "bf16", 12000, 16, 4112, 2), (8, 8, 64, "bf16", 12000, 16, 4113, 2), (2, 1, 128, "bf16", 8193 + 16, 16, 2049, 3),
+    (5, 5, 128, "bf16", 5000, 16, 2500, 3), (9, 9, 64, "bf16", 5000, 16, 2049, 3),
     (1, 1, 64, "bf16", 2, 1, 2, 1)])
 def test_short_layer_step_in_one_launch(gpu_device, Hq, Hk, d, dtype, N, W, budget, n_held):
     sh = synth.Shape(Hq=Hq, Hk=Hk, d=d, N=N, W=W, S=7, budget=budget, L_min=0, L_obs=n_held + 1, dtype=dtype)
@@ -444,6 +447,14 @@ def test_short_layer_step_in_one_launch(gpu_device, Hq, Hk, d, dtype, N, W, budg
     for g in range(Hk):
         np.testing.assert_array_equal(got["Kc"][g], L.k[g][got["I_head"][g]])
         np.testing.assert_array_equal(got["Vc"][g], L.v[g][got["I_head"][g]])
+
+
+@pytest.mark.parametrize("budget", [2048, 2049])
+def test_short_layer_step_below_l_min(gpu_device, budget):
+    """One head, compacted in the launch that selects and in its own, in a layer that has no statistic: the state only advances."""
+    sh = synth.Shape(Hq=2, Hk=1, d=128, N=5000, W=16, S=7, budget=budget, L_min=9)
+    got = _layer_step_case(gpu_device, synth.iid_layer(sh, 2250 + budget, name=f"below-l-min-{budget}"), layer_idx=3)
+    assert (got["stat"].evaluated, got["stat"].n_rows) == (0, 0)
 
 
 def test_short_layer_steps_on_two_streams(gpu_device):

@@ -1,5 +1,5 @@
-"""Host arithmetic of a scoring launch, no GPU needed: how key tiles are shared out among workgroups, which keys are loaded past
-the last-level cache."""
+"""Host arithmetic of launches, no GPU needed: how key tiles are shared out among workgroups, which keys are loaded past the
+last-level cache, where a short context is compacted."""
 import random
 import subprocess
 
@@ -45,3 +45,11 @@ def test_keys_that_are_read_again_stay_in_the_cache(tmp_path_factory):
     out = subprocess.run([_client(tmp_path_factory, "stream_client")], input="".join("%d %d %d\n" % q for q in ask),
                          check=True, capture_output=True, text=True).stdout
     assert [int(x) for x in out.split()] == [1, 0, 0, 1, 0, 1, 0, 0, 0]
+
+
+def test_compaction_of_few_heads_has_a_launch_of_its_own(tmp_path_factory):
+    """Beside the selection only what one die's units take at once, or heads that spread over the dies."""
+    ask = [(1, 32), (1, 33), (1, 36), (4, 32), (4, 34), (5, 1000), (8, 1000), (9, 16), (9, 17), (16, 1000), (17, 1000)]
+    out = subprocess.run([_client(tmp_path_factory, "short_client")], input="".join("%d %d\n" % q for q in ask),
+                         check=True, capture_output=True, text=True).stdout
+    assert [int(x) for x in out.split()] == [1, 0, 0, 1, 0, 1, 1, 1, 0, 1, 1]
