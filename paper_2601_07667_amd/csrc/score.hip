@@ -394,7 +394,11 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
     tile += split.step(it);
     ++it;
   };
-  // tiles of visible keys only, then those that touch the window block or the end
+  // Tiles of visible keys only, then those that touch the window block or the end.  `raised` is the wavefront's own, so the wavefronts of
+  // a workgroup may be in different loops here and meet at barriers that are different statements: every turn of either loop passes
+  // exactly one, in step(), and all wavefronts take n_my turns, and s_barrier counts the workgroup's arrivals wherever they come
+  // from.  No turn may get another barrier, or none.  (One loop with a branch around the two foldings in it: 256K, W = 64, 289 us the
+  // scoring, so 300; a vote of the wavefronts in LDS: 28 heads, W = 13, 128K 60.6, 61.4.)
   const int plain = T / KT;
   if constexpr (kLazy<TE, P, NW, PAD>) {
     while (it < n_my && tile < plain && raised <= 3 + it / 4) step(std::false_type(), std::true_type());

@@ -303,8 +303,8 @@ def test_heavy_tailed_keys(gpu_device):
 @pytest.mark.parametrize("Hq,Hk,d,W,dtype", [(8, 2, 128, 16, "bf16"), (6, 1, 128, 32, "bf16"), (4, 2, 64, 16, "f32"), (4, 2, 256, 8, "bf16")])
 @pytest.mark.parametrize("levels", [(0, 1, 2, 1), (0, 4, 8, 12, 16), (0, 100, 30), (60, 0), (0, 200, 0, 201, 90), (-90, -60, -90)])
 def test_logits_on_several_levels(gpu_device, Hq, Hk, d, W, dtype, levels):
-    """The reference of pass 1's sums of exponentials follows the logits only when they leave it behind.  The logits are up to 200
-    here, where their own rounding to fp32 (and of the product with log2 e) moves a probability by up to 200 * 2^-23 * 2: 5e-5."""
+    """A tile or two a workgroup of pass 1: first references far apart, and the combination of what the workgroups found (many tiles
+    a workgroup: the test below).  The logits are up to 200 here, where their own rounding to fp32 (and of the product with log2 e) moves a probability by up to 200 * 2^-23 * 2: 5e-5."""
     L = _small(Hq, Hk, d, 64 * 40 + 7, W, S=1, dtype=dtype, seed=d + len(levels))
     L.q_obs[:, :, 0] = 1.0
     for i, lo in enumerate(range(0, L.shape.N, 32)):
@@ -314,6 +314,37 @@ def test_logits_on_several_levels(gpu_device, Hq, Hk, d, W, dtype, levels):
     P, s = _run_score(gpu_device, L)
     np.testing.assert_allclose(P, P_ref, rtol=5e-5, atol=1e-30)
     np.testing.assert_allclose(s, s_ref, rtol=5e-5, atol=1e-30)
+
+
+# 64 KV heads leave each workgroup of pass 1 a dozen or fewer per head, 24 or more of the 289 tiles each, one after the other through the
+# range of keys: levels that stay within what a reference holds; that leave it behind now and then, once by more than fp32 holds without it;
+# that rise with every tile, where a wavefront soon keeps a running maximum; that fall.  Three and four wavefronts of 32 rows, three of 64;
+# the rows of each query head, which are a wavefront's or half of one's, meet another share of the levels, so that wavefronts of a
+# workgroup part.
+@pytest.mark.parametrize("G,d", [(3, 128), (4, 64), (5, 128)])
+@pytest.mark.parametrize("levels", [(0, 2, 1, 3, 0), (0, 12, 5, 24, 24, 40), (0, 150, 20, 190), tuple(range(0, 168, 6)),
+                                    tuple(range(168, 0, -6))], ids=["stay", "move", "overflow", "rise", "fall"])
+def test_reference_of_the_sums_over_many_tiles(gpu_device, G, d, levels):
+    """The bound is that of test_logits_on_several_levels: logits of up to 200, rounded to fp32."""
+    import torch
+    Hk, own, W, N = 64, 4, 32, 64 * 288 + 7                    # four KV heads' queries, each 16 times
+    rng = np.random.default_rng(G * d + len(levels))
+    q = rng.standard_normal((own * G, W, d))
+    k = rng.standard_normal((N, d))
+    q[:, :, 0] = np.tile(np.resize([1.0, 0.0, 0.5, -0.25, 1.0], G), own)[:, None]
+    k[:, 0] = np.asarray(levels)[np.arange(N) * len(levels) // N] * np.sqrt(d)
+    q, k = synth.round_bf16(q), synth.round_bf16(k)
+    sh = synth.Shape(Hq=Hk * G, Hk=Hk, d=d, N=N, W=W, S=1, budget=W + 8)
+    P_ref, _ = orc.score_layer(q, np.broadcast_to(k.astype(np.float64), (own, N, d)), W, 1)
+    q, P_ref = np.tile(q, (Hk // own, 1, 1)), np.tile(P_ref, (Hk // own, 1))
+    ctx = gu.ctx_for(sh)
+    p = asl.make_params(sh.Hq, Hk, d, N, W, 1, sh.budget, k_strides=(0, d))                     # one set of keys for all heads
+    P = torch.full((Hk, sh.T), float("nan"), device=gpu_device)
+    s = torch.full((sh.T,), float("nan"), device=gpu_device)
+    ctx.asl_score_layer(p, gu.to_dev(q, "bf16", gpu_device), gu.to_dev(k, "bf16", gpu_device), P, s)
+    np.testing.assert_allclose(P.cpu().numpy(), P_ref, rtol=5e-5, atol=1e-30)
+    np.testing.assert_allclose(s.cpu().numpy(), P_ref.sum(axis=0), rtol=5e-5, atol=1e-30)
+    ctx.close()
 
 
 def test_config2_full(gpu_device):
