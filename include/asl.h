@@ -221,7 +221,9 @@ asl_status asl_gather_rows(asl_ctx* ctx, const void* src, int64_t src_row_stride
  * the single calls.  After the scoring, ranking and top-k + compaction are independent; the call
  * runs them side by side in three launches on `stream`: two that each carry a stage of the ranking and one of the
  * top-k, and one with the statistic (below l_min the note that it was not evaluated) beside the
- * compaction.  Contexts of up to 12288 past tokens take one launch for all of it.
+ * compaction.  Contexts of up to 12288 past tokens take one launch for all of it, or two, the second with statistic and
+ * compaction: with a compaction of more than 4096 selected tokens, of more than 64 KV heads, or of few heads that keep much
+ * (one head of more than 512 KiB of keys, e.g. 2048 tokens of d = 128 in bf16; heads that are no multiple of eight alike).
  *   scores  [Hk+1, T] f32 out: rows 0..Hk-1 = P (per KV head), row Hk = s (all heads).
  *   idx_out [Hk+1, k+W] int32 out: rows 0..Hk-1 = Alg. 1's per-head I, row Hk = Alg. 2's select_idx
  *           (to be used only when out->selected is set).
@@ -248,11 +250,15 @@ asl_status asl_layer_step(asl_ctx* ctx, const asl_params* params, const void* q_
  * before the next layer starts; the compacted KV of a layer is needed at decoding time. */
 asl_status asl_join(asl_ctx* ctx, void* stream);
 
-/* Health check (not a step of the paper's method).  The workgroups of a statistic launch hand partial sums to
- * its first one inside the launch, which waits for them with a bounded number of polls; if its wait runs
- * out it raises a fault word in the workspace and writes no result (every wave still exits).  This call
- * waits for the device to go idle, returns the word in *fault_out (0 = no wait ever ran out) and clears it.
- * Results of calls issued since the last check are valid iff it reads 0.  Synchronises: not for the hot loop. */
+/* Health check (not a step of the paper's method).  Workgroups of a launch that wait for other workgroups of it do so with
+ * a bounded number of polls, and raise a fault word in the workspace if their wait runs out (every wave still exits):
+ *  - the first workgroup of a statistic, for the others' partial sums: it then reports no result (evaluated = 0) and leaves the
+ *    state as it was;
+ *  - the compacting wavefronts of a layer step of up to 12288 past tokens, for the selection of their head's tokens: each then
+ *    leaves its part of k_out and v_out unwritten, while scores, idx_out, ranks and statistic are as ever.
+ * This call waits for the device to go idle, returns the word in *fault_out (0 = no wait ever ran out) and clears it.
+ * Results of calls issued since the last check, k_out and v_out among them, are valid iff it reads 0; the calls themselves
+ * have returned ASL_OK.  Synchronises: not for the hot loop. */
 asl_status asl_device_fault(asl_ctx* ctx, int32_t* fault_out);
 
 /* Measurement aid (not a step of the paper's method; for callers that time the kernels of the

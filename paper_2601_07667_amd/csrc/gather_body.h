@@ -72,7 +72,7 @@ constexpr int kPickedUnroll = 2;
 // The same for rows that another workgroup of this launch is still selecting: the block's source tokens are read from the words
 // (tag, token) in which it leaves them, T + i for the row's last, window tokens.  A word that carries the launch's tag is whole
 // and this launch's, whatever it held before, so nothing else is ordered between the two.  k: the row's selected tokens; picks:
-// the row's words.  Returns false, nothing written, if they have not come after kFlagSpinLimit polls.
+// the row's words.  Returns false, the wavefront's part not written, if its words have not come after kFlagSpinLimit polls.
 template <bool POW2, int NT>
 __device__ __forceinline__ bool gather_picked_body(const GatherArgs& a, int bx, int h, int which, int T, int k,
                                                    const unsigned long long* picks, uint32_t tag) {
