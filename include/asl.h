@@ -222,8 +222,8 @@ asl_status asl_gather_rows(asl_ctx* ctx, const void* src, int64_t src_row_stride
  * runs them side by side in three launches on `stream`: two that each carry a stage of the ranking and one of the
  * top-k, and one with the statistic (below l_min the note that it was not evaluated) beside the
  * compaction.  Contexts of up to 12288 past tokens take one launch for all of it, or two, the second with statistic and
- * compaction: with a compaction of more than 4096 selected tokens, of more than 64 KV heads, or of few heads that keep much
- * (one head of more than 512 KiB of keys, e.g. 2048 tokens of d = 128 in bf16; heads that are no multiple of eight alike).
+ * compaction: if that is of more than 4096 selected tokens, of more than 64 KV heads, or of up to four that keep more than
+ * 512 KiB of keys each (2048 tokens of d = 128 in bf16; nine heads: half of it).
  *   scores  [Hk+1, T] f32 out: rows 0..Hk-1 = P (per KV head), row Hk = s (all heads).
  *   idx_out [Hk+1, k+W] int32 out: rows 0..Hk-1 = Alg. 1's per-head I, row Hk = Alg. 2's select_idx
  *           (to be used only when out->selected is set).

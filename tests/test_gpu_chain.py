@@ -449,6 +449,53 @@ def test_short_layer_step_in_one_launch(gpu_device, Hq, Hk, d, dtype, N, W, budg
         np.testing.assert_array_equal(got["Vc"][g], L.v[g][got["I_head"][g]])
 
 
+def _unlike_iid(kind, T, rng):
+    """Scores whose ranking by bins leaves the first way, short bins: ties, clusters, bins of hundreds of keys side by side."""
+    s = np.exp(2 * rng.standard_normal(T)).astype(np.float32)
+    third = rng.permutation(T)[:T // 3]
+    if kind == "equal":
+        s[:] = 0.25
+    elif kind == "third equal":
+        s[third] = 0.5
+    elif kind == "few values":
+        s = np.round(3 * rng.standard_normal(T)).astype(np.float32)
+    elif kind == "cluster":
+        s = (1 + 0.02 * rng.standard_normal(T)).astype(np.float32)
+        s[rng.permutation(T)[:T // 300]] += (300 * rng.random(T // 300) + 50).astype(np.float32)
+    else:                                              # two bins of 200 keys and a dozen short ones between them, a few bins apart
+        apart = 0.98 if kind == "two bins" else 0.985
+        near = (s > 0.96) & (s < 1.02)
+        s[near] *= 0.9
+        at = rng.permutation(T)[:412]
+        s[at[:200]] = 1 + 2e-4 * rng.random(200)
+        s[at[200:400]] = apart if kind == "a cluster and a tie" else apart * (1 + 2e-4 * rng.random(200))
+        s[at[400:]] = apart + (1 - apart) * np.linspace(0.2, 0.8, 12)
+    return s
+
+
+@pytest.mark.parametrize("T", [8193, 10007, 12288])
+@pytest.mark.parametrize("kind", ["equal", "third equal", "few values", "cluster", "two bins", "a cluster and a tie"])
+def test_short_statistic_of_scores_unlike_iid_ones(gpu_device, T, kind):
+    """The workgroup that has a token's rank adds up its part of the statistic: every token once, however its rank was found."""
+    import torch
+    dev, n_held, k, W = gpu_device, 3, 500, 16
+    rng = np.random.default_rng(T + len(kind))
+    ctx, p = asl.Asl(T + W, 1, W), asl.make_params(1, 1, 64, T + W, W, 7, W + k)
+    held = np.stack([rng.permutation(T) for _ in range(n_held)])
+    for turn in range(4):                              # the pair of bins at other places of a workgroup's 64
+        scores = _unlike_iid(kind, T, rng)
+        ring = torch.zeros((n_held + 1, T), dtype=torch.int32, device=dev)
+        ring[:n_held] = torch.from_numpy(held.astype(np.int32)).to(dev)
+        state, stat = asl.new_state(dev), asl.new_stat(dev)
+        asl.write_state(state, n_valid_rows=n_held, last_layer=n_held - 1)
+        ctx.asl_rank_stat(p, torch.from_numpy(scores).to(dev), n_held, 0, n_held + 1, 0.0, ring, state, stat)
+        rank = ring[n_held].cpu().numpy().astype(np.int64)
+        np.testing.assert_array_equal(rank, orc.rank_desc(scores.astype(np.float64)))
+        st = asl.read_struct(stat, asl.AslStat)
+        assert (st.evaluated, st.n_rows, st.union_size, st.numerator) == (1, *_exact_statistic(held, rank, k)), (kind, turn)
+    ctx.close()
+
+
 @pytest.mark.parametrize("budget", [2048, 2049])
 def test_short_layer_step_below_l_min(gpu_device, budget):
     """One head, compacted in the launch that selects and in its own, in a layer that has no statistic: the state only advances."""
@@ -467,17 +514,19 @@ def test_short_layer_steps_on_two_streams(gpu_device):
     p, T, n_idx = gu.params_of(sh), sh.T, sh.k + sh.W
     ops = [[gu.to_dev(x, "bf16", dev) for x in (L.q_obs, L.k, L.v)] for L in layers]
 
-    def buffers():
-        return dict(ctx=asl.Asl(sh.N, sh.Hk + 1, sh.Hq * sh.W), scores=torch.zeros((sh.Hk + 1, T), device=dev),
-                    ring=torch.zeros((sh.L_obs, T), dtype=torch.int32, device=dev), state=asl.new_state(dev), stat=asl.new_stat(dev),
-                    I=torch.zeros((sh.Hk + 1, n_idx), dtype=torch.int32, device=dev),
-                    K=torch.zeros((sh.Hk, n_idx, sh.d), dtype=torch.bfloat16, device=dev),
-                    V=torch.zeros((sh.Hk, n_idx, sh.d), dtype=torch.bfloat16, device=dev))
+    def buffers():                                     # each step's outputs are kept
+        return dict(ctx=asl.Asl(sh.N, sh.Hk + 1, sh.Hq * sh.W), scores=torch.zeros((reps, sh.Hk + 1, T), device=dev),
+                    ring=torch.zeros((sh.L_obs, T), dtype=torch.int32, device=dev), state=asl.new_state(dev),
+                    stat=torch.stack([asl.new_stat(dev) for _ in range(reps)]),
+                    I=torch.zeros((reps, sh.Hk + 1, n_idx), dtype=torch.int32, device=dev),
+                    K=torch.zeros((reps, sh.Hk, n_idx, sh.d), dtype=torch.bfloat16, device=dev),
+                    V=torch.zeros((reps, sh.Hk, n_idx, sh.d), dtype=torch.bfloat16, device=dev))
 
-    def step(b, i, j, compact=True):
+    def step(b, i, j):
         q, k, v = ops[(i + j) % 2]
-        b["ctx"].asl_layer_step(p, q, k, v, j, 0, sh.L_obs, 0.0, b["scores"], b["ring"], b["state"], b["stat"], b["I"],
-                                b["K"] if compact else None, b["V"] if compact else None)
+        compact = j % 5 != 3
+        b["ctx"].asl_layer_step(p, q, k, v, j, 0, sh.L_obs, 0.0, b["scores"][j], b["ring"], b["state"], b["stat"][j], b["I"][j],
+                                b["K"][j] if compact else None, b["V"][j] if compact else None)
 
     ref, got = [buffers() for _ in range(2)], [buffers() for _ in range(2)]
     for i in range(2):
@@ -488,12 +537,13 @@ def test_short_layer_steps_on_two_streams(gpu_device):
     for j in range(reps):
         for i in range(2):
             with torch.cuda.stream(streams[i]):
-                step(got[i], i, j, compact=j % 5 != 3)
+                step(got[i], i, j)
     torch.cuda.synchronize()
     for i in range(2):
         assert got[i]["ctx"].asl_device_fault() == 0
         for name in ("scores", "ring", "state", "stat", "I", "K", "V"):
-            assert torch.equal(got[i][name], ref[i][name]), f"stream {i}: {name}"
+            assert torch.equal(got[i][name], ref[i][name]), f"stream {i}: {name} of step " + str(
+                [j for j in range(reps) if not torch.equal(got[i][name][j], ref[i][name][j])] if len(got[i][name]) == reps else "any")
         ref[i]["ctx"].close()
         got[i]["ctx"].close()
 
@@ -561,13 +611,14 @@ def test_layer_step_of_scores_with_a_period(gpu_device):
     assert _step_ms(gpu_device, L) < 5 * plain + 0.1
 
 
-def test_layer_step_is_reproducible(gpu_device):
-    """200 repetitions of asl_layer_step on the C3 layer, and of the single ranking and top-k calls on its
-    scores: every output has the same bits every time (the workgroups of the ranking and statistic
+@pytest.mark.parametrize("short", [False, True])
+def test_layer_step_is_reproducible(gpu_device, short):
+    """200 repetitions of asl_layer_step on the C3 layer, and on one whose tail is one launch, and of the single ranking and top-k
+    calls on its scores: every output has the same bits every time (the workgroups of the ranking and statistic
     launches hand counts to each other inside the launch; nothing may depend on who came first)."""
     import torch
     dev = gpu_device
-    L = synth.config_layer(3)
+    L = synth.iid_layer(synth.Shape(Hq=16, Hk=8, d=128, N=9000, W=16, S=7, budget=2048), 2400) if short else synth.config_layer(3)
     sh = L.shape
     ctx = asl.Asl(sh.N, sh.Hk + 1, sh.Hq * sh.W)
     p = gu.params_of(sh)
