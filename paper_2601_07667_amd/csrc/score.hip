@@ -253,11 +253,13 @@ __device__ __forceinline__ float max2(float a, float b) { return __builtin_fmaxf
 // -> 81.1 the layer step).  One branch for all row blocks, behind all of their arithmetic: with one per block half of it stood in
 // a basic block without MFMAs (144.6).  Not for the shapes whose calls are start-up mostly: their one or two sub-tiles take the
 // branch every time (d = 256, 8K, 17.2 -> 17.7); nor for up to 64 query rows, where the key stream bounds the pass and another loop
-// is only more code (28 heads, W = 5, the scoring, 64K 36.9, without 36.1; 128K 60.5, 59.2).  And a wavefront whose references move in more than an eighth of the sub-tiles goes on
+// is only more code (28 heads, W = 5, the scoring, 64K 36.9, without 36.1; 128K 60.5, 59.2); nor for 97 to 128 rows of d = 64 (two heads,
+// 128 rows, 120K 31.2, 30.4; 242K 48.7, 47.1; but 96 rows 39.6, 40.7; why those gain and these lose has not been taken apart).  And a wavefront whose references move in more than an eighth of the sub-tiles goes on
 // with the running maximum: logits of hundreds that grow (lognormal key lengths, 256K, W = 64) took
 // 166 us without that, 149 with it, 147 with the running maximum throughout.
 constexpr float kRescale = 256.f;
-template <typename TE, int P, int NW, bool PAD> constexpr bool kLazy = sizeof(TE) == 2 && P <= 16 && !PAD && NW > 2;
+template <typename TE, int P, int NW, int RB, bool PAD>
+constexpr bool kLazy = sizeof(TE) == 2 && P <= 16 && !PAD && NW > 2 && !(P <= 8 && NW == 4 && RB == 1);
 template <int RB, bool MASK, bool LAZY>
 __device__ __forceinline__ void rowstats_fold(const f32x16 (&acc)[RB], int key_lo, int N, int T,
                                               const int (&wi)[RB], float c1, float (&m_run)[RB], float (&z_run)[RB], int& raised) {
@@ -400,7 +402,7 @@ score_rowstats_kernel(const char* __restrict__ q_obs, const char* __restrict__ k
   // from.  No turn may get another barrier, or none.  (One loop with a branch around the two foldings in it: 256K, W = 64, 289 us the
   // scoring, so 300; a vote of the wavefronts in LDS: 28 heads, W = 13, 128K 60.6, 61.4.)
   const int plain = T / KT;
-  if constexpr (kLazy<TE, P, NW, PAD>) {
+  if constexpr (kLazy<TE, P, NW, RB, PAD>) {
     while (it < n_my && tile < plain && raised <= 3 + it / 4) step(std::false_type(), std::true_type());
   }
   while (it < n_my && tile < plain) step(std::false_type(), std::false_type());

@@ -321,7 +321,7 @@ def test_logits_on_several_levels(gpu_device, Hq, Hk, d, W, dtype, levels):
 # that rise with every tile, where a wavefront soon keeps a running maximum; that fall.  Three and four wavefronts of 32 rows, three of 64;
 # the rows of each query head, which are a wavefront's or half of one's, meet another share of the levels, so that wavefronts of a
 # workgroup part.
-@pytest.mark.parametrize("G,d", [(3, 128), (4, 64), (5, 128)])
+@pytest.mark.parametrize("G,d", [(3, 128), (4, 128), (3, 64), (4, 64), (5, 128), (5, 64)])
 @pytest.mark.parametrize("levels", [(0, 2, 1, 3, 0), (0, 12, 5, 24, 24, 40), (0, 150, 20, 190), tuple(range(0, 168, 6)),
                                     tuple(range(168, 0, -6))], ids=["stay", "move", "overflow", "rise", "fall"])
 def test_reference_of_the_sums_over_many_tiles(gpu_device, G, d, levels):
