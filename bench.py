@@ -368,8 +368,8 @@ def main() -> int:
             return lay[0] - 1
 
         # the same steps with the rows' log-sum-exp handed over, so K is streamed once per layer
-        if not args.lse:
-            lse_own = window_lse_all()
+        lse_own = None if args.lse else window_lse_all()
+        if lse_own is not None:
             ms = timed(lambda: step(adv(), lse_own), args.steps)
             legs["lse_supplied"] = {"ms_per_step": round(ms, 5), "value": round(sh.N / (ms * 1e-3), 1),
                                     "note": "lse [Hq,W] handed over (here produced by asl_window_lse outside the "
