@@ -7,7 +7,7 @@
 // the row statistics, pass 2 streams K again for the normalised column sums.  When the caller
 // hands over the rows' log-sum-exp, pass 1 is skipped.
 //
-// Work split: a workgroup owns one KV head and every so many-th of its key tiles; wave w owns RB blocks of
+// Work split: a workgroup owns one KV head and every so many-th of its key tiles (one wavefront: a contiguous share); wave w owns RB blocks of
 // 32 query rows (RB = 1 up to M = 128 rows, 2 above for the main bf16 shapes) and keeps their
 // fragments in registers for the whole kernel; K tiles of 64 or 32 keys stream global -> LDS directly
 // (ring of 3 buffers, XOR-swizzled) and every wave reads all of them as the other MFMA operand
@@ -249,8 +249,8 @@ __device__ __forceinline__ float max2(float a, float b) { return __builtin_fmaxf
 // exponentials = z_run * 2^m_run.
 // LAZY: the reference is the largest logit up to some sub-tile, and stays until a sub-tile's sum of 16 is above kRescale: no term
 // is then more than 2^8 times the reference's, which the fp32 sum holds as exactly as the terms below it, and the maximum of the 16 and
-// the rescaling, a fifth of the vector work, are left out (256K, W = 64, pass 1 147.7 -> 138.5 us; 128K 132.9 -> 130.8, 64K 84.2
-// -> 81.1 the layer step).  One branch for all row blocks, behind all of their arithmetic: with one per block half of it stood in
+// the rescaling, a fifth of the vector work, are left out (256K, W = 64, pass 1 147.7 -> 138.5 us; the layer step, on a slow box,
+// 128K 132.9 -> 130.8, 64K 84.2 -> 81.1).  One branch for all row blocks, behind all of their arithmetic: with one per block half of it stood in
 // a basic block without MFMAs (144.6).  Not for the shapes whose calls are start-up mostly: their one or two sub-tiles take the
 // branch every time (d = 256, 8K, 17.2 -> 17.7); nor for up to 64 query rows, where the key stream bounds the pass and another loop
 // is only more code (28 heads, W = 5, the scoring, 64K 36.9, without 36.1; 128K 60.5, 59.2); nor for 97 to 128 rows of d = 64 (two heads,
@@ -615,8 +615,8 @@ score_colsum_kernel(const char* __restrict__ q_obs, const char* __restrict__ k, 
   ASL_LOAD_Q_FRAGS();
   TilePieces<P, NT> tp;
   tp.init(kst, tid, last_piece);
-  // The tiles are taken from the last to the first: pass 1 took them first to last, so those read most
-  // recently (still in the last-level cache) are the ones this pass reads first.
+  // The tiles are taken from the last to the first: pass 1 took them first to last, so those read most recently are the ones this
+  // pass reads first, and of keys that go through the last-level cache (not STREAM) finds there.
   const int n_my = split.count(chunk);
   int ahead = split.tile(chunk, n_my - 1), tile = ahead, prev = ahead, prev2 = ahead;   // next tile to load; this one, the two before
   // prologue: STAGES-1 tiles in flight before the row offsets are worked out, so that their latency
